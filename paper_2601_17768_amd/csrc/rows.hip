@@ -255,20 +255,20 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
   }
 }
 
-// RMSNorm for many rows at d = 4096: one workgroup of 1024 threads per block of 16 rows, thread
+// RMSNorm at d = 4096: one workgroup of 64 R threads per R neighbouring rows, thread
 // (w, g, r) owning the partial sum p[w][g] of row r - the same 64 partials per row, accumulated in
 // the same order and combined in the same tree as in rmsnorm_kernel, so the bits are the same; only
-// the work distribution differs.  With 16 rows of a token block side by side every 16-byte piece of
-// the residual stream and of the output tiles is read or written as part of a full 256-byte run
-// (the wave-per-row kernel touches every 128-byte line for half of its bytes).
-__global__ __launch_bounds__(1024) void rmsnorm_block_kernel(const float* __restrict__ x,
-                                                             const uint16_t* __restrict__ gain,
-                                                             uint16_t* __restrict__ y, float eps) {
+// the work distribution differs.  R (4, 8 or 16; see launch_rmsnorm) trades CUs at work against the length of the
+// contiguous runs (16 R bytes) that a workgroup reads and writes in the token-interleaved layouts.
+template <int R>
+__global__ __launch_bounds__(64 * R) void rmsnorm_block_kernel(const float* __restrict__ x,
+                                                               const uint16_t* __restrict__ gain,
+                                                               uint16_t* __restrict__ y, float eps) {
   constexpr int D = 4096, U = 8;                         // tiles of 32 features per thread: t = u * 16 + w
-  __shared__ float part[64][16];
-  __shared__ float inv_s[16];
-  const int r = threadIdx.x & 15, wg = threadIdx.x >> 4, w = wg >> 2, g = wg & 3;
-  const int row = blockIdx.x * 16 + r;
+  __shared__ float part[64][R];
+  __shared__ float inv_s[R];
+  const int r = threadIdx.x % R, wg = threadIdx.x / R, w = wg >> 2, g = wg & 3;
+  const int row = blockIdx.x * R + r;
   const float* xr = x + resid_off(row, 0, D);
   uint4* yr = (uint4*)(y + pk_off(row, 0, D));
   f32x4 a[U], b[U];
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(1024) void rmsnorm_block_kernel(const float* __rest
   }
   part[wg][r] = ss;
   __syncthreads();
-  if (threadIdx.x < 16) {
+  if (threadIdx.x < R) {
     float total = 0.f;
 #pragma unroll
     for (int ww = 0; ww < 16; ++ww) {
@@ -342,9 +342,18 @@ void launch_embed(const llm42_model* m, const int32_t* candidates, const Workspa
 
 void launch_rmsnorm(const float* x, const uint16_t* gain, uint16_t* y, int m_pad, int d, float eps,
                     hipStream_t st) {
-  if (d == 4096 && m_pad >= 256 && m_pad % 16 == 0) rmsnorm_block_kernel<<<m_pad / 16, 1024, 0, st>>>(x, gain, y, eps);
+  // us per launch, wave per row | 4 | 8 | 16 rows per workgroup (back to back, residual stream in the caches):
+  //   128 rows 3.8 | 3.4 | 4.3 | 6.3      256 rows 6.7 | 3.5 | 4.5 | 6.5      512 rows 6.7 | 4.4 | 4.7 | 6.7
+  //   1024 rows 10.6 | 8.2 | 5.7 | 7.3    1536 rows 15.8 | 10.8 | 7.7 | 7.9   2048 rows 17.8 | 13.4 | 9.3 | 8.5
+  //   4096 rows 31.5 | 25.6 | 16.8 | 17.1
+  // Few rows are bound by how many CUs load; many by lines that two workgroups fetch (4 rows take half of a 128-byte
+  // line, a single row an eighth).  Around 2048 rows 16 rows per workgroup still fill half the CUs and have the longest runs.
+  if (d == 4096 && m_pad >= 128) {
+    if (m_pad <= 512) rmsnorm_block_kernel<4><<<m_pad / 4, 256, 0, st>>>(x, gain, y, eps);
+    else if (m_pad <= 1536 || m_pad > 2560) rmsnorm_block_kernel<8><<<m_pad / 8, 512, 0, st>>>(x, gain, y, eps);
+    else rmsnorm_block_kernel<16><<<m_pad / 16, 1024, 0, st>>>(x, gain, y, eps);
+  }
   // few rows: one wave per workgroup, so that the rows' loads are spread over as many CUs as there are rows
-  // (measured at 512 .. 1024 rows as well: there the block kernel is up to twice as fast)
   else if (m_pad <= 256) rmsnorm_kernel<<<m_pad, 64, 0, st>>>(x, gain, y, m_pad, d, eps);
   else rmsnorm_kernel<<<(m_pad + 3) / 4, 256, 0, st>>>(x, gain, y, m_pad, d, eps);
 }

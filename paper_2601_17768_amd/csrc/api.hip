@@ -107,6 +107,12 @@ void attention_mode(const llm42_model* m, int num_seqs, int max_context, Workspa
   ws.attn_units = attention_units(ws.attn_super, max_context);
 }
 
+// Rows of the GEMM grid.  (384 would be three token tiles of 128: too few for the 128 x 128 tile to fill the device, and
+// the 64 x 128 tile then needs a second round of workgroups - 512 padded rows run faster than 384.)
+int padded_rows(int rows) {
+  return rows <= 16 ? 16 : rows <= 32 ? 32 : rows <= 64 ? 64 : rows <= 256 ? pad_to(rows, 128) : rows <= 512 ? 512 : pad_to(rows, 256);
+}
+
 // Carve the workspace.  Called with base == nullptr to size it.
 Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context, char* base, bool batch_chosen = false,
                 size_t min_part_rows = 0) {
@@ -116,10 +122,7 @@ Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context,
   ws.num_cus = m->num_cus;
   ws.batch_chosen = batch_chosen;
   ws.m_rows = num_seqs * window;
-  // (384 padded rows would be three token tiles of 128: too few for the 128 x 128 tile to fill the device, and the
-  // 64 x 128 tile then needs a second round of workgroups - 512 padded rows run faster than 384)
-  ws.m_pad = ws.m_rows <= 16 ? 16 : ws.m_rows <= 32 ? 32 : ws.m_rows <= 64 ? 64
-             : ws.m_rows <= 256 ? pad_to(ws.m_rows, 128) : ws.m_rows <= 512 ? 512 : pad_to(ws.m_rows, 256);
+  ws.m_pad = padded_rows(ws.m_rows);
   ws.r_pad = pad_to(m->group * window, 16);
   attention_mode(m, num_seqs, max_context, ws);
   size_t off = 0;
@@ -170,7 +173,26 @@ size_t sized_for_up_to(const llm42_model* m, int max_seqs, int window, int max_c
   return carve(m, max_seqs, window, max_context, nullptr, false, part_rows).bytes;
 }
 
-// One pass of the verifier over num_seqs x window rows; arguments already checked.
+// Layer `ly` behind its attention.
+void run_mlp(const llm42_model* m, const llm42_model::Layer& ly, const Workspace& ws, hipStream_t st) {
+  const llm42_config& c = m->cfg;
+  TIMED(LLM42_K_O_PROJ, launch_gemm_residual(ly.wo, ws.attn, ws.resid, c.d_model, m->d_attn, ws, st));
+  TIMED(LLM42_K_RMSNORM, launch_rmsnorm(ws.resid, ly.ffn_norm, ws.normed, ws.m_pad, c.d_model, c.rms_eps, st));
+  TIMED(LLM42_K_GATE_UP, launch_gemm_swiglu(m, (int)(&ly - m->layers), ws, st));
+  TIMED(LLM42_K_DOWN, launch_gemm_residual(ly.wdown, ws.hidden, ws.resid, c.d_model, m->ffn_k, ws, st));
+}
+
+// Final norm, LM head and sampler.
+void run_head(const llm42_model* m, int window, int num_seqs, int32_t* out_tokens, float* out_logits,
+              const llm42_sampling* sampling, const Workspace& ws, hipStream_t st) {
+  const llm42_config& c = m->cfg;
+  TIMED(LLM42_K_RMSNORM, launch_rmsnorm(ws.resid, m->final_norm, ws.normed, ws.m_pad, c.d_model, c.rms_eps, st));
+  TIMED(LLM42_K_LM_HEAD, launch_gemm_logits(m, window, out_logits, sampling, ws, st));
+  TIMED(LLM42_K_ARGMAX, launch_argmax_merge(m, num_seqs, window, out_tokens, ws, st));
+}
+
+// One pass of the verifier over num_seqs x window rows; arguments already checked.  A prefill pass ends with the last
+// layer's attention: behind it only the rows of last prompt tokens are needed.
 llm42_status run_pass(const llm42_model* m, const llm42_kv_cache* kv, const int32_t* seq_lens, const int32_t* candidates,
                       int window, const int32_t* n_valid, int num_seqs, int max_context, int32_t* out_tokens,
                       int32_t* seq_status, float* out_logits, const int32_t* dump_seq_ids, int n_dump,
@@ -185,38 +207,41 @@ llm42_status run_pass(const llm42_model* m, const llm42_kv_cache* kv, const int3
     TIMED(LLM42_K_RMSNORM, launch_rmsnorm(ws.resid, ly.attn_norm, ws.normed, ws.m_pad, c.d_model, c.rms_eps, st));
     TIMED(LLM42_K_QKV, launch_gemm_qkv(m, l, kv, window, ws, st));
     TIMED(LLM42_K_ATTENTION, launch_attention(m, l, kv, num_seqs, window, max_context, ws, st));
-    TIMED(LLM42_K_O_PROJ, launch_gemm_residual(ly.wo, ws.attn, ws.resid, c.d_model, m->d_attn, ws, st));
-    TIMED(LLM42_K_RMSNORM, launch_rmsnorm(ws.resid, ly.ffn_norm, ws.normed, ws.m_pad, c.d_model, c.rms_eps, st));
-    TIMED(LLM42_K_GATE_UP, launch_gemm_swiglu(m, l, ws, st));
-    TIMED(LLM42_K_DOWN, launch_gemm_residual(ly.wdown, ws.hidden, ws.resid, c.d_model, m->ffn_k, ws, st));
+    if (prefill_pass && l + 1 == c.n_layers) return LLM42_OK;   // the rest is run once, for the rows that need it (run_tail)
+    run_mlp(m, ly, ws, st);
   }
-  TIMED(LLM42_K_RMSNORM, launch_rmsnorm(ws.resid, m->final_norm, ws.normed, ws.m_pad, c.d_model, c.rms_eps, st));
-  TIMED(LLM42_K_LM_HEAD, launch_gemm_logits(m, window, out_logits, sampling, ws, st));
-  TIMED(LLM42_K_ARGMAX, launch_argmax_merge(m, num_seqs, window, out_tokens, ws, st));
+  run_head(m, window, num_seqs, out_tokens, out_logits, sampling, ws, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(LLM42_EHIP, "verifier pass: launch failed: %s", hipGetErrorString(e));
   return LLM42_OK;
 }
 
 // Buffers of llm42_prefill behind the verifier's own workspace: the candidate rows of the current
-// pass, their count and the cached length per sequence, the pass's tokens, a status word per sequence.
+// pass, their count and the cached length per sequence, a status word per sequence; and the rows of the tail (below).
 struct PrefillExtra {
-  int32_t *cand, *n_valid, *lens_now, *pass_tokens, *status;
+  int32_t *cand, *n_valid, *lens_now, *status;
+  int32_t *tail_pos, *tail_seq;   // [padded num_seqs]
+  uint16_t* tail_attn;            // attention output and residual stream of the rows that the tail of the model is run on
+  float* tail_resid;
   size_t bytes;   // workspace size including these
 };
-PrefillExtra carve_prefill(size_t verifier_bytes, int num_seqs, int window, char* base) {
+PrefillExtra carve_prefill(const llm42_model* m, size_t verifier_bytes, int num_seqs, int window, char* base) {
   PrefillExtra x;
   size_t off = align_up(verifier_bytes, 256);
   auto take = [&](size_t bytes) {
     char* p = base ? base + off : nullptr;
     off = align_up(off + bytes, 256);
-    return (int32_t*)p;
+    return p;
   };
-  x.cand = take(sizeof(int32_t) * (size_t)num_seqs * window);
-  x.n_valid = take(sizeof(int32_t) * num_seqs);
-  x.lens_now = take(sizeof(int32_t) * num_seqs);
-  x.pass_tokens = take(sizeof(int32_t) * (size_t)num_seqs * window);
-  x.status = take(sizeof(int32_t) * num_seqs);
+  x.cand = (int32_t*)take(sizeof(int32_t) * (size_t)num_seqs * window);
+  x.n_valid = (int32_t*)take(sizeof(int32_t) * num_seqs);
+  x.lens_now = (int32_t*)take(sizeof(int32_t) * num_seqs);
+  x.status = (int32_t*)take(sizeof(int32_t) * num_seqs);
+  const size_t rows = padded_rows(num_seqs);
+  x.tail_pos = (int32_t*)take(sizeof(int32_t) * rows);
+  x.tail_seq = (int32_t*)take(sizeof(int32_t) * rows);
+  x.tail_attn = (uint16_t*)take(2 * rows * m->d_attn);
+  x.tail_resid = (float*)take(4 * rows * m->cfg.d_model);
   x.bytes = off;
   return x;
 }
@@ -496,7 +521,7 @@ llm42_status llm42_prefill_workspace_bytes(const llm42_model* m, int32_t max_seq
   size_t v = 0;
   if (!out_bytes) return fail(LLM42_EINVAL, "prefill_workspace_bytes: null argument");
   if (llm42_status st = llm42_workspace_bytes(m, max_seqs, chunk, max_context, &v)) return st;
-  *out_bytes = carve_prefill(v, max_seqs, chunk, nullptr).bytes;
+  *out_bytes = carve_prefill(m, v, max_seqs, chunk, nullptr).bytes;
   return LLM42_OK;
 }
 
@@ -521,19 +546,33 @@ llm42_status llm42_prefill(const llm42_model* m, const llm42_kv_cache* kv, const
                 (long long)kv->max_blocks_per_seq * LLM42_KV_BLOCK);
   if ((uintptr_t)workspace % 256) return fail(LLM42_EWORKSPACE, "prefill: workspace not 256-byte aligned");
   const Workspace ws = carve(m, num_seqs, chunk, max_context, (char*)workspace);
-  const PrefillExtra x = carve_prefill(ws.bytes, num_seqs, chunk, (char*)workspace);
+  const PrefillExtra x = carve_prefill(m, ws.bytes, num_seqs, chunk, (char*)workspace);
   if (x.bytes > workspace_bytes) return fail(LLM42_EWORKSPACE, "prefill: workspace %zu < %zu bytes", workspace_bytes, x.bytes);
   hipStream_t st = (hipStream_t)hip_stream;
   int32_t* status = seq_status ? seq_status : x.status;
   const int passes = max_prompt_len == 0 ? 1 : (max_prompt_len + chunk - 1) / chunk;   // one pass at least: it sets the outputs
+  // Only the last prompt token of a sequence needs anything behind the last layer's attention (every row's K and V are in
+  // the cache by then): those rows are collected over the passes and the tail - the last layer's MLP, final norm, LM head,
+  // sampler - runs once over num_seqs rows instead of in every pass over all of them.  It works in the passes' buffers.
+  Workspace tail = ws;
+  tail.m_rows = num_seqs;
+  tail.m_pad = padded_rows(num_seqs);
+  tail.row_pos = x.tail_pos;
+  tail.row_seq = x.tail_seq;
+  tail.attn = x.tail_attn;
+  tail.resid = x.tail_resid;
   for (int p = 0; p < passes; ++p) {
     launch_prefill_window(prompt_tokens, prompt_offsets, seq_lens, num_seqs, chunk, p, max_prompt_len, x.cand, x.n_valid,
                           x.lens_now, status, out_next_tokens, st);
     if (max_prompt_len == 0) break;
-    if (llm42_status rc = run_pass(m, kv, x.lens_now, x.cand, chunk, x.n_valid, num_seqs, max_context, x.pass_tokens, status,
-                                   nullptr, nullptr, 0, ws, st, sampling, true))
+    if (llm42_status rc = run_pass(m, kv, x.lens_now, x.cand, chunk, x.n_valid, num_seqs, max_context, nullptr, status,
+                                   nullptr, nullptr, 0, ws, st, nullptr, true))
       return rc;
-    launch_prefill_pick(prompt_offsets, num_seqs, chunk, p, x.pass_tokens, status, out_next_tokens, st);
+    launch_prefill_gather(m, prompt_offsets, num_seqs, chunk, p, max_prompt_len, status, ws, tail, st);
+  }
+  if (max_prompt_len > 0) {
+    run_mlp(m, m->layers[m->cfg.n_layers - 1], tail, st);
+    run_head(m, 1, num_seqs, out_next_tokens, nullptr, sampling, tail, st);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(LLM42_EHIP, "prefill: launch failed: %s", hipGetErrorString(e));

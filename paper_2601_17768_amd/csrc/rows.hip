@@ -46,7 +46,7 @@ __global__ void prepare_kernel(const int32_t* __restrict__ seq_lens, const int32
     row_seq[row] = s;
     // where the row's K and V go (a block id that passed the check above), for the QKV epilogue
     row_blk[row] = live ? block_table[(size_t)s * max_blocks_per_seq + ((L + i) >> 4)] : 0;
-    out_tokens[row] = -1;              // overwritten by the arg-max merge for live rows
+    if (out_tokens) out_tokens[row] = -1;   // overwritten by the arg-max merge for live rows
   }
   // the rotary factors of every live row, laid out by row so that the QKV epilogue finds them without
   // knowing the position first
@@ -109,17 +109,35 @@ __global__ void prefill_window_kernel(const int32_t* __restrict__ prompt_tokens,
   }
 }
 
-// After a prefill pass: the sequences whose last prompt token was in this pass take the pass's
-// token for that row.  A sequence that failed a check keeps -1.
-__global__ void prefill_pick_kernel(const int32_t* __restrict__ prompt_offsets, int window, int chunk_index,
-                                    const int32_t* __restrict__ pass_tokens, int num_seqs,
-                                    const int32_t* __restrict__ seq_status, int32_t* __restrict__ out_next) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= num_seqs) return;
-  const int len = prompt_offsets[s + 1] - prompt_offsets[s];
-  const int last = len - 1 - chunk_index * window;        // row of the last prompt token in this pass
-  if (len > 0 && last >= 0 && last < window)
-    out_next[s] = seq_status[s] == 0 ? pass_tokens[(size_t)s * window + last] : -1;
+// The last prompt token of every sequence, carried from the pass that holds it to the one tail of the model that runs
+// after all passes: its attention output and residual stream at the last layer move to row `s` of the tail's buffers.
+// One workgroup per tail row; pass 0 clears every row that it does not fill (position -1: takes no part).  A sequence
+// that failed a check in this pass or an earlier one keeps -1.
+__global__ __launch_bounds__(256) void prefill_gather_kernel(const int32_t* __restrict__ prompt_offsets, int window,
+                                                             int chunk_index, int num_seqs, int max_prompt_len,
+                                                             const int32_t* __restrict__ seq_status,
+                                                             const int32_t* __restrict__ row_pos,
+                                                             const uint16_t* __restrict__ attn, int d_attn,
+                                                             const float* __restrict__ resid, int d,
+                                                             int32_t* __restrict__ tail_pos, int32_t* __restrict__ tail_seq,
+                                                             uint16_t* __restrict__ tail_attn, float* __restrict__ tail_resid) {
+  const int s = blockIdx.x;
+  int row = -1;
+  if (s < num_seqs) {
+    const int len = prompt_offsets[s + 1] - prompt_offsets[s];
+    const int last = len - 1 - chunk_index * window;      // row of the last prompt token in this pass
+    if (len > 0 && len <= max_prompt_len && last >= 0 && last < window) row = s * window + last;
+  }
+  if (row < 0 && chunk_index > 0) return;                 // filled by another pass
+  const bool live = row >= 0 && row_pos[row] >= 0 && seq_status[s] == 0;
+  if (threadIdx.x == 0) {
+    tail_pos[s] = live ? row_pos[row] : -1;
+    tail_seq[s] = s < num_seqs ? s : 0;
+  }
+  for (int c = threadIdx.x * 8; c < d_attn; c += 256 * 8)
+    *(uint4*)(tail_attn + pk_off(s, c, d_attn)) = live ? *(const uint4*)(attn + pk_off(row, c, d_attn)) : make_uint4(0, 0, 0, 0);
+  for (int f = threadIdx.x * 4; f < d; f += 256 * 4)
+    *(f32x4*)(tail_resid + resid_off(s, f, d)) = live ? *(const f32x4*)(resid + resid_off(row, f, d)) : (f32x4){0.f, 0.f, 0.f, 0.f};
 }
 
 // One wave per 16 rows x 32 features of the residual stream: lane
@@ -329,10 +347,12 @@ void launch_prefill_window(const int32_t* prompt_tokens, const int32_t* prompt_o
                                                  n_valid, lens_now, seq_status, out_next);
 }
 
-void launch_prefill_pick(const int32_t* prompt_offsets, int num_seqs, int window, int chunk_index,
-                         const int32_t* pass_tokens, const int32_t* seq_status, int32_t* out_next, hipStream_t st) {
-  prefill_pick_kernel<<<(num_seqs + 255) / 256, 256, 0, st>>>(prompt_offsets, window, chunk_index, pass_tokens, num_seqs,
-                                                             seq_status, out_next);
+void launch_prefill_gather(const llm42_model* m, const int32_t* prompt_offsets, int num_seqs, int window, int chunk_index,
+                           int max_prompt_len, const int32_t* seq_status, const Workspace& ws, const Workspace& tail,
+                           hipStream_t st) {
+  prefill_gather_kernel<<<tail.m_pad, 256, 0, st>>>(prompt_offsets, window, chunk_index, num_seqs, max_prompt_len, seq_status,
+                                                    ws.row_pos, ws.attn, m->d_attn, ws.resid, m->cfg.d_model, tail.row_pos,
+                                                    tail.row_seq, tail.attn, tail.resid);
 }
 
 void launch_embed(const llm42_model* m, const int32_t* candidates, const Workspace& ws, hipStream_t st) {

@@ -120,3 +120,21 @@ def test_flagged_and_empty_prompts(tiny):
         B.llm42_prefill(sess.model, kv, num_blocks, bt, torch.zeros(n, dtype=torch.int32, device=DEV),
                         d(np.concatenate(prompts).astype(np.int32)), d(offsets), 24, chunk, max_context, first,
                         ws[:1024], status)
+
+
+@pytest.mark.parametrize("n_seq,chunk", [(16, 16), (17, 4), (65, 3)])
+def test_last_rows_of_many_prompts(tiny, n_seq, chunk):
+    """The rows behind the last layer's attention are run once for all sequences, in 16 to 128 padded rows, whichever
+    pass each prompt ends in: the same tokens and cache as the windows driven one by one."""
+    shape, w, sess = tiny
+    rng = wl.rng_for(203, n_seq)
+    lens = rng.integers(1, 4 * chunk + 2, size=n_seq).astype(np.int32)
+    prompts = [wl.random_tokens(rng, int(n), shape.vocab) for n in lens]
+    table, num_blocks = wl.make_block_table(rng, lens + 8, 16, spare_blocks=4)
+    bt = torch.as_tensor(table, device=DEV)
+    kv_ref, kv = sess.kv_cache(num_blocks, fill=float("nan")), sess.kv_cache(num_blocks, fill=float("nan"))
+    ref = sess.prefill_by_windows(kv_ref, bt, prompts, window=chunk + 1)
+    got = sess.prefill(kv, bt, prompts, window=chunk)
+    torch.cuda.synchronize()
+    assert got.tolist() == ref.tolist() and int(got.min()) >= 0
+    assert torch.equal(kv.view(torch.int16), kv_ref.view(torch.int16))

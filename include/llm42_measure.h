@@ -46,8 +46,8 @@ llm42_status llm42_measure_verify_window_batch_chosen(
 /* How a call of this shape distributes its attention work (the distribution never changes a bit
  * of the result; tests use this to know which kernels a case exercised).  Writes five values to
  * the HOST array `out`:
- *   out[0]  keys per work item: 256 (one workgroup per chunk, all folds in the merge pass) or
- *           2048 (one per super, chunks folded in registers);
+ *   out[0]  keys per work item: 256 (one workgroup per chunk, all folds in the merge pass; in short
+ *           calls one wave per chunk, folded by its workgroup) or 2048 (one workgroup per super);
  *   out[1]  1 if every context fits one 2048-key unit and the attention kernel writes the
  *           output itself (no merge pass);
  *   out[2]  1 if the call may take whole sequences as work items - the device decides from the

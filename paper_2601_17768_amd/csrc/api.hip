@@ -104,6 +104,22 @@ void attention_mode(const llm42_model* m, int num_seqs, int max_context, Workspa
   ws.attn_seq = col_blocks >= 8 && supers > 1 && pairs >= 2LL * ws.num_cus;
   ws.attn_direct = supers == 1 && pairs >= 128;
   ws.attn_super = ws.attn_direct || pairs * supers >= 192;
+  // Contexts within one super and few blocks of query rows: one workgroup per block of 16 rows, a wave per chunk, output
+  // written by the same launch (attention_split_kernel).  It wins while the launch is latency - every row block fetches the
+  // K and V for itself - and loses once those fetches fill the device.  us per layer, before -> with it, head_dim 128:
+  //   1 row block:  1 sequence x 512 keys 15.8 -> 11.8, 8 x 1000 20.8 -> 14.5, 16 x 1900 48.6 -> 25.6, 64 x 512 44 -> 35,
+  //                 64 x 1900 97 -> 98, 128 x 512 83 -> 68, 128 x 1900 190 -> 192; 1 x 1900 16.8 -> 18.2
+  //   2 row blocks: 8 x 512 18.0 -> 13.4, 16 x 1900 49 -> 44, 24 x 512 24.8 -> 28.0
+  //   4:  1 x 512 15.3 -> 11.8, 5 x 512 17.4 -> 14.9, 5 x 1000 19.4 -> 21.4, 16 x 100 13.8 -> 17.4
+  //   8:  1 x 512 17.6 -> 12.2, 1 x 1000 18.3 -> 15.4, 2 x 1000 18.8 -> 18.7, 5 x 512 19.8 -> 26.3;  16: 2 x 512 19.6 -> 14.2
+  // (A single long sequence is better off with its chunks spread over the CUs, merge pass and all.)
+  const long long wgs = (long long)num_seqs * c.n_kv_heads * col_blocks, cus = ws.num_cus;
+  const bool spread = max_context > 1280 && wgs * 6 < cus;
+  ws.attn_split = supers == 1 && !spread &&
+                  (col_blocks == 1   ? wgs <= 2 * cus || max_context <= 1024
+                   : col_blocks == 2 ? wgs <= cus
+                                     : wgs <= cus && max_context <= 1280 && wgs * max_context <= 512 * cus);
+  ws.attn_list = !ws.attn_split || wgs > cus;
   ws.attn_units = attention_units(ws.attn_super, max_context);
 }
 
@@ -200,7 +216,7 @@ llm42_status run_pass(const llm42_model* m, const llm42_kv_cache* kv, const int3
   const llm42_config& c = m->cfg;
   TIMED(LLM42_K_PREPARE, launch_prepare(m, kv, seq_lens, candidates, n_valid, num_seqs, window, max_context,
                                         dump_seq_ids, n_dump, out_tokens, seq_status, ws, st, prefill_pass));
-  TIMED(LLM42_K_PREPARE, launch_attention_plan(m, num_seqs, max_context, ws, st));
+  if (ws.attn_list) TIMED(LLM42_K_PREPARE, launch_attention_plan(m, num_seqs, max_context, ws, st));
   TIMED(LLM42_K_EMBED, launch_embed(m, candidates, ws, st));
   for (int l = 0; l < c.n_layers; ++l) {
     const llm42_model::Layer& ly = m->layers[l];

@@ -138,6 +138,64 @@ __device__ __forceinline__ void store_output(uint16_t* __restrict__ out, int d_a
   }
 }
 
+// What a step does between its two products, for one block of 16 query rows: masks the raw scores `sc` of the 64 keys
+// from k0, advances (m, l) and rescales acc, and leaves P in bf16 in `pf`, as the operand of the P V product.
+template <int DB, bool MASKED>
+__device__ __forceinline__ void softmax_update(f32x4 (&sc)[4], int k0, int g, int qpos, float scale_log2, float& m, float& l,
+                                               f32x4 (&acc)[DB], u32x4 (&pf)[2], const bool first) {
+  if (MASKED) {
+    // a select, not arithmetic: scores of keys past k_hi come from stale tiles and may be anything
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (k0 + b * 16 + g * 4 + e > qpos) sc[b][e] = -INFINITY;
+  }
+  float mx = fmaxf(fmaxf(sc[0][0], sc[0][1]), sc[0][2]);
+  mx = fmaxf(fmaxf(mx, sc[0][3]), sc[1][0]);
+  mx = fmaxf(fmaxf(mx, sc[1][1]), sc[1][2]);
+  mx = fmaxf(fmaxf(mx, sc[1][3]), sc[2][0]);
+  mx = fmaxf(fmaxf(mx, sc[2][1]), sc[2][2]);
+  mx = fmaxf(fmaxf(mx, sc[2][3]), sc[3][0]);
+  mx = fmaxf(fmaxf(mx, sc[3][1]), sc[3][2]);
+  mx = rows_max(fmaxf(mx, sc[3][3]));
+  // scaling by a positive constant is monotonic: max(scaled) == scaled(max), bit for bit
+  const float m_step = mx * scale_log2;
+  // The partial's reference exponent m moves up to this step's maximum only when that exceeds it by more than
+  // kLazy (then p = exp2(score - m) stays at or below 2^kLazy); otherwise it stands and alpha is exactly 1.
+  // (An empty partial has m = -inf: +inf > kLazy takes the step's maximum; -inf - -inf is NaN and keeps -inf.)
+  const float m_new = (m_step - m > kLazy) ? m_step : m;
+  const float m_use = (MASKED && m_new == -INFINITY) ? 0.f : m_new;
+  const float alpha = __builtin_amdgcn_exp2f(m - m_use);
+  float rs = 0.f;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      sc[b][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[b][e], scale_log2, -m_use));
+    rs += ((sc[b][0] + sc[b][1]) + sc[b][2]) + sc[b][3];
+  }
+  rs = rows_sum(rs);
+  // Rescaling by alpha is skipped where it cannot change a bit: in the first step of a partial (l and acc are
+  // zero, and zero times alpha is zero) and where alpha is exactly 1 for every row of the wave.
+  if (!first && __builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+    l *= alpha;
+#pragma unroll
+    for (int d = 0; d < DB; ++d) acc[d] *= alpha;
+  }
+  l += rs;
+  m = m_new;
+  // k-slot e of lane group g is key g*4+e of the first block of a pair (e < 4) or of the
+  // second (e >= 4); V uses the same assignment
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) {
+    pf[kk][0] = pack2_bf16(sc[2 * kk][0], sc[2 * kk][1]);
+    pf[kk][1] = pack2_bf16(sc[2 * kk][2], sc[2 * kk][3]);
+    pf[kk][2] = pack2_bf16(sc[2 * kk + 1][0], sc[2 * kk + 1][1]);
+    pf[kk][3] = pack2_bf16(sc[2 * kk + 1][2], sc[2 * kk + 1][3]);
+  }
+}
+
 // One online-softmax step over the 64 keys [k0, k0 + 64): `lk` / `lv` are the step's four K and
 // four V tiles in LDS.  MASKED = false is the same arithmetic with the comparisons that cannot
 // fail left out: every key of the step is at or below every position of this wave's rows (and
@@ -181,57 +239,7 @@ __device__ __forceinline__ void softmax_step(const uint4* lk, const uint16_t* lv
   u32x4 pf[CB][2];
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
-    if (MASKED) {
-      // a select, not arithmetic: scores of keys past k_hi come from stale tiles and may be anything
-#pragma unroll
-      for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (k0 + b * 16 + g * 4 + e > qpos[cb]) sc[cb][b][e] = -INFINITY;
-    }
-    float mx = fmaxf(fmaxf(sc[cb][0][0], sc[cb][0][1]), sc[cb][0][2]);
-    mx = fmaxf(fmaxf(mx, sc[cb][0][3]), sc[cb][1][0]);
-    mx = fmaxf(fmaxf(mx, sc[cb][1][1]), sc[cb][1][2]);
-    mx = fmaxf(fmaxf(mx, sc[cb][1][3]), sc[cb][2][0]);
-    mx = fmaxf(fmaxf(mx, sc[cb][2][1]), sc[cb][2][2]);
-    mx = fmaxf(fmaxf(mx, sc[cb][2][3]), sc[cb][3][0]);
-    mx = fmaxf(fmaxf(mx, sc[cb][3][1]), sc[cb][3][2]);
-    mx = rows_max(fmaxf(mx, sc[cb][3][3]));
-    // scaling by a positive constant is monotonic: max(scaled) == scaled(max), bit for bit
-    const float m_step = mx * scale_log2;
-    // The partial's reference exponent m moves up to this step's maximum only when that exceeds it by more than
-    // kLazy (then p = exp2(score - m) stays at or below 2^kLazy); otherwise it stands and alpha is exactly 1.
-    // (An empty partial has m = -inf: +inf > kLazy takes the step's maximum; -inf - -inf is NaN and keeps -inf.)
-    const float m_new = (m_step - m[cb] > kLazy) ? m_step : m[cb];
-    const float m_use = (MASKED && m_new == -INFINITY) ? 0.f : m_new;
-    const float alpha = __builtin_amdgcn_exp2f(m[cb] - m_use);
-    float rs = 0.f;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        sc[cb][b][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[cb][b][e], scale_log2, -m_use));
-      rs += ((sc[cb][b][0] + sc[cb][b][1]) + sc[cb][b][2]) + sc[cb][b][3];
-    }
-    rs = rows_sum(rs);
-    // Rescaling by alpha is skipped where it cannot change a bit: in the first step of a partial (l and acc are
-    // zero, and zero times alpha is zero) and where alpha is exactly 1 for every row of the wave.
-    if (!first && __builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-      l[cb] *= alpha;
-#pragma unroll
-      for (int d = 0; d < DB; ++d) acc[cb][d] *= alpha;
-    }
-    l[cb] += rs;
-    m[cb] = m_new;
-    // k-slot e of lane group g is key g*4+e of the first block of a pair (e < 4) or of the
-    // second (e >= 4); V uses the same assignment
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      pf[cb][kk][0] = pack2_bf16(sc[cb][2 * kk][0], sc[cb][2 * kk][1]);
-      pf[cb][kk][1] = pack2_bf16(sc[cb][2 * kk][2], sc[cb][2 * kk][3]);
-      pf[cb][kk][2] = pack2_bf16(sc[cb][2 * kk + 1][0], sc[cb][2 * kk + 1][1]);
-      pf[cb][kk][3] = pack2_bf16(sc[cb][2 * kk + 1][2], sc[cb][2 * kk + 1][3]);
-    }
+    softmax_update<DB, MASKED>(sc[cb], k0, g, qpos[cb], scale_log2, m[cb], l[cb], acc[cb], pf[cb], first);
   }
   // ---- acc^T[feature][query] += V^T P^T, 32 keys per MFMA ------------------------------
   __builtin_amdgcn_sched_barrier(0);
@@ -653,6 +661,168 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
   fetch_wait<0>();                      // the dummy fetches too
 }
 
+// Contexts within one super, for few sequences or few query rows per (sequence, kv head): a workgroup of 4 waves takes ONE
+// block of 16 query rows, wave w walking chunks w and w + 4 on its own - K and V operands straight from global memory into registers, two
+// steps ahead, no ring and no barrier - and the chunk partials are folded through LDS in the schedule's order.  What
+// bounds such a call is the latency of one fetch after the other: four waves in a row of steps each put a whole super's
+// first 512 keys in flight at once.  The K and V of a (sequence, kv head) are fetched once per row block (from L2 after
+// the first), so it is used while the row blocks are few (see attention_mode).
+// A lane takes V 16 bytes at a time: the keys of group g of TWO neighbouring features.  MFMA row c of product h of block
+// pair p is then feature (2 p + c / 8) * 16 + 2 (c % 8) + h, and the lane ends up with 8 consecutive features of its row:
+// (2 p + g / 2) * 16 + (g % 2) * 8 + 2 e + h for e = 0 .. 3.  Which row of the product a feature has does not touch its sum.
+// items == nullptr: item t is of sequence t / per_item (no list to wait for).
+template <int HD>
+__global__ __launch_bounds__(256) void attention_split_kernel(
+    const uint16_t* __restrict__ q, const bf16x8* __restrict__ k_plane, const u32x4* __restrict__ v_plane,
+    const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_len, const int32_t* __restrict__ seq_n,
+    const int4* __restrict__ items, const int32_t* __restrict__ item_count, int num_seqs, int n_kv_heads, int group,
+    int window, int r_pad, int max_blocks_per_seq, float scale_log2, uint16_t* __restrict__ attn_out, int d_attn) {
+  constexpr int DK = HD / 32, DB = HD / 16, TV4 = HD * 2, PER = SUPER_KEYS / CHUNK, NW = 4, SPC = CHUNK / STEP;
+  static_assert(PER == 2 * NW, "two chunks of a super per wave");
+  __shared__ f32x4 fold_acc[PER][DB * 64];
+  __shared__ float2 fold_ml[PER][16];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int col = lane & 15, g = lane >> 4;
+  const int row_blocks = r_pad / 16, per_item = n_kv_heads * row_blocks;
+  const int total = (items ? *item_count : num_seqs) * per_item;
+  for (int t = blockIdx.x; t < total; t += gridDim.x) {
+    const int it = t / per_item, rem = t - it * per_item;
+    const int s = items ? items[it].x : it;
+    const int rb = rem % row_blocks, kvh = rem / row_blocks;
+    // requested before the length is known (clamped to the table, not yet to the sequence): lanes 0 .. 15 the blocks of
+    // the wave's first chunk, 16 .. 31 those of its second
+    const int my_blk = (wave + (g & 1) * NW) * (CHUNK / 16) + col;
+    const int raw = block_table[(size_t)s * max_blocks_per_seq + min(my_blk, max_blocks_per_seq - 1)];
+    bf16x8 qf[DK];
+    const uint16_t* qb = q + ((size_t)s * n_kv_heads + kvh) * r_pad * HD + (size_t)rb * DK * 512;
+#pragma unroll
+    for (int d = 0; d < DK; ++d) qf[d] = *(const bf16x8*)(qb + d * 512 + lane * 8);
+    const int L = seq_len[s], n = seq_n[s];
+    const int row = rb * 16 + col, i = row % window;
+    const int qpos = L >= 0 && row < group * window && i < n ? L + i : -1;
+    int wmax = qpos, wmin = qpos;      // highest and lowest position among the block's rows (dead rows: -1)
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) {
+      wmax = max(wmax, __shfl_xor(wmax, off));
+      wmin = min(wmin, __shfl_xor(wmin, off));
+    }
+    wmax = __builtin_amdgcn_readfirstlane(wmax);
+    wmin = __builtin_amdgcn_readfirstlane(wmin);
+    const int k_hi = wmax + 1;                                             // exclusive; at most SUPER_KEYS
+    const int chunks = (k_hi + CHUNK - 1) / CHUNK;                         // chunks any row looks into (0: no live row)
+    if (wave < chunks) {
+      // this wave's steps: those of chunk `wave`, then those of chunk `wave` + 4
+      auto steps_of = [&](int c) { return c < chunks ? (min(k_hi - c * CHUNK, CHUNK) + STEP - 1) / STEP : 0; };
+      const int steps = steps_of(wave) + steps_of(wave + NW);
+      const int last_blk = (k_hi - 1) >> 4;
+      // blocks past the last needed one: the table may hold anything there, and the steps' last blocks are masked; the
+      // sequence's first block stands in for them
+      const int safe_id = block_table[(size_t)s * max_blocks_per_seq];
+      const int ids = my_blk <= last_blk ? raw : safe_id;
+      bf16x8 ka[4][DK], kc[4][DK];
+      u32x4 va[4][DB / 2], vc[4][DB / 2];
+      auto tile_of = [&](int u, int b) {   // (a step past the wave's last one: the last one once more)
+        const int id = __builtin_amdgcn_readlane(ids, min(u, steps - 1) * 4 + b);
+        return ((size_t)id * n_kv_heads + kvh) * TV4;
+      };
+      auto load_k = [&](bf16x8(&kb)[4][DK], int u) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const bf16x8* p = k_plane + tile_of(u, b) + lane;
+#pragma unroll
+          for (int d = 0; d < DK; ++d) kb[b][d] = p[d * 64];
+        }
+      };
+      auto load_v = [&](u32x4(&vb)[4][DB / 2], int u) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const u32x4* p = v_plane + tile_of(u, b) + ((col >> 3) * 4 + g) * 8 + (col & 7);
+#pragma unroll
+          for (int d = 0; d < DB / 2; ++d) vb[b][d] = p[d * 64];
+        }
+      };
+      float m = -INFINITY, l = 0.f;
+      f32x4 acc[DB];
+#pragma unroll
+      for (int d = 0; d < DB; ++d) acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      auto step = [&](int u, bf16x8(&kb)[4][DK], u32x4(&vb)[4][DB / 2]) __attribute__((always_inline)) {
+        const int c = wave + (u / SPC) * NW, k0 = c * CHUNK + (u % SPC) * STEP;
+        f32x4 sc[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+          for (int d = 0; d < DK; ++d)
+            sc[b] = mfma16(kb[b][d], qf[d], d == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : sc[b]);
+        load_k(kb, u + 2);
+        u32x4 pf[2];
+        const bool inner = k0 + STEP - 1 <= wmin;                          // wave-uniform
+        if (inner) softmax_update<DB, false>(sc, k0, g, qpos, scale_log2, m, l, acc, pf, u % SPC == 0);
+        else softmax_update<DB, true>(sc, k0, g, qpos, scale_log2, m, l, acc, pf, u % SPC == 0);
+        if (!inner) {
+          // slots at or beyond k_hi hold stale, never-written or foreign data: zero, so that 0 * garbage is no NaN
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const int kp = k0 + b * 16 + g * 4;
+#pragma unroll
+            for (int d = 0; d < DB / 2; ++d) {
+              u32x4& v = vb[b][d];
+              if (kp + 0 >= k_hi) v[0] &= 0xFFFF0000u, v[2] &= 0xFFFF0000u;
+              if (kp + 1 >= k_hi) v[0] &= 0x0000FFFFu, v[2] &= 0x0000FFFFu;
+              if (kp + 2 >= k_hi) v[1] &= 0xFFFF0000u, v[3] &= 0xFFFF0000u;
+              if (kp + 3 >= k_hi) v[1] &= 0x0000FFFFu, v[3] &= 0x0000FFFFu;
+            }
+          }
+        }
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+          for (int d = 0; d < DB; ++d) {
+            const u32x4 x = vb[2 * kk][d / 2], y = vb[2 * kk + 1][d / 2];
+            const u32x4 v = d % 2 == 0 ? (u32x4){x[0], x[1], y[0], y[1]} : (u32x4){x[2], x[3], y[2], y[3]};
+            acc[d] = mfma16(__builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, pf[kk]), acc[d]);
+          }
+        load_v(vb, u + 2);
+        if (u % SPC == SPC - 1 || u + 1 == steps) {                        // the chunk is complete
+#pragma unroll
+          for (int d = 0; d < DB; ++d) {
+            fold_acc[c][d * 64 + lane] = acc[d];
+            acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
+          }
+          if (g == 0) fold_ml[c][col] = make_float2(m, l);
+          m = -INFINITY;
+          l = 0.f;
+        }
+      };
+      load_k(ka, 0);
+      load_v(va, 0);
+      load_k(kc, 1);
+      load_v(vc, 1);
+      for (int u = 0; u < steps; u += 2) {
+        step(u, ka, va);
+        if (u + 1 < steps) step(u + 1, kc, vc);
+      }
+    }
+    __syncthreads();
+    // every thread folds the chunks of eight features of one row: chunk 0, 1, 2, ... as in the other kernels
+    if (wave < DB / 2 && qpos >= 0) {
+      float2 ml = fold_ml[0][col];
+      float M = ml.x, Ls = ml.y;
+      f32x4 A[2] = {fold_acc[0][2 * wave * 64 + lane], fold_acc[0][(2 * wave + 1) * 64 + lane]};
+      for (int c = 1; c < chunks; ++c) {
+        ml = fold_ml[c][col];
+        const f32x4 part[2] = {fold_acc[c][2 * wave * 64 + lane], fold_acc[c][(2 * wave + 1) * 64 + lane]};
+        fold<2>(M, Ls, A, ml.x, ml.y, part);
+      }
+      const int f = (2 * wave + g / 2) * 16 + (g & 1) * 8;                 // the first of the lane's 8 features
+      u32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = pack2_bf16(A[0][e] / Ls, A[1][e] / Ls);
+      *(u32x4*)(attn_out + pk_off(s * window + i, (kvh * group + row / window) * HD + f, d_attn)) = o;
+    }
+    __syncthreads();        // the partials are read before the next item's are written
+  }
+}
+
 // The work items of a call: every (sequence, unit) pair that holds keys, as (s, unit, L, n), sorted
 // by the number of 64-key steps it takes, longest first (the attention kernels deal them out in that
 // order, which keeps the tail of a launch short); and the per-layer queue counters.  The order
@@ -855,6 +1025,17 @@ void launch_stream(const llm42_model* m, const uint16_t* kp, const uint16_t* vp,
 }
 
 template <int HD>
+void launch_split(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, const llm42_kv_cache* kv, int num_seqs,
+                  int window, const Workspace& ws, hipStream_t st) {
+  const llm42_config& c = m->cfg;
+  const float scale_log2 = (1.0f / sqrtf((float)c.head_dim)) * 1.44269504088896340736f;
+  const unsigned grid = (unsigned)std::min<long long>(m->num_cus, (long long)num_seqs * c.n_kv_heads * (ws.r_pad / 16));
+  attention_split_kernel<HD><<<grid, 256, 0, st>>>(
+      ws.q, (const bf16x8*)kp, (const u32x4*)vp, kv->block_table, ws.seq_len, ws.seq_n, ws.attn_list ? ws.attn_items : nullptr,
+      ws.attn_ctrl, num_seqs, c.n_kv_heads, m->group, window, ws.r_pad, kv->max_blocks_per_seq, scale_log2, ws.attn, m->d_attn);
+}
+
+template <int HD>
 void launch_hd(const llm42_model* m, int layer, const uint16_t* kp, const uint16_t* vp, const llm42_kv_cache* kv,
                int num_seqs, int window, const Workspace& ws, hipStream_t st) {
   // 8 row blocks or more per (sequence, kv head): 8 waves of one row block each, two per SIMD, so
@@ -862,6 +1043,10 @@ void launch_hd(const llm42_model* m, int layer, const uint16_t* kp, const uint16
   const bool wide = ws.r_pad / 16 >= 8;
   // (a call that may take whole sequences as items launches that kernel too; the plan's choice, made on the device
   // from the lengths, leaves one of the two with nothing to do)
+  if (ws.attn_split) {
+    launch_split<HD>(m, kp, vp, kv, num_seqs, window, ws, st);
+    return;
+  }
   if (ws.attn_seq) launch_stream<HD, true, true, true>(m, kp, vp, kv, num_seqs, window, ws, st);
   if (ws.attn_super) {
     if (wide && ws.batch_chosen) launch_stream<HD, true, false>(m, kp, vp, kv, num_seqs, window, ws, st);
@@ -879,7 +1064,7 @@ void launch_attention_plan(const llm42_model* m, int num_seqs, int max_context, 
   // as a whole-sequence item a unit has as many keys as the longest sequence of the call may have
   const int seq_unit_keys = ws.attn_seq ? (max_context + STEP - 1) / STEP * STEP : 0;
   const int seq_per_item = m->cfg.n_kv_heads * ((ws.r_pad / 16 + 7) / 8);
-  attention_plan_kernel<<<1, 256, 0, st>>>(ws.seq_len, ws.seq_n, num_seqs, ws.attn_super ? SUPER_KEYS : CHUNK,
+  attention_plan_kernel<<<1, 256, 0, st>>>(ws.seq_len, ws.seq_n, num_seqs, ws.attn_super || ws.attn_split ? SUPER_KEYS : CHUNK,
                                            seq_unit_keys, seq_per_item, (int)stream_grid(m, num_seqs, 1, ws.r_pad),
                                            ws.attn_items, ws.attn_ctrl, ws.attn_ctrl + 1, m->cfg.n_layers,
                                            ws.attn_ctrl + 1 + m->cfg.n_layers);

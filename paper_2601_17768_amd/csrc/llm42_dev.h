@@ -97,6 +97,9 @@ struct Workspace {
   bool attn_super; // one workgroup per super (many sequences) instead of per chunk
   bool attn_direct; // every sequence fits one super: the attention kernel writes the final output, no merge pass
   bool attn_seq;    // the call may take whole sequences as attention items (the plan kernel decides from the lengths)
+  bool attn_split;  // whatever the three above say: a workgroup per (sequence, kv head, block of 16 query rows), chunks
+                    // dealt to its waves, output written by the same launch
+  bool attn_list;   // the launches take their items from the plan kernel's list (else: sequence by sequence)
   bool batch_chosen; // off the fixed schedule (fast-path decode step, cost-of-determinism measurement): the batch may
                      // choose the split of the residual projections and the attention partials
   int32_t *row_pos, *row_seq, *seq_len, *seq_n, *dump_slot;

@@ -129,6 +129,8 @@ int padded_rows(int rows) {
   return rows <= 16 ? 16 : rows <= 32 ? 32 : rows <= 64 ? 64 : rows <= 256 ? pad_to(rows, 128) : rows <= 512 ? 512 : pad_to(rows, 256);
 }
 
+ResidLayout resid_layout(int m_pad, int d) { return m_pad <= 512 ? ResidLayout{d, 4} : ResidLayout{4, 64}; }
+
 // Carve the workspace.  Called with base == nullptr to size it.
 Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context, char* base, bool batch_chosen = false,
                 size_t min_part_rows = 0) {
@@ -154,6 +156,7 @@ Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context,
   ws.dump_slot = (int32_t*)take(sizeof(int32_t) * num_seqs);
   ws.row_blk = (int32_t*)take(sizeof(int32_t) * ws.m_pad);
   ws.row_rope = (float2*)take(sizeof(float2) * (size_t)ws.m_pad * (c.head_dim / 2));
+  ws.rl = resid_layout(ws.m_pad, c.d_model);
   ws.resid = (float*)take(4ull * ws.m_pad * c.d_model);
   ws.normed = (uint16_t*)take(2ull * ws.m_pad * c.d_model);
   ws.q = (uint16_t*)take(2ull * num_seqs * c.n_kv_heads * ws.r_pad * c.head_dim);
@@ -168,7 +171,11 @@ Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context,
   ws.attn_ctrl_offset = off;
   ws.attn_ctrl = (int32_t*)take(sizeof(int32_t) * (2 + c.n_layers));
   ws.amax = (float2*)take(8ull * ws.m_pad * (c.vocab / 16));
-  ws.split_part = (float*)take(ws.m_pad > 64 ? 2 * 4ull * ws.m_pad * c.d_model : 0);
+  // (up to 64 rows the halves of a split GEMM live in the arg-max partials where those are large enough: nothing uses them
+  // before the last of the halves has been added)
+  const size_t halves = 2 * 4ull * ws.m_pad * c.d_model;
+  if (ws.m_pad <= 64 && halves <= 8ull * ws.m_pad * (c.vocab / 16)) ws.split_part = (float*)ws.amax;
+  else ws.split_part = (float*)take(halves);
   ws.bytes = off;
   return ws;
 }
@@ -189,20 +196,23 @@ size_t sized_for_up_to(const llm42_model* m, int max_seqs, int window, int max_c
   return carve(m, max_seqs, window, max_context, nullptr, false, part_rows).bytes;
 }
 
-// Layer `ly` behind its attention.
-void run_mlp(const llm42_model* m, const llm42_model::Layer& ly, const Workspace& ws, hipStream_t st) {
+// Layer `ly` behind its attention.  Returns whether the residual stream still lacks the down-projection (see
+// launch_gemm_residual).
+bool run_mlp(const llm42_model* m, const llm42_model::Layer& ly, const Workspace& ws, hipStream_t st) {
   const llm42_config& c = m->cfg;
-  TIMED(LLM42_K_O_PROJ, launch_gemm_residual(ly.wo, ws.attn, ws.resid, c.d_model, m->d_attn, ws, st));
-  TIMED(LLM42_K_RMSNORM, launch_rmsnorm(ws.resid, ly.ffn_norm, ws.normed, ws.m_pad, c.d_model, c.rms_eps, st));
+  bool pending;
+  TIMED(LLM42_K_O_PROJ, pending = launch_gemm_residual(ly.wo, ws.attn, ws.resid, c.d_model, m->d_attn, ws, st));
+  TIMED(LLM42_K_RMSNORM, launch_rmsnorm(pending, ly.ffn_norm, c.d_model, c.rms_eps, ws, st));
   TIMED(LLM42_K_GATE_UP, launch_gemm_swiglu(m, (int)(&ly - m->layers), ws, st));
-  TIMED(LLM42_K_DOWN, launch_gemm_residual(ly.wdown, ws.hidden, ws.resid, c.d_model, m->ffn_k, ws, st));
+  TIMED(LLM42_K_DOWN, pending = launch_gemm_residual(ly.wdown, ws.hidden, ws.resid, c.d_model, m->ffn_k, ws, st));
+  return pending;
 }
 
 // Final norm, LM head and sampler.
-void run_head(const llm42_model* m, int window, int num_seqs, int32_t* out_tokens, float* out_logits,
+void run_head(const llm42_model* m, bool pending, int window, int num_seqs, int32_t* out_tokens, float* out_logits,
               const llm42_sampling* sampling, const Workspace& ws, hipStream_t st) {
   const llm42_config& c = m->cfg;
-  TIMED(LLM42_K_RMSNORM, launch_rmsnorm(ws.resid, m->final_norm, ws.normed, ws.m_pad, c.d_model, c.rms_eps, st));
+  TIMED(LLM42_K_RMSNORM, launch_rmsnorm(pending, m->final_norm, c.d_model, c.rms_eps, ws, st));
   TIMED(LLM42_K_LM_HEAD, launch_gemm_logits(m, window, out_logits, sampling, ws, st));
   TIMED(LLM42_K_ARGMAX, launch_argmax_merge(m, num_seqs, window, out_tokens, ws, st));
 }
@@ -218,15 +228,16 @@ llm42_status run_pass(const llm42_model* m, const llm42_kv_cache* kv, const int3
                                         dump_seq_ids, n_dump, out_tokens, seq_status, ws, st, prefill_pass));
   if (ws.attn_list) TIMED(LLM42_K_PREPARE, launch_attention_plan(m, num_seqs, max_context, ws, st));
   TIMED(LLM42_K_EMBED, launch_embed(m, candidates, ws, st));
+  bool pending = false;
   for (int l = 0; l < c.n_layers; ++l) {
     const llm42_model::Layer& ly = m->layers[l];
-    TIMED(LLM42_K_RMSNORM, launch_rmsnorm(ws.resid, ly.attn_norm, ws.normed, ws.m_pad, c.d_model, c.rms_eps, st));
+    TIMED(LLM42_K_RMSNORM, launch_rmsnorm(pending, ly.attn_norm, c.d_model, c.rms_eps, ws, st));
     TIMED(LLM42_K_QKV, launch_gemm_qkv(m, l, kv, window, ws, st));
     TIMED(LLM42_K_ATTENTION, launch_attention(m, l, kv, num_seqs, window, max_context, ws, st));
     if (prefill_pass && l + 1 == c.n_layers) return LLM42_OK;   // the rest is run once, for the rows that need it (run_tail)
-    run_mlp(m, ly, ws, st);
+    pending = run_mlp(m, ly, ws, st);
   }
-  run_head(m, window, num_seqs, out_tokens, out_logits, sampling, ws, st);
+  run_head(m, pending, window, num_seqs, out_tokens, out_logits, sampling, ws, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(LLM42_EHIP, "verifier pass: launch failed: %s", hipGetErrorString(e));
   return LLM42_OK;
@@ -573,10 +584,12 @@ llm42_status llm42_prefill(const llm42_model* m, const llm42_kv_cache* kv, const
   Workspace tail = ws;
   tail.m_rows = num_seqs;
   tail.m_pad = padded_rows(num_seqs);
+  tail.rl = resid_layout(tail.m_pad, m->cfg.d_model);
   tail.row_pos = x.tail_pos;
   tail.row_seq = x.tail_seq;
   tail.attn = x.tail_attn;
   tail.resid = x.tail_resid;
+  // (the halves of its split GEMMs too: split_part has room for the passes' rows, which are no fewer)
   for (int p = 0; p < passes; ++p) {
     launch_prefill_window(prompt_tokens, prompt_offsets, seq_lens, num_seqs, chunk, p, max_prompt_len, x.cand, x.n_valid,
                           x.lens_now, status, out_next_tokens, st);
@@ -587,8 +600,8 @@ llm42_status llm42_prefill(const llm42_model* m, const llm42_kv_cache* kv, const
     launch_prefill_gather(m, prompt_offsets, num_seqs, chunk, p, max_prompt_len, status, ws, tail, st);
   }
   if (max_prompt_len > 0) {
-    run_mlp(m, m->layers[m->cfg.n_layers - 1], tail, st);
-    run_head(m, 1, num_seqs, out_next_tokens, nullptr, sampling, tail, st);
+    const bool pending = run_mlp(m, m->layers[m->cfg.n_layers - 1], tail, st);
+    run_head(m, pending, 1, num_seqs, out_next_tokens, nullptr, sampling, tail, st);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(LLM42_EHIP, "prefill: launch failed: %s", hipGetErrorString(e));

@@ -97,6 +97,7 @@ struct QkvEpi {
 
 struct ResidualEpi {
   float* resid;   // fp32 residual stream [m_pad][n], updated in place (one lane owns each element)
+  ResidLayout rl;
   int n;
   struct Row {};
   struct Pre {
@@ -104,10 +105,10 @@ struct ResidualEpi {
   };
   __device__ Row row_info(int) const { return Row{}; }
   __device__ Pre pre(int nb, int lane, int row, const Row&) const {
-    return Pre{*(const f32x4*)(resid + resid_off(row, nb * 16 + (lane >> 4) * 4, n))};
+    return Pre{*(const f32x4*)(resid + rl.off(row, nb * 16 + (lane >> 4) * 4, n))};
   }
   __device__ void operator()(int nb, int lane, int row, const f32x4 acc, const Pre& p) const {
-    *(f32x4*)(resid + resid_off(row, nb * 16 + (lane >> 4) * 4, n)) = p.old + acc;
+    *(f32x4*)(resid + rl.off(row, nb * 16 + (lane >> 4) * 4, n)) = p.old + acc;
   }
 };
 
@@ -217,6 +218,7 @@ __host__ __device__ inline int split_point(int k_tiles) { return (k_tiles + 1) /
 // two y-planes of one launch, each with a buffer of its own).
 struct StorePartialEpi {
   float* partial;   // [m_pad][n] in the residual-stream layout
+  ResidLayout rl;
   int n;
   size_t plane;     // distance (floats) from the first half's buffer to the second's
   struct Row {};
@@ -224,84 +226,178 @@ struct StorePartialEpi {
   __device__ Row row_info(int) const { return Row{}; }
   __device__ Pre pre(int, int, int, const Row&) const { return Pre{}; }
   __device__ void operator()(int nb, int lane, int row, const f32x4 acc, const Pre&) const {
-    *(f32x4*)(partial + resid_off(row, nb * 16 + (lane >> 4) * 4, n)) = acc;
+    *(f32x4*)(partial + rl.off(row, nb * 16 + (lane >> 4) * 4, n)) = acc;
   }
 };
 
-// Small-batch kernel for narrow outputs (at most 64 tokens): HBM-bound weight streaming with one
-// workgroup per block of 16 features, so that every CU streams.  SPLIT groups of 4 waves each own
-// one half of the k range.  Inside a group all 4 waves fetch the block's weight tiles, CH k-tiles
-// per round (each wave every 4th tile), and park them in LDS; waves 0 .. MB-1 of the group then
-// each advance one 16-token block's accumulator through the round's tiles in ascending k, with
-// their own activation tiles prefetched in registers.  The next round's weight loads are issued
-// before the current round is consumed.  Only the fetch is spread over the waves; the accumulation
-// order per output element is the one stated above.
-template <int MB, int SPLIT, class Epi>
-__global__ __launch_bounds__(256 * SPLIT) void gemm_coop_kernel(const bf16x8* __restrict__ w,
-                                                                const bf16x8* __restrict__ x, int k_tiles, Epi epi) {
-  constexpr int CH = 32;
-  __shared__ bf16x8 wlds[SPLIT][CH * 64];
-  __shared__ f32x4 merge[MB][64];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int grp = wave >> 2, gw = wave & 3;
-  const int nb = blockIdx.x;
-  const int h = SPLIT == 2 ? split_point(k_tiles) : k_tiles;
-  const int k_begin = grp == 0 ? 0 : h;
-  const int k_count = grp == 0 ? h : k_tiles - h;
-  const int my_rounds = k_count / CH;                // full rounds of this group; the rest is the tail
-  const int rounds = h / CH;                         // group 0 never has fewer than group 1
-  const bf16x8* wp = w + ((size_t)nb * k_tiles + k_begin) * 64 + lane;
-  const bf16x8* xp = x + ((size_t)gw * k_tiles + k_begin) * 64 + lane;   // consumer gw owns token block gw
-  const bool consumer = gw < MB;
+// 1 KiB from global memory (wave-uniform `base` + per-lane byte offset `voff`) straight into LDS at
+// byte address `dst` + 16 * lane (M0 holds the wave-uniform destination).  Written as assembly on
+// purpose: with the compiler's own form of this load every later LDS read waits for all earlier
+// ones, which un-pipelines the operand reads.  The compiler therefore does not count these loads;
+// lds_fetch_wait() is the only wait that covers them.  Nothing else in these kernels uses M0.
+// STREAM marks the load non-temporal (weights that no other workgroup reads).
+template <bool STREAM = false>
+__device__ __forceinline__ void lds_fetch_1k(const void* base, uint32_t voff, uint32_t dst) {
+  if constexpr (STREAM)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" : : "v"(voff), "s"(base), "s"(dst) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(dst) : "memory", "m0");
+}
+// At most N of the fetches this wave has issued are still on their way (they complete in order).
+template <int N>
+__device__ __forceinline__ void lds_fetch_wait() {
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+
+// The fetches of at most `ahead` rounds of PW each are still on their way.
+template <int R, int PW>
+__device__ __forceinline__ void wait_for_rounds(int ahead) {
+  static_assert(R >= 3 && R <= 9 && (R - 2) * PW <= 63, "vmcnt counts up to 63");
+  switch (ahead) {
+    case 1: lds_fetch_wait<PW>(); break;
+    case 2: lds_fetch_wait<(R > 3 ? 2 : 0) * PW>(); break;
+    case 3: lds_fetch_wait<(R > 4 ? 3 : 0) * PW>(); break;
+    case 4: lds_fetch_wait<(R > 5 ? 4 : 0) * PW>(); break;
+    case 5: lds_fetch_wait<(R > 6 ? 5 : 0) * PW>(); break;
+    case 6: lds_fetch_wait<(R > 7 ? 6 : 0) * PW>(); break;
+    case 7: lds_fetch_wait<(R > 8 ? 7 : 0) * PW>(); break;
+    default: lds_fetch_wait<0>();
+  }
+}
+
+// Small-batch kernel for narrow outputs (at most 64 tokens): bound by the weight stream, with one workgroup on every CU.  A
+// workgroup owns NBW blocks of 16 features over one k range (a half of a split GEMM: blockIdx.y) and all MB token blocks.
+// F waves do nothing but fetch: per k-tile the NBW weight and MB activation tiles go from global memory straight into a ring
+// of R rounds of CH k-tiles in LDS; the other NBW * MB waves own one 16 x 16 block each and advance it through the round in
+// ascending k.  One barrier per round: behind it round r has landed, and the slot of round r - 1 is refilled.
+// Two feature blocks share their activation tiles, and the two halves of a split GEMM are workgroups of their own (their
+// sum is taken by the RMSNorm that follows), so a launch of as many workgroups moves half the activation bytes of the
+// kernel this replaces (one block per workgroup, both halves in it): down-projection 25.2 -> 20.5 us at 16 rows,
+// 27.8 -> 22.0 at 32, 33.8 -> 28.7 at 64; O-projection 10.0 -> 7.7, 11.2 -> 8.6, 12.9 -> 10.7; QKV 13.6 -> 10.3,
+// 16.4 -> 14.2, 20.0 -> 17.1 (a dependent read of the weights alone takes 22, 9 and 11 us).
+template <int NBW, int MB, int CH, int R, int F, class Epi>
+__global__ __launch_bounds__(64 * (NBW * MB + F)) void gemm_narrow_kernel(const bf16x8* __restrict__ w,
+                                                                         const bf16x8* __restrict__ x, int n_blocks,
+                                                                         int k_tiles, int split, Epi epi) {
+  constexpr int ST = NBW + MB;                       // operand tiles per k-tile
+  constexpr int PW = CH * ST / F;                    // tiles a fetching wave requests per round
+  static_assert(CH * ST % F == 0, "the fetching waves take equal shares");
+  __shared__ bf16x8 ring[R][CH * ST * 64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int n0 = blockIdx.x * NBW;
+  const int k_begin = blockIdx.y ? split : 0, k_count = blockIdx.y ? k_tiles - split : split;
+  const int rounds = (k_count + CH - 1) / CH;
+  if constexpr (std::is_same<Epi, StorePartialEpi>::value) epi.partial += blockIdx.y * epi.plane;
+  if (wave >= NBW * MB) {
+    const int fw = wave - NBW * MB;
+    const uint32_t dst = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0][0];
+    const bf16x8* src[PW];
+    int kt[PW];
+#pragma unroll
+    for (int i = 0; i < PW; ++i) {
+      const int q = fw * PW + i, op = q % ST;
+      kt[i] = q / ST;
+      src[i] = (op < NBW ? w + (size_t)min(n0 + op, n_blocks - 1) * k_tiles * 64 : x + (size_t)(op - NBW) * k_tiles * 64) + (size_t)k_begin * 64;
+    }
+    auto fetch = [&](int r) {
+#pragma unroll
+      for (int i = 0; i < PW; ++i) {
+        const uint32_t off = (uint32_t)min(r * CH + kt[i], k_count - 1) * 1024u + lane * 16u;
+        const uint32_t d = dst + (uint32_t)(((r % R) * CH * ST + fw * PW + i) * 1024);
+        if ((fw * PW + i) % ST < NBW) lds_fetch_1k<true>(src[i], off, d);
+        else lds_fetch_1k(src[i], off, d);
+      }
+    };
+    for (int r = 0; r < min(R - 1, rounds); ++r) fetch(r);
+    for (int r = 0; r < rounds; ++r) {
+      wait_for_rounds<R, PW>(min(R - 2, rounds - 1 - r));
+      __syncthreads();
+      if (r + R - 1 < rounds) fetch(r + R - 1);
+    }
+    return;
+  }
+  const int bi = wave / MB, bm = wave % MB, nb = n0 + bi, row = bm * 16 + (lane & 15);
+  const typename Epi::Pre pre = epi.pre(min(nb, n_blocks - 1), lane, row, epi.row_info(row));
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  bf16x8 wa[CH / 4], wb[CH / 4], xr[CH];
-  // Weight tiles are requested two rounds ahead (register sets wa / wb alternate), activation tiles
-  // one round ahead.  No load sits behind a per-load condition: the compiler would serialise them.
-  auto load_w = [&](bf16x8(&dst)[CH / 4], int r) {
-    const bf16x8* p = wp + (size_t)r * CH * 64;
-#pragma unroll
-    for (int i = 0; i < CH / 4; ++i) dst[i] = __builtin_nontemporal_load(p + (size_t)(i * 4 + gw) * 64);
-  };
-  auto load_x = [&](int r) {
-    const bf16x8* p = xp + (size_t)r * CH * 64;
-#pragma unroll
-    for (int j = 0; j < CH; ++j) xr[j] = p[(size_t)j * 64];
-  };
-  auto round = [&](bf16x8(&cur)[CH / 4], int r) {   // consume round r (held in cur), refill cur with round r + 2
-    const bool live = r < my_rounds;
-    if (live) {
-#pragma unroll
-      for (int i = 0; i < CH / 4; ++i) wlds[grp][(i * 4 + gw) * 64 + lane] = cur[i];
-    }
+  const int full = k_count / CH;
+  for (int r = 0; r < rounds; ++r) {
     __syncthreads();
-    if (r + 2 < my_rounds) load_w(cur, r + 2);
-    if (consumer && live) {
+    const bf16x8* p = ring[r % R] + lane;
+    if (r < full) {
+      bf16x8 a[CH], b[CH];
 #pragma unroll
-      for (int j = 0; j < CH; ++j) acc = mfma16(wlds[grp][j * 64 + lane], xr[j], acc);
-      if (r + 1 < my_rounds) load_x(r + 1);
+      for (int j = 0; j < CH; ++j) {
+        a[j] = p[(j * ST + bi) * 64];
+        b[j] = p[(j * ST + NBW + bm) * 64];
+      }
+#pragma unroll
+      for (int j = 0; j < CH; ++j) acc = mfma16(a[j], b[j], acc);
+    } else {
+      for (int j = 0; j < k_count - r * CH; ++j) acc = mfma16(p[(j * ST + bi) * 64], p[(j * ST + NBW + bm) * 64], acc);
     }
-    __syncthreads();
-  };
-  if (my_rounds > 0) {
-    load_w(wa, 0);
-    if (consumer) load_x(0);
   }
-  if (my_rounds > 1) load_w(wb, 1);
+  if (nb < n_blocks) epi(nb, lane, row, acc, pre);
+}
+
+// Small-batch kernel for narrow outputs that are NOT split although few workgroups share them (the residual projections of
+// the fast path): one workgroup per block of 16 features.  F waves fetch the block's weight tiles into a ring of R rounds of
+// CH k-tiles in LDS, MB waves own one token block each, with its activation tiles two rounds ahead in registers.  Down-
+// projection 29.9 -> 26.9 us at 32 rows and 37.2 -> 34.1 at 64 against a ring through registers and two barriers a round;
+// gemm_narrow_kernel, on half the CUs here, takes 37 and 45.
+template <int MB, int CH, int R, int F, class Epi>
+__global__ __launch_bounds__(64 * (MB + F)) void gemm_ring_kernel(const bf16x8* __restrict__ w,
+                                                                  const bf16x8* __restrict__ x, int k_tiles, Epi epi) {
+  constexpr int PW = CH / F;                         // weight tiles a fetching wave requests per round
+  static_assert(CH % F == 0, "the fetching waves take equal shares");
+  __shared__ bf16x8 ring[R][CH * 64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const bool consumer = wave < MB;
+  const int nb = blockIdx.x, rounds = k_tiles / CH;  // full rounds; the rest is the tail
+  const bf16x8* wbase = w + (size_t)nb * k_tiles * 64;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   typename Epi::Pre pre{};
-  if (consumer && grp == 0) pre = epi.pre(nb, lane, gw * 16 + (lane & 15), epi.row_info(gw * 16 + (lane & 15)));
-  for (int r = 0; r < rounds; r += 2) {
-    round(wa, r);
-    if (r + 1 < rounds) round(wb, r + 1);
+  if (!consumer) {
+    const int fw = wave - MB;
+    const uint32_t dst = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0][0];
+    auto fetch = [&](int r) {
+#pragma unroll
+      for (int i = 0; i < PW; ++i)
+        lds_fetch_1k<true>(wbase, (uint32_t)((r * CH + i * F + fw) * 1024 + lane * 16), dst + (uint32_t)(((r % R) * CH + i * F + fw) * 1024));
+    };
+    for (int r = 0; r < min(R - 1, rounds); ++r) fetch(r);
+    for (int r = 0; r < rounds; ++r) {
+      wait_for_rounds<R, PW>(min(R - 2, rounds - 1 - r));
+      __syncthreads();                               // round r is in LDS; everyone is done with round r - 1
+      if (r + R - 1 < rounds) fetch(r + R - 1);   // into the slot of round r - 1
+    }
+  } else {
+    const bf16x8* xp = x + (size_t)wave * k_tiles * 64 + lane;
+    const int row = wave * 16 + (lane & 15);
+    bf16x8 xa[CH], xb[CH];
+    auto load_x = [&](bf16x8(&dst)[CH], int r) __attribute__((always_inline)) {
+      const bf16x8* p = xp + (size_t)min(r, rounds - 1) * CH * 64;   // (past the last round: the last one again)
+#pragma unroll
+      for (int j = 0; j < CH; ++j) dst[j] = p[(size_t)j * 64];
+    };
+    auto body = [&](bf16x8(&cur)[CH], int r) __attribute__((always_inline)) {
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < CH; ++j) acc = mfma16(ring[r % R][j * 64 + lane], cur[j], acc);
+      load_x(cur, r + 2);
+    };
+    pre = epi.pre(nb, lane, row, epi.row_info(row));
+    if (rounds > 0) {
+      load_x(xa, 0);
+      load_x(xb, 1);
+    }
+    for (int r = 0; r < rounds; r += 2) {
+      body(xa, r);
+      if (r + 1 < rounds) body(xb, r + 1);
+    }
+    const bf16x8* wp = wbase + lane;                 // tail of fewer than CH tiles: tile by tile
+    for (int kt = rounds * CH; kt < k_tiles; ++kt) acc = mfma16(wp[(size_t)kt * 64], xp[(size_t)kt * 64], acc);
   }
-  if (consumer) {   // tail of fewer than CH tiles (model dimensions that are no multiple of 1024): tile by tile
-    for (int kt = my_rounds * CH; kt < k_count; ++kt) acc = mfma16(wp[(size_t)kt * 64], xp[(size_t)kt * 64], acc);
-  }
-  if (SPLIT == 2) {
-    if (consumer && grp == 1) merge[gw][lane] = acc;
-    __syncthreads();
-    if (consumer && grp == 0) acc = acc + merge[gw][lane];
-  }
-  if (consumer && grp == 0) epi(nb, lane, gw * 16 + (lane & 15), acc, pre);
+  if (consumer) epi(nb, lane, wave * 16 + (lane & 15), acc, pre);
 }
 
 // Small-batch kernel for wide outputs (at most 64 tokens): 8 waves per workgroup, every wave owns
@@ -468,14 +564,6 @@ __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restri
 // of the super-tile.
 // Accumulation order per output element: k ascending inside [k_begin, k_begin + k_count), exactly
 // as in the small-batch kernels; with ADD_PARTIAL the other half's fp32 partial is added at the end.
-// 1 KiB from global memory (wave-uniform `base` + per-lane byte offset `voff`) straight into LDS at
-// byte address `dst` + 16 * lane (M0 holds the wave-uniform destination).  Written as assembly on
-// purpose: with the compiler's own form of this load every later LDS read waits for all earlier
-// ones, which un-pipelines the operand reads.  The compiler therefore does not count these loads;
-// lds_fetch_wait() is the only wait that covers them.  Nothing else in these kernels uses M0.
-__device__ __forceinline__ void lds_fetch_1k(const void* base, uint32_t voff, uint32_t dst) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(dst) : "memory", "m0");
-}
 // acc += a * b with the accumulator pinned to the same four accumulation registers before and after.
 // (Left to the compiler, some instantiations of the tiled kernel compute into a temporary and copy
 // it back - four moves behind every MFMA of the main loop.)  The compiler does not know that this is
@@ -485,12 +573,6 @@ __device__ __forceinline__ void mfma16_inplace(const bf16x8 a, const bf16x8 b, f
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 __device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
-
-// At most N of the fetches this wave has issued are still on their way (they complete in order).
-template <int N>
-__device__ __forceinline__ void lds_fetch_wait() {
-  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
 
 template <int WBN, int WBM, int NST, int WGS, bool ADD_PARTIAL, class Epi, int WN = 2>
 __global__ __launch_bounds__(128 * WN, WGS) void gemm_tiled_kernel(const bf16x8* __restrict__ w, const bf16x8* __restrict__ x,
@@ -621,7 +703,7 @@ __global__ __launch_bounds__(128 * WN, WGS) void gemm_tiled_kernel(const bf16x8*
       const int nb = n0 + wn * WBN + i;
       if (nb < n_blocks) {
         f32x4 v = acc[i][j];
-        if (ADD_PARTIAL) v = v + *(const f32x4*)(partial + resid_off(row, nb * 16 + (lane >> 4) * 4, n));
+        if constexpr (ADD_PARTIAL) v = v + *(const f32x4*)(partial + epi.rl.off(row, nb * 16 + (lane >> 4) * 4, n));
         epi(nb, lane, row, v, epi.pre(nb, lane, row, ri));
       }
     }
@@ -629,22 +711,8 @@ __global__ __launch_bounds__(128 * WN, WGS) void gemm_tiled_kernel(const bf16x8*
   }
 }
 
-// p0 + p1 of a split GEMM whose halves ran side by side, handed to the GEMM's epilogue with the
-// same (feature block, lane, row) ownership as in the GEMM kernels: one wave per 16 x 16 block.
-template <class Epi>
-__global__ __launch_bounds__(256) void split_combine_kernel(const float* __restrict__ p0, const float* __restrict__ p1,
-                                                            int n_blocks, int n, Epi epi) {
-  const int lane = threadIdx.x & 63;
-  const int nb = blockIdx.x * 4 + (threadIdx.x >> 6), row = blockIdx.y * 16 + (lane & 15);
-  if (nb >= n_blocks) return;
-  const size_t off = resid_off(row, nb * 16 + (lane >> 4) * 4, n);
-  const typename Epi::Pre pre = epi.pre(nb, lane, row, epi.row_info(row));
-  const f32x4 v = *(const f32x4*)(p0 + off) + *(const f32x4*)(p1 + off);
-  epi(nb, lane, row, v, pre);
-}
-
-// side_by_side (split GEMMs only): both k-halves in one launch of twice the workgroups plus a small
-// combining pass, instead of two launches one after the other - for launches that do not fill the
+// side_by_side (split GEMMs only): both k-halves in one launch of twice the workgroups, their sum left to the RMSNorm that
+// follows, instead of two launches one after the other - for launches that do not fill the
 // device by themselves.  The arithmetic per output element is the same either way.
 template <int WBN, int WBM, int NST, int WGS, int SPLIT, class Epi, int WN = 2>
 void launch_tiled(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, int n, const Workspace& ws,
@@ -680,24 +748,22 @@ void launch_tiled(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles,
       }
     }
   const unsigned grid = 8u * (unsigned)g * (unsigned)((supers + 7) / 8);
-  if (SPLIT == 1) {
+  if constexpr (SPLIT == 1) {
     gemm_tiled_kernel<WBN, WBM, NST, WGS, false, Epi, WN><<<grid, threads, 0, st>>>(wp, xp, n_blocks, k_tiles, 0, k_tiles,
                                                                                     nullptr, n, tiles_n, tiles_m, sm, g, 1, epi);
-    return;
-  }
+  } else {
   const int h = split_point(k_tiles);
   const size_t plane = (size_t)ws.m_pad * n;
-  StorePartialEpi pe{ws.split_part, n, plane};
+  StorePartialEpi pe{ws.split_part, ws.rl, n, plane};
   if (side_by_side) {
     gemm_tiled_kernel<WBN, WBM, NST, WGS, false, StorePartialEpi, WN><<<grid, threads, 0, st>>>(
         wp, xp, n_blocks, k_tiles, 0, h, nullptr, n, tiles_n, tiles_m, sm, g, 2, pe);
-    split_combine_kernel<Epi><<<dim3((n_blocks + 3) / 4, ws.m_pad / 16), 256, 0, st>>>(ws.split_part, ws.split_part + plane,
-                                                                                      n_blocks, n, epi);
   } else {
     gemm_tiled_kernel<WBN, WBM, NST, WGS, false, StorePartialEpi, WN><<<grid, threads, 0, st>>>(
         wp, xp, n_blocks, k_tiles, h, k_tiles - h, nullptr, n, tiles_n, tiles_m, sm, g, 1, pe);
     gemm_tiled_kernel<WBN, WBM, NST, WGS, true, Epi, WN><<<grid, threads, 0, st>>>(wp, xp, n_blocks, k_tiles, 0, h, ws.split_part,
                                                                                    n, tiles_n, tiles_m, sm, g, 1, epi);
+  }
   }
 }
 
@@ -709,7 +775,30 @@ enum GemmKind { GEMM_QKV = 0, GEMM_RESIDUAL = 1, GEMM_GATE_UP = 2, GEMM_LOGITS =
 constexpr int kSplit[4] = {1, 2, 1, 1};
 
 template <int SPLIT, class Epi>
-void launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padded, int n, const Workspace& ws,
+void launch_narrow(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, int n, const Workspace& ws, const Epi& epi,
+                   hipStream_t st) {
+  if constexpr (SPLIT == 1 && std::is_same<Epi, ResidualEpi>::value) {
+    if (ws.m_pad == 16) gemm_ring_kernel<1, 16, 5, 2, Epi><<<n_blocks, 64 * 3, 0, st>>>(wp, xp, k_tiles, epi);
+    else if (ws.m_pad == 32) gemm_ring_kernel<2, 16, 5, 2, Epi><<<n_blocks, 64 * 4, 0, st>>>(wp, xp, k_tiles, epi);
+    else gemm_ring_kernel<4, 16, 5, 2, Epi><<<n_blocks, 64 * 6, 0, st>>>(wp, xp, k_tiles, epi);
+  } else {
+    const int split = SPLIT == 2 ? split_point(k_tiles) : k_tiles;
+    const dim3 grid((n_blocks + 1) / 2, SPLIT);
+    auto go = [&](const auto& e) {
+      using E = std::decay_t<decltype(e)>;
+      // (ring depths within a few percent of each other: what counts is four fetching waves and few barriers)
+      if (ws.m_pad == 16) gemm_narrow_kernel<2, 1, 8, 4, 4, E><<<grid, 64 * 6, 0, st>>>(wp, xp, n_blocks, k_tiles, split, e);
+      else if (ws.m_pad == 32) gemm_narrow_kernel<2, 2, 4, 5, 4, E><<<grid, 64 * 8, 0, st>>>(wp, xp, n_blocks, k_tiles, split, e);
+      else gemm_narrow_kernel<2, 4, 4, 6, 4, E><<<grid, 64 * 12, 0, st>>>(wp, xp, n_blocks, k_tiles, split, e);
+    };
+    if constexpr (SPLIT == 2) go(StorePartialEpi{ws.split_part, ws.rl, n, (size_t)ws.m_pad * n});
+    else go(epi);
+  }
+}
+
+// Returns whether a split GEMM left its two halves in split_part.
+template <int SPLIT, class Epi>
+bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padded, int n, const Workspace& ws,
                  bool wide, const Epi& epi, hipStream_t st) {
   const int k_tiles = k_padded / 32, m_pad = ws.m_pad;
   const bf16x8* wp = (const bf16x8*)w;
@@ -730,11 +819,9 @@ void launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
         else gemm_xshare_kernel<4, 8, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
       }
     } else {
-      if (m_pad == 16) gemm_coop_kernel<1, SPLIT, Epi><<<n_blocks, 256 * SPLIT, 0, st>>>(wp, xp, k_tiles, epi);
-      else if (m_pad == 32) gemm_coop_kernel<2, SPLIT, Epi><<<n_blocks, 256 * SPLIT, 0, st>>>(wp, xp, k_tiles, epi);
-      else gemm_coop_kernel<4, SPLIT, Epi><<<n_blocks, 256 * SPLIT, 0, st>>>(wp, xp, k_tiles, epi);
+      launch_narrow<SPLIT>(wp, xp, n_blocks, k_tiles, n, ws, epi, st);
     }
-    return;
+    return SPLIT == 2;
   }
   // More than 64 tokens: m_pad is 128, 256 or 512, or a multiple of 256 beyond that.  Larger tiles
   // move fewer operand bytes per flop, smaller ones give more workgroups; measured over 128 .. 4096 rows
@@ -757,7 +844,7 @@ void launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
     // launches (not on gate/up, whose 128 x 128 tiles already fill the device twice over).
     if (m_pad == 768 || m_pad == 1024 || (kQkv && m_pad == 1280)) {
       launch_tiled<2, 8, 6, 1, SPLIT, Epi, 4>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, side_by_side);
-      return;
+      return side_by_side;
     }
   }
   if constexpr (kQkv) {
@@ -769,7 +856,7 @@ void launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
     const bool whole_rounds = n_blocks % 12 == 0 && t192 % (2 * cus) == 0 && t256 % (2 * cus) != 0;
     if (whole_rounds || (!big && n_blocks % 12 == 0 && t192 <= 2 * cus && t128 > 2 * cus)) {
       launch_tiled<6, 4, 4, 2, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, false);
-      return;
+      return side_by_side;
     }
   }
   if (big)
@@ -778,6 +865,7 @@ void launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
     launch_tiled<4, 4, 4, 2, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, side_by_side);
   else
     launch_tiled<2, 4, 12, 1, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, side_by_side);
+  return side_by_side;
 }
 
 }  // namespace
@@ -803,13 +891,13 @@ void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, 
   launch_gemm<kSplit[GEMM_QKV]>(m->layers[layer].wqkv, ws.normed, m->n_qkv / 16, c.d_model, m->n_qkv, ws, false, e, st);
 }
 
-void launch_gemm_residual(const uint16_t* w, const uint16_t* x, float* resid, int n, int k_padded,
+bool launch_gemm_residual(const uint16_t* w, const uint16_t* x, float* resid, int n, int k_padded,
                           const Workspace& ws, hipStream_t st) {
-  ResidualEpi e{resid, n};
+  ResidualEpi e{resid, ws.rl, n};
   // Off the fixed schedule (fast path, cost-of-determinism measurement) the split follows the batch,
   // as in an ordinary engine: two halves while there are few rows to spread over the device, none beyond.
-  if (ws.batch_chosen && ws.m_rows > 16) launch_gemm<1>(w, x, n / 16, k_padded, n, ws, false, e, st);
-  else launch_gemm<kSplit[GEMM_RESIDUAL]>(w, x, n / 16, k_padded, n, ws, false, e, st);
+  if (ws.batch_chosen && ws.m_rows > 16) return launch_gemm<1>(w, x, n / 16, k_padded, n, ws, false, e, st);
+  return launch_gemm<kSplit[GEMM_RESIDUAL]>(w, x, n / 16, k_padded, n, ws, false, e, st);
 }
 
 void launch_gemm_swiglu(const llm42_model* m, int layer, const Workspace& ws, hipStream_t st) {

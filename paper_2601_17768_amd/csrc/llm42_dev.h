@@ -31,12 +31,15 @@ __host__ __device__ inline size_t pk_off(int r, int c, int c_padded) {
          (size_t)((((c & 31) >> 3) * 16 + (r & 15)) * 8 + (c & 7));
 }
 
-// Residual stream: fp32, [token block of 16][feature group of 4][token][4], so the four
-// consecutive features a lane owns after a GEMM are one 16-byte access and a wave's
-// accesses are contiguous.
-__host__ __device__ inline size_t resid_off(int row, int feat, int n) {
-  return (((size_t)(row >> 4) * (size_t)(n >> 2) + (size_t)(feat >> 2)) * 16 + (size_t)(row & 15)) * 4 + (feat & 3);
-}
+// Residual stream and the halves of a split GEMM: fp32, in pieces of four consecutive features of a row (what a GEMM's lane
+// owns).  Few rows: row-major, rs = n and fs = 4, so that a row of the RMSNorm is one contiguous run.  Many rows: the 16
+// rows of a token block interleaved, rs = 4 and fs = 64, so that a wave of a GEMM's epilogue accesses 1 KiB in one run.
+struct ResidLayout {
+  int rs, fs;   // floats from a row to the next of its block of 16, from a group of four features to the next
+  __host__ __device__ size_t off(int row, int feat, int n) const {
+    return (size_t)(row >> 4) * 16 * (size_t)n + (size_t)((row & 15) * rs) + (size_t)(feat >> 2) * fs + (feat & 3);
+  }
+};
 
 __device__ inline float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
 
@@ -106,13 +109,14 @@ struct Workspace {
   int32_t* row_blk;    // physical KV block that holds the row's position (0 for dead rows)
   float2* row_rope;    // [m_pad][head_dim/2] (cos, sin) at the row's position
   float* resid;
+  ResidLayout rl;      // of resid and split_part
   uint16_t *normed, *q, *attn, *hidden;
   float *part_acc, *part_ml;
   int4* attn_items;     // (sequence, unit, length, rows) of every unit that holds keys, built once per call
   int32_t* attn_ctrl;   // [0] number of items, [1 + layer] work queue counter of that layer's attention launch,
                         // [1 + n_layers] 1 if the items are whole sequences
   size_t attn_ctrl_offset;   // byte offset of attn_ctrl in the workspace
-  float* split_part;   // fp32 partials of a split GEMM on the large-batch path, [2][m_pad][d_model]
+  float* split_part;   // fp32 halves of a split GEMM, [2][m_pad][d_model]
   float2* amax;   // [m_pad][vocab/16] (value, index bits)
   size_t bytes;
 };
@@ -137,12 +141,13 @@ void launch_prefill_gather(const llm42_model* m, const int32_t* prompt_offsets, 
                            int max_prompt_len, const int32_t* seq_status, const Workspace& ws, const Workspace& tail,
                            hipStream_t st);
 void launch_embed(const llm42_model* m, const int32_t* candidates, const Workspace& ws, hipStream_t st);
-void launch_rmsnorm(const float* x, const uint16_t* gain, uint16_t* y, int m_pad, int d, float eps,
-                    hipStream_t st);
+// pending: the last residual GEMM left its halves in split_part (what launch_gemm_residual returned)
+void launch_rmsnorm(bool pending, const uint16_t* gain, int d, float eps, const Workspace& ws, hipStream_t st);
 
 void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, int window, const Workspace& ws,
                      hipStream_t st);
-void launch_gemm_residual(const uint16_t* w, const uint16_t* x, float* resid, int n, int k_padded,
+// true: the residual stream is not complete yet; the halves are in split_part, for the RMSNorm that follows
+bool launch_gemm_residual(const uint16_t* w, const uint16_t* x, float* resid, int n, int k_padded,
                           const Workspace& ws, hipStream_t st);
 void launch_gemm_swiglu(const llm42_model* m, int layer, const Workspace& ws, hipStream_t st);
 void launch_gemm_logits(const llm42_model* m, int window, float* out_logits, const llm42_sampling* sampling,

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256) void prefill_gather_kernel(const int32_t* __re
                                                              const int32_t* __restrict__ row_pos,
                                                              const uint16_t* __restrict__ attn, int d_attn,
                                                              const float* __restrict__ resid, int d,
-                                                             int32_t* __restrict__ tail_pos, int32_t* __restrict__ tail_seq,
+                                                             ResidLayout rl, ResidLayout tail_rl, int32_t* __restrict__ tail_pos, int32_t* __restrict__ tail_seq,
                                                              uint16_t* __restrict__ tail_attn, float* __restrict__ tail_resid) {
   const int s = blockIdx.x;
   int row = -1;
@@ -137,14 +137,15 @@ __global__ __launch_bounds__(256) void prefill_gather_kernel(const int32_t* __re
   for (int c = threadIdx.x * 8; c < d_attn; c += 256 * 8)
     *(uint4*)(tail_attn + pk_off(s, c, d_attn)) = live ? *(const uint4*)(attn + pk_off(row, c, d_attn)) : make_uint4(0, 0, 0, 0);
   for (int f = threadIdx.x * 4; f < d; f += 256 * 4)
-    *(f32x4*)(tail_resid + resid_off(s, f, d)) = live ? *(const f32x4*)(resid + resid_off(row, f, d)) : (f32x4){0.f, 0.f, 0.f, 0.f};
+    *(f32x4*)(tail_resid + tail_rl.off(s, f, d)) = live ? *(const f32x4*)(resid + rl.off(row, f, d)) : (f32x4){0.f, 0.f, 0.f, 0.f};
 }
 
 // One wave per 16 rows x 32 features of the residual stream: lane
 // (row = lane % 16, g = lane / 16) converts 8 features of its row's embedding to
 // fp32 (exact).  Dead rows get zeros so that everything downstream stays finite.
 __global__ void embed_kernel(const uint16_t* __restrict__ table, const int32_t* __restrict__ candidates,
-                             const int32_t* __restrict__ row_pos, int m_rows, int d, float* __restrict__ resid) {
+                             const int32_t* __restrict__ row_pos, int m_rows, int d, float* __restrict__ resid,
+                             ResidLayout rl) {
   const int col_tiles = d / 32;
   const size_t tile = (size_t)blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
   const int lane = threadIdx.x & 63;
@@ -160,8 +161,8 @@ __global__ void embed_kernel(const uint16_t* __restrict__ table, const int32_t* 
               bf16_bits_to_f32(v.y >> 16)};
   f32x4 hi = {bf16_bits_to_f32(v.z & 0xFFFFu), bf16_bits_to_f32(v.z >> 16), bf16_bits_to_f32(v.w & 0xFFFFu),
               bf16_bits_to_f32(v.w >> 16)};
-  *(f32x4*)(resid + resid_off(row, feat, d)) = lo;
-  *(f32x4*)(resid + resid_off(row, feat + 4, d)) = hi;
+  *(f32x4*)(resid + rl.off(row, feat, d)) = lo;
+  *(f32x4*)(resid + rl.off(row, feat + 4, d)) = hi;
 }
 
 // Sum of the 64 per-lane partial sums of squares of a row (lane w*4+g owns p[w][g]) in the fixed
@@ -185,6 +186,28 @@ __device__ inline void emit_normed(uint4* yr, int f, const f32x4 a, const f32x4 
   yr[(f >> 5) * 64 + ((f & 31) >> 3) * 16] = o;
 }
 
+// The pending halves of a split GEMM added to U tiles (t0, t0 + 16, ...) of a row's residual stream, which go back to
+// memory: old + (p0 + p1), as everywhere.
+template <int U>
+__device__ __forceinline__ void add_pending(float* __restrict__ xr, const float* __restrict__ p0, const float* __restrict__ p1,
+                                            int fs, int t0, int g, f32x4 (&a)[U], f32x4 (&b)[U]) {
+  f32x4 q0[U], q1[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int o = ((t0 + u * 16) * 8 + g * 2) * fs;
+    q0[u] = *(const f32x4*)(p0 + o) + *(const f32x4*)(p1 + o);
+    q1[u] = *(const f32x4*)(p0 + o + fs) + *(const f32x4*)(p1 + o + fs);
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int o = ((t0 + u * 16) * 8 + g * 2) * fs;
+    a[u] = a[u] + q0[u];
+    b[u] = b[u] + q1[u];
+    *(f32x4*)(xr + o) = a[u];
+    *(f32x4*)(xr + o + fs) = b[u];
+  }
+}
+
 // RMSNorm, one wave per row (1 or 4 rows per workgroup); fp32 residual stream in, bf16
 // tile layout (the next GEMM's activation operand) out.
 // Reduction schedule per row (a function of d only): 64 partial sums p[w][g],
@@ -192,7 +215,13 @@ __device__ inline void emit_normed(uint4* yr, int f, const f32x4 a, const f32x4 
 // of features t*32 + g*8 .. +7 for t = w, w+16, w+32, ...; then per w the four g
 // are added as (p[w][g] + p[w][g^1]) + (p[w][g^2] + p[w][g^3]), and the 16 results
 // are added in ascending w.  Lane w*4+g of the row's wave owns p[w][g].
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ x, const uint16_t* __restrict__ gain,
+// PEND: the residual GEMM before left its two k-halves in p0 and p1 instead of adding them: the stream is
+// x + (p0 + p1), and goes back to x.  (A pass over the stream that reads it anyway; the combining launch that it replaces
+// was 4 us at 256 rows and 20 us at 2048, twice a layer.)
+template <bool PEND>
+__global__ __launch_bounds__(256) void rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ p0,
+                                                      const float* __restrict__ p1, ResidLayout rl,
+                                                      const uint16_t* __restrict__ gain,
                                                       uint16_t* __restrict__ y, int m_pad, int d, float eps) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -201,7 +230,9 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
   const int col_tiles = d / 32;
   constexpr int U = 8;                                   // tiles in flight per lane
   const int full = col_tiles / (16 * U);                 // rounds in which every lane has U tiles
-  const float* xr = x + resid_off(row, 0, d);            // feature f of this row: xr + (f / 4) * 64 + f % 4
+  const size_t ro = rl.off(row, 0, d);
+  const int fs = rl.fs;
+  float* xr = x + ro;                                    // features f .. f + 3 of this row: xr + (f / 4) * fs
   uint4* yr = (uint4*)(y + pk_off(row, 0, d));           // 8 features from f (f % 8 == 0): yr + (f/32)*64 + ((f%32)/8)*16
   float ss = 0.f;
   // (no load sits behind a per-load condition: the compiler would serialise such loads)
@@ -212,10 +243,11 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int f = (u * 16 + w) * 32 + g * 8;
-      a[u] = *(const f32x4*)(xr + (f >> 2) * 64);
-      b[u] = *(const f32x4*)(xr + (f >> 2) * 64 + 64);
+      a[u] = *(const f32x4*)(xr + (f >> 2) * fs);
+      b[u] = *(const f32x4*)(xr + (f >> 2) * fs + fs);
       gv[u] = *(const uint4*)(gain + f);
     }
+    if (PEND) add_pending<U>(xr, p0 + ro, p1 + ro, fs, w, g, a, b);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
@@ -233,9 +265,10 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int f = ((rd * U + u) * 16 + w) * 32 + g * 8;
-      a[u] = *(const f32x4*)(xr + (f >> 2) * 64);
-      b[u] = *(const f32x4*)(xr + (f >> 2) * 64 + 64);
+      a[u] = *(const f32x4*)(xr + (f >> 2) * fs);
+      b[u] = *(const f32x4*)(xr + (f >> 2) * fs + fs);
     }
+    if (PEND) add_pending<U>(xr, p0 + ro, p1 + ro, fs, rd * U * 16 + w, g, a, b);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
@@ -246,11 +279,12 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
   }
   for (int t = full * U * 16 + w; t < col_tiles; t += 16) {
     const int f = t * 32 + g * 8;
-    const f32x4 a = *(const f32x4*)(xr + (f >> 2) * 64), b = *(const f32x4*)(xr + (f >> 2) * 64 + 64);
+    f32x4 a[1] = {*(const f32x4*)(xr + (f >> 2) * fs)}, b[1] = {*(const f32x4*)(xr + (f >> 2) * fs + fs)};
+    if (PEND) add_pending<1>(xr, p0 + ro, p1 + ro, fs, t, g, a, b);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ss = __builtin_fmaf(a[i], a[i], ss);
+    for (int i = 0; i < 4; ++i) ss = __builtin_fmaf(a[0][i], a[0][i], ss);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ss = __builtin_fmaf(b[i], b[i], ss);
+    for (int i = 0; i < 4; ++i) ss = __builtin_fmaf(b[0][i], b[0][i], ss);
   }
   const float inv = row_inv_rms(ss, d, eps);
   for (int rd = 0; rd < full; ++rd) {
@@ -259,8 +293,8 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int f = ((rd * U + u) * 16 + w) * 32 + g * 8;
-      a[u] = *(const f32x4*)(xr + (f >> 2) * 64);
-      b[u] = *(const f32x4*)(xr + (f >> 2) * 64 + 64);
+      a[u] = *(const f32x4*)(xr + (f >> 2) * fs);
+      b[u] = *(const f32x4*)(xr + (f >> 2) * fs + fs);
       gv[u] = *(const uint4*)(gain + f);
     }
 #pragma unroll
@@ -268,7 +302,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
   }
   for (int t = full * U * 16 + w; t < col_tiles; t += 16) {
     const int f = t * 32 + g * 8;
-    emit_normed(yr, f, *(const f32x4*)(xr + (f >> 2) * 64), *(const f32x4*)(xr + (f >> 2) * 64 + 64),
+    emit_normed(yr, f, *(const f32x4*)(xr + (f >> 2) * fs), *(const f32x4*)(xr + (f >> 2) * fs + fs),
                 *(const uint4*)(gain + f), inv);
   }
 }
@@ -276,10 +310,11 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
 // RMSNorm at d = 4096: one workgroup of 64 R threads per R neighbouring rows, thread
 // (w, g, r) owning the partial sum p[w][g] of row r - the same 64 partials per row, accumulated in
 // the same order and combined in the same tree as in rmsnorm_kernel, so the bits are the same; only
-// the work distribution differs.  R (4, 8 or 16; see launch_rmsnorm) trades CUs at work against the length of the
-// contiguous runs (16 R bytes) that a workgroup reads and writes in the token-interleaved layouts.
-template <int R>
-__global__ __launch_bounds__(64 * R) void rmsnorm_block_kernel(const float* __restrict__ x,
+// the work distribution differs.  R (see launch_rmsnorm) trades CUs at work against the length of the
+// contiguous runs (16 R bytes) that a workgroup writes in the tile layout, and reads where the rows are interleaved.
+template <int R, bool PEND>
+__global__ __launch_bounds__(64 * R) void rmsnorm_block_kernel(float* __restrict__ x, const float* __restrict__ p0,
+                                                               const float* __restrict__ p1, ResidLayout rl,
                                                                const uint16_t* __restrict__ gain,
                                                                uint16_t* __restrict__ y, float eps) {
   constexpr int D = 4096, U = 8;                         // tiles of 32 features per thread: t = u * 16 + w
@@ -287,17 +322,20 @@ __global__ __launch_bounds__(64 * R) void rmsnorm_block_kernel(const float* __re
   __shared__ float inv_s[R];
   const int r = threadIdx.x % R, wg = threadIdx.x / R, w = wg >> 2, g = wg & 3;
   const int row = blockIdx.x * R + r;
-  const float* xr = x + resid_off(row, 0, D);
+  const size_t ro = rl.off(row, 0, D);
+  const int fs = rl.fs;
+  float* xr = x + ro;
   uint4* yr = (uint4*)(y + pk_off(row, 0, D));
   f32x4 a[U], b[U];
   uint4 gv[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int f = (u * 16 + w) * 32 + g * 8;
-    a[u] = *(const f32x4*)(xr + (f >> 2) * 64);
-    b[u] = *(const f32x4*)(xr + (f >> 2) * 64 + 64);
+    a[u] = *(const f32x4*)(xr + (f >> 2) * fs);
+    b[u] = *(const f32x4*)(xr + (f >> 2) * fs + fs);
     gv[u] = *(const uint4*)(gain + f);
   }
+  if (PEND) add_pending<U>(xr, p0 + ro, p1 + ro, fs, w, g, a, b);
   float ss = 0.f;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -351,29 +389,40 @@ void launch_prefill_gather(const llm42_model* m, const int32_t* prompt_offsets, 
                            int max_prompt_len, const int32_t* seq_status, const Workspace& ws, const Workspace& tail,
                            hipStream_t st) {
   prefill_gather_kernel<<<tail.m_pad, 256, 0, st>>>(prompt_offsets, window, chunk_index, num_seqs, max_prompt_len, seq_status,
-                                                    ws.row_pos, ws.attn, m->d_attn, ws.resid, m->cfg.d_model, tail.row_pos,
+                                                    ws.row_pos, ws.attn, m->d_attn, ws.resid, m->cfg.d_model, ws.rl, tail.rl, tail.row_pos,
                                                     tail.row_seq, tail.attn, tail.resid);
 }
 
 void launch_embed(const llm42_model* m, const int32_t* candidates, const Workspace& ws, hipStream_t st) {
   const int tiles = ws.m_pad / 16 * (m->cfg.d_model / 32);   // a multiple of 4 (d_model % 128 == 0 is checked)
-  embed_kernel<<<tiles / 4, 256, 0, st>>>(m->embed, candidates, ws.row_pos, ws.m_rows, m->cfg.d_model, ws.resid);
+  embed_kernel<<<tiles / 4, 256, 0, st>>>(m->embed, candidates, ws.row_pos, ws.m_rows, m->cfg.d_model, ws.resid, ws.rl);
 }
 
-void launch_rmsnorm(const float* x, const uint16_t* gain, uint16_t* y, int m_pad, int d, float eps,
-                    hipStream_t st) {
-  // us per launch, wave per row | 4 | 8 | 16 rows per workgroup (back to back, residual stream in the caches):
-  //   128 rows 3.8 | 3.4 | 4.3 | 6.3      256 rows 6.7 | 3.5 | 4.5 | 6.5      512 rows 6.7 | 4.4 | 4.7 | 6.7
-  //   1024 rows 10.6 | 8.2 | 5.7 | 7.3    1536 rows 15.8 | 10.8 | 7.7 | 7.9   2048 rows 17.8 | 13.4 | 9.3 | 8.5
-  //   4096 rows 31.5 | 25.6 | 16.8 | 17.1
-  // Few rows are bound by how many CUs load; many by lines that two workgroups fetch (4 rows take half of a 128-byte
-  // line, a single row an eighth).  Around 2048 rows 16 rows per workgroup still fill half the CUs and have the longest runs.
-  if (d == 4096 && m_pad >= 128) {
-    if (m_pad <= 512) rmsnorm_block_kernel<4><<<m_pad / 4, 256, 0, st>>>(x, gain, y, eps);
-    else if (m_pad <= 1536 || m_pad > 2560) rmsnorm_block_kernel<8><<<m_pad / 8, 512, 0, st>>>(x, gain, y, eps);
-    else rmsnorm_block_kernel<16><<<m_pad / 16, 1024, 0, st>>>(x, gain, y, eps);
+template <bool PEND>
+static void launch_norm(float* x, const float* p0, const float* p1, ResidLayout rl, const uint16_t* gain, uint16_t* y, int m_pad, int d,
+                        float eps, hipStream_t st) {
+  // us per launch behind a launch that wrote the operands (they come from other XCDs' writes then), by the rows per workgroup
+  // (1: a wave per row, 4 waves a workgroup from 512 rows on), without | with pending halves:
+  //                  row-major                                 token blocks interleaved
+  //           1            2            4            8         |  4            8            16
+  //    128    3.4 |  4.2   3.4 |  5.0   4.6 |  9.3   6.8 | 16.6 |  4.1 |  7.9   4.4 |  7.8   6.6 | 14.4
+  //    256    5.3 |  7.7   4.7 |  7.6   5.7 | 11.8   7.9 | 19.0 |  5.5 |  9.4   5.5 | 10.2   7.7 | 16.3
+  //    512    7.7 | 10.9   7.4 | 12.5   7.4 | 12.7   9.6 | 19.5 |  8.2 | 11.6   7.3 | 11.4   9.4 | 20.2
+  //   1024   12.0 | 19.9  11.7 | 16.8  10.8 | 19.4  12.3 | 23.9 | 10.4 | 20.9  10.7 | 13.7  12.4 | 20.2
+  //   2048   19.8 | 28.5  20.0 | 27.0  17.8 | 29.3  18.0 | 27.0 | 15.5 | 43.5  11.5 | 25.8  19.6 | 24.1
+  //   4096   27.1 | 52.0  26.9 | 53.4  25.2 | 52.2  24.6 | 52.2 | 29.2 | 82.3  21.6 | 47.3  23.8 | 46.2
+  // Few rows are bound by what a CU pulls from beyond its L2 (20 - 25 GB/s) and want as many CUs as there are, many rows by
+  // the length of the runs that they read and write.
+  if (d == 4096 && m_pad > 128 && !(PEND && m_pad > 256 && m_pad <= 512)) {
+    if (m_pad <= 512) rmsnorm_block_kernel<2, PEND><<<m_pad / 2, 128, 0, st>>>(x, p0, p1, rl, gain, y, eps);
+    else rmsnorm_block_kernel<8, PEND><<<m_pad / 8, 512, 0, st>>>(x, p0, p1, rl, gain, y, eps);
   }
-  // few rows: one wave per workgroup, so that the rows' loads are spread over as many CUs as there are rows
-  else if (m_pad <= 256) rmsnorm_kernel<<<m_pad, 64, 0, st>>>(x, gain, y, m_pad, d, eps);
-  else rmsnorm_kernel<<<(m_pad + 3) / 4, 256, 0, st>>>(x, gain, y, m_pad, d, eps);
+  else if (m_pad <= 256) rmsnorm_kernel<PEND><<<m_pad, 64, 0, st>>>(x, p0, p1, rl, gain, y, m_pad, d, eps);
+  else rmsnorm_kernel<PEND><<<(m_pad + 3) / 4, 256, 0, st>>>(x, p0, p1, rl, gain, y, m_pad, d, eps);
+}
+
+void launch_rmsnorm(bool pending, const uint16_t* gain, int d, float eps, const Workspace& ws, hipStream_t st) {
+  const float* p0 = ws.split_part;
+  if (pending) launch_norm<true>(ws.resid, p0, p0 + (size_t)ws.m_pad * d, ws.rl, gain, ws.normed, ws.m_pad, d, eps, st);
+  else launch_norm<false>(ws.resid, nullptr, nullptr, ws.rl, gain, ws.normed, ws.m_pad, d, eps, st);
 }

@@ -549,10 +549,135 @@ __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restri
   }
 }
 
-// Large-batch kernel (more than 64 tokens): MFMA-bound, LDS-tiled.  A workgroup of 2*WN waves (WN along
-// the features x 2 along the tokens; WN = 2 unless stated) owns a tile of 16*WN*WBN features x 32*WBM
+// Kernel for 65 to 1280 tokens: a tile of WN * WBN feature blocks x WM * WBM token blocks per workgroup, with waves that do
+// nothing but fetch, as in gemm_narrow_kernel: F of them move a round of CH k-tiles at a time into a ring of R rounds in LDS,
+// WN x WM others own WBN x WBM blocks each and advance them in ascending k.  Here a launch has one workgroup per CU (two of
+// the 128 x 128 tile), and what bounds it is that one's LDS port (operand tiles in, WBN + WBM of them out per WBN * WBM
+// MFMAs), its share of L2 and the barrier per round; without fetch instructions and waits between their MFMAs, and with 8
+// waves where gemm_tiled_kernel has 4, the consumers get through a round faster.  PRE: round r + 1 has landed, too, when
+// round r begins, so the first operands of a round are read before the barrier that opens it (one round less in flight).
+// us per launch within a pass (events), gemm_tiled_kernel -> this, 8B shapes:
+//            QKV            O-projection   down-projection   gate/up          LM head
+//    128     35.8 -> 25.4   20.7 -> 16.6    53.4 ->  42.0    59.2 ->  58.3     250 ->  227
+//    256     35.7 -> 29.6   21.1 -> 18.8    53.7 ->  48.3    75.7 ->  71.8     349 ->  316
+//    512     47.5 -> 44.0   26.6 -> 26.0    70.0 ->  69.9   113.1    117.4     594 ->  513
+//    768     67.1 -> 55.4   35.8 -> 33.9   100.4 ->  95.7   168.0    171.7     799 ->  759
+//   1024     67.7 -> 57.1   37.4 -> 37.1   103.9 -> 104.5   210.5    229.9    1040 -> 1013
+//   1280     71.8 -> 67.4   60.4 -> 57.8   180.7 -> 163.4   264.2    282.0    1325 -> 1250
+//   1792     98.9    107.9  63.8    67.0   181.7    188.7   349.3    386.3    1946 -> 1702
+//   4096    191.3    206.6                                  705.9    842.5    4314 -> 4289
+// Workgroup ids are dealt round-robin to the 8 XCDs; each XCD takes a contiguous run of the tiles, token tiles fastest, so
+// that the tiles that share weights share an L2.
+template <int WN, int WM, int WBN, int WBM, int CH, int R, int F, int WGS, bool PRE, class Epi>
+__global__ __launch_bounds__(64 * (WN * WM + F), (WGS * (WN * WM + F) + 3) / 4) void gemm_mid_kernel(
+    const bf16x8* __restrict__ w, const bf16x8* __restrict__ x, int n_blocks, int k_tiles, int split, int planes, int tiles_n,
+    int tiles_m, int per_xcd, Epi epi) {
+  constexpr int TBN = WN * WBN, TBM = WM * WBM, ST = TBN + TBM;
+  constexpr int PW = CH * ST / F;                    // tiles a fetching wave requests per round
+  static_assert(CH * ST % F == 0, "the fetching waves take equal shares");
+  static_assert(CH == 1 || CH % 2 == 0, "operand registers alternate");
+  __shared__ bf16x8 ring[R][CH * ST * 64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), all = tiles_n * tiles_m;
+  const int plane = tile / all, at = tile - plane * all;
+  if (plane >= planes) return;
+  const int n0 = at / tiles_m * TBN, m0 = at % tiles_m * TBM;      // first feature / token block of the tile
+  const int k_begin = plane ? split : 0, k_count = plane ? k_tiles - split : split;
+  const int rounds = (k_count + CH - 1) / CH;
+  if constexpr (std::is_same<Epi, StorePartialEpi>::value) epi.partial += plane * epi.plane;
+  if (wave >= WN * WM) {
+    const int fw = wave - WN * WM;
+    const uint32_t dst = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0][0];
+    const bf16x8* src[PW];
+#pragma unroll
+    for (int i = 0; i < PW; ++i) {
+      const int op = (fw * PW + i) % ST;             // feature blocks past the matrix re-read the last one
+      src[i] = (op < TBN ? w + (size_t)min(n0 + op, n_blocks - 1) * k_tiles * 64 : x + (size_t)(m0 + op - TBN) * k_tiles * 64) +
+               (size_t)k_begin * 64;
+    }
+    auto fetch = [&](int r) {                        // (k-tiles past the range re-read the last one)
+#pragma unroll
+      for (int i = 0; i < PW; ++i)
+        lds_fetch_1k(src[i], (uint32_t)min(r * CH + (fw * PW + i) / ST, k_count - 1) * 1024u + lane * 16u,
+                     dst + (uint32_t)(((r % R) * CH * ST + fw * PW + i) * 1024));
+    };
+    for (int r = 0; r < min(R - 1, rounds); ++r) fetch(r);
+    for (int r = 0; r < rounds; ++r) {
+      wait_for_rounds<R, PW>(max(0, min(R - 2 - PRE, rounds - 1 - PRE - r)));
+      __syncthreads();                               // round r (PRE: and r + 1) is in LDS; everyone is done with round r - 1
+      if (r + R - 1 < rounds) fetch(r + R - 1);      // into the slot of round r - 1
+    }
+    return;
+  }
+  const int wn = wave / WM, wm = wave % WM;
+  f32x4 acc[WBN][WBM];
+#pragma unroll
+  for (int i = 0; i < WBN; ++i)
+#pragma unroll
+    for (int j = 0; j < WBM; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  bf16x8 a[2][WBN], b[2][WBM];
+  auto operands = [&](int r, int j, int set) __attribute__((always_inline)) {
+    const bf16x8* p = ring[r % R] + lane;
+#pragma unroll
+    for (int i = 0; i < WBN; ++i) a[set][i] = p[(j * ST + wn * WBN + i) * 64];
+#pragma unroll
+    for (int i = 0; i < WBM; ++i) b[set][i] = p[(j * ST + TBN + wm * WBM + i) * 64];
+  };
+  auto multiply = [&](int set) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < WBM; ++j)
+#pragma unroll
+      for (int i = 0; i < WBN; ++i) acc[i][j] = mfma16(a[set][i], b[set][j], acc[i][j]);
+  };
+  // the k-tiles of round r, operand sets alternating from `set`; the next k-tile's operands are requested ahead of the
+  // MFMAs (the scheduling barriers keep the compiler from sinking the reads next to their uses)
+  auto round = [&](int r, auto set) __attribute__((always_inline)) {
+    constexpr int S = decltype(set)::value;
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+      if (j + 1 < CH) operands(r, j + 1, (S + j + 1) & 1);
+      else if (PRE) operands(r + 1, 0, (S + j + 1) & 1);           // (behind the last round: a stale tile that nothing uses)
+      __builtin_amdgcn_sched_barrier(0);
+      if (CH == 1 || r * CH + j < k_count) multiply((S + j) & 1);  // (the last round may be partial)
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  using First = std::integral_constant<int, 0>;
+  using Second = std::integral_constant<int, 1>;
+  if constexpr (PRE) {
+    __syncthreads();
+    operands(0, 0, 0);
+    int r = 0;
+    for (; r + 1 < rounds; r += 2) {
+      round(r, First{});
+      __syncthreads();
+      round(r + 1, std::conditional_t<CH == 1, Second, First>{});
+      if (r + 2 < rounds) __syncthreads();
+    }
+    if (r < rounds) round(r, First{});
+  } else {
+    for (int r = 0; r < rounds; ++r) {
+      __syncthreads();
+      operands(r, 0, 0);
+      round(r, First{});
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < WBM; ++j) {
+    const int row = (m0 + wm * WBM + j) * 16 + (lane & 15);
+    const typename Epi::Row ri = epi.row_info(row);
+#pragma unroll
+    for (int i = 0; i < WBN; ++i) {
+      const int nb = n0 + wn * WBN + i;
+      if (nb < n_blocks) epi(nb, lane, row, acc[i][j], epi.pre(nb, lane, row, ri));
+    }
+    __builtin_amdgcn_sched_barrier(0);               // one token block at a time, to keep the registers for two workgroups
+  }
+}
+
+// Large-batch kernel: MFMA-bound, LDS-tiled.  A workgroup of 2 x 2 waves owns a tile of 32*WBN features x 32*WBM
 // tokens; each wave owns WBN x WBM MFMA blocks (WBN*WBM*4
-// accumulator registers).  Per stage of one k-tile the waves move the tile's WN*WBN + 2*WBM operand
+// accumulator registers).  Per stage of one k-tile the waves move the tile's 2*WBN + 2*WBM operand
 // tiles (1 KiB each, already in MFMA operand order) from global memory straight into a ring of NST
 // stages in LDS; every wave reads its WBN weight operands and WBM activation operands per k-tile
 // with conflict-free 16-byte LDS reads.  WGS workgroups share a CU: one wave per SIMD cannot keep
@@ -574,15 +699,14 @@ __device__ __forceinline__ void mfma16_inplace(const bf16x8 a, const bf16x8 b, f
 }
 __device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 
-template <int WBN, int WBM, int NST, int WGS, bool ADD_PARTIAL, class Epi, int WN = 2>
-__global__ __launch_bounds__(128 * WN, WGS) void gemm_tiled_kernel(const bf16x8* __restrict__ w, const bf16x8* __restrict__ x,
+template <int WBN, int WBM, int NST, int WGS, bool ADD_PARTIAL, class Epi>
+__global__ __launch_bounds__(256, WGS) void gemm_tiled_kernel(const bf16x8* __restrict__ w, const bf16x8* __restrict__ x,
                                                          int n_blocks, int k_tiles, int k_begin, int k_count,
                                                          const float* __restrict__ partial, int n, int tiles_n,
                                                          int tiles_m, int sm_tiles, int group_tiles, int planes, Epi epi) {
-  constexpr int TBN = WN * WBN, TBM = 2 * WBM;  // 16-row blocks per tile side (features, tokens)
+  constexpr int TBN = 2 * WBN, TBM = 2 * WBM;   // 16-row blocks per tile side (features, tokens)
   constexpr int ST = TBN + TBM;                 // operand tiles per stage of one k-tile (weights then activations)
-  constexpr int NWV = 2 * WN;                   // waves per workgroup: WN along the features x 2 along the tokens
-  constexpr int PW = (ST + NWV - 1) / NWV;      // operand tiles each wave fetches per stage (where ST is no multiple of
+  constexpr int PW = (ST + 3) / 4;              // operand tiles each wave fetches per stage (where ST is no multiple of
                                                 // the wave count the last waves fetch the stage's last tile again: the same
                                                 // bytes to the same place, which keeps every wave's fetch count the same)
   // NST = ring of stages in LDS
@@ -714,11 +838,11 @@ __global__ __launch_bounds__(128 * WN, WGS) void gemm_tiled_kernel(const bf16x8*
 // side_by_side (split GEMMs only): both k-halves in one launch of twice the workgroups, their sum left to the RMSNorm that
 // follows, instead of two launches one after the other - for launches that do not fill the
 // device by themselves.  The arithmetic per output element is the same either way.
-template <int WBN, int WBM, int NST, int WGS, int SPLIT, class Epi, int WN = 2>
+template <int WBN, int WBM, int NST, int WGS, int SPLIT, class Epi>
 void launch_tiled(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, int n, const Workspace& ws,
                   const Epi& epi, hipStream_t st, bool side_by_side = false) {
-  const int tiles_n = (n_blocks + WN * WBN - 1) / (WN * WBN), tiles_m = ws.m_pad / (32 * WBM);
-  constexpr unsigned threads = 128 * WN;
+  const int tiles_n = (n_blocks + 2 * WBN - 1) / (2 * WBN), tiles_m = ws.m_pad / (32 * WBM);
+  constexpr unsigned threads = 256;
   const int planes = SPLIT == 2 && side_by_side ? 2 : 1;
   // Super-tiles of g = sn x sm tiles (see the kernel), dealt round-robin to the 8 XCDs.  sm: as square as the tiles
   // allow (a 128 x 256 tile counts double on the token side), but the widest that leaves at most 15 % of the token
@@ -726,7 +850,7 @@ void launch_tiled(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles,
   // with free LDS before they can leave (1280 rows took as long as 2048 that way; a column of width 1 on the other
   // hand makes every XCD fetch 32 weight tiles per k-step, which cost 4 % at 1792 rows).  g: the largest of 32, 16, 8, 4 that leaves
   // the busiest XCD within 3 % of the least workgroup slots any of them gives it (few super-tiles deal out unevenly).
-  const int sm_max = 2 * WBM > WN * WBN ? 4 : 8;
+  const int sm_max = 2 * WBM > 2 * WBN ? 4 : 8;
   int g = 4, sm = 1, sn = 4, supers = 0;
   long long least = -1;
   for (int pass = 0; pass < 2; ++pass)
@@ -749,19 +873,19 @@ void launch_tiled(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles,
     }
   const unsigned grid = 8u * (unsigned)g * (unsigned)((supers + 7) / 8);
   if constexpr (SPLIT == 1) {
-    gemm_tiled_kernel<WBN, WBM, NST, WGS, false, Epi, WN><<<grid, threads, 0, st>>>(wp, xp, n_blocks, k_tiles, 0, k_tiles,
+    gemm_tiled_kernel<WBN, WBM, NST, WGS, false, Epi><<<grid, threads, 0, st>>>(wp, xp, n_blocks, k_tiles, 0, k_tiles,
                                                                                     nullptr, n, tiles_n, tiles_m, sm, g, 1, epi);
   } else {
   const int h = split_point(k_tiles);
   const size_t plane = (size_t)ws.m_pad * n;
   StorePartialEpi pe{ws.split_part, ws.rl, n, plane};
   if (side_by_side) {
-    gemm_tiled_kernel<WBN, WBM, NST, WGS, false, StorePartialEpi, WN><<<grid, threads, 0, st>>>(
+    gemm_tiled_kernel<WBN, WBM, NST, WGS, false, StorePartialEpi><<<grid, threads, 0, st>>>(
         wp, xp, n_blocks, k_tiles, 0, h, nullptr, n, tiles_n, tiles_m, sm, g, 2, pe);
   } else {
-    gemm_tiled_kernel<WBN, WBM, NST, WGS, false, StorePartialEpi, WN><<<grid, threads, 0, st>>>(
+    gemm_tiled_kernel<WBN, WBM, NST, WGS, false, StorePartialEpi><<<grid, threads, 0, st>>>(
         wp, xp, n_blocks, k_tiles, h, k_tiles - h, nullptr, n, tiles_n, tiles_m, sm, g, 1, pe);
-    gemm_tiled_kernel<WBN, WBM, NST, WGS, true, Epi, WN><<<grid, threads, 0, st>>>(wp, xp, n_blocks, k_tiles, 0, h, ws.split_part,
+    gemm_tiled_kernel<WBN, WBM, NST, WGS, true, Epi><<<grid, threads, 0, st>>>(wp, xp, n_blocks, k_tiles, 0, h, ws.split_part,
                                                                                    n, tiles_n, tiles_m, sm, g, 1, epi);
   }
   }
@@ -796,6 +920,52 @@ void launch_narrow(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles
   }
 }
 
+// Tiles of gemm_mid_kernel, in blocks of 16, and what they cost in 1/100 us per k-tile, fitted to launches within a pass
+// (the table at gemm_mid_kernel holds the best of each): one round of up to one workgroup per CU takes base + slope x its
+// share of the CUs, each of several rounds `more`.  A CU holds two of the 128 x 128 tile.
+struct MidTile {
+  int bn, bm, base, slope, more;
+};
+constexpr MidTile kMidTiles[6] = {{4, 4, 18, 0, 17}, {4, 8, 21, 0, 20}, {8, 8, 31, 0, 27}, {12, 8, 44, 0, 38}, {16, 8, 39, 7, 46}, {8, 16, 28, 19, 46}};
+
+// The cheapest of them for n_blocks x m_pad rows, `planes` times over.
+inline int pick_mid(int n_blocks, int m_pad, int planes, long long cus) {
+  int best = 0;
+  long long least = 0;
+  for (int t = 0; t < 6; ++t) {
+    const MidTile& q = kMidTiles[t];
+    if (m_pad % (16 * q.bm)) continue;
+    const long long tiles = (long long)((n_blocks + q.bn - 1) / q.bn) * (m_pad / (16 * q.bm)) * planes;
+    const long long rounds = (tiles + cus - 1) / cus;
+    const bool few_over = t == 2 && rounds == 2 && tiles * 4 <= cus * 5;   // (most CUs still have one 128 x 128 tile)
+    const long long cost = rounds == 1 ? q.base * 10 + q.slope * 10 * tiles / cus : few_over ? 460 : q.more * 10 * rounds;
+    if (t == 0 || cost < least) best = t, least = cost;
+  }
+  return best;
+}
+
+template <int WN, int WM, int WBN, int WBM, int CH, int R, int F, int WGS, bool PRE, class Epi>
+void launch_mid_tile(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, int split, int planes, int m_pad,
+                     const Epi& epi, hipStream_t st) {
+  const int tiles_n = (n_blocks + WN * WBN - 1) / (WN * WBN), tiles_m = m_pad / (16 * WM * WBM);
+  const int per_xcd = (tiles_n * tiles_m * planes + 7) / 8;
+  gemm_mid_kernel<WN, WM, WBN, WBM, CH, R, F, WGS, PRE, Epi><<<8 * per_xcd, 64 * (WN * WM + F), 0, st>>>(
+      wp, xp, n_blocks, k_tiles, split, planes, tiles_n, tiles_m, per_xcd, epi);
+}
+
+template <class Epi>
+void launch_mid(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, int split, int planes, int m_pad,
+                const Epi& epi, hipStream_t st) {
+  switch (tile) {
+    case 0: return launch_mid_tile<2, 2, 2, 2, 4, 4, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, m_pad, epi, st);
+    case 1: return launch_mid_tile<2, 4, 2, 2, 4, 3, 4, 1, false>(wp, xp, n_blocks, k_tiles, split, planes, m_pad, epi, st);
+    case 2: return launch_mid_tile<4, 2, 2, 4, 1, 5, 4, 2, false>(wp, xp, n_blocks, k_tiles, split, planes, m_pad, epi, st);
+    case 3: return launch_mid_tile<4, 2, 3, 4, 1, 6, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, m_pad, epi, st);
+    case 4: return launch_mid_tile<4, 2, 4, 4, 1, 5, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, m_pad, epi, st);
+    default: return launch_mid_tile<2, 4, 4, 4, 1, 6, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, m_pad, epi, st);
+  }
+}
+
 // Returns whether a split GEMM left its two halves in split_part.
 template <int SPLIT, class Epi>
 bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padded, int n, const Workspace& ws,
@@ -823,49 +993,52 @@ bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
     }
     return SPLIT == 2;
   }
-  // More than 64 tokens: m_pad is 128, 256 or 512, or a multiple of 256 beyond that.  Larger tiles
-  // move fewer operand bytes per flop, smaller ones give more workgroups; measured over 128 .. 4096 rows
-  // of the 8B shapes, the best choice is the largest tile that still yields about as many workgroups as
-  // the device has CUs.  Where the epilogue is heavy (rotary embedding and cache writes) the 128 x 256
-  // tile waits until it fills the device, since its epilogues overlap less with other workgroups' main
-  // loops; the LM head never takes it.  A split GEMM runs its halves side by side unless each half
-  // fills the device by itself.
+  constexpr bool kLogits = std::is_same<Epi, LogitsEpi>::value, kQkv = std::is_same<Epi, QkvEpi>::value;
   const long long cus = ws.num_cus;
   const long long t256 = m_pad % 256 == 0 ? (long long)((n_blocks + 7) / 8) * (m_pad / 256) : 0;
   const long long t128 = (long long)((n_blocks + 7) / 8) * (m_pad / 128);
-  const bool side_by_side = SPLIT == 2 && t256 < 2 * cus;
-  const int p = side_by_side ? 2 : 1;
-  constexpr bool kLogits = std::is_same<Epi, LogitsEpi>::value, kQkv = std::is_same<Epi, QkvEpi>::value;
-  const bool big = !kLogits && (kQkv ? t256 >= 2 * cus : t256 * p * 5 >= 4 * cus);
-  if constexpr (!std::is_same<Epi, SwigluEpi>::value) {
-    // 768 and 1024 rows (and 1280 of the QKV projection): too few 128 x 256 tiles for two workgroups per CU, and one
-    // workgroup of four waves per CU keeps neither the MFMA pipe nor the fetch path busy.  The same tile with EIGHT
-    // waves (32 x 128 per wave, one workgroup per CU, six stages in flight) measured 3 - 13 % faster on these
-    // launches (not on gate/up, whose 128 x 128 tiles already fill the device twice over).
-    if (m_pad == 768 || m_pad == 1024 || (kQkv && m_pad == 1280)) {
-      launch_tiled<2, 8, 6, 1, SPLIT, Epi, 4>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, side_by_side);
-      return side_by_side;
-    }
+  // The ranges where gemm_mid_kernel is the faster one: up to 1280 rows for QKV and the split projections; up to 256 for
+  // gate/up, whose launches have enough 128 x 256 tiles for two workgroups per CU of gemm_tiled_kernel beyond that; any
+  // number for the LM head (1 - 14 %), there with the tile that re-reads the activations least: 128 x 256 for 256 - 2048 rows,
+  // 256 x 128 otherwise (2560 rows: 2541 us against 2862, 8192: 8318 against 10782; 2048: 2095 against 2061).
+  if (kLogits || m_pad <= (std::is_same<Epi, SwigluEpi>::value ? 256 : 1280)) {
+    const int tile = !kLogits ? pick_mid(n_blocks, m_pad, SPLIT, cus) : m_pad % 256 == 0 && m_pad <= 2048 ? 5 : 4;
+    if constexpr (SPLIT == 2)
+      launch_mid(tile, wp, xp, n_blocks, k_tiles, split_point(k_tiles), 2, m_pad,
+                 StorePartialEpi{ws.split_part, ws.rl, n, (size_t)m_pad * n}, st);
+    else launch_mid(tile, wp, xp, n_blocks, k_tiles, k_tiles, 1, m_pad, epi, st);
+    return SPLIT == 2;
   }
-  if constexpr (kQkv) {
-    // A 192 x 128 tile where it puts the whole QKV projection into one round of workgroups (two per CU) and the
-    // 128 x 128 tile would need a second one: 2048 rows of the 8B shape are 512 such tiles (3.67 -> 3.24 ms per pass).
-    const long long t192 = (long long)((n_blocks + 11) / 12) * (m_pad / 128);
-    // ... and where 192 x 128 tiles make whole rounds and 128 x 256 tiles do not (4096 rows: 1024 against 768 tiles,
-    // 6.20 -> 6.10 ms per pass; 6144 rows: 9.54 -> 8.85).
-    const bool whole_rounds = n_blocks % 12 == 0 && t192 % (2 * cus) == 0 && t256 % (2 * cus) != 0;
-    if (whole_rounds || (!big && n_blocks % 12 == 0 && t192 <= 2 * cus && t128 > 2 * cus)) {
-      launch_tiled<6, 4, 4, 2, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, false);
-      return side_by_side;
+  if constexpr (!kLogits) {
+    // More rows (m_pad is a multiple of 256 here).  Larger tiles
+    // move fewer operand bytes per flop, smaller ones give more workgroups; the best choice is the largest tile that still
+    // yields about as many workgroups as
+    // the device has CUs.  Where the epilogue is heavy (rotary embedding and cache writes) the 128 x 256
+    // tile waits until it fills the device, since its epilogues overlap less with other workgroups' main
+    // loops.  A split GEMM runs its halves side by side unless each half
+    // fills the device by itself.
+    const bool side_by_side = SPLIT == 2 && t256 < 2 * cus;
+    const int p = side_by_side ? 2 : 1;
+    const bool big = kQkv ? t256 >= 2 * cus : t256 * p * 5 >= 4 * cus;
+    if constexpr (kQkv) {
+      // A 192 x 128 tile where it puts the whole QKV projection into one round of workgroups (two per CU) and the
+      // 128 x 128 tile would need a second one: 2048 rows of the 8B shape are 512 such tiles (3.67 -> 3.24 ms per pass).
+      const long long t192 = (long long)((n_blocks + 11) / 12) * (m_pad / 128);
+      // ... and where 192 x 128 tiles make whole rounds and 128 x 256 tiles do not (4096 rows: 1024 against 768 tiles,
+      // 6.20 -> 6.10 ms per pass; 6144 rows: 9.54 -> 8.85).
+      const bool whole_rounds = n_blocks % 12 == 0 && t192 % (2 * cus) == 0 && t256 % (2 * cus) != 0;
+      if (whole_rounds || (!big && n_blocks % 12 == 0 && t192 <= 2 * cus && t128 > 2 * cus)) {
+        launch_tiled<6, 4, 4, 2, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, false);
+        return side_by_side;
+      }
     }
+    if (big)
+      launch_tiled<LLM42_TILE_BIG, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, side_by_side);
+    else
+      launch_tiled<4, 4, 4, 2, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, side_by_side);
+    return side_by_side;
   }
-  if (big)
-    launch_tiled<LLM42_TILE_BIG, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, side_by_side);
-  else if (t128 * p * 4 >= 3 * cus)
-    launch_tiled<4, 4, 4, 2, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, side_by_side);
-  else
-    launch_tiled<2, 4, 12, 1, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, side_by_side);
-  return side_by_side;
+  return false;
 }
 
 }  // namespace

@@ -169,7 +169,7 @@ Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context,
   ws.part_ml = (float*)take(8ull * part_rows);
   ws.attn_items = (int4*)take(sizeof(int4) * std::max((size_t)num_seqs * ws.attn_units, min_part_rows / ((size_t)c.n_kv_heads * ws.r_pad)));
   ws.attn_ctrl_offset = off;
-  ws.attn_ctrl = (int32_t*)take(sizeof(int32_t) * (2 + c.n_layers));
+  ws.attn_ctrl = (int32_t*)take(sizeof(int32_t) * (3 + c.n_layers));
   ws.amax = (float2*)take(8ull * ws.m_pad * (c.vocab / 16));
   // (up to 64 rows the halves of a split GEMM live in the arg-max partials where those are large enough: nothing uses them
   // before the last of the halves has been added)
@@ -222,12 +222,15 @@ void run_head(const llm42_model* m, bool pending, int window, int num_seqs, int3
 llm42_status run_pass(const llm42_model* m, const llm42_kv_cache* kv, const int32_t* seq_lens, const int32_t* candidates,
                       int window, const int32_t* n_valid, int num_seqs, int max_context, int32_t* out_tokens,
                       int32_t* seq_status, float* out_logits, const int32_t* dump_seq_ids, int n_dump,
-                      const Workspace& ws, hipStream_t st, const llm42_sampling* sampling, bool prefill_pass) {
+                      Workspace& ws, hipStream_t st, const llm42_sampling* sampling, bool prefill_pass) {
   const llm42_config& c = m->cfg;
+  // Partly filled windows: the rows are packed, and what pads the end of the grid is skipped.  (Each workgroup of the prepare
+  // launch adds up the counts before it, so not for very many sequences.)
+  ws.live = n_valid && num_seqs <= 4096 ? ws.attn_ctrl + 2 + c.n_layers : nullptr;
   TIMED(LLM42_K_PREPARE, launch_prepare(m, kv, seq_lens, candidates, n_valid, num_seqs, window, max_context,
                                         dump_seq_ids, n_dump, out_tokens, seq_status, ws, st, prefill_pass));
   if (ws.attn_list) TIMED(LLM42_K_PREPARE, launch_attention_plan(m, num_seqs, max_context, ws, st));
-  TIMED(LLM42_K_EMBED, launch_embed(m, candidates, ws, st));
+  TIMED(LLM42_K_EMBED, launch_embed(m, candidates, window, ws, st));
   bool pending = false;
   for (int l = 0; l < c.n_layers; ++l) {
     const llm42_model::Layer& ly = m->layers[l];
@@ -296,7 +299,7 @@ llm42_status verify_impl(const char* who, const llm42_model* m, const llm42_kv_c
     return fail(LLM42_ECAPACITY, "%s: max_context %d exceeds block-table capacity %lld", who, max_context,
                 (long long)kv->max_blocks_per_seq * LLM42_KV_BLOCK);
   if ((uintptr_t)workspace % 256) return fail(LLM42_EWORKSPACE, "%s: workspace not 256-byte aligned", who);
-  const Workspace ws = carve(m, num_seqs, window, max_context, (char*)workspace, batch_chosen);
+  Workspace ws = carve(m, num_seqs, window, max_context, (char*)workspace, batch_chosen);
   if (ws.bytes > workspace_bytes)
     return fail(LLM42_EWORKSPACE, "%s: workspace %zu < %zu bytes", who, workspace_bytes, ws.bytes);
   return run_pass(m, kv, seq_lens, candidates, window, n_valid, num_seqs, max_context, out_tokens, seq_status,
@@ -572,7 +575,7 @@ llm42_status llm42_prefill(const llm42_model* m, const llm42_kv_cache* kv, const
     return fail(LLM42_ECAPACITY, "prefill: max_context %d exceeds block-table capacity %lld", max_context,
                 (long long)kv->max_blocks_per_seq * LLM42_KV_BLOCK);
   if ((uintptr_t)workspace % 256) return fail(LLM42_EWORKSPACE, "prefill: workspace not 256-byte aligned");
-  const Workspace ws = carve(m, num_seqs, chunk, max_context, (char*)workspace);
+  Workspace ws = carve(m, num_seqs, chunk, max_context, (char*)workspace);
   const PrefillExtra x = carve_prefill(m, ws.bytes, num_seqs, chunk, (char*)workspace);
   if (x.bytes > workspace_bytes) return fail(LLM42_EWORKSPACE, "prefill: workspace %zu < %zu bytes", workspace_bytes, x.bytes);
   hipStream_t st = (hipStream_t)hip_stream;

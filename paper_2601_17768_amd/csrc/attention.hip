@@ -117,13 +117,13 @@ __device__ __forceinline__ float rows_sum(float x) {
   return __uint_as_float(r.x) + __uint_as_float(r.y);
 }
 
-// The output of query row r (of sequence s, kv head kvh): acc / l in bf16, into the tile layout of the
+// The output of query row r (of the sequence whose rows begin at `base`, kv head kvh): acc / l in bf16, into the tile layout of the
 // O-projection's activation operand - exactly what the merge pass computes from a row's folded partials.
 // The lane holds features d * 16 + g * 4 .. + 3 of the row; the lanes g and g ^ 1 of a row trade halves so that each
 // writes 8 consecutive features of every second block d (16 bytes per lane and store, half as many stores).
 // Called by all four lanes of a row or by none.
 template <int HD>
-__device__ __forceinline__ void store_output(uint16_t* __restrict__ out, int d_attn, int s, int kvh, int group, int window,
+__device__ __forceinline__ void store_output(uint16_t* __restrict__ out, int d_attn, int base, int kvh, int group, int window,
                                              int r, int g, const f32x4 (&acc)[HD / 16], float l) {
   const int i = r % window, hq = kvh * group + r / window;
   const bool odd = g & 1;
@@ -134,7 +134,7 @@ __device__ __forceinline__ void store_output(uint16_t* __restrict__ out, int d_a
     // even g keeps block d and takes its neighbour's four features of it; odd g keeps block d + 1
     const uint32_t t0 = __shfl_xor(odd ? a0 : b0, 16), t1 = __shfl_xor(odd ? a1 : b1, 16);
     const u32x4 o = odd ? (u32x4){t0, t1, b0, b1} : (u32x4){a0, a1, t0, t1};
-    *(u32x4*)(out + pk_off(s * window + i, hq * HD + (d + (odd ? 1 : 0)) * 16 + (g & 2) * 4, d_attn)) = o;
+    *(u32x4*)(out + pk_off(base + i, hq * HD + (d + (odd ? 1 : 0)) * 16 + (g & 2) * 4, d_attn)) = o;
   }
 }
 
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(NW * 64) void attention_kernel(
 #pragma unroll
     for (int d = 0; d < DK; ++d) qf[cb][d] = *(const bf16x8*)(qb + d * 512 + lane * 8);
   }
-  const int L = seq_len[s], n = seq_n[s];
+  const int L = seq_len[s], tag = seq_n[s], n = tag_rows(tag);
   if (L < 0) return;                                         // whole workgroup
 
   int qpos[CB];
@@ -434,7 +434,7 @@ __global__ __launch_bounds__(NW * 64) void attention_kernel(
   for (int cb = 0; cb < CB; ++cb) {
     if (qpos[cb] < k_lo) continue;
     if (SUPER && attn_out) {   // (one unit per sequence: no partial, no merge pass)
-      store_output<HD>(attn_out, d_attn, s, kvh, group, window, row[cb], g, sacc[cb], sl[cb]);
+      store_output<HD>(attn_out, d_attn, tag_base(tag), kvh, group, window, row[cb], g, sacc[cb], sl[cb]);
       continue;
     }
     const size_t prow = (((size_t)s * n_kv_heads + kvh) * n_units + unit) * r_pad + row[cb];
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
   // the ord-th piece of work of this workgroup (wave-uniform; scalar loads)
   struct Work {
     bool valid;
-    int s, kvh, yb, unit, L, n, k_lo, k_hi, n_steps;
+    int s, kvh, yb, unit, L, n, base, k_lo, k_hi, n_steps;
   };
   auto work_of = [&](int ord) {
     Work x;
@@ -513,8 +513,8 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     const int tt = x.valid ? t : 0;
     const int it = tt / per_item, rem = tt - it * per_item;
     // (past the end: a harmless stand-in, so that the dummy fetches read valid memory)
-    const int4 su = x.valid ? items[it] : make_int4(0, 0, 0, 1);
-    x.s = su.x, x.unit = su.y, x.L = su.z, x.n = su.w;
+    const int4 su = x.valid ? items[it] : make_int4(0, 0, 0, seq_tag(1, 0));
+    x.s = su.x, x.unit = su.y, x.L = su.z, x.n = tag_rows(su.w), x.base = tag_base(su.w);
     x.kvh = rem / y_blocks, x.yb = rem % y_blocks;
     x.k_lo = SEQ ? 0 : x.unit * UNIT;
     x.k_hi = SEQ ? x.L + x.n : min(x.L + x.n, x.k_lo + UNIT);
@@ -644,10 +644,10 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     }
     // -- partial of this unit for every row that reaches into it
     if (SEQ) {
-      if (qpos[0] >= 0) store_output<HD>(attn_out, d_attn, c.s, c.kvh, group, window, row[0], g, tacc, tl);
+      if (qpos[0] >= 0) store_output<HD>(attn_out, d_attn, c.base, c.kvh, group, window, row[0], g, tacc, tl);
     } else if (SUPER && attn_out) {   // one unit per sequence: no partial, no merge pass
       if (qpos[0] >= 0)
-        store_output<HD>(attn_out, d_attn, c.s, c.kvh, group, window, row[0], g, FOLD ? sacc[0] : acc[0], FOLD ? sl[0] : l[0]);
+        store_output<HD>(attn_out, d_attn, c.base, c.kvh, group, window, row[0], g, FOLD ? sacc[0] : acc[0], FOLD ? sl[0] : l[0]);
     } else if (qpos[0] >= c.k_lo) {
       const size_t prow = (((size_t)c.s * n_kv_heads + c.kvh) * n_units + c.unit) * r_pad + row[0];
       float* pa = part_acc + prow * HD;
@@ -697,7 +697,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(
     const uint16_t* qb = q + ((size_t)s * n_kv_heads + kvh) * r_pad * HD + (size_t)rb * DK * 512;
 #pragma unroll
     for (int d = 0; d < DK; ++d) qf[d] = *(const bf16x8*)(qb + d * 512 + lane * 8);
-    const int L = seq_len[s], n = seq_n[s];
+    const int L = seq_len[s], tag = seq_n[s], n = tag_rows(tag);
     const int row = rb * 16 + col, i = row % window;
     const int qpos = L >= 0 && row < group * window && i < n ? L + i : -1;
     int wmax = qpos, wmin = qpos;      // highest and lowest position among the block's rows (dead rows: -1)
@@ -817,7 +817,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(
       u32x4 o;
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = pack2_bf16(A[0][e] / Ls, A[1][e] / Ls);
-      *(u32x4*)(attn_out + pk_off(s * window + i, (kvh * group + row / window) * HD + f, d_attn)) = o;
+      *(u32x4*)(attn_out + pk_off(tag_base(tag) + i, (kvh * group + row / window) * HD + f, d_attn)) = o;
     }
     __syncthreads();        // the partials are read before the next item's are written
   }
@@ -858,7 +858,7 @@ __global__ __launch_bounds__(256) void attention_plan_kernel(const int32_t* __re
     __syncthreads();
     for (int s = threadIdx.x; s < num_seqs; s += 256) {
       if (seq_len[s] < 0) continue;
-      const int keys = seq_len[s] + seq_n[s];                // positions 0 .. keys-1 are attended to
+      const int keys = seq_len[s] + tag_rows(seq_n[s]);      // positions 0 .. keys-1 are attended to
       const int full = keys / unit;
       if (full) atomicAdd(&count[nb], full);
       if (keys % unit) atomicAdd(&count[class_of(keys, full)], 1);
@@ -876,9 +876,9 @@ __global__ __launch_bounds__(256) void attention_plan_kernel(const int32_t* __re
     __syncthreads();
     for (int s = threadIdx.x; s < num_seqs; s += 256) {
       if (seq_len[s] < 0) continue;
-      const int L = seq_len[s], n = seq_n[s], keys = L + n;
+      const int L = seq_len[s], tag = seq_n[s], keys = L + tag_rows(tag);
       const int units = (keys + unit - 1) / unit;
-      for (int u = 0; u < units; ++u) items[atomicAdd(&cursor[class_of(keys, u)], 1)] = make_int4(s, u, L, n);
+      for (int u = 0; u < units; ++u) items[atomicAdd(&cursor[class_of(keys, u)], 1)] = make_int4(s, u, L, tag);
     }
     __syncthreads();                                         // the list is complete (and visible to this workgroup)
   };
@@ -897,7 +897,7 @@ __global__ __launch_bounds__(256) void attention_plan_kernel(const int32_t* __re
         const int t = ord * seq_grid + ((ord & 1) ? seq_grid - 1 - w : w);
         if (t >= total) break;
         const int4 it = items[t / seq_per_item];
-        load += (it.z + it.w + STEP - 1) / STEP + 1;
+        load += (it.z + tag_rows(it.w) + STEP - 1) / STEP + 1;
       }
       atomicAdd(&load_sum, (unsigned long long)load);
       atomicMax(&load_max, load);
@@ -924,13 +924,10 @@ __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const
   const int r = blockIdx.y * (blockDim.x / QUADS) + threadIdx.x / QUADS;   // (pairs can outnumber what grid.y allows)
   const int s = blockIdx.x / n_kv_heads, kvh = blockIdx.x % n_kv_heads;
   if (r >= group * window) return;
-  const int L = seq_len[s], n = seq_n[s];
+  const int L = seq_len[s], tag = seq_n[s];
   const int i = r % window, hq = kvh * group + r / window;
-  uint2* dst = (uint2*)(out + pk_off(s * window + i, hq * HD + quad * 4, d_attn));
-  if (L < 0 || i >= n) {
-    *dst = make_uint2(0, 0);
-    return;
-  }
+  if (L < 0 || i >= tag_rows(tag)) return;   // no such row, or one that prepare_kernel has given zeros
+  uint2* dst = (uint2*)(out + pk_off(tag_base(tag) + i, hq * HD + quad * 4, d_attn));
   const size_t base = ((size_t)s * n_kv_heads + kvh) * n_units;
   auto slot_ml = [&](int u) { return *(const float2*)(part_ml + ((base + u) * r_pad + r) * 2); };
   auto slot_acc = [&](int u) { return *(const f32x4*)(part_acc + ((base + u) * r_pad + r) * HD + quad * 4); };

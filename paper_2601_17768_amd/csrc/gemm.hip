@@ -32,23 +32,23 @@ struct QkvEpi {
   // alone (the per-row block id and rotary factors are laid out once per call), so none of these
   // loads waits for another.
   struct Row {   // per token row
-    int pos, s, blk;
+    int pos, tag, blk;
   };
   struct Pre {   // per (token row, feature block)
-    int pos, s, blk;
+    int pos, tag, blk;
     float2 cs0, cs1;
   };
   __device__ Row row_info(int row) const {
     Row r;
     r.pos = row_pos[row];
-    r.s = row_seq[row];
+    r.tag = row_seq[row];
     r.blk = row_blk[row];
     return r;
   }
   __device__ Pre pre(int nb, int lane, int row, const Row& r) const {
     Pre p;
     p.pos = r.pos;
-    p.s = r.s;
+    p.tag = r.tag;
     p.blk = r.blk;
     const int j0 = (nb % (head_dim >> 4)) * 8 + (lane >> 4) * 2;
     const float4 cs = row_rope[(size_t)row * (head_dim >> 2) + (j0 >> 1)];
@@ -63,7 +63,7 @@ struct QkvEpi {
     const int head = nb / blocks_per_head, t = nb % blocks_per_head, g = lane >> 4;
     const int j0 = t * 8 + g * 2;           // features j0, j0+1 and their rotary partners j0 + hd/2, j0+1 + hd/2
     const int half = head_dim >> 1;
-    const int s = p.s;
+    const int s = tag_seq(p.tag);
     float lo0 = acc[0], lo1 = acc[1], hi0 = acc[2], hi1 = acc[3];
     if (head < n_q_heads + n_kv_heads) {
       const float2 cs0 = p.cs0, cs1 = p.cs1;
@@ -73,7 +73,7 @@ struct QkvEpi {
     }
     const uint32_t lo = pack2_bf16(lo0, lo1), hi = pack2_bf16(hi0, hi1);
     if (head < n_q_heads) {
-      const int kvh = head / group, r = (head % group) * window + (row - s * window);
+      const int kvh = head / group, r = (head % group) * window + tag_index(p.tag);
       uint16_t* base = q + ((size_t)s * n_kv_heads + kvh) * r_pad * head_dim;
       *(uint32_t*)(base + pk_off(r, j0, head_dim)) = lo;
       *(uint32_t*)(base + pk_off(r, j0 + half, head_dim)) = hi;
@@ -141,7 +141,7 @@ struct LogitsEpi {
   uint64_t seed;
   const int64_t* request_ids;
   struct Row {
-    int pos, s, slot;
+    int pos, s, i, slot;
     uint64_t key;      // hash of (seed, request, position): the row's noise stream
   };
   typedef Row Pre;
@@ -155,7 +155,9 @@ struct LogitsEpi {
   __device__ Row row_info(int row) const {
     Row p;
     p.pos = row_pos[row];
-    p.s = row_seq[row];
+    const int tag = row_seq[row];
+    p.s = tag_seq(tag);
+    p.i = tag_index(tag);
     p.slot = out_logits ? dump_slot[p.s] : -1;
     p.key = 0;
     if (inv_temp != 0.f) {
@@ -168,9 +170,9 @@ struct LogitsEpi {
   __device__ void operator()(int nb, int lane, int row, const f32x4 acc, const Pre& p) const {
     const int n0 = nb * 16 + (lane >> 4) * 4;
     if (out_logits && p.pos >= 0) {
-      const int s = p.s, slot = p.slot;
+      const int slot = p.slot;
       if (slot >= 0)
-        *(f32x4*)(out_logits + ((size_t)slot * window + (row - s * window)) * vocab + n0) = acc;
+        *(f32x4*)(out_logits + ((size_t)slot * window + p.i) * vocab + n0) = acc;
     }
     // what the sampler ranks: the logits, or (temperature > 0) logit / temperature + Gumbel noise
     f32x4 val = acc;
@@ -571,16 +573,18 @@ __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restri
 template <int WN, int WM, int WBN, int WBM, int CH, int R, int F, int WGS, bool PRE, class Epi>
 __global__ __launch_bounds__(64 * (WN * WM + F), (WGS * (WN * WM + F) + 3) / 4) void gemm_mid_kernel(
     const bf16x8* __restrict__ w, const bf16x8* __restrict__ x, int n_blocks, int k_tiles, int split, int planes, int tiles_n,
-    int tiles_m, int per_xcd, Epi epi) {
+    int tiles_m, const int32_t* __restrict__ live, Epi epi) {
   constexpr int TBN = WN * WBN, TBM = WM * WBM, ST = TBN + TBM;
   constexpr int PW = CH * ST / F;                    // tiles a fetching wave requests per round
   static_assert(CH * ST % F == 0, "the fetching waves take equal shares");
   static_assert(CH == 1 || CH % 2 == 0, "operand registers alternate");
   __shared__ bf16x8 ring[R][CH * ST * 64];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), all = tiles_n * tiles_m;
+  if (live) tiles_m = max(1, (*live + 16 * TBM - 1) / (16 * TBM));   // packed rows: the tiles that hold any
+  const int all = tiles_n * tiles_m, per_xcd = (all * planes + 7) / 8;
+  const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   const int plane = tile / all, at = tile - plane * all;
-  if (plane >= planes) return;
+  if ((int)(blockIdx.x >> 3) >= per_xcd || plane >= planes) return;
   const int n0 = at / tiles_m * TBN, m0 = at % tiles_m * TBM;      // first feature / token block of the tile
   const int k_begin = plane ? split : 0, k_count = plane ? k_tiles - split : split;
   const int rounds = (k_count + CH - 1) / CH;
@@ -703,7 +707,8 @@ template <int WBN, int WBM, int NST, int WGS, bool ADD_PARTIAL, class Epi>
 __global__ __launch_bounds__(256, WGS) void gemm_tiled_kernel(const bf16x8* __restrict__ w, const bf16x8* __restrict__ x,
                                                          int n_blocks, int k_tiles, int k_begin, int k_count,
                                                          const float* __restrict__ partial, int n, int tiles_n,
-                                                         int tiles_m, int sm_tiles, int group_tiles, int planes, Epi epi) {
+                                                         int tiles_m, int sm_tiles, int group_tiles, int planes,
+                                                         const int32_t* __restrict__ live, Epi epi) {
   constexpr int TBN = 2 * WBN, TBM = 2 * WBM;   // 16-row blocks per tile side (features, tokens)
   constexpr int ST = TBN + TBM;                 // operand tiles per stage of one k-tile (weights then activations)
   constexpr int PW = (ST + 3) / 4;              // operand tiles each wave fetches per stage (where ST is no multiple of
@@ -721,6 +726,7 @@ __global__ __launch_bounds__(256, WGS) void gemm_tiled_kernel(const bf16x8* __re
   // G is 32 when that still gives every XCD a super-tile, less for small launches; SM follows the
   // number of token tiles.  (A workgroup without a tile still has to wait for a CU with free LDS
   // before it can leave, so holes in the numbering are expensive.)
+  if (live) tiles_m = max(1, (*live + 16 * TBM - 1) / (16 * TBM));   // packed rows: the tiles that hold any
   const int G = group_tiles, SM = sm_tiles, SN = G / SM;
   const int sup_n = (tiles_n + SN - 1) / SN, sup_m = (tiles_m + SM - 1) / SM;
   const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
@@ -835,6 +841,10 @@ __global__ __launch_bounds__(256, WGS) void gemm_tiled_kernel(const bf16x8* __re
   }
 }
 
+// Packed rows: a launch of one workgroup per CU or less does not get faster by having fewer of them (and would only wait
+// for the count, 0.7 us); beyond that the tiles that hold no row are left out.
+inline const int32_t* live_of(const Workspace& ws, long long tiles) { return tiles > ws.num_cus ? ws.live : nullptr; }
+
 // side_by_side (split GEMMs only): both k-halves in one launch of twice the workgroups, their sum left to the RMSNorm that
 // follows, instead of two launches one after the other - for launches that do not fill the
 // device by themselves.  The arithmetic per output element is the same either way.
@@ -872,21 +882,22 @@ void launch_tiled(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles,
       }
     }
   const unsigned grid = 8u * (unsigned)g * (unsigned)((supers + 7) / 8);
+  const int32_t* live = live_of(ws, (long long)tiles_n * tiles_m * planes);
   if constexpr (SPLIT == 1) {
     gemm_tiled_kernel<WBN, WBM, NST, WGS, false, Epi><<<grid, threads, 0, st>>>(wp, xp, n_blocks, k_tiles, 0, k_tiles,
-                                                                                    nullptr, n, tiles_n, tiles_m, sm, g, 1, epi);
+                                                                                    nullptr, n, tiles_n, tiles_m, sm, g, 1, live, epi);
   } else {
   const int h = split_point(k_tiles);
   const size_t plane = (size_t)ws.m_pad * n;
   StorePartialEpi pe{ws.split_part, ws.rl, n, plane};
   if (side_by_side) {
     gemm_tiled_kernel<WBN, WBM, NST, WGS, false, StorePartialEpi><<<grid, threads, 0, st>>>(
-        wp, xp, n_blocks, k_tiles, 0, h, nullptr, n, tiles_n, tiles_m, sm, g, 2, pe);
+        wp, xp, n_blocks, k_tiles, 0, h, nullptr, n, tiles_n, tiles_m, sm, g, 2, live, pe);
   } else {
     gemm_tiled_kernel<WBN, WBM, NST, WGS, false, StorePartialEpi><<<grid, threads, 0, st>>>(
-        wp, xp, n_blocks, k_tiles, h, k_tiles - h, nullptr, n, tiles_n, tiles_m, sm, g, 1, pe);
+        wp, xp, n_blocks, k_tiles, h, k_tiles - h, nullptr, n, tiles_n, tiles_m, sm, g, 1, live, pe);
     gemm_tiled_kernel<WBN, WBM, NST, WGS, true, Epi><<<grid, threads, 0, st>>>(wp, xp, n_blocks, k_tiles, 0, h, ws.split_part,
-                                                                                   n, tiles_n, tiles_m, sm, g, 1, epi);
+                                                                                   n, tiles_n, tiles_m, sm, g, 1, live, epi);
   }
   }
 }
@@ -945,24 +956,24 @@ inline int pick_mid(int n_blocks, int m_pad, int planes, long long cus) {
 }
 
 template <int WN, int WM, int WBN, int WBM, int CH, int R, int F, int WGS, bool PRE, class Epi>
-void launch_mid_tile(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, int split, int planes, int m_pad,
+void launch_mid_tile(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, int split, int planes, const Workspace& ws,
                      const Epi& epi, hipStream_t st) {
-  const int tiles_n = (n_blocks + WN * WBN - 1) / (WN * WBN), tiles_m = m_pad / (16 * WM * WBM);
+  const int tiles_n = (n_blocks + WN * WBN - 1) / (WN * WBN), tiles_m = ws.m_pad / (16 * WM * WBM);
   const int per_xcd = (tiles_n * tiles_m * planes + 7) / 8;
   gemm_mid_kernel<WN, WM, WBN, WBM, CH, R, F, WGS, PRE, Epi><<<8 * per_xcd, 64 * (WN * WM + F), 0, st>>>(
-      wp, xp, n_blocks, k_tiles, split, planes, tiles_n, tiles_m, per_xcd, epi);
+      wp, xp, n_blocks, k_tiles, split, planes, tiles_n, tiles_m, live_of(ws, (long long)tiles_n * tiles_m * planes), epi);
 }
 
 template <class Epi>
-void launch_mid(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, int split, int planes, int m_pad,
+void launch_mid(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, int split, int planes, const Workspace& ws,
                 const Epi& epi, hipStream_t st) {
   switch (tile) {
-    case 0: return launch_mid_tile<2, 2, 2, 2, 4, 4, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, m_pad, epi, st);
-    case 1: return launch_mid_tile<2, 4, 2, 2, 4, 3, 4, 1, false>(wp, xp, n_blocks, k_tiles, split, planes, m_pad, epi, st);
-    case 2: return launch_mid_tile<4, 2, 2, 4, 1, 5, 4, 2, false>(wp, xp, n_blocks, k_tiles, split, planes, m_pad, epi, st);
-    case 3: return launch_mid_tile<4, 2, 3, 4, 1, 6, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, m_pad, epi, st);
-    case 4: return launch_mid_tile<4, 2, 4, 4, 1, 5, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, m_pad, epi, st);
-    default: return launch_mid_tile<2, 4, 4, 4, 1, 6, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, m_pad, epi, st);
+    case 0: return launch_mid_tile<2, 2, 2, 2, 4, 4, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, ws, epi, st);
+    case 1: return launch_mid_tile<2, 4, 2, 2, 4, 3, 4, 1, false>(wp, xp, n_blocks, k_tiles, split, planes, ws, epi, st);
+    case 2: return launch_mid_tile<4, 2, 2, 4, 1, 5, 4, 2, false>(wp, xp, n_blocks, k_tiles, split, planes, ws, epi, st);
+    case 3: return launch_mid_tile<4, 2, 3, 4, 1, 6, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, ws, epi, st);
+    case 4: return launch_mid_tile<4, 2, 4, 4, 1, 5, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, ws, epi, st);
+    default: return launch_mid_tile<2, 4, 4, 4, 1, 6, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, ws, epi, st);
   }
 }
 
@@ -1004,9 +1015,9 @@ bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
   if (kLogits || m_pad <= (std::is_same<Epi, SwigluEpi>::value ? 256 : 1280)) {
     const int tile = !kLogits ? pick_mid(n_blocks, m_pad, SPLIT, cus) : m_pad % 256 == 0 && m_pad <= 2048 ? 5 : 4;
     if constexpr (SPLIT == 2)
-      launch_mid(tile, wp, xp, n_blocks, k_tiles, split_point(k_tiles), 2, m_pad,
+      launch_mid(tile, wp, xp, n_blocks, k_tiles, split_point(k_tiles), 2, ws,
                  StorePartialEpi{ws.split_part, ws.rl, n, (size_t)m_pad * n}, st);
-    else launch_mid(tile, wp, xp, n_blocks, k_tiles, k_tiles, 1, m_pad, epi, st);
+    else launch_mid(tile, wp, xp, n_blocks, k_tiles, k_tiles, 1, ws, epi, st);
     return SPLIT == 2;
   }
   if constexpr (!kLogits) {

@@ -90,6 +90,14 @@ struct llm42_model {
   float* rope;        // [max_position][head_dim/2][2] (cos, sin), fp32
 };
 
+// (at most 65536 rows, windows of at most 512)
+__host__ __device__ inline int row_tag(int s, int i) { return s << 10 | i; }
+__host__ __device__ inline int tag_seq(int tag) { return tag >> 10; }
+__host__ __device__ inline int tag_index(int tag) { return tag & 1023; }
+__host__ __device__ inline int seq_tag(int n, int base) { return base << 10 | n; }
+__host__ __device__ inline int tag_rows(int tag) { return tag & 1023; }
+__host__ __device__ inline int tag_base(int tag) { return tag >> 10; }
+
 // Workspace carving, identical in llm42_workspace_bytes and llm42_verify_window.
 struct Workspace {
   int num_cus;    // compute units of the device
@@ -105,7 +113,12 @@ struct Workspace {
   bool attn_list;   // the launches take their items from the plan kernel's list (else: sequence by sequence)
   bool batch_chosen; // off the fixed schedule (fast-path decode step, cost-of-determinism measurement): the batch may
                      // choose the split of the residual projections and the attention partials
-  int32_t *row_pos, *row_seq, *seq_len, *seq_n, *dump_slot;
+  // Rows of a pass: sequence s has rows base(s) .. base(s) + n(s) - 1.  With n_valid the rows are packed - base(s) is the sum
+  // of the counts before - and *live of them exist (host: null otherwise); without, base(s) = s * window.
+  int32_t *row_pos, *row_seq;        // position (-1: takes no part), row_tag(s, i)
+  int32_t *seq_len, *seq_n;          // cached length (-1: takes no part), seq_tag(n, base)
+  int32_t *dump_slot;
+  int32_t* live;
   int32_t* row_blk;    // physical KV block that holds the row's position (0 for dead rows)
   float2* row_rope;    // [m_pad][head_dim/2] (cos, sin) at the row's position
   float* resid;
@@ -114,7 +127,7 @@ struct Workspace {
   float *part_acc, *part_ml;
   int4* attn_items;     // (sequence, unit, length, rows) of every unit that holds keys, built once per call
   int32_t* attn_ctrl;   // [0] number of items, [1 + layer] work queue counter of that layer's attention launch,
-                        // [1 + n_layers] 1 if the items are whole sequences
+                        // [1 + n_layers] 1 if the items are whole sequences, [2 + n_layers] *live
   size_t attn_ctrl_offset;   // byte offset of attn_ctrl in the workspace
   float* split_part;   // fp32 halves of a split GEMM, [2][m_pad][d_model]
   float2* amax;   // [m_pad][vocab/16] (value, index bits)
@@ -140,7 +153,7 @@ void launch_prefill_window(const int32_t* prompt_tokens, const int32_t* prompt_o
 void launch_prefill_gather(const llm42_model* m, const int32_t* prompt_offsets, int num_seqs, int window, int chunk_index,
                            int max_prompt_len, const int32_t* seq_status, const Workspace& ws, const Workspace& tail,
                            hipStream_t st);
-void launch_embed(const llm42_model* m, const int32_t* candidates, const Workspace& ws, hipStream_t st);
+void launch_embed(const llm42_model* m, const int32_t* candidates, int window, const Workspace& ws, hipStream_t st);
 // pending: the last residual GEMM left its halves in split_part (what launch_gemm_residual returned)
 void launch_rmsnorm(bool pending, const uint16_t* gain, int d, float eps, const Workspace& ws, hipStream_t st);
 

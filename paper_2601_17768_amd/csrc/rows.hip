@@ -15,16 +15,24 @@ __global__ void prepare_kernel(const int32_t* __restrict__ seq_lens, const int32
                                int32_t* seq_status, int32_t* row_pos, int32_t* row_seq, int32_t* ws_len,
                                int32_t* ws_n, int32_t* dump_slot, const float2* __restrict__ rope, int half_dim,
                                int32_t* row_blk, float2* row_rope, int min_n, int status_or,
-                               uint16_t* __restrict__ attn_zero, int d_attn) {
-  __shared__ int status;
+                               uint16_t* __restrict__ attn_zero, int d_attn, int32_t* __restrict__ live) {
+  __shared__ int status, before;
   const int s = blockIdx.x;
-  if (threadIdx.x == 0) status = 0;
+  if (threadIdx.x == 0) status = 0, before = 0;
   __syncthreads();
   const int L = seq_lens[s];
   const int n = n_valid ? n_valid[s] : window;
   int bad = 0;
   // (min_n is 1; a prefill pass passes 0: a sequence whose prompt has ended takes no part in the pass)
-  if (L < 0 || n < min_n || n > window || (int64_t)L + n > max_context) bad = LLM42_SEQ_BAD_LENGTH;
+  auto bad_length = [&](int len, int cnt) { return len < 0 || cnt < min_n || cnt > window || (int64_t)len + cnt > max_context; };
+  if (bad_length(L, n)) bad = LLM42_SEQ_BAD_LENGTH;
+  // `live` given: packed rows.  What fails a check of its length has none, what fails a later one keeps dead rows.
+  const int rows = !live ? window : bad ? 0 : n;
+  if (live) {
+    int sum = 0;
+    for (int t = threadIdx.x; t < s; t += blockDim.x) sum += bad_length(seq_lens[t], n_valid[t]) ? 0 : n_valid[t];
+    if (sum) atomicAdd(&before, sum);
+  }
   if (!bad) {
     const int blocks = (L + n + LLM42_KV_BLOCK - 1) / LLM42_KV_BLOCK;   // <= max_blocks_per_seq (host checked)
     for (int b = threadIdx.x; b < blocks; b += blockDim.x) {
@@ -38,36 +46,38 @@ __global__ void prepare_kernel(const int32_t* __restrict__ seq_lens, const int32
   }
   if (bad) atomicOr(&status, bad);   // integer OR: order-free
   __syncthreads();
-  const int st = status;
+  const int st = status, base = live ? before : s * window;
   for (int i = threadIdx.x; i < window; i += blockDim.x) {
-    const int row = s * window + i;
-    const bool live = st == 0 && i < n;
-    row_pos[row] = live ? L + i : -1;
-    row_seq[row] = s;
+    if (out_tokens) out_tokens[(size_t)s * window + i] = -1;   // overwritten by the arg-max merge for rows that take part
+    if (i >= rows) continue;
+    const int row = base + i;
+    const bool part = st == 0 && i < n;
+    row_pos[row] = part ? L + i : -1;
+    row_seq[row] = row_tag(s, i);
     // where the row's K and V go (a block id that passed the check above), for the QKV epilogue
-    row_blk[row] = live ? block_table[(size_t)s * max_blocks_per_seq + ((L + i) >> 4)] : 0;
-    if (out_tokens) out_tokens[row] = -1;   // overwritten by the arg-max merge for live rows
+    row_blk[row] = part ? block_table[(size_t)s * max_blocks_per_seq + ((L + i) >> 4)] : 0;
   }
   // the rotary factors of every live row, laid out by row so that the QKV epilogue finds them without
   // knowing the position first
   if (st == 0) {
     for (int e = threadIdx.x; e < n * half_dim; e += blockDim.x) {
       const int i = e / half_dim, j = e - i * half_dim;
-      row_rope[(size_t)(s * window + i) * half_dim + j] = rope[(size_t)(L + i) * half_dim + j];
+      row_rope[(size_t)(base + i) * half_dim + j] = rope[(size_t)(L + i) * half_dim + j];
     }
   }
-  // Without a merge pass (attn_zero given) nothing writes the attention output of rows that take no part:
-  // give them zeros once, so that everything downstream of them stays finite.
-  if (attn_zero) {
+  // Nothing writes the attention output of rows that take no part: give them zeros once, so that everything downstream of
+  // them stays finite.
+  if (st != 0 || n < rows) {
     const int chunks = d_attn / 8;
-    for (int e = threadIdx.x; e < window * chunks; e += blockDim.x) {
+    for (int e = threadIdx.x; e < rows * chunks; e += blockDim.x) {
       const int i = e / chunks, c8 = e - i * chunks;
-      if (st != 0 || i >= n) *(uint4*)(attn_zero + pk_off(s * window + i, c8 * 8, d_attn)) = make_uint4(0, 0, 0, 0);
+      if (st != 0 || i >= n) *(uint4*)(attn_zero + pk_off(base + i, c8 * 8, d_attn)) = make_uint4(0, 0, 0, 0);
     }
   }
   if (threadIdx.x == 0) {
     ws_len[s] = st == 0 && n > 0 ? L : -1;
-    ws_n[s] = st == 0 ? n : 0;
+    ws_n[s] = seq_tag(st == 0 ? n : 0, base);
+    if (live && s == (int)gridDim.x - 1) *live = base + rows;
     if (seq_status) seq_status[s] = status_or ? (seq_status[s] | st) : st;
     int slot = -1;
     for (int j = 0; j < n_dump; ++j)
@@ -76,10 +86,11 @@ __global__ void prepare_kernel(const int32_t* __restrict__ seq_lens, const int32
   }
 }
 
-// Rows beyond num_seqs*window that only pad the GEMM grid.
-__global__ void prepare_pad_rows_kernel(int32_t* row_pos, int32_t* row_seq, int32_t* row_blk, int from, int to) {
+// Rows beyond those of the sequences (`from`, or *live where rows are packed) that only pad the GEMM grid.
+__global__ void prepare_pad_rows_kernel(int32_t* row_pos, int32_t* row_seq, int32_t* row_blk, int from, int to,
+                                        const int32_t* __restrict__ live) {
   const int r = from + blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < to) {
+  if (r < to && (!live || r >= *live)) {
     row_pos[r] = -1;
     row_seq[r] = 0;
     row_blk[r] = 0;
@@ -116,6 +127,7 @@ __global__ void prefill_window_kernel(const int32_t* __restrict__ prompt_tokens,
 __global__ __launch_bounds__(256) void prefill_gather_kernel(const int32_t* __restrict__ prompt_offsets, int window,
                                                              int chunk_index, int num_seqs, int max_prompt_len,
                                                              const int32_t* __restrict__ seq_status,
+                                                             const int32_t* __restrict__ seq_n,
                                                              const int32_t* __restrict__ row_pos,
                                                              const uint16_t* __restrict__ attn, int d_attn,
                                                              const float* __restrict__ resid, int d,
@@ -126,13 +138,13 @@ __global__ __launch_bounds__(256) void prefill_gather_kernel(const int32_t* __re
   if (s < num_seqs) {
     const int len = prompt_offsets[s + 1] - prompt_offsets[s];
     const int last = len - 1 - chunk_index * window;      // row of the last prompt token in this pass
-    if (len > 0 && len <= max_prompt_len && last >= 0 && last < window) row = s * window + last;
+    if (len > 0 && len <= max_prompt_len && last >= 0 && last < window && tag_rows(seq_n[s]) > last) row = tag_base(seq_n[s]) + last;
   }
   if (row < 0 && chunk_index > 0) return;                 // filled by another pass
   const bool live = row >= 0 && row_pos[row] >= 0 && seq_status[s] == 0;
   if (threadIdx.x == 0) {
     tail_pos[s] = live ? row_pos[row] : -1;
-    tail_seq[s] = s < num_seqs ? s : 0;
+    tail_seq[s] = row_tag(s < num_seqs ? s : 0, 0);
   }
   for (int c = threadIdx.x * 8; c < d_attn; c += 256 * 8)
     *(uint4*)(tail_attn + pk_off(s, c, d_attn)) = live ? *(const uint4*)(attn + pk_off(row, c, d_attn)) : make_uint4(0, 0, 0, 0);
@@ -144,7 +156,8 @@ __global__ __launch_bounds__(256) void prefill_gather_kernel(const int32_t* __re
 // (row = lane % 16, g = lane / 16) converts 8 features of its row's embedding to
 // fp32 (exact).  Dead rows get zeros so that everything downstream stays finite.
 __global__ void embed_kernel(const uint16_t* __restrict__ table, const int32_t* __restrict__ candidates,
-                             const int32_t* __restrict__ row_pos, int m_rows, int d, float* __restrict__ resid,
+                             const int32_t* __restrict__ row_pos, const int32_t* __restrict__ row_seq, int window, int d,
+                             float* __restrict__ resid,
                              ResidLayout rl) {
   const int col_tiles = d / 32;
   const size_t tile = (size_t)blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
@@ -153,8 +166,8 @@ __global__ void embed_kernel(const uint16_t* __restrict__ table, const int32_t* 
   const int row = rb * 16 + (lane & 15);
   const int feat = cb * 32 + (lane >> 4) * 8;
   uint4 v = make_uint4(0, 0, 0, 0);
-  if (row < m_rows && row_pos[row] >= 0) {
-    const int tok = candidates[row];
+  if (row_pos[row] >= 0) {   // (also set for the rows that only pad)
+    const int tag = row_seq[row], tok = candidates[(size_t)tag_seq(tag) * window + tag_index(tag)];
     v = *(const uint4*)(table + (size_t)tok * d + feat);
   }
   f32x4 lo = {bf16_bits_to_f32(v.x & 0xFFFFu), bf16_bits_to_f32(v.x >> 16), bf16_bits_to_f32(v.y & 0xFFFFu),
@@ -316,7 +329,9 @@ template <int R, bool PEND>
 __global__ __launch_bounds__(64 * R) void rmsnorm_block_kernel(float* __restrict__ x, const float* __restrict__ p0,
                                                                const float* __restrict__ p1, ResidLayout rl,
                                                                const uint16_t* __restrict__ gain,
-                                                               uint16_t* __restrict__ y, float eps) {
+                                                               uint16_t* __restrict__ y, float eps,
+                                                               const int32_t* __restrict__ live) {
+  if (live && (int)blockIdx.x * R >= *live) return;      // packed rows: only what pads (workgroup-uniform)
   constexpr int D = 4096, U = 8;                         // tiles of 32 features per thread: t = u * 16 + w
   __shared__ float part[64][R];
   __shared__ float inv_s[R];
@@ -372,10 +387,10 @@ void launch_prepare(const llm42_model* m, const llm42_kv_cache* kv, const int32_
                                           out_tokens, seq_status, ws.row_pos, ws.row_seq, ws.seq_len, ws.seq_n,
                                           ws.dump_slot, (const float2*)m->rope, m->cfg.head_dim / 2, ws.row_blk,
                                           ws.row_rope, prefill_pass ? 0 : 1, prefill_pass ? 1 : 0,
-                                          ws.attn_direct || ws.attn_seq || ws.attn_split ? ws.attn : nullptr, m->d_attn);
-  if (ws.m_pad > ws.m_rows)
-    prepare_pad_rows_kernel<<<(ws.m_pad - ws.m_rows + 63) / 64, 64, 0, st>>>(ws.row_pos, ws.row_seq, ws.row_blk,
-                                                                            ws.m_rows, ws.m_pad);
+                                          ws.attn, m->d_attn, ws.live);
+  const int from = ws.live ? 0 : ws.m_rows;
+  if (ws.m_pad > from)
+    prepare_pad_rows_kernel<<<(ws.m_pad - from + 63) / 64, 64, 0, st>>>(ws.row_pos, ws.row_seq, ws.row_blk, from, ws.m_pad, ws.live);
 }
 
 void launch_prefill_window(const int32_t* prompt_tokens, const int32_t* prompt_offsets, const int32_t* seq_lens,
@@ -389,18 +404,18 @@ void launch_prefill_gather(const llm42_model* m, const int32_t* prompt_offsets, 
                            int max_prompt_len, const int32_t* seq_status, const Workspace& ws, const Workspace& tail,
                            hipStream_t st) {
   prefill_gather_kernel<<<tail.m_pad, 256, 0, st>>>(prompt_offsets, window, chunk_index, num_seqs, max_prompt_len, seq_status,
-                                                    ws.row_pos, ws.attn, m->d_attn, ws.resid, m->cfg.d_model, ws.rl, tail.rl, tail.row_pos,
+                                                    ws.seq_n, ws.row_pos, ws.attn, m->d_attn, ws.resid, m->cfg.d_model, ws.rl, tail.rl, tail.row_pos,
                                                     tail.row_seq, tail.attn, tail.resid);
 }
 
-void launch_embed(const llm42_model* m, const int32_t* candidates, const Workspace& ws, hipStream_t st) {
+void launch_embed(const llm42_model* m, const int32_t* candidates, int window, const Workspace& ws, hipStream_t st) {
   const int tiles = ws.m_pad / 16 * (m->cfg.d_model / 32);   // a multiple of 4 (d_model % 128 == 0 is checked)
-  embed_kernel<<<tiles / 4, 256, 0, st>>>(m->embed, candidates, ws.row_pos, ws.m_rows, m->cfg.d_model, ws.resid, ws.rl);
+  embed_kernel<<<tiles / 4, 256, 0, st>>>(m->embed, candidates, ws.row_pos, ws.row_seq, window, m->cfg.d_model, ws.resid, ws.rl);
 }
 
 template <bool PEND>
 static void launch_norm(float* x, const float* p0, const float* p1, ResidLayout rl, const uint16_t* gain, uint16_t* y, int m_pad, int d,
-                        float eps, hipStream_t st) {
+                        float eps, const int32_t* live, hipStream_t st) {
   // us per launch behind a launch that wrote the operands (they come from other XCDs' writes then), by the rows per workgroup
   // (1: a wave per row, 4 waves a workgroup from 512 rows on), without | with pending halves:
   //                  row-major                                 token blocks interleaved
@@ -414,8 +429,8 @@ static void launch_norm(float* x, const float* p0, const float* p1, ResidLayout 
   // Few rows are bound by what a CU pulls from beyond its L2 (20 - 25 GB/s) and want as many CUs as there are, many rows by
   // the length of the runs that they read and write.
   if (d == 4096 && m_pad > 128 && !(PEND && m_pad > 256 && m_pad <= 512)) {
-    if (m_pad <= 512) rmsnorm_block_kernel<2, PEND><<<m_pad / 2, 128, 0, st>>>(x, p0, p1, rl, gain, y, eps);
-    else rmsnorm_block_kernel<8, PEND><<<m_pad / 8, 512, 0, st>>>(x, p0, p1, rl, gain, y, eps);
+    if (m_pad <= 512) rmsnorm_block_kernel<2, PEND><<<m_pad / 2, 128, 0, st>>>(x, p0, p1, rl, gain, y, eps, nullptr);
+    else rmsnorm_block_kernel<8, PEND><<<m_pad / 8, 512, 0, st>>>(x, p0, p1, rl, gain, y, eps, live);
   }
   else if (m_pad <= 256) rmsnorm_kernel<PEND><<<m_pad, 64, 0, st>>>(x, p0, p1, rl, gain, y, m_pad, d, eps);
   else rmsnorm_kernel<PEND><<<(m_pad + 3) / 4, 256, 0, st>>>(x, p0, p1, rl, gain, y, m_pad, d, eps);
@@ -423,6 +438,6 @@ static void launch_norm(float* x, const float* p0, const float* p1, ResidLayout 
 
 void launch_rmsnorm(bool pending, const uint16_t* gain, int d, float eps, const Workspace& ws, hipStream_t st) {
   const float* p0 = ws.split_part;
-  if (pending) launch_norm<true>(ws.resid, p0, p0 + (size_t)ws.m_pad * d, ws.rl, gain, ws.normed, ws.m_pad, d, eps, st);
-  else launch_norm<false>(ws.resid, nullptr, nullptr, ws.rl, gain, ws.normed, ws.m_pad, d, eps, st);
+  if (pending) launch_norm<true>(ws.resid, p0, p0 + (size_t)ws.m_pad * d, ws.rl, gain, ws.normed, ws.m_pad, d, eps, ws.live, st);
+  else launch_norm<false>(ws.resid, nullptr, nullptr, ws.rl, gain, ws.normed, ws.m_pad, d, eps, ws.live, st);
 }

@@ -14,7 +14,8 @@ __device__ inline void take_better(float& bv, int& bi, float ov, int oi) {
 // One workgroup per row.  max with the lowest-index tie-break is associative and
 // commutative, so the order of this reduction cannot change the result.
 __global__ __launch_bounds__(256) void argmax_merge_kernel(const float2* __restrict__ amax,
-                                                           const int32_t* __restrict__ row_pos, int n_blocks,
+                                                           const int32_t* __restrict__ row_pos,
+                                                           const int32_t* __restrict__ row_seq, int window, int n_blocks,
                                                            int32_t* __restrict__ out_tokens) {
   __shared__ float sv[4];
   __shared__ int si[4];
@@ -45,7 +46,8 @@ __global__ __launch_bounds__(256) void argmax_merge_kernel(const float2* __restr
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int w = 1; w < 4; ++w) take_better(bv, bi, sv[w], si[w]);
-    out_tokens[row] = bi;
+    const int tag = row_seq[row];
+    out_tokens[(size_t)tag_seq(tag) * window + tag_index(tag)] = bi;
   }
 }
 
@@ -79,7 +81,7 @@ __global__ void commit_kernel(const int32_t* __restrict__ candidates, const int3
 
 void launch_argmax_merge(const llm42_model* m, int num_seqs, int window, int32_t* out_tokens, const Workspace& ws,
                          hipStream_t st) {
-  argmax_merge_kernel<<<num_seqs * window, 256, 0, st>>>(ws.amax, ws.row_pos, m->cfg.vocab / 16, out_tokens);
+  argmax_merge_kernel<<<num_seqs * window, 256, 0, st>>>(ws.amax, ws.row_pos, ws.row_seq, window, m->cfg.vocab / 16, out_tokens);
 }
 
 void launch_commit(const int32_t* candidates, const int32_t* out_tokens, const int32_t* n_valid, int num_seqs,

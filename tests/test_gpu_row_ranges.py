@@ -8,6 +8,7 @@ import torch
 
 from helpers import wl
 from gpu_helpers import VerifierSession, gpu_kv_tokens
+from paper_2601_17768_amd import binding as B
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -22,7 +23,7 @@ def env():
     sess.close()
 
 
-def _run(shape, sess, n_seq, slot, n_valid=None):
+def _run(shape, sess, n_seq, slot, n_valid=None, bad_token_of=None, expect_status=None):
     rng = wl.rng_for(47, 3)
     kv_target = torch.empty((2, 4, shape.n_kv_heads, 16 * shape.head_dim), dtype=torch.bfloat16, device=DEV)
     kv_target.normal_(generator=torch.Generator(device=DEV).manual_seed(1))
@@ -37,12 +38,14 @@ def _run(shape, sess, n_seq, slot, n_valid=None):
     kv[0][:, bt[slot, :4].long()] = kv_target
     cand = wl.random_tokens(rng, n_seq * WINDOW, shape.vocab).reshape(n_seq, WINDOW)
     cand[slot] = target
+    if bad_token_of is not None:
+        cand[bad_token_of, 0] = shape.vocab
     nv = None if n_valid is None else torch.as_tensor(n_valid.astype(np.int32), device=DEV)
     out, status, logits = sess.verify(kv, bt, torch.as_tensor(lens, device=DEV), torch.as_tensor(cand, device=DEV), n_valid=nv,
                                       dump_seq_ids=torch.tensor([slot], dtype=torch.int32, device=DEV),
                                       max_context=int(lens.max()) + WINDOW)
     torch.cuda.synchronize()
-    assert int(status.max()) == 0
+    assert status.tolist() == ([0] * n_seq if expect_status is None else expect_status)
     k, v = gpu_kv_tokens(kv, bt[slot], CONTEXT + WINDOW, shape.head_dim)
     return out.cpu(), logits[0].cpu(), k.cpu(), v.cpu()
 
@@ -60,3 +63,61 @@ def test_same_bits_at_every_row_count(env, alone, n_seq):
     out, logits, k, v = _run(*env, n_seq, slot)
     assert torch.equal(out[slot], alone[0]) and int(out.min()) >= 0
     assert torch.equal(logits, alone[1]) and torch.equal(k, alone[2]) and torch.equal(v, alone[3])
+
+
+@pytest.mark.parametrize("n_seq", [4, 9, 20, 41, 65, 97, 130, 200])
+def test_same_bits_among_partly_filled_windows(env, alone, n_seq):
+    """Partly filled windows are packed: the target's rows begin wherever the counts before it end (odd offsets, across
+    tiles), sequences that fail a check have no rows or dead ones, and what lies behind the last row is skipped."""
+    rng = wl.rng_for(47, 5, n_seq)
+    n_valid = rng.integers(1, WINDOW + 1, size=n_seq)
+    slot = n_seq - 2
+    n_valid[slot] = WINDOW
+    n_valid[0] = WINDOW + 1                                     # refused by its length: no rows
+    expect = [0] * n_seq
+    expect[0], expect[1] = B.LLM42_SEQ_BAD_LENGTH, B.LLM42_SEQ_BAD_TOKEN    # (the second one's rows are there, and dead)
+    out, logits, k, v = _run(*env, n_seq, slot, n_valid, bad_token_of=1, expect_status=expect)
+    assert torch.equal(out[slot], alone[0])
+    assert torch.equal(logits, alone[1]) and torch.equal(k, alone[2]) and torch.equal(v, alone[3])
+    live = torch.as_tensor(np.arange(WINDOW)[None, :] < n_valid[:, None])
+    live[:2] = False
+    assert bool(((out >= 0) == live).all())
+
+
+@pytest.mark.timeout(300)
+def test_partly_filled_windows_as_whole_sequence_items():
+    shape = wl.TINY
+    sess = VerifierSession(shape, wl.make_weights(shape, seed=48), max_position=2400, device=DEV)
+    window, slot, L = 64, 131, 2200
+    target = wl.random_tokens(wl.rng_for(48, 1), window, shape.vocab)
+
+    def run(n_seq, slot):
+        rng = wl.rng_for(48, 2, n_seq)
+        lens = rng.integers(2150, 2250, size=n_seq).astype(np.int32)
+        lens[slot] = L
+        n_valid = rng.integers(1, window + 1, size=n_seq).astype(np.int32)
+        n_valid[slot] = 41
+        table, blocks = wl.make_block_table(rng, lens + window, 16, spare_blocks=2)
+        bt = torch.as_tensor(table, device=DEV)
+        kv = sess.kv_cache(blocks)
+        kv.normal_(generator=torch.Generator(device=DEV).manual_seed(n_seq))
+        mine = torch.empty((shape.n_layers, 2, 142, shape.n_kv_heads, 16 * shape.head_dim), dtype=torch.bfloat16, device=DEV)
+        kv[:, :, bt[slot, :142].long()] = mine.normal_(generator=torch.Generator(device=DEV).manual_seed(7))
+        cand = wl.random_tokens(rng, n_seq * window, shape.vocab).reshape(n_seq, window)
+        cand[slot] = target
+        d = lambda a: torch.as_tensor(a, device=DEV)
+        mc = int(lens.max()) + window
+        out, status, logits = sess.verify(kv, bt, d(lens), d(cand), n_valid=d(n_valid), max_context=mc,
+                                          dump_seq_ids=torch.tensor([slot], dtype=torch.int32, device=DEV))
+        torch.cuda.synchronize()
+        assert int(status.max()) == 0
+        plan = B.llm42_measure_attention_plan(sess.model, n_seq, window, mc)
+        if plan["may_take_sequences"]:
+            flag = sess.workspace(n_seq, window, mc)[plan["sequences_flag_offset"]:plan["sequences_flag_offset"] + 4]
+            assert int(flag.view(torch.int32)[0]) == 1
+        return out[slot].cpu(), logits[0, :41].cpu(), plan["may_take_sequences"]
+
+    few, many = run(1, 0), run(256, slot)
+    assert many[2] and not few[2]
+    assert torch.equal(few[0], many[0]) and torch.equal(few[1], many[1])
+    sess.close()

@@ -945,26 +945,32 @@ __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const
       fold<1>(M, Ls, A, ml.x, ml.y, B);
     }
   } else {
-    constexpr int PER = SUPER_KEYS / CHUNK;
+    // The partials of half a super are requested together (those past the last one clamped to it): folding them as they
+    // come is one dependent round trip after the other.
+    constexpr int PER = SUPER_KEYS / CHUNK, U = 4;
     const int last = (L + i) / CHUNK;
     M = 0.f;
     Ls = 0.f;
     A[0] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    for (int c0 = 0; c0 <= last; c0 += PER) {
-      float2 ml = slot_ml(c0);
-      float m2 = ml.x, l2 = ml.y;
-      f32x4 a2[1] = {slot_acc(c0)};
-      for (int c = c0 + 1; c <= min(c0 + PER - 1, last); ++c) {
-        ml = slot_ml(c);
-        const f32x4 B[1] = {slot_acc(c)};
-        fold<1>(m2, l2, a2, ml.x, ml.y, B);
+    float m2 = 0.f, l2 = 0.f;
+    f32x4 a2[1] = {(f32x4){0.f, 0.f, 0.f, 0.f}};
+    for (int c0 = 0; c0 <= last; c0 += U) {
+      float2 ml[U];
+      f32x4 acc[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        ml[u] = slot_ml(min(c0 + u, last));
+        acc[u] = slot_acc(min(c0 + u, last));
       }
-      if (c0 == 0) {
-        M = m2;
-        Ls = l2;
-        A[0] = a2[0];
-      } else {
-        fold<1>(M, Ls, A, m2, l2, a2);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const f32x4 B[1] = {acc[u]};
+        if (u == 0 && c0 % PER == 0) m2 = ml[0].x, l2 = ml[0].y, a2[0] = acc[0];
+        else if (c0 + u <= last) fold<1>(m2, l2, a2, ml[u].x, ml[u].y, B);
+      }
+      if (c0 % PER == PER - U || c0 + U > last) {   // the super is complete
+        if (c0 < PER) M = m2, Ls = l2, A[0] = a2[0];
+        else fold<1>(M, Ls, A, m2, l2, a2);
       }
     }
   }

@@ -15,7 +15,7 @@ __global__ void prepare_kernel(const int32_t* __restrict__ seq_lens, const int32
                                int32_t* seq_status, int32_t* row_pos, int32_t* row_seq, int32_t* ws_len,
                                int32_t* ws_n, int32_t* dump_slot, const float2* __restrict__ rope, int half_dim,
                                int32_t* row_blk, float2* row_rope, int min_n, int status_or,
-                               uint16_t* __restrict__ attn_zero, int d_attn, int32_t* __restrict__ live) {
+                               uint16_t* __restrict__ attn_zero, int d_attn, int32_t* __restrict__ live, int m_pad) {
   __shared__ int status, before;
   const int s = blockIdx.x;
   if (threadIdx.x == 0) status = 0, before = 0;
@@ -57,6 +57,15 @@ __global__ void prepare_kernel(const int32_t* __restrict__ seq_lens, const int32
     // where the row's K and V go (a block id that passed the check above), for the QKV epilogue
     row_blk[row] = part ? block_table[(size_t)s * max_blocks_per_seq + ((L + i) >> 4)] : 0;
   }
+  // rows beyond those of the sequences, which only pad the GEMM grid: the last sequence's workgroup knows where they begin
+  // (a launch of their own took 4 us of the smallest passes)
+  if (s == (int)gridDim.x - 1) {
+    for (int row = base + rows + (int)threadIdx.x; row < m_pad; row += blockDim.x) {
+      row_pos[row] = -1;
+      row_seq[row] = 0;
+      row_blk[row] = 0;
+    }
+  }
   // the rotary factors of every live row, laid out by row so that the QKV epilogue finds them without
   // knowing the position first
   if (st == 0) {
@@ -83,17 +92,6 @@ __global__ void prepare_kernel(const int32_t* __restrict__ seq_lens, const int32
     for (int j = 0; j < n_dump; ++j)
       if (dump_seq_ids[j] == s) slot = j;
     dump_slot[s] = slot;
-  }
-}
-
-// Rows beyond those of the sequences (`from`, or *live where rows are packed) that only pad the GEMM grid.
-__global__ void prepare_pad_rows_kernel(int32_t* row_pos, int32_t* row_seq, int32_t* row_blk, int from, int to,
-                                        const int32_t* __restrict__ live) {
-  const int r = from + blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < to && (!live || r >= *live)) {
-    row_pos[r] = -1;
-    row_seq[r] = 0;
-    row_blk[r] = 0;
   }
 }
 
@@ -387,10 +385,7 @@ void launch_prepare(const llm42_model* m, const llm42_kv_cache* kv, const int32_
                                           out_tokens, seq_status, ws.row_pos, ws.row_seq, ws.seq_len, ws.seq_n,
                                           ws.dump_slot, (const float2*)m->rope, m->cfg.head_dim / 2, ws.row_blk,
                                           ws.row_rope, prefill_pass ? 0 : 1, prefill_pass ? 1 : 0,
-                                          ws.attn, m->d_attn, ws.live);
-  const int from = ws.live ? 0 : ws.m_rows;
-  if (ws.m_pad > from)
-    prepare_pad_rows_kernel<<<(ws.m_pad - from + 63) / 64, 64, 0, st>>>(ws.row_pos, ws.row_seq, ws.row_blk, from, ws.m_pad, ws.live);
+                                          ws.attn, m->d_attn, ws.live, ws.m_pad);
 }
 
 void launch_prefill_window(const int32_t* prompt_tokens, const int32_t* prompt_offsets, const int32_t* seq_lens,

@@ -165,17 +165,21 @@ Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context,
   // (min_part_rows: llm42_workspace_bytes sizes the partials for every call of up to max_seqs sequences - a call of
   // fewer sequences may run per chunk where the largest runs per super, with 8 x the slots per sequence)
   const size_t part_rows = std::max((size_t)num_seqs * c.n_kv_heads * ws.attn_units * ws.r_pad, min_part_rows);
-  ws.part_acc = (float*)take(4ull * part_rows * c.head_dim);
-  ws.part_ml = (float*)take(8ull * part_rows);
   ws.attn_items = (int4*)take(sizeof(int4) * std::max((size_t)num_seqs * ws.attn_units, min_part_rows / ((size_t)c.n_kv_heads * ws.r_pad)));
   ws.attn_ctrl_offset = off;
-  ws.attn_ctrl = (int32_t*)take(sizeof(int32_t) * (3 + c.n_layers));
+  ws.attn_ctrl = (int32_t*)take(sizeof(int32_t) * (2 + c.n_layers));
+  const size_t partials = off;
+  ws.part_acc = (float*)take(4ull * part_rows * c.head_dim);
+  ws.part_ml = (float*)take(8ull * part_rows);
   ws.amax = (float2*)take(8ull * ws.m_pad * (c.vocab / 16));
-  // (up to 64 rows the halves of a split GEMM live in the arg-max partials where those are large enough: nothing uses them
-  // before the last of the halves has been added)
+  // Up to 64 rows the halves of a split GEMM lie over the attention and the arg-max partials, which hold nothing between a
+  // layer's attention and the next layer's (or the LM head): a call needs no more scratch for them unless those are
+  // smaller than the halves' 512 d_model bytes, and then it is far from what LLM42_STATIC_SCRATCH_BYTES holds.
   const size_t halves = 2 * 4ull * ws.m_pad * c.d_model;
-  if (ws.m_pad <= 64 && halves <= 8ull * ws.m_pad * (c.vocab / 16)) ws.split_part = (float*)ws.amax;
-  else ws.split_part = (float*)take(halves);
+  if (ws.m_pad <= 64) {
+    ws.split_part = base ? (float*)(base + partials) : nullptr;
+    off = std::max(off, align_up(partials + halves, 256));
+  } else ws.split_part = (float*)take(halves);
   ws.bytes = off;
   return ws;
 }
@@ -226,7 +230,7 @@ llm42_status run_pass(const llm42_model* m, const llm42_kv_cache* kv, const int3
   const llm42_config& c = m->cfg;
   // Partly filled windows: the rows are packed, and what pads the end of the grid is skipped.  (Each workgroup of the prepare
   // launch adds up the counts before it, so not for very many sequences.)
-  ws.live = n_valid && num_seqs <= 4096 ? ws.attn_ctrl + 2 + c.n_layers : nullptr;
+  ws.live = n_valid && num_seqs <= 4096 ? ws.seq_n + num_seqs - 1 : nullptr;
   TIMED(LLM42_K_PREPARE, launch_prepare(m, kv, seq_lens, candidates, n_valid, num_seqs, window, max_context,
                                         dump_seq_ids, n_dump, out_tokens, seq_status, ws, st, prefill_pass));
   if (ws.attn_list) TIMED(LLM42_K_PREPARE, launch_attention_plan(m, num_seqs, max_context, ws, st));

@@ -580,7 +580,7 @@ __global__ __launch_bounds__(64 * (WN * WM + F), (WGS * (WN * WM + F) + 3) / 4) 
   static_assert(CH == 1 || CH % 2 == 0, "operand registers alternate");
   __shared__ bf16x8 ring[R][CH * ST * 64];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (live) tiles_m = max(1, (*live + 16 * TBM - 1) / (16 * TBM));   // packed rows: the tiles that hold any
+  if (live) tiles_m = max(1, (live_rows(live) + 16 * TBM - 1) / (16 * TBM));   // packed rows: the tiles that hold any
   const int all = tiles_n * tiles_m, per_xcd = (all * planes + 7) / 8;
   const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   const int plane = tile / all, at = tile - plane * all;
@@ -726,7 +726,7 @@ __global__ __launch_bounds__(256, WGS) void gemm_tiled_kernel(const bf16x8* __re
   // G is 32 when that still gives every XCD a super-tile, less for small launches; SM follows the
   // number of token tiles.  (A workgroup without a tile still has to wait for a CU with free LDS
   // before it can leave, so holes in the numbering are expensive.)
-  if (live) tiles_m = max(1, (*live + 16 * TBM - 1) / (16 * TBM));   // packed rows: the tiles that hold any
+  if (live) tiles_m = max(1, (live_rows(live) + 16 * TBM - 1) / (16 * TBM));   // packed rows: the tiles that hold any
   const int G = group_tiles, SM = sm_tiles, SN = G / SM;
   const int sup_n = (tiles_n + SN - 1) / SN, sup_m = (tiles_m + SM - 1) / SM;
   const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;

@@ -97,6 +97,8 @@ __host__ __device__ inline int tag_index(int tag) { return tag & 1023; }
 __host__ __device__ inline int seq_tag(int n, int base) { return base << 10 | n; }
 __host__ __device__ inline int tag_rows(int tag) { return tag & 1023; }
 __host__ __device__ inline int tag_base(int tag) { return tag >> 10; }
+// Packed rows end where those of the last sequence do (its tag, Workspace::live, says where).
+__device__ inline int live_rows(const int32_t* live) { return tag_base(*live) + tag_rows(*live); }
 
 // Workspace carving, identical in llm42_workspace_bytes and llm42_verify_window.
 struct Workspace {
@@ -114,11 +116,11 @@ struct Workspace {
   bool batch_chosen; // off the fixed schedule (fast-path decode step, cost-of-determinism measurement): the batch may
                      // choose the split of the residual projections and the attention partials
   // Rows of a pass: sequence s has rows base(s) .. base(s) + n(s) - 1.  With n_valid the rows are packed - base(s) is the sum
-  // of the counts before - and *live of them exist (host: null otherwise); without, base(s) = s * window.
+  // of the counts before - and live_rows(live) of them exist; without, base(s) = s * window and `live` is null.
   int32_t *row_pos, *row_seq;        // position (-1: takes no part), row_tag(s, i)
   int32_t *seq_len, *seq_n;          // cached length (-1: takes no part), seq_tag(n, base)
   int32_t *dump_slot;
-  int32_t* live;
+  const int32_t* live;               // the last sequence's entry of seq_n
   int32_t* row_blk;    // physical KV block that holds the row's position (0 for dead rows)
   float2* row_rope;    // [m_pad][head_dim/2] (cos, sin) at the row's position
   float* resid;
@@ -127,7 +129,7 @@ struct Workspace {
   float *part_acc, *part_ml;
   int4* attn_items;     // (sequence, unit, length, rows) of every unit that holds keys, built once per call
   int32_t* attn_ctrl;   // [0] number of items, [1 + layer] work queue counter of that layer's attention launch,
-                        // [1 + n_layers] 1 if the items are whole sequences, [2 + n_layers] *live
+                        // [1 + n_layers] 1 if the items are whole sequences
   size_t attn_ctrl_offset;   // byte offset of attn_ctrl in the workspace
   float* split_part;   // fp32 halves of a split GEMM, [2][m_pad][d_model]
   float2* amax;   // [m_pad][vocab/16] (value, index bits)

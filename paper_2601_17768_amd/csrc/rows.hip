@@ -15,7 +15,7 @@ __global__ void prepare_kernel(const int32_t* __restrict__ seq_lens, const int32
                                int32_t* seq_status, int32_t* row_pos, int32_t* row_seq, int32_t* ws_len,
                                int32_t* ws_n, int32_t* dump_slot, const float2* __restrict__ rope, int half_dim,
                                int32_t* row_blk, float2* row_rope, int min_n, int status_or,
-                               uint16_t* __restrict__ attn_zero, int d_attn, int32_t* __restrict__ live, int m_pad) {
+                               uint16_t* __restrict__ attn_zero, int d_attn, bool packed, int m_pad) {
   __shared__ int status, before;
   const int s = blockIdx.x;
   if (threadIdx.x == 0) status = 0, before = 0;
@@ -26,9 +26,9 @@ __global__ void prepare_kernel(const int32_t* __restrict__ seq_lens, const int32
   // (min_n is 1; a prefill pass passes 0: a sequence whose prompt has ended takes no part in the pass)
   auto bad_length = [&](int len, int cnt) { return len < 0 || cnt < min_n || cnt > window || (int64_t)len + cnt > max_context; };
   if (bad_length(L, n)) bad = LLM42_SEQ_BAD_LENGTH;
-  // `live` given: packed rows.  What fails a check of its length has none, what fails a later one keeps dead rows.
-  const int rows = !live ? window : bad ? 0 : n;
-  if (live) {
+  // Packed rows: what fails a check of its length has none, what fails a later one keeps dead rows.
+  const int rows = !packed ? window : bad ? 0 : n;
+  if (packed) {
     int sum = 0;
     for (int t = threadIdx.x; t < s; t += blockDim.x) sum += bad_length(seq_lens[t], n_valid[t]) ? 0 : n_valid[t];
     if (sum) atomicAdd(&before, sum);
@@ -46,7 +46,7 @@ __global__ void prepare_kernel(const int32_t* __restrict__ seq_lens, const int32
   }
   if (bad) atomicOr(&status, bad);   // integer OR: order-free
   __syncthreads();
-  const int st = status, base = live ? before : s * window;
+  const int st = status, base = packed ? before : s * window;
   for (int i = threadIdx.x; i < window; i += blockDim.x) {
     if (out_tokens) out_tokens[(size_t)s * window + i] = -1;   // overwritten by the arg-max merge for rows that take part
     if (i >= rows) continue;
@@ -86,7 +86,6 @@ __global__ void prepare_kernel(const int32_t* __restrict__ seq_lens, const int32
   if (threadIdx.x == 0) {
     ws_len[s] = st == 0 && n > 0 ? L : -1;
     ws_n[s] = seq_tag(st == 0 ? n : 0, base);
-    if (live && s == (int)gridDim.x - 1) *live = base + rows;
     if (seq_status) seq_status[s] = status_or ? (seq_status[s] | st) : st;
     int slot = -1;
     for (int j = 0; j < n_dump; ++j)
@@ -329,7 +328,7 @@ __global__ __launch_bounds__(64 * R) void rmsnorm_block_kernel(float* __restrict
                                                                const uint16_t* __restrict__ gain,
                                                                uint16_t* __restrict__ y, float eps,
                                                                const int32_t* __restrict__ live) {
-  if (live && (int)blockIdx.x * R >= *live) return;      // packed rows: only what pads (workgroup-uniform)
+  if (live && (int)blockIdx.x * R >= live_rows(live)) return;      // packed rows: only what pads (workgroup-uniform)
   constexpr int D = 4096, U = 8;                         // tiles of 32 features per thread: t = u * 16 + w
   __shared__ float part[64][R];
   __shared__ float inv_s[R];
@@ -385,7 +384,7 @@ void launch_prepare(const llm42_model* m, const llm42_kv_cache* kv, const int32_
                                           out_tokens, seq_status, ws.row_pos, ws.row_seq, ws.seq_len, ws.seq_n,
                                           ws.dump_slot, (const float2*)m->rope, m->cfg.head_dim / 2, ws.row_blk,
                                           ws.row_rope, prefill_pass ? 0 : 1, prefill_pass ? 1 : 0,
-                                          ws.attn, m->d_attn, ws.live, ws.m_pad);
+                                          ws.attn, m->d_attn, ws.live != nullptr, ws.m_pad);
 }
 
 void launch_prefill_window(const int32_t* prompt_tokens, const int32_t* prompt_offsets, const int32_t* seq_lens,

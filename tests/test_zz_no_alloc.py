@@ -71,3 +71,21 @@ def test_static_scratch_entry_matches_the_workspace_entry_twice_in_a_row():
     torch.cuda.synchronize()
     assert bool((out == -7).all())
     sess.close()
+
+
+@pytest.mark.timeout(300)
+def test_small_vocabulary_leaves_the_built_in_area_to_the_attention_partials():
+    """64 rows at d_model 4096 with few logits: the k-halves of the residual projections (2 MiB here) lie over partials
+    that are dead by then, so a call whose other buffers just fit the built-in area is accepted."""
+    shape = wl.LLAMA_8B.replace(n_layers=1, n_q_heads=8, n_kv_heads=8, head_dim=64, d_ffn=1024, vocab=512)
+    supers = 29                                          # attention partials: 2 MiB + 64 KiB per 2048 keys of context
+    max_context, n_seq = supers * 2048, 64
+    sess = VerifierSession(shape, wl.make_weights(shape, seed=53), max_position=max_context, device=DEV)
+    need = B.llm42_workspace_bytes(sess.model, n_seq, 1, max_context)
+    assert B.LLM42_STATIC_SCRATCH_BYTES - (2 << 20) < need <= B.LLM42_STATIC_SCRATCH_BYTES
+    rng = wl.rng_for(53, 1)
+    kv, num_blocks, bt, lens, cand, n_valid, _ = _case(sess, shape, rng, n_seq, 1, 1, 300)
+    wide = torch.zeros((n_seq, max_context // 16), dtype=torch.int32, device=DEV)
+    wide[:, :bt.shape[1]] = bt
+    _both_ways(sess, shape, (kv, num_blocks, wide, lens, cand, n_valid, max_context), 1)
+    sess.close()

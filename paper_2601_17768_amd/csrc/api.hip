@@ -504,11 +504,11 @@ llm42_status llm42_measure_attention_plan(const llm42_model* m, int32_t num_seqs
       (int64_t)num_seqs * window > LLM42_MAX_ROWS)
     return fail(LLM42_EINVAL, "measure_attention_plan: num_seqs/window/max_context out of range");
   const Workspace ws = carve(m, num_seqs, window, max_context, nullptr);
-  out[0] = ws.attn_super ? 2048 : 256;
-  out[1] = ws.attn_direct ? 1 : 0;
+  out[0] = ws.attn_super && !ws.attn_split ? 2048 : 256;
+  out[1] = ws.attn_direct || ws.attn_split ? 1 : 0;
   out[2] = ws.attn_seq ? 1 : 0;
   out[3] = (int64_t)(ws.attn_ctrl_offset + sizeof(int32_t) * (1 + m->cfg.n_layers));
-  out[4] = ws.r_pad / 16 >= 8 ? 1 : 0;
+  out[4] = ws.attn_split ? 2 : ws.r_pad / 16 >= 8 ? 1 : 0;
   return LLM42_OK;
 }
 

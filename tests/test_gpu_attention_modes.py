@@ -2,7 +2,8 @@
 (element by element, spec tolerance) on contexts that reach past one, two and three
 2048-key units: one workgroup per 256-key chunk (4-wave and 8-wave streaming kernels, all folds in
 the merge pass), one per 2048-key super (chunks folded in registers, supers in the merge pass),
-the attention kernel writing the output itself (contexts within one unit), and whole sequences
+the attention kernel writing the output itself (contexts within one unit), one workgroup per 16 query
+rows with the chunks dealt to its waves (few workgroups, contexts within one unit), and whole sequences
 as work items (supers folded in registers too).  The distribution never changes a bit, so
 the same target must also give the same bits in every company."""
 import numpy as np
@@ -35,7 +36,7 @@ def env():
 
 def _run(env, L, window, companions, slot, expect, seed):
     """Verify tokens[L : L + window] behind the checker's prefix, among `companions` (contexts, KV = seeded
-    noise).  expect: item_keys / direct / streaming / sequences as the plan must report them."""
+    noise).  expect: item_keys / direct / streaming / split / sequences as the plan must report them."""
     shape, w, cfg, tokens, okv, sess = env
     rng = wl.rng_for(42, seed)
     lens = np.concatenate([companions[:slot], [L], companions[slot:]]).astype(np.int32)
@@ -51,6 +52,7 @@ def _run(env, L, window, companions, slot, expect, seed):
     plan = B.llm42_measure_attention_plan(sess.model, n_seq, window, max_context)
     assert plan["item_keys"] == expect["item_keys"] and plan["direct"] == expect["direct"], plan
     assert plan["streaming"] == expect["streaming"] and plan["may_take_sequences"] == expect["sequences"], plan
+    assert plan["split"] == expect.get("split", False), plan
     d = lambda a: torch.as_tensor(a, device=DEV)
     out, status, logits = sess.verify(kv, bt, d(lens), d(cand), dump_seq_ids=torch.tensor([slot], dtype=torch.int32, device=DEV),
                                       max_context=max_context)
@@ -76,6 +78,7 @@ SUPER4 = dict(item_keys=2048, direct=False, streaming=False, sequences=False)
 SUPER8 = dict(item_keys=2048, direct=False, streaming=True, sequences=False)
 DIRECT4 = dict(item_keys=2048, direct=True, streaming=False, sequences=False)
 DIRECT8 = dict(item_keys=2048, direct=True, streaming=True, sequences=False)
+SPLIT = dict(item_keys=256, direct=True, streaming=False, sequences=False, split=True)
 SEQS = dict(item_keys=2048, direct=False, streaming=True, sequences=True)
 
 
@@ -87,7 +90,9 @@ def test_contexts_past_one_unit_in_every_distribution(env, L):
     some = wl.uniform_lengths(rng, 100, 100, L)              # 101 sequences: one workgroup per super
     even = wl.uniform_lengths(rng, 255, L - 100, L)          # 256 sequences of about the same length: whole sequences
     # (window 8 behind 2040 keys ends exactly at the first unit's last key: such a call needs no merge pass)
-    got8 = [_run(env, L, 8, none, 0, CHUNK4, 1), _run(env, L, 8, some, 17, DIRECT4 if L + 8 <= 2048 else SUPER4, 2)]
+    got8 = [_run(env, L, 8, none, 0, CHUNK4, 1), _run(env, L, 8, some, 17, SPLIT if L + 8 <= 2048 else SUPER4, 2)]
+    if L + 8 <= 2048:                                        # 301 sequences: more workgroups than the split kernel takes
+        got8.append(_run(env, L, 8, wl.uniform_lengths(rng, 300, 100, L), 17, DIRECT4, 9))
     got64 = [_run(env, L, 64, none, 0, CHUNK8, 3), _run(env, L, 64, some, 100, SUPER8, 4),
              _run(env, L, 64, even, 100, SEQS, 5)]
     for g in got8[1:]:
@@ -102,7 +107,8 @@ def test_contexts_within_one_unit_without_a_merge_pass(env):
     L = 1970
     rng = wl.rng_for(42, 63)
     many = wl.uniform_lengths(rng, 63, 50, 1980)             # 64 sequences, every context within 2048 keys
-    a = _run(env, L, 8, many, 40, DIRECT4, 6)
+    a = _run(env, L, 8, many, 40, SPLIT, 6)
+    a16 = _run(env, L, 16, wl.uniform_lengths(rng, 69, 50, 1970), 40, DIRECT4, 10)   # 2 row blocks x 70 sequences x 2 kv heads
     b = _run(env, L, 64, many, 0, DIRECT8, 7)
     c = _run(env, L, 64, np.zeros(0, dtype=np.int32), 0, CHUNK8, 8)
-    assert torch.equal(b, c) and torch.equal(a, b[:8])
+    assert torch.equal(b, c) and torch.equal(a, b[:8]) and torch.equal(a16, b[:16])

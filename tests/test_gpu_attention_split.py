@@ -8,6 +8,7 @@ import torch
 
 from helpers import wl
 from gpu_helpers import VerifierSession
+from paper_2601_17768_amd import binding as B
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -22,7 +23,7 @@ def env(request):
     sess.close()
 
 
-def _run(shape, sess, L, window, rows, others, other_len, max_context):
+def _run(shape, sess, L, window, rows, others, other_len, max_context, split=None):
     """Target first among `others` sequences of `other_len` cached keys; its cache is the same in every company and
     holds NaN behind its last position."""
     rng = wl.rng_for(51, L, window)
@@ -43,6 +44,8 @@ def _run(shape, sess, L, window, rows, others, other_len, max_context):
     cand[0] = cand_t
     nv = np.full(1 + others, window, dtype=np.int32)
     nv[0] = rows
+    if split is not None:
+        assert B.llm42_measure_attention_plan(sess.model, 1 + others, window, max_context)["split"] == split
     d = lambda a: torch.as_tensor(a, device=DEV)
     out, status, logits = sess.verify(kv, bt, d(lens), d(cand), n_valid=d(nv), max_context=max_context,
                                       dump_seq_ids=torch.zeros(1, dtype=torch.int32, device=DEV))
@@ -58,8 +61,8 @@ def test_same_bits_as_in_a_large_group(env, L, window, rows):
         pytest.skip("such a call takes the other kernels anyway")
     shape, sess = env
     # alone, bounded tightly: the split kernel; behind a bound beyond one super: chunk items and the merge pass
-    alone = _run(shape, sess, L, window, rows, 0, 0, max(L + window, 16))
-    merged = _run(shape, sess, L, window, rows, 0, 0, 2048 if L + window > 1280 else 1281)
+    alone = _run(shape, sess, L, window, rows, 0, 0, max(L + window, 16), split=True)
+    merged = _run(shape, sess, L, window, rows, 0, 0, 2048 if L + window > 1280 else 1281, split=False)
     assert torch.isfinite(alone[1]).all()
     assert torch.equal(alone[0], merged[0]) and torch.equal(alone[1], merged[1])
     # several items per workgroup of the split kernel (300 sequences x 1-2 kv heads > 256), or the other kernels

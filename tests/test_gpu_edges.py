@@ -122,7 +122,7 @@ def test_one_workspace_serves_every_smaller_call(tiny):
     then needs more partial slots per sequence."""
     from paper_2601_17768_amd import binding as B
     shape, w, sess = tiny
-    window, max_seqs, max_context = 16, 110, 512
+    window, max_seqs, max_context = 24, 110, 1024
     rng = wl.rng_for(105, 1)
     ws = torch.empty(B.llm42_workspace_bytes(sess.model, max_seqs, window, max_context), dtype=torch.uint8, device=DEV)
     modes = set()
@@ -142,4 +142,5 @@ def test_one_workspace_serves_every_smaller_call(tiny):
                               window, None, max_context, out, ws)
     torch.cuda.synchronize()
     assert int(out.min()) >= 0
-    assert modes == {(256, False), (2048, True)}      # both work splits were crossed
+    # chunks dealt to waves (1 .. 21 sequences), chunk partials and the merge pass (22 .. 63), supers (64 and more)
+    assert modes == {(256, True), (256, False), (2048, True)}

@@ -115,8 +115,14 @@ void attention_mode(const llm42_model* m, int num_seqs, int max_context, Workspa
   // (A single long sequence is better off with its chunks spread over the CUs, merge pass and all.)
   const long long wgs = (long long)num_seqs * c.n_kv_heads * col_blocks, cus = ws.num_cus;
   const bool spread = max_context > 1280 && wgs * 6 < cus;
+  // Head dimension 64, one row block: a CU holds two of the workgroups there (see launch_split); us per layer, other kernels ->
+  // this one, by workgroups x keys: 384 x 500 20 -> 17, 512 x 250 18 -> 13, 512 x 1000 32 -> 28, 512 x 1900 49 -> 52,
+  // 1024 x 500 38 -> 31 - 36, 1024 x 1000 57 -> 56 - 60, 2048 x 64 35 -> 23, 2048 x 500 66 -> 63, 2048 x 1000 106 -> 112,
+  // 8192 x 250 142 -> 145.  Head dimension 128: 1024 x 1000 116 -> 111, 512 x 1900 98 -> 97 - 101.
+  const int one_block_limit = c.head_dim == 64 ? (wgs <= cus ? 2048 : wgs <= 2 * cus ? 1280 : 512)
+                                               : (wgs <= 2 * cus ? 2048 : 1024);
   ws.attn_split = supers == 1 && !spread &&
-                  (col_blocks == 1   ? wgs <= 2 * cus || max_context <= 1024
+                  (col_blocks == 1   ? max_context <= one_block_limit
                    : col_blocks == 2 ? wgs <= cus
                                      : wgs <= cus && max_context <= 1280 && wgs * max_context <= 512 * cus);
   ws.attn_list = !ws.attn_split || wgs > cus;

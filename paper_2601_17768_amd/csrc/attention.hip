@@ -1032,7 +1032,11 @@ void launch_split(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, 
                   int window, const Workspace& ws, hipStream_t st) {
   const llm42_config& c = m->cfg;
   const float scale_log2 = (1.0f / sqrtf((float)c.head_dim)) * 1.44269504088896340736f;
-  const unsigned grid = (unsigned)std::min<long long>(m->num_cus, (long long)num_seqs * c.n_kv_heads * (ws.r_pad / 16));
+  // As many workgroups as the device holds at once: one per CU at head dimension 128 (its 418 registers per wave), two at 64
+  // (250 registers, 33 KiB of LDS).  One per CU there left half of each idle: 2048 workgroups' worth of work 62 us at 250
+  // keys and 36 at 64, with two per CU 39 and 23.
+  constexpr int kPerCu = HD == 64 ? 2 : 1;
+  const unsigned grid = (unsigned)std::min<long long>((long long)kPerCu * m->num_cus, (long long)num_seqs * c.n_kv_heads * (ws.r_pad / 16));
   attention_split_kernel<HD><<<grid, 256, 0, st>>>(
       ws.q, (const bf16x8*)kp, (const u32x4*)vp, kv->block_table, ws.seq_len, ws.seq_n, ws.attn_list ? ws.attn_items : nullptr,
       ws.attn_ctrl, num_seqs, c.n_kv_heads, m->group, window, ws.r_pad, kv->max_blocks_per_seq, scale_log2, ws.attn, m->d_attn);

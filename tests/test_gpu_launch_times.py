@@ -1,0 +1,65 @@
+"""Launches that a choice of kernel or tile must not make slower: each case compares two launches of the same process on the
+same device, between which the choice differs or should not matter.  The margins are far above the spread of a median
+(1 - 2 %) and far below what the wrong choice cost where it was measured (named at each case)."""
+import statistics
+
+import numpy as np
+import pytest
+import torch
+
+from helpers import wl
+from gpu_helpers import VerifierSession
+from paper_2601_17768_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _session(max_position, **dims):
+    shape = wl.LLAMA_8B.replace(n_layers=1, **dims)
+    return shape, VerifierSession(shape, wl.make_weights(shape, seed=57), max_position=max_position, device=DEV)
+
+
+def _times(shape, sess, n_seq, window, context, max_context=None, decode=False):
+    """Microseconds per pass of every launch class (median of 9 passes, behind 3 that are not counted)."""
+    rng = wl.rng_for(57, n_seq, window)
+    table, blocks = wl.make_block_table(rng, np.full(n_seq, context + window), 16, max_blocks_per_seq=(max(max_context or 0, context + window) + 15) // 16)
+    bt = torch.as_tensor(table, device=DEV)
+    kv = sess.kv_cache(blocks)
+    kv.normal_(generator=torch.Generator(device=DEV).manual_seed(3))
+    lens = torch.full((n_seq,), context, dtype=torch.int32, device=DEV)
+    cand = torch.as_tensor(wl.random_tokens(rng, n_seq * window, shape.vocab).reshape(n_seq, window), device=DEV)
+    out = torch.empty((n_seq, window), dtype=torch.int32, device=DEV)
+    max_context = max_context or context + window
+    ws = sess.workspace(n_seq, window, max_context)
+
+    def one():
+        if decode:
+            B.llm42_decode_step(sess.model, kv, blocks, bt, lens, cand.view(-1), max_context, out.view(-1), ws)
+        else:
+            B.llm42_verify_window(sess.model, kv, blocks, bt, lens, cand, window, None, max_context, out, ws)
+    for _ in range(3):
+        one()
+    torch.cuda.synchronize()
+    passes = 9
+    B.llm42_profile_enable(None, passes * 64)
+    for _ in range(passes):
+        one()
+    got = B.llm42_profile_collect(passes * 64)
+    per = len(got) // passes
+    assert per * passes == len(got)
+    kinds = {k for k, _ in got}
+    return {k: statistics.median(1e3 * sum(ms for kk, ms in got[p * per:(p + 1) * per] if kk == k) for p in range(passes))
+            for k in kinds}
+
+
+@pytest.mark.parametrize("n_seq,context", [(128, 250), (256, 100), (64, 500)])
+def test_attention_is_not_slower_for_a_tight_context_bound(n_seq, context):
+    """16 kv heads of 64 features: 1024 to 4096 workgroups of one row block.  A loose bound keeps the chunk-per-wave kernel away
+    (1.2 - 1.4 times as fast at these sizes while that one ran one workgroup per CU)."""
+    shape, sess = _session(1200, d_model=1024, n_q_heads=16, n_kv_heads=16, head_dim=64, d_ffn=1024, vocab=1024)
+    tight = _times(shape, sess, n_seq, 1, context)["attention"]
+    loose = _times(shape, sess, n_seq, 1, context, max_context=1100)["attention"]
+    print(f"{n_seq} x {context}: tight bound {tight:.1f} us, loose {loose:.1f} us")
+    assert tight <= 1.08 * loose
+    sess.close()

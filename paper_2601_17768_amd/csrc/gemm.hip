@@ -845,6 +845,16 @@ __global__ __launch_bounds__(256, WGS) void gemm_tiled_kernel(const bf16x8* __re
 // for the count, 0.7 us); beyond that the tiles that hold no row are left out.
 inline const int32_t* live_of(const Workspace& ws, long long tiles) { return tiles > ws.num_cus ? ws.live : nullptr; }
 
+// Token tiles side by side in a super-tile: the widest of 1, 2, 4 and 8 that leaves at most 15 % of the token columns empty.
+inline int super_width(int tiles_m, int most) {
+  int width = 1;
+  for (int w = 2; w <= most; w *= 2) {
+    const int padded = (tiles_m + w - 1) / w * w;
+    if ((padded - tiles_m) * 100 <= padded * 15) width = w;
+  }
+  return width;
+}
+
 // side_by_side (split GEMMs only): both k-halves in one launch of twice the workgroups, their sum left to the RMSNorm that
 // follows, instead of two launches one after the other - for launches that do not fill the
 // device by themselves.  The arithmetic per output element is the same either way.
@@ -865,12 +875,7 @@ void launch_tiled(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles,
   long long least = -1;
   for (int pass = 0; pass < 2; ++pass)
     for (int cand = 32; cand >= 4; cand /= 2) {
-      int csm = 1;
-      for (int w = 2; w <= sm_max && w <= cand; w *= 2) {
-        const int padded = (tiles_m + w - 1) / w * w;
-        if ((padded - tiles_m) * 100 <= padded * 15) csm = w;
-      }
-      const int csn = cand / csm;
+      const int csm = super_width(tiles_m, std::min(sm_max, cand)), csn = cand / csm;
       const int csupers = ((tiles_n + csn - 1) / csn) * ((tiles_m + csm - 1) / csm) * planes;
       const long long per_xcd = (long long)((csupers + 7) / 8) * cand;
       if (pass == 0) {
@@ -939,11 +944,11 @@ struct MidTile {
 };
 constexpr MidTile kMidTiles[6] = {{4, 4, 18, 0, 17}, {4, 8, 21, 0, 20}, {8, 8, 31, 0, 27}, {12, 8, 44, 0, 38}, {16, 8, 39, 7, 46}, {8, 16, 28, 19, 46}};
 
-// The cheapest of them for n_blocks x m_pad rows, `planes` times over.
-inline int pick_mid(int n_blocks, int m_pad, int planes, long long cus) {
+// The cheapest of the first `most` of them for n_blocks x m_pad rows, `planes` times over.
+inline int pick_mid(int n_blocks, int m_pad, int planes, long long cus, int most = 6) {
   int best = 0;
   long long least = 0;
-  for (int t = 0; t < 6; ++t) {
+  for (int t = 0; t < most; ++t) {
     const MidTile& q = kMidTiles[t];
     if (m_pad % (16 * q.bm)) continue;
     const long long tiles = (long long)((n_blocks + q.bn - 1) / q.bn) * (m_pad / (16 * q.bm)) * planes;
@@ -1008,26 +1013,37 @@ bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
   const long long cus = ws.num_cus;
   const long long t256 = m_pad % 256 == 0 ? (long long)((n_blocks + 7) / 8) * (m_pad / 256) : 0;
   const long long t128 = (long long)((n_blocks + 7) / 8) * (m_pad / 128);
-  // The ranges where gemm_mid_kernel is the faster one: up to 1280 rows for QKV and the split projections; up to 256 for
-  // gate/up, whose launches have enough 128 x 256 tiles for two workgroups per CU of gemm_tiled_kernel beyond that; any
-  // number for the LM head (1 - 14 %), there with the tile that re-reads the activations least: 128 x 256 for 256 - 2048 rows,
-  // 256 x 128 otherwise (2560 rows: 2541 us against 2862, 8192: 8318 against 10782; 2048: 2095 against 2061).
-  if (kLogits || m_pad <= (std::is_same<Epi, SwigluEpi>::value ? 256 : 1280)) {
-    const int tile = !kLogits ? pick_mid(n_blocks, m_pad, SPLIT, cus) : m_pad % 256 == 0 && m_pad <= 2048 ? 5 : 4;
-    if constexpr (SPLIT == 2)
-      launch_mid(tile, wp, xp, n_blocks, k_tiles, split_point(k_tiles), 2, ws,
-                 StorePartialEpi{ws.split_part, ws.rl, n, (size_t)m_pad * n}, st);
-    else launch_mid(tile, wp, xp, n_blocks, k_tiles, k_tiles, 1, ws, epi, st);
-    return SPLIT == 2;
-  }
-  if constexpr (!kLogits) {
-    // More rows (m_pad is a multiple of 256 here).  Larger tiles
-    // move fewer operand bytes per flop, smaller ones give more workgroups; the best choice is the largest tile that still
-    // yields about as many workgroups as
-    // the device has CUs.  Where the epilogue is heavy (rotary embedding and cache writes) the 128 x 256
-    // tile waits until it fills the device, since its epilogues overlap less with other workgroups' main
-    // loops.  A split GEMM runs its halves side by side unless each half
-    // fills the device by itself.
+  if constexpr (kLogits) {
+    // LM head: more than 2048 rows take gemm_tiled_kernel with 128 x 128 tiles, which fill the device there (8B, gemm_mid_kernel
+    // -> this: 3072 rows 2870 -> 2750 us, 4096 3910 -> 3770, 8192 7870 -> 7390; vocabulary 65536: 8192 rows 4220 -> 3810;
+    // d_model 1024, vocabulary 50304: 4096 rows 503 -> 465), unless its super-tiles eight wide would be ragged (3584 rows: 3390
+    // against 5580).  Below, the tile that re-reads the activations least, 128 x 256 for 256 - 2048 rows and 256 x 128
+    // otherwise (8B, 2048 rows, logits written out: 1990 us against 2043) - if there are enough of either: a small vocabulary takes the cheapest of
+    // all the tiles (4096 logits, 128 rows: 62 us against 24, 512 rows: 59 against 28), and with few k-tiles, where a
+    // tile's epilogue weighs most, the cheapest of those that share a CU (32 k-tiles x 50304 logits, 512 rows: 74 against 61).
+    if (m_pad > 2048 && t128 * 4 >= 3 * cus && !(super_width(m_pad / 128, 8) == 8 && m_pad % 1024)) {
+      launch_tiled<4, 4, 4, 2, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, false);
+      return false;
+    }
+    const int tile = pick_mid(n_blocks, m_pad, 1, cus, k_tiles < 64 ? 3 : 6);
+    launch_mid(tile < 4 ? tile : m_pad % 256 == 0 && m_pad <= 2048 ? 5 : 4, wp, xp, n_blocks, k_tiles, k_tiles, 1, ws, epi, st);
+    return false;
+  } else {
+    // The ranges where gemm_mid_kernel is the faster one: up to 1280 rows for QKV and the split projections; up to 256 for
+    // gate/up, whose launches have enough 128 x 256 tiles for two workgroups per CU of gemm_tiled_kernel beyond that.
+    if (m_pad <= (std::is_same<Epi, SwigluEpi>::value ? 256 : 1280)) {
+      const int tile = pick_mid(n_blocks, m_pad, SPLIT, cus);
+      if constexpr (SPLIT == 2)
+        launch_mid(tile, wp, xp, n_blocks, k_tiles, split_point(k_tiles), 2, ws,
+                   StorePartialEpi{ws.split_part, ws.rl, n, (size_t)m_pad * n}, st);
+      else launch_mid(tile, wp, xp, n_blocks, k_tiles, k_tiles, 1, ws, epi, st);
+      return SPLIT == 2;
+    }
+    // More rows (m_pad is a multiple of 256 here).  Larger tiles move fewer operand bytes per flop, smaller ones give more
+    // workgroups; the best choice is the largest tile that still yields about as many workgroups as the device has CUs.
+    // Where the epilogue is heavy (rotary embedding and cache writes) the 128 x 256 tile waits until it fills the device,
+    // since its epilogues overlap less with other workgroups' main loops.  A split GEMM runs its halves side by side unless
+    // each half fills the device by itself.
     const bool side_by_side = SPLIT == 2 && t256 < 2 * cus;
     const int p = side_by_side ? 2 : 1;
     const bool big = kQkv ? t256 >= 2 * cus : t256 * p * 5 >= 4 * cus;
@@ -1049,7 +1065,6 @@ bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
       launch_tiled<4, 4, 4, 2, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, side_by_side);
     return side_by_side;
   }
-  return false;
 }
 
 }  // namespace

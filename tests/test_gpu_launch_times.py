@@ -63,3 +63,19 @@ def test_attention_is_not_slower_for_a_tight_context_bound(n_seq, context):
     print(f"{n_seq} x {context}: tight bound {tight:.1f} us, loose {loose:.1f} us")
     assert tight <= 1.08 * loose
     sess.close()
+
+
+@pytest.fixture(scope="module")
+def square():
+    """QKV projection and LM head of the same 6144 x 4096 matrix size."""
+    shape, sess = _session(256, d_ffn=2048, vocab=6144)
+    yield shape, sess
+    sess.close()
+
+
+@pytest.mark.parametrize("rows", [128, 256, 512])
+def test_lm_head_of_a_small_vocabulary_costs_what_the_qkv_projection_does(square, rows):
+    """(53 - 57 us against 18 - 42 while the LM head took one of the two largest tiles at any vocabulary.)"""
+    t = _times(*square, rows // 16, 16, 16)
+    print(f"{rows} rows: LM head {t['lm_head']:.1f} us, QKV {t['qkv']:.1f} us")
+    assert t["lm_head"] <= 1.2 * t["qkv"]

@@ -57,7 +57,7 @@ def alone(env):
     return out[0], logits, k, v
 
 
-@pytest.mark.parametrize("n_seq", [2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 40, 41, 64, 65, 96, 97, 128, 160, 161])
+@pytest.mark.parametrize("n_seq", [2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 40, 41, 64, 65, 96, 97, 128, 160, 161, 192, 224, 256])
 def test_same_bits_at_every_row_count(env, alone, n_seq):
     slot = n_seq - 1
     out, logits, k, v = _run(*env, n_seq, slot)

@@ -936,6 +936,14 @@ void launch_narrow(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles
   }
 }
 
+// x + (p0 + p1) over the row blocks that hold rows: the halves of a split GEMM where the RMSNorm does not add them.
+__global__ __launch_bounds__(256) void add_halves_kernel(float* __restrict__ x, const float* __restrict__ p0,
+                                                         const float* __restrict__ p1, int n, const int32_t* __restrict__ live) {
+  const size_t at = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;                 // (a workgroup lies within a row block: n % 128 == 0)
+  if (live && (int)((size_t)blockIdx.x * 64 / n) * 16 >= live_rows(live)) return;
+  *(f32x4*)(x + at) = *(const f32x4*)(x + at) + (*(const f32x4*)(p0 + at) + *(const f32x4*)(p1 + at));
+}
+
 // Tiles of gemm_mid_kernel, in blocks of 16, and what they cost in 1/100 us per k-tile, fitted to launches within a pass
 // (the table at gemm_mid_kernel holds the best of each): one round of up to one workgroup per CU takes base + slope x its
 // share of the CUs, each of several rounds `more`.  A CU holds two of the 128 x 128 tile.
@@ -980,6 +988,20 @@ void launch_mid(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, int 
     case 4: return launch_mid_tile<4, 2, 4, 4, 1, 5, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, ws, epi, st);
     default: return launch_mid_tile<2, 4, 4, 4, 1, 6, 4, 1, true>(wp, xp, n_blocks, k_tiles, split, planes, ws, epi, st);
   }
+}
+
+// The halves in split_part: left to the RMSNorm that follows (true), or added here where that one runs a wave per row over
+// interleaved rows (more than 512, d_model other than 4096), whose pieces of 16 bytes cost more than this launch saves: at
+// 2048 rows the projections with their norms take 298 us a pass of two layers against 338 (d_model 2048), 140 against 153
+// (1024), and at 1280 rows of d_model 8192 1839 against 2037.
+template <class Epi>
+bool halves_pending(const Workspace& ws, int n, const Epi& epi, hipStream_t st) {
+  if constexpr (std::is_same<Epi, ResidualEpi>::value) {
+    if (norm_adds_halves(ws.m_pad, n)) return true;
+    const size_t plane = (size_t)ws.m_pad * n;
+    add_halves_kernel<<<(unsigned)(plane / 1024), 256, 0, st>>>(epi.resid, ws.split_part, ws.split_part + plane, n, ws.live);
+  }
+  return false;
 }
 
 // Returns whether a split GEMM left its two halves in split_part.
@@ -1037,7 +1059,7 @@ bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
         launch_mid(tile, wp, xp, n_blocks, k_tiles, split_point(k_tiles), 2, ws,
                    StorePartialEpi{ws.split_part, ws.rl, n, (size_t)m_pad * n}, st);
       else launch_mid(tile, wp, xp, n_blocks, k_tiles, k_tiles, 1, ws, epi, st);
-      return SPLIT == 2;
+      return SPLIT == 2 && halves_pending(ws, n, epi, st);
     }
     // More rows (m_pad is a multiple of 256 here).  Larger tiles move fewer operand bytes per flop, smaller ones give more
     // workgroups; the best choice is the largest tile that still yields about as many workgroups as the device has CUs.
@@ -1063,7 +1085,7 @@ bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
       launch_tiled<LLM42_TILE_BIG, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, side_by_side);
     else
       launch_tiled<4, 4, 4, 2, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, side_by_side);
-    return side_by_side;
+    return side_by_side && halves_pending(ws, n, epi, st);
   }
 }
 

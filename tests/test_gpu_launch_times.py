@@ -79,3 +79,15 @@ def test_lm_head_of_a_small_vocabulary_costs_what_the_qkv_projection_does(square
     t = _times(*square, rows // 16, 16, 16)
     print(f"{rows} rows: LM head {t['lm_head']:.1f} us, QKV {t['qkv']:.1f} us")
     assert t["lm_head"] <= 1.2 * t["qkv"]
+
+
+def test_norms_of_half_the_width_take_no_longer():
+    """2048 rows: the RMSNorms behind split projections at d_model 2048 and 4096 (90 us a pass against 70 while they added
+    the halves at both widths)."""
+    t = {}
+    for d in (2048, 4096):
+        shape, sess = _session(64, d_model=d, d_ffn=2048, vocab=1024)
+        t[d] = _times(shape, sess, 128, 16, 16)["rmsnorm"]
+        sess.close()
+    print(f"RMSNorms at 2048 rows: d_model 2048 {t[2048]:.1f} us, 4096 {t[4096]:.1f} us")
+    assert t[2048] <= t[4096]

@@ -91,3 +91,15 @@ def test_norms_of_half_the_width_take_no_longer():
         sess.close()
     print(f"RMSNorms at 2048 rows: d_model 2048 {t[2048]:.1f} us, 4096 {t[4096]:.1f} us")
     assert t[2048] <= t[4096]
+
+
+def test_few_tiles_are_made_smaller_at_any_row_count():
+    """The tests' small model: as many workgroups as CUs or fewer at all of these row counts, so more rows cost little (1.9
+    times as much for QKV from 1024 to 2048 rows and 1.3 for gate/up from 256 to 512 where only 128 x 128 tiles were left)."""
+    sess = VerifierSession(wl.TINY, wl.make_weights(wl.TINY, seed=57), max_position=64, device=DEV)
+    t = {rows: _times(wl.TINY, sess, rows // 16, 16, 16) for rows in (256, 512, 1024, 2048)}
+    print(f"QKV at 1024 and 2048 rows: {t[1024]['qkv']:.1f} and {t[2048]['qkv']:.1f} us; "
+          f"gate/up at 256 and 512: {t[256]['gate_up']:.1f} and {t[512]['gate_up']:.1f} us")
+    assert t[2048]["qkv"] <= 1.35 * t[1024]["qkv"]
+    assert t[512]["gate_up"] <= 1.18 * t[256]["gate_up"]
+    sess.close()

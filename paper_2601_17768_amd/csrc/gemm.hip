@@ -961,9 +961,9 @@ inline int pick_mid(int n_blocks, int m_pad, int planes, long long cus, int most
     if (m_pad % (16 * q.bm)) continue;
     const long long tiles = (long long)((n_blocks + q.bn - 1) / q.bn) * (m_pad / (16 * q.bm)) * planes;
     const long long rounds = (tiles + cus - 1) / cus;
-    const bool few_over = t == 2 && rounds == 2 && tiles * 4 <= cus * 5;   // (most CUs still have one 128 x 128 tile)
-    const long long cost = rounds == 1 ? q.base * 10 + q.slope * 10 * tiles / cus : few_over ? 460 : q.more * 10 * rounds;
-    if (t == 0 || cost < least) best = t, least = cost;
+    const long long cost = rounds == 1 ? q.base * 10 + q.slope * 10 * tiles / cus : q.more * 10 * rounds;
+    // (as many rounds of 256 x 128 as of 128 x 256: the latter, by 1 - 4 %; gate/up of 57344 x 8192 at 256 rows 268 -> 255 us)
+    if (t == 0 || cost < least || (t == 5 && best == 4 && cost == least)) best = t, least = cost;
   }
   return best;
 }

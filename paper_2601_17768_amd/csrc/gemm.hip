@@ -923,6 +923,17 @@ void launch_narrow(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles
     else gemm_ring_kernel<4, 16, 5, 2, Epi><<<n_blocks, 64 * 6, 0, st>>>(wp, xp, k_tiles, epi);
   } else {
     const int split = SPLIT == 2 ? split_point(k_tiles) : k_tiles;
+    // Unsplit with no more blocks than CUs: a workgroup for each (QKV of 3072 x 1024 at 16, 32 and 64 rows: 6.7, 7.0 and 8.7 us
+    // with two blocks each, 6.3, 6.6 and 7.7 with one; 3072 x 2048: 8.4, 9.2 and 11.5 -> 7.1, 8.2 and 10.0; with 320 and
+    // more blocks two are the faster ones, 64 rows of 5120 x 3072 15.4 against 20.5).
+    if constexpr (SPLIT == 1) {
+      if (n_blocks <= ws.num_cus) {
+        if (ws.m_pad == 16) gemm_narrow_kernel<1, 1, 8, 4, 4, Epi><<<n_blocks, 64 * 5, 0, st>>>(wp, xp, n_blocks, k_tiles, split, epi);
+        else if (ws.m_pad == 32) gemm_narrow_kernel<1, 2, 4, 5, 4, Epi><<<n_blocks, 64 * 6, 0, st>>>(wp, xp, n_blocks, k_tiles, split, epi);
+        else gemm_narrow_kernel<1, 4, 4, 6, 4, Epi><<<n_blocks, 64 * 8, 0, st>>>(wp, xp, n_blocks, k_tiles, split, epi);
+        return;
+      }
+    }
     const dim3 grid((n_blocks + 1) / 2, SPLIT);
     auto go = [&](const auto& e) {
       using E = std::decay_t<decltype(e)>;

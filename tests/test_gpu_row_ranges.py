@@ -84,6 +84,21 @@ def test_same_bits_among_partly_filled_windows(env, alone, n_seq):
     assert bool(((out >= 0) == live).all())
 
 
+@pytest.mark.parametrize("d_model,n_kv_heads", [(1024, 2), (2048, 4)])
+def test_same_bits_with_few_feature_blocks(d_model, n_kv_heads):
+    """At most one block of 16 QKV features per CU: up to 64 rows a workgroup takes one block, not two; from 65 rows on the
+    tiles of other kernels.  32 and 64 k-tiles, so every ring of the small-batch kernel is refilled."""
+    shape = wl.LLAMA_8B.replace(n_layers=1, d_model=d_model, n_q_heads=16, n_kv_heads=n_kv_heads, head_dim=64, d_ffn=2048, vocab=1024)
+    sess = VerifierSession(shape, wl.make_weights(shape, seed=49), max_position=128, device=DEV)
+    want = _run(shape, sess, 5, 4)                              # 80 rows
+    assert torch.isfinite(want[1]).all()
+    for n_seq in (1, 2, 3, 4):
+        out, logits, k, v = _run(shape, sess, n_seq, n_seq - 1)
+        assert torch.equal(out[n_seq - 1], want[0][4]) and torch.equal(logits, want[1]), n_seq
+        assert torch.equal(k, want[2]) and torch.equal(v, want[3]), n_seq
+    sess.close()
+
+
 @pytest.mark.timeout(300)
 def test_partly_filled_windows_as_whole_sequence_items():
     shape = wl.TINY

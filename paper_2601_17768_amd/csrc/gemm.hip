@@ -917,34 +917,35 @@ constexpr int kSplit[4] = {1, 2, 1, 1};
 template <int SPLIT, class Epi>
 void launch_narrow(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, int n, const Workspace& ws, const Epi& epi,
                    hipStream_t st) {
-  if constexpr (SPLIT == 1 && std::is_same<Epi, ResidualEpi>::value) {
-    if (ws.m_pad == 16) gemm_ring_kernel<1, 16, 5, 2, Epi><<<n_blocks, 64 * 3, 0, st>>>(wp, xp, k_tiles, epi);
-    else if (ws.m_pad == 32) gemm_ring_kernel<2, 16, 5, 2, Epi><<<n_blocks, 64 * 4, 0, st>>>(wp, xp, k_tiles, epi);
-    else gemm_ring_kernel<4, 16, 5, 2, Epi><<<n_blocks, 64 * 6, 0, st>>>(wp, xp, k_tiles, epi);
-  } else {
-    const int split = SPLIT == 2 ? split_point(k_tiles) : k_tiles;
-    // Unsplit with no more blocks than CUs: a workgroup for each (QKV of 3072 x 1024 at 16, 32 and 64 rows: 6.7, 7.0 and 8.7 us
-    // with two blocks each, 6.3, 6.6 and 7.7 with one; 3072 x 2048: 8.4, 9.2 and 11.5 -> 7.1, 8.2 and 10.0; with 320 and
-    // more blocks two are the faster ones, 64 rows of 5120 x 3072 15.4 against 20.5).
-    if constexpr (SPLIT == 1) {
-      if (n_blocks <= ws.num_cus) {
+  const int split = SPLIT == 2 ? split_point(k_tiles) : k_tiles;
+  if constexpr (SPLIT == 1) {
+    // Unsplit with no more blocks than CUs: a workgroup for each.  QKV by gemm_narrow_kernel (3072 x 1024 at 16, 32 and 64 rows:
+    // 6.7, 7.0 and 8.7 us with two blocks each, 6.3, 6.6 and 7.7 with one; 3072 x 2048: 8.4, 9.2 and 11.5 -> 7.1, 8.2 and
+    // 10.0), the residual projections by gemm_ring_kernel.  With more blocks two per workgroup are the faster ones: QKV of
+    // 5120 x 3072 at 64 rows 15.4 us against 20.5; down-projection of 8192 x 28672 at 32 and 64 rows 83 and 102 against 106
+    // and 121 by the ring, 5120 x 13824 42 and 48 against 49 and 58.
+    if (n_blocks <= ws.num_cus) {
+      if constexpr (std::is_same<Epi, ResidualEpi>::value) {
+        if (ws.m_pad == 32) gemm_ring_kernel<2, 16, 5, 2, Epi><<<n_blocks, 64 * 4, 0, st>>>(wp, xp, k_tiles, epi);
+        else gemm_ring_kernel<4, 16, 5, 2, Epi><<<n_blocks, 64 * 6, 0, st>>>(wp, xp, k_tiles, epi);
+      } else {
         if (ws.m_pad == 16) gemm_narrow_kernel<1, 1, 8, 4, 4, Epi><<<n_blocks, 64 * 5, 0, st>>>(wp, xp, n_blocks, k_tiles, split, epi);
         else if (ws.m_pad == 32) gemm_narrow_kernel<1, 2, 4, 5, 4, Epi><<<n_blocks, 64 * 6, 0, st>>>(wp, xp, n_blocks, k_tiles, split, epi);
         else gemm_narrow_kernel<1, 4, 4, 6, 4, Epi><<<n_blocks, 64 * 8, 0, st>>>(wp, xp, n_blocks, k_tiles, split, epi);
-        return;
       }
+      return;
     }
-    const dim3 grid((n_blocks + 1) / 2, SPLIT);
-    auto go = [&](const auto& e) {
-      using E = std::decay_t<decltype(e)>;
-      // (ring depths within a few percent of each other: what counts is four fetching waves and few barriers)
-      if (ws.m_pad == 16) gemm_narrow_kernel<2, 1, 8, 4, 4, E><<<grid, 64 * 6, 0, st>>>(wp, xp, n_blocks, k_tiles, split, e);
-      else if (ws.m_pad == 32) gemm_narrow_kernel<2, 2, 4, 5, 4, E><<<grid, 64 * 8, 0, st>>>(wp, xp, n_blocks, k_tiles, split, e);
-      else gemm_narrow_kernel<2, 4, 4, 6, 4, E><<<grid, 64 * 12, 0, st>>>(wp, xp, n_blocks, k_tiles, split, e);
-    };
-    if constexpr (SPLIT == 2) go(StorePartialEpi{ws.split_part, ws.rl, n, (size_t)ws.m_pad * n});
-    else go(epi);
   }
+  const dim3 grid((n_blocks + 1) / 2, SPLIT);
+  auto go = [&](const auto& e) {
+    using E = std::decay_t<decltype(e)>;
+    // (ring depths within a few percent of each other: what counts is four fetching waves and few barriers)
+    if (ws.m_pad == 16) gemm_narrow_kernel<2, 1, 8, 4, 4, E><<<grid, 64 * 6, 0, st>>>(wp, xp, n_blocks, k_tiles, split, e);
+    else if (ws.m_pad == 32) gemm_narrow_kernel<2, 2, 4, 5, 4, E><<<grid, 64 * 8, 0, st>>>(wp, xp, n_blocks, k_tiles, split, e);
+    else gemm_narrow_kernel<2, 4, 4, 6, 4, E><<<grid, 64 * 12, 0, st>>>(wp, xp, n_blocks, k_tiles, split, e);
+  };
+  if constexpr (SPLIT == 2) go(StorePartialEpi{ws.split_part, ws.rl, n, (size_t)ws.m_pad * n});
+  else go(epi);
 }
 
 // x + (p0 + p1) over the row blocks that hold rows: the halves of a split GEMM where the RMSNorm does not add them.

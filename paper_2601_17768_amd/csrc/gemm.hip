@@ -1064,10 +1064,13 @@ bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
     return false;
   } else {
     // The ranges where gemm_mid_kernel is the faster one: up to 1280 rows for QKV and the split projections; up to 256 for
-    // gate/up, whose launches have enough 128 x 256 tiles for two workgroups per CU of gemm_tiled_kernel beyond that.
+    // gate/up, whose launches have enough 128 x 256 tiles for two workgroups per CU of gemm_tiled_kernel beyond that - as the
+    // two halves of a split projection have from d_model 8192 and 1024 rows on (its O- and down-projection and their norms,
+    // 1280 rows, two layers: 1824 us against 1902).
     // And wherever 128 x 128 tiles leave more than a quarter of the CUs without one, for its 64-row tiles (the two-layer model of
     // the tests, gemm_tiled_kernel -> this: QKV at 2048 rows 16.3 -> 9.4 us, at 4096 16.5 -> 11.2; gate/up at 512 rows 8.6 -> 6.7).
-    if (m_pad <= (std::is_same<Epi, SwigluEpi>::value ? 256 : 1280) || t128 * SPLIT * 4 < 3 * cus) {
+    const bool two_per_cu = SPLIT == 2 && t256 * 2 >= 2 * cus;
+    if ((m_pad <= (std::is_same<Epi, SwigluEpi>::value ? 256 : 1280) && !two_per_cu) || t128 * SPLIT * 4 < 3 * cus) {
       const int tile = pick_mid(n_blocks, m_pad, SPLIT, cus);
       if constexpr (SPLIT == 2)
         launch_mid(tile, wp, xp, n_blocks, k_tiles, split_point(k_tiles), 2, ws,

@@ -68,3 +68,18 @@ def test_same_bits_as_in_a_large_group(env, L, window, rows):
     # several items per workgroup of the split kernel (300 sequences x 1-2 kv heads > 256), or the other kernels
     crowd = _run(shape, sess, L, window, rows, 300, 20, max(L, 20) + window)
     assert torch.equal(alone[0], crowd[0]) and torch.equal(alone[1], crowd[1])
+
+
+@pytest.mark.parametrize("L", [1279, 1281, 1535, 1536, 1791, 1792, 2040])
+@pytest.mark.parametrize("window,rows", [(1, 1), (8, 8), (8, 3)])
+def test_second_chunk_of_every_wave(env, L, window, rows):
+    """Contexts of six to eight chunks: each wave walks two.  Enough company that the call takes the split kernel at such
+    contexts; alone they go through chunk items and the merge pass."""
+    shape, sess = env
+    merged = _run(shape, sess, L, window, rows, 0, 0, max(L + window, 1281), split=False)
+    assert torch.isfinite(merged[1]).all()
+    among = _run(shape, sess, L, window, rows, 60, 20, L + window, split=True)
+    assert torch.equal(merged[0], among[0]) and torch.equal(merged[1], among[1])
+    if shape.head_dim == 128 and window == 1:   # one row block, more workgroups than CUs: the items come from the plan's list
+        listed = _run(shape, sess, L, window, rows, 300, 20, L + window, split=True)
+        assert torch.equal(merged[0], listed[0]) and torch.equal(merged[1], listed[1])

@@ -65,7 +65,7 @@ def test_same_bits_at_every_row_count(env, alone, n_seq):
     assert torch.equal(logits, alone[1]) and torch.equal(k, alone[2]) and torch.equal(v, alone[3])
 
 
-@pytest.mark.parametrize("n_seq", [4, 9, 20, 41, 65, 97, 130, 200])
+@pytest.mark.parametrize("n_seq", [4, 9, 20, 41, 65, 97, 130, 200, 256, 300])
 def test_same_bits_among_partly_filled_windows(env, alone, n_seq):
     """Partly filled windows are packed: the target's rows begin wherever the counts before it end (odd offsets, across
     tiles), sequences that fail a check have no rows or dead ones, and what lies behind the last row is skipped."""
@@ -135,4 +135,34 @@ def test_partly_filled_windows_as_whole_sequence_items():
     few, many = run(1, 0), run(256, slot)
     assert many[2] and not few[2]
     assert torch.equal(few[0], many[0]) and torch.equal(few[1], many[1])
+    sess.close()
+
+
+def test_partly_filled_windows_of_more_sequences_than_are_packed():
+    """Beyond 4096 sequences the rows are not packed: padding rows stay where they are, with zeros for their attention output."""
+    shape = wl.TINY
+    sess = VerifierSession(shape, wl.make_weights(shape, seed=50), max_position=64, device=DEV)
+    n_seq, window = 4100, 4
+    rng = wl.rng_for(50, 1)
+    lens = rng.integers(0, 40, size=n_seq).astype(np.int32)
+    n_valid = rng.integers(1, window + 1, size=n_seq).astype(np.int32)
+    n_valid[3], sample = 0, [0, 1, 2, 2000, 4095, 4096, 4099]     # (a count of 0 is refused)
+    table, blocks = wl.make_block_table(rng, lens + window, 16, spare_blocks=2)
+    bt = torch.as_tensor(table, device=DEV)
+    kv = sess.kv_cache(blocks)
+    kv.normal_(generator=torch.Generator(device=DEV).manual_seed(5))
+    cand = wl.random_tokens(rng, n_seq * window, shape.vocab).reshape(n_seq, window)
+    d = lambda a: torch.as_tensor(a, device=DEV)
+    out, status, logits = sess.verify(kv, bt, d(lens), d(cand), n_valid=d(n_valid),
+                                      dump_seq_ids=torch.tensor(sample, dtype=torch.int32, device=DEV))
+    torch.cuda.synchronize()
+    assert status.nonzero().flatten().tolist() == [3] and int(status[3]) == B.LLM42_SEQ_BAD_LENGTH
+    taken = torch.as_tensor(np.arange(window)[None, :] < n_valid[:, None])
+    assert bool(((out.cpu() >= 0) == taken).all())
+    for j, s in enumerate(sample):
+        n = int(n_valid[s])
+        one, _, alone = sess.verify(kv, bt[s:s + 1].contiguous(), d(lens[s:s + 1]), d(cand[s:s + 1]), n_valid=d(n_valid[s:s + 1]),
+                                    dump_seq_ids=torch.zeros(1, dtype=torch.int32, device=DEV))
+        torch.cuda.synchronize()
+        assert torch.equal(alone[0, :n], logits[j, :n]) and torch.equal(one[0], out[s]), s
     sess.close()

@@ -823,7 +823,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(
   }
 }
 
-// The work items of a call: every (sequence, unit) pair that holds keys, as (s, unit, L, n), sorted
+// The work items of a call: every (sequence, unit) pair that holds keys, as (s, unit, L, seq_tag), sorted
 // by the number of 64-key steps it takes, longest first (the attention kernels deal them out in that
 // order, which keeps the tail of a launch short); and the per-layer queue counters.  The order
 // inside a class of equal length is whatever the slot counter gives: it decides only which

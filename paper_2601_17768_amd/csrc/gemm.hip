@@ -216,8 +216,8 @@ struct LogitsEpi {
 // ---------------------------------------------------------------------------------------------
 __host__ __device__ inline int split_point(int k_tiles) { return (k_tiles + 1) / 2; }
 
-// fp32 partial of one k-half of a split GEMM (large-batch path: the halves are two launches, or the
-// two y-planes of one launch, each with a buffer of its own).
+// fp32 partial of one k-half of a split GEMM (the halves are workgroups of one launch, each with a buffer of its own, or two
+// launches, the second of which adds the first one's).
 struct StorePartialEpi {
   float* partial;   // [m_pad][n] in the residual-stream layout
   ResidLayout rl;
@@ -551,7 +551,7 @@ __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restri
   }
 }
 
-// Kernel for 65 to 1280 tokens: a tile of WN * WBN feature blocks x WM * WBM token blocks per workgroup, with waves that do
+// Kernel for 65 to 1280 tokens (LM head to 2048; few features at any number, see launch_gemm): a tile of WN * WBN feature blocks x WM * WBM token blocks per workgroup, with waves that do
 // nothing but fetch, as in gemm_narrow_kernel: F of them move a round of CH k-tiles at a time into a ring of R rounds in LDS,
 // WN x WM others own WBN x WBM blocks each and advance them in ascending k.  Here a launch has one workgroup per CU (two of
 // the 128 x 128 tile), and what bounds it is that one's LDS port (operand tiles in, WBN + WBM of them out per WBN * WBM
@@ -567,7 +567,7 @@ __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restri
 //   1024     67.7 -> 57.1   37.4 -> 37.1   103.9 -> 104.5   210.5    229.9    1040 -> 1013
 //   1280     71.8 -> 67.4   60.4 -> 57.8   180.7 -> 163.4   264.2    282.0    1325 -> 1250
 //   1792     98.9    107.9  63.8    67.0   181.7    188.7   349.3    386.3    1946 -> 1702
-//   4096    191.3    206.6                                  705.9    842.5    4314 -> 4289
+//   4096    191.3    206.6                                  705.9    842.5    3770    3910
 // Workgroup ids are dealt round-robin to the 8 XCDs; each XCD takes a contiguous run of the tiles, token tiles fastest, so
 // that the tiles that share weights share an L2.
 template <int WN, int WM, int WBN, int WBM, int CH, int R, int F, int WGS, bool PRE, class Epi>
@@ -855,8 +855,8 @@ inline int super_width(int tiles_m, int most) {
   return width;
 }
 
-// side_by_side (split GEMMs only): both k-halves in one launch of twice the workgroups, their sum left to the RMSNorm that
-// follows, instead of two launches one after the other - for launches that do not fill the
+// side_by_side (split GEMMs only): both k-halves in one launch of twice the workgroups, their sum taken by what follows
+// (see halves_pending), instead of two launches one after the other - for launches that do not fill the
 // device by themselves.  The arithmetic per output element is the same either way.
 template <int WBN, int WBM, int NST, int WGS, int SPLIT, class Epi>
 void launch_tiled(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, int n, const Workspace& ws,

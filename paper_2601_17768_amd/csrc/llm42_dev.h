@@ -127,7 +127,7 @@ struct Workspace {
   ResidLayout rl;      // of resid and split_part
   uint16_t *normed, *q, *attn, *hidden;
   float *part_acc, *part_ml;
-  int4* attn_items;     // (sequence, unit, length, rows) of every unit that holds keys, built once per call
+  int4* attn_items;     // (sequence, unit, length, seq_tag) of every unit that holds keys, built once per call
   int32_t* attn_ctrl;   // [0] number of items, [1 + layer] work queue counter of that layer's attention launch,
                         // [1 + n_layers] 1 if the items are whole sequences
   size_t attn_ctrl_offset;   // byte offset of attn_ctrl in the workspace

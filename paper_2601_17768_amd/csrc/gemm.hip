@@ -551,7 +551,8 @@ __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restri
   }
 }
 
-// Kernel for 65 to 1280 tokens (LM head to 2048; few features at any number, see launch_gemm): a tile of WN * WBN feature blocks x WM * WBM token blocks per workgroup, with waves that do
+// Kernel for 65 to 1280 tokens (LM head to 2048; few features at any number, see launch_gemm): a tile of WN * WBN feature
+// blocks x WM * WBM token blocks per workgroup, with waves that do
 // nothing but fetch, as in gemm_narrow_kernel: F of them move a round of CH k-tiles at a time into a ring of R rounds in LDS,
 // WN x WM others own WBN x WBM blocks each and advance them in ascending k.  Here a launch has one workgroup per CU (two of
 // the 128 x 128 tile), and what bounds it is that one's LDS port (operand tiles in, WBN + WBM of them out per WBN * WBM
@@ -1052,9 +1053,10 @@ bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
     // -> this: 3072 rows 2870 -> 2750 us, 4096 3910 -> 3770, 8192 7870 -> 7390; vocabulary 65536: 8192 rows 4220 -> 3810;
     // d_model 1024, vocabulary 50304: 4096 rows 503 -> 465), unless its super-tiles eight wide would be ragged (3584 rows: 3390
     // against 5580).  Below, the tile that re-reads the activations least, 128 x 256 for 256 - 2048 rows and 256 x 128
-    // otherwise (8B, 2048 rows, logits written out: 1990 us against 2043) - if there are enough of either: a small vocabulary takes the cheapest of
-    // all the tiles (4096 logits, 128 rows: 62 us against 24, 512 rows: 59 against 28), and with few k-tiles, where a
-    // tile's epilogue weighs most, the cheapest of those that share a CU (32 k-tiles x 50304 logits, 512 rows: 74 against 61).
+    // otherwise (8B, 2048 rows, logits written out: 1990 us against 2043) - if there are enough of either: a small vocabulary
+    // takes the cheapest of all the tiles (4096 logits, 128 rows: 62 us against 24, 512 rows: 59 against 28), and with few
+    // k-tiles, where a tile's epilogue weighs most, the cheapest of those that share a CU (32 k-tiles x 50304 logits, 512 rows:
+    // 81 against 65).
     if (m_pad > 2048 && t128 * 4 >= 3 * cus && !(super_width(m_pad / 128, 8) == 8 && m_pad % 1024)) {
       launch_tiled<4, 4, 4, 2, SPLIT, Epi>(wp, xp, n_blocks, k_tiles, n, ws, epi, st, false);
       return false;

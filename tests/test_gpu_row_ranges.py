@@ -166,3 +166,19 @@ def test_partly_filled_windows_of_more_sequences_than_are_packed():
         torch.cuda.synchronize()
         assert torch.equal(alone[0, :n], logits[j, :n]) and torch.equal(one[0], out[s]), s
     sess.close()
+
+
+@pytest.mark.parametrize("n_seq", [9, 41, 97])
+def test_same_bits_when_the_last_sequence_is_refused(env, alone, n_seq):
+    """Where the packed rows end is read from the last sequence's tag: refused for its length (no rows), then for a token."""
+    rng = wl.rng_for(47, 6, n_seq)
+    n_valid = rng.integers(1, WINDOW + 1, size=n_seq)
+    slot = n_seq - 2
+    n_valid[slot] = WINDOW
+    for code in (B.LLM42_SEQ_BAD_LENGTH, B.LLM42_SEQ_BAD_TOKEN):
+        n_valid[-1] = 0 if code == B.LLM42_SEQ_BAD_LENGTH else 7
+        expect = [0] * (n_seq - 1) + [code]
+        out, logits, k, v = _run(*env, n_seq, slot, n_valid, bad_token_of=n_seq - 1 if code == B.LLM42_SEQ_BAD_TOKEN else None,
+                                 expect_status=expect)
+        assert torch.equal(out[slot], alone[0]) and int(out[-1].max()) == -1
+        assert torch.equal(logits, alone[1]) and torch.equal(k, alone[2]) and torch.equal(v, alone[3])

@@ -111,5 +111,5 @@ def test_unsplit_residual_projections_of_many_features():
     shape, sess = _session(64, d_model=8192, d_ffn=8192, vocab=1024)
     split, plain = _times(shape, sess, 32, 1, 16), _times(shape, sess, 32, 1, 16, decode=True)
     print(f"O and down: split {split['o_proj']:.1f} and {split['down']:.1f} us, unsplit {plain['o_proj']:.1f} and {plain['down']:.1f}")
-    assert plain["down"] <= 1.1 * split["down"] and plain["o_proj"] <= 1.15 * split["o_proj"]
+    assert plain["down"] <= 1.15 * split["down"] and plain["o_proj"] <= 1.15 * split["o_proj"]
     sess.close()

@@ -157,7 +157,7 @@ void launch_prefill_gather(const llm42_model* m, const int32_t* prompt_offsets, 
                            hipStream_t st);
 void launch_embed(const llm42_model* m, const int32_t* candidates, int window, const Workspace& ws, hipStream_t st);
 // Whether the RMSNorm behind a split GEMM adds its halves to the residual stream (see launch_gemm).
-inline bool norm_adds_halves(int m_pad, int d) { return m_pad <= 512 || d == 4096; }
+inline bool norm_adds_halves(int m_pad, int d) { return m_pad <= 512 || d == 1024 || d == 2048 || d == 4096 || d == 8192; }
 // pending: the last residual GEMM left its halves in split_part (what launch_gemm_residual returned)
 void launch_rmsnorm(bool pending, const uint16_t* gain, int d, float eps, const Workspace& ws, hipStream_t st);
 

@@ -1,5 +1,7 @@
 // Row-wise kernels of the verifier pass: input validation and row metadata,
 // embedding gather, RMSNorm.
+#include <type_traits>
+
 #include "llm42_dev.h"
 
 namespace {
@@ -317,19 +319,19 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(float* __restrict__ x, con
   }
 }
 
-// RMSNorm at d = 4096: one workgroup of 64 R threads per R neighbouring rows, thread
+// RMSNorm at d = 512 U (U = 2, 4, 8, 16): one workgroup of 64 R threads per R neighbouring rows, thread
 // (w, g, r) owning the partial sum p[w][g] of row r - the same 64 partials per row, accumulated in
 // the same order and combined in the same tree as in rmsnorm_kernel, so the bits are the same; only
 // the work distribution differs.  R (see launch_rmsnorm) trades CUs at work against the length of the
 // contiguous runs (16 R bytes) that a workgroup writes in the tile layout, and reads where the rows are interleaved.
-template <int R, bool PEND>
+template <int R, int U, bool PEND>
 __global__ __launch_bounds__(64 * R) void rmsnorm_block_kernel(float* __restrict__ x, const float* __restrict__ p0,
                                                                const float* __restrict__ p1, ResidLayout rl,
                                                                const uint16_t* __restrict__ gain,
                                                                uint16_t* __restrict__ y, float eps,
                                                                const int32_t* __restrict__ live) {
   if (live && (int)blockIdx.x * R >= live_rows(live)) return;      // packed rows: only what pads (workgroup-uniform)
-  constexpr int D = 4096, U = 8;                         // tiles of 32 features per thread: t = u * 16 + w
+  constexpr int D = 512 * U;                             // U tiles of 32 features per thread: t = u * 16 + w
   __shared__ float part[64][R];
   __shared__ float inv_s[R];
   const int r = threadIdx.x % R, wg = threadIdx.x / R, w = wg >> 2, g = wg & 3;
@@ -422,10 +424,17 @@ static void launch_norm(float* x, const float* p0, const float* p1, ResidLayout 
   //   4096   27.1 | 52.0  26.9 | 53.4  25.2 | 52.2  24.6 | 52.2 | 29.2 | 82.3  21.6 | 47.3  23.8 | 46.2
   // Few rows are bound by what a CU pulls from beyond its L2 (20 - 25 GB/s) and want as many CUs as there are, many rows by
   // the length of the runs that they read and write.
-  if (d == 4096 && m_pad > 128 && !(PEND && m_pad > 256 && m_pad <= 512)) {
-    if (m_pad <= 512) rmsnorm_block_kernel<2, PEND><<<m_pad / 2, 128, 0, st>>>(x, p0, p1, rl, gain, y, eps, nullptr);
-    else rmsnorm_block_kernel<8, PEND><<<m_pad / 8, 512, 0, st>>>(x, p0, p1, rl, gain, y, eps, live);
-  }
+  // The widths 1024, 2048 and 8192 follow beyond 512 rows, where a wave per row reads pieces of 16 bytes (norms of one layer and
+  // the final one, halves of two projections left to two of the three, wave per row with the halves added before -> this with
+  // them: 2048 rows d 2048 44.6 + 2 adding launches -> 38.3, d 8192 197.7 + 2 -> 148.9, d 1024 27.4 + 2 -> 26.8).
+  const bool rows8 = m_pad > 512;
+  auto block8 = [&](auto u) { rmsnorm_block_kernel<8, decltype(u)::value, PEND><<<m_pad / 8, 512, 0, st>>>(x, p0, p1, rl, gain, y, eps, live); };
+  if (rows8 && d == 1024) block8(std::integral_constant<int, 2>{});
+  else if (rows8 && d == 2048) block8(std::integral_constant<int, 4>{});
+  else if (rows8 && d == 4096) block8(std::integral_constant<int, 8>{});
+  else if (rows8 && d == 8192) block8(std::integral_constant<int, 16>{});
+  else if (d == 4096 && m_pad > 128 && !(PEND && m_pad > 256))
+    rmsnorm_block_kernel<2, 8, PEND><<<m_pad / 2, 128, 0, st>>>(x, p0, p1, rl, gain, y, eps, nullptr);
   else if (m_pad <= 256) rmsnorm_kernel<PEND><<<m_pad, 64, 0, st>>>(x, p0, p1, rl, gain, y, m_pad, d, eps);
   else rmsnorm_kernel<PEND><<<(m_pad + 3) / 4, 256, 0, st>>>(x, p0, p1, rl, gain, y, m_pad, d, eps);
 }

@@ -252,7 +252,7 @@ def run_workload(name, sess, shape, weights, args, with_cpu_baseline):
     else:
         gu_flops = 2.0 * rows * shape.d_model * 2 * shape.d_ffn
         achieved = gu_flops / (gu_ms * 1e-3) / 1e12
-        roofline = {"bound": "mfma", "kernel": "gate/up GEMM + SwiGLU (gemm_tiled_kernel)",
+        roofline = {"bound": "mfma", "kernel": "gate/up GEMM + SwiGLU (gemm_direct_kernel)",
                     "achieved": round(achieved, 1), "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(achieved / MFMA_PEAK_TFLOPS, 4), "traffic": traffic,
                     "flops_per_launch": gu_flops, "avg_launch_ms": round(gu_ms, 5), "launches_timed": len(gu)}

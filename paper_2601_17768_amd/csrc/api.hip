@@ -223,8 +223,9 @@ void run_head(const llm42_model* m, bool pending, int window, int num_seqs, int3
               const llm42_sampling* sampling, const Workspace& ws, hipStream_t st) {
   const llm42_config& c = m->cfg;
   TIMED(LLM42_K_RMSNORM, launch_rmsnorm(pending, m->final_norm, c.d_model, c.rms_eps, ws, st));
-  TIMED(LLM42_K_LM_HEAD, launch_gemm_logits(m, window, out_logits, sampling, ws, st));
-  TIMED(LLM42_K_ARGMAX, launch_argmax_merge(m, num_seqs, window, out_tokens, ws, st));
+  int parts;
+  TIMED(LLM42_K_LM_HEAD, parts = launch_gemm_logits(m, window, out_logits, sampling, ws, st));
+  TIMED(LLM42_K_ARGMAX, launch_argmax_merge(parts, num_seqs, window, out_tokens, ws, st));
 }
 
 // One pass of the verifier over num_seqs x window rows; arguments already checked.  A prefill pass ends with the last

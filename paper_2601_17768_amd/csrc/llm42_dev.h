@@ -132,7 +132,7 @@ struct Workspace {
                         // [1 + n_layers] 1 if the items are whole sequences
   size_t attn_ctrl_offset;   // byte offset of attn_ctrl in the workspace
   float* split_part;   // fp32 halves of a split GEMM, [2][m_pad][d_model]
-  float2* amax;   // [m_pad][vocab/16] (value, index bits)
+  float2* amax;   // [m_pad][vocab/16 or fewer] (value, index bits)
   size_t bytes;
 };
 
@@ -167,15 +167,15 @@ void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, 
 bool launch_gemm_residual(const uint16_t* w, const uint16_t* x, float* resid, int n, int k_padded,
                           const Workspace& ws, hipStream_t st);
 void launch_gemm_swiglu(const llm42_model* m, int layer, const Workspace& ws, hipStream_t st);
-void launch_gemm_logits(const llm42_model* m, int window, float* out_logits, const llm42_sampling* sampling,
-                        const Workspace& ws, hipStream_t st);
+// Returns the number of arg-max partials per row that it leaves in amax.
+int launch_gemm_logits(const llm42_model* m, int window, float* out_logits, const llm42_sampling* sampling,
+                       const Workspace& ws, hipStream_t st);
 
 int attention_units(bool super_mode, int max_context);
 void launch_attention_plan(const llm42_model* m, int num_seqs, int max_context, const Workspace& ws, hipStream_t st);
 void launch_attention(const llm42_model* m, int layer, const llm42_kv_cache* kv, int num_seqs, int window,
                       int max_context, const Workspace& ws, hipStream_t st);
-void launch_argmax_merge(const llm42_model* m, int num_seqs, int window, int32_t* out_tokens, const Workspace& ws,
-                         hipStream_t st);
+void launch_argmax_merge(int parts, int num_seqs, int window, int32_t* out_tokens, const Workspace& ws, hipStream_t st);
 void launch_commit(const int32_t* candidates, const int32_t* out_tokens, const int32_t* n_valid, int num_seqs,
                    int window, int32_t* seq_lens, int32_t* committed_counts, int32_t* committed_tokens,
                    int32_t* rolled_back_counts, hipStream_t st);

@@ -15,7 +15,7 @@ __device__ inline void take_better(float& bv, int& bi, float ov, int oi) {
 // commutative, so the order of this reduction cannot change the result.
 __global__ __launch_bounds__(256) void argmax_merge_kernel(const float2* __restrict__ amax,
                                                            const int32_t* __restrict__ row_pos,
-                                                           const int32_t* __restrict__ row_seq, int window, int n_blocks,
+                                                           const int32_t* __restrict__ row_seq, int window, int parts,
                                                            int32_t* __restrict__ out_tokens) {
   __shared__ float sv[4];
   __shared__ int si[4];
@@ -23,17 +23,17 @@ __global__ __launch_bounds__(256) void argmax_merge_kernel(const float2* __restr
   if (row_pos[row] < 0) return;   // dead row: out_tokens stays -1 (whole workgroup leaves)
   float bv = -INFINITY;
   int bi = 0x7FFFFFFF;
-  const float2* p = amax + (size_t)row * n_blocks;
+  const float2* p = amax + (size_t)row * parts;
   constexpr int U = 8;                                    // partials in flight per thread
   int b = threadIdx.x;
-  for (; b + (U - 1) * 256 < n_blocks; b += U * 256) {
+  for (; b + (U - 1) * 256 < parts; b += U * 256) {
     float2 v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = p[b + u * 256];
 #pragma unroll
     for (int u = 0; u < U; ++u) take_better(bv, bi, v[u].x, __float_as_int(v[u].y));
   }
-  for (; b < n_blocks; b += 256) {
+  for (; b < parts; b += 256) {
     const float2 v = p[b];
     take_better(bv, bi, v.x, __float_as_int(v.y));
   }
@@ -79,9 +79,8 @@ __global__ void commit_kernel(const int32_t* __restrict__ candidates, const int3
 
 }  // namespace
 
-void launch_argmax_merge(const llm42_model* m, int num_seqs, int window, int32_t* out_tokens, const Workspace& ws,
-                         hipStream_t st) {
-  argmax_merge_kernel<<<num_seqs * window, 256, 0, st>>>(ws.amax, ws.row_pos, ws.row_seq, window, m->cfg.vocab / 16, out_tokens);
+void launch_argmax_merge(int parts, int num_seqs, int window, int32_t* out_tokens, const Workspace& ws, hipStream_t st) {
+  argmax_merge_kernel<<<num_seqs * window, 256, 0, st>>>(ws.amax, ws.row_pos, ws.row_seq, window, parts, out_tokens);
 }
 
 void launch_commit(const int32_t* candidates, const int32_t* out_tokens, const int32_t* n_valid, int num_seqs,

@@ -6,7 +6,7 @@ of the kernel sources it was measured on (bench.py reports the figure only while
         --output-format csv -- python3 bench.py --workload c5 --no-others --layers 2 --steps 1 --warmup 1 \\
         --no-cpu-baseline --no-graph --pmc-calibration
     (the same with WRITE_SIZE into <write dir>)
-    python -m paper_2601_17768_amd.pmc_traffic --workload c5 --kernel gate_up --regex "gemm_tiled.*Swiglu" \\
+    python -m paper_2601_17768_amd.pmc_traffic --workload c5 --kernel gate_up --regex "gemm_direct.*Swiglu" \\
         --fetch <fetch dir> --write <write dir>
 
 The counters come in KiB per dispatch; each is scaled by what the same counter reads for the plain elementwise

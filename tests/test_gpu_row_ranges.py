@@ -99,6 +99,26 @@ def test_same_bits_with_few_feature_blocks(d_model, n_kv_heads):
     sess.close()
 
 
+@pytest.fixture(scope="module")
+def ragged():
+    """28, 449 and 14 k-tiles (halves of 225 and 224, of 7 and 7), feature blocks that no tile divides: partial rounds and partial
+    tiles in every kernel of more than 64 rows."""
+    shape = wl.LLAMA_8B.replace(n_layers=1, d_model=896, n_q_heads=14, n_kv_heads=2, head_dim=64, d_ffn=14352, vocab=33296)
+    sess = VerifierSession(shape, wl.make_weights(shape, seed=50), max_position=128, device=DEV)
+    want = _run(shape, sess, 1, 0)                              # 16 rows: the small-batch kernels
+    assert torch.isfinite(want[1]).all()
+    yield shape, sess, want
+    sess.close()
+
+
+@pytest.mark.parametrize("n_seq", [5, 8, 12, 16, 24, 32, 40, 48, 56, 64, 72, 80, 96, 112, 128, 160, 192, 256])
+def test_same_bits_with_partial_rounds_and_tiles(ragged, n_seq):
+    shape, sess, want = ragged
+    out, logits, k, v = _run(shape, sess, n_seq, n_seq - 1)
+    assert torch.equal(out[n_seq - 1], want[0][0]) and torch.equal(logits, want[1])
+    assert torch.equal(k, want[2]) and torch.equal(v, want[3])
+
+
 @pytest.mark.timeout(300)
 def test_partly_filled_windows_as_whole_sequence_items():
     shape = wl.TINY

@@ -239,6 +239,7 @@ llm42_status run_pass(const llm42_model* m, const llm42_kv_cache* kv, const int3
   // Partly filled windows: the rows are packed, and what pads the end of the grid is skipped.  (Each workgroup of the prepare
   // launch adds up the counts before it, so not for very many sequences.)
   ws.live = n_valid && num_seqs <= 4096 ? ws.seq_n + num_seqs - 1 : nullptr;
+  ws.partly_filled = ws.live && !prefill_pass;
   TIMED(LLM42_K_PREPARE, launch_prepare(m, kv, seq_lens, candidates, n_valid, num_seqs, window, max_context,
                                         dump_seq_ids, n_dump, out_tokens, seq_status, ws, st, prefill_pass));
   if (ws.attn_list) TIMED(LLM42_K_PREPARE, launch_attention_plan(m, num_seqs, max_context, ws, st));

@@ -388,30 +388,36 @@ bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
     return SPLIT == 2;
   }
   constexpr Kind kind = std::is_same<Epi, QkvEpi>::value ? QKV : is_logits<Epi>::value ? LM_HEAD : PLAIN;
-  const Choice whole = pick_tile(kind, n_blocks, m_pad, SPLIT == 2 ? split_point(k_tiles) : k_tiles, 1, ws.num_cus);
-  if constexpr (SPLIT == 2) {
-    // The two halves in one launch, their sum left to what follows - or one after the other, the second adding the first one's
-    // partial and the residual stream in its epilogue, where their workgroups take the same time either way: it saves the norms
-    // the halves.  us for the projections and norms of one layer, one launch | two: 8B 1024 rows 199 | 205, 1280 210 | 237, 1536
-    // 260 | 263, 2048 324 | 309, 4096 623 | 606; d_model 8192, 1024 rows 594 | 554, 4096 2246 | 2074; d_model 2048, 4096 rows
-    // 174 | 162.  From 2048 rows on up to a third more is taken for it: the norms are a quarter of the layer there (d_model 2048,
-    // 2048 rows: norms 38 | 26, but 95 | 106 in all; 127 before this kernel).
-    const int h = split_point(k_tiles);
-    const Choice halves = pick_tile(kind, n_blocks, m_pad, h, 2, ws.num_cus);
-    const StorePartialEpi partial{ws.split_part, ws.rl, n, (size_t)m_pad * n};
-    if (whole.cost * 2 * 100 <= halves.cost * (m_pad < 2048 ? 103 : 135)) {
-      launch_direct(whole.tile, wp, xp, n_blocks, KRange{k_tiles, h, 1, 1}, ws, partial, st);
-      launch_direct(whole.tile, wp, xp, n_blocks, KRange{k_tiles, h, 0, 1}, ws, ResidualAddEpi{epi.resid, ws.split_part, ws.rl, n}, st);
-      return false;
+  const int h = SPLIT == 2 ? split_point(k_tiles) : k_tiles;
+  const Work one{kind, n_blocks, h, 1, ws.num_cus}, both{kind, n_blocks, h, 2, ws.num_cus};
+  // The two halves in one launch, their sum left to what follows - or one after the other, the second adding the first one's
+  // partial and the residual stream in its epilogue, where their workgroups take the same time either way: it saves the norms
+  // the halves.  us for the projections and norms of one layer, one launch | two: 8B 1024 rows 199 | 205, 1280 210 | 237, 1536
+  // 260 | 263, 2048 324 | 309, 4096 623 | 606; d_model 8192, 1024 rows 594 | 554, 4096 2246 | 2074; d_model 2048, 4096 rows
+  // 174 | 162.  From 2048 rows on up to a third more is taken for it: the norms are a quarter of the layer there (d_model 2048,
+  // 2048 rows: norms 38 | 26, but 95 | 106 in all; 127 before this kernel).
+  const bool in_turn = SPLIT == 2 && pick_tile(one, m_pad).cost * 2 * 100 <= pick_tile(both, m_pad).cost * (m_pad < 2048 ? 103 : 135);
+  const Work& work = SPLIT == 2 && !in_turn ? both : one;
+  const auto launch = [&](int rows, int more_than) {
+    const int tile = pick_tile(work, rows).tile;
+    if constexpr (SPLIT == 2) {
+      const StorePartialEpi partial{ws.split_part, ws.rl, n, (size_t)m_pad * n};
+      if (in_turn) {
+        launch_direct(tile, wp, xp, n_blocks, Range{k_tiles, h, 1, 1, rows, more_than}, ws, partial, st);
+        launch_direct(tile, wp, xp, n_blocks, Range{k_tiles, h, 0, 1, rows, more_than}, ws, ResidualAddEpi{epi.resid, ws.split_part, ws.rl, n}, st);
+      } else {
+        launch_direct(tile, wp, xp, n_blocks, Range{k_tiles, h, 0, 2, rows, more_than}, ws, partial, st);
+      }
+    } else if constexpr (std::is_same<Epi, ResidualEpi>::value) {
+      launch_direct(tile, wp, xp, n_blocks, Range{k_tiles, k_tiles, 0, 1, rows, more_than}, ws, ResidualAddEpi{epi.resid, nullptr, ws.rl, n}, st);
+    } else {
+      launch_direct(tile, wp, xp, n_blocks, Range{k_tiles, k_tiles, 0, 1, rows, more_than}, ws, epi, st);
     }
-    launch_direct(halves.tile, wp, xp, n_blocks, KRange{k_tiles, h, 0, 2}, ws, partial, st);
-    return halves_pending(ws, n, epi, st);
-  } else if constexpr (std::is_same<Epi, ResidualEpi>::value) {
-    launch_direct(whole.tile, wp, xp, n_blocks, KRange{k_tiles, k_tiles, 0, 1}, ws, ResidualAddEpi{epi.resid, nullptr, ws.rl, n}, st);
-  } else {
-    launch_direct(whole.tile, wp, xp, n_blocks, KRange{k_tiles, k_tiles, 0, 1}, ws, epi, st);
-  }
-  return false;
+  };
+  const int fewer = ws.partly_filled && m_pad >= 768 && kind != LM_HEAD ? rows_apart(work, m_pad, pick_tile(work, m_pad)) : 0;
+  if (fewer) launch(fewer, -1);
+  launch(m_pad, fewer ? fewer : -1);
+  return SPLIT == 2 && !in_turn && halves_pending(ws, n, epi, st);
 }
 
 }  // namespace
@@ -464,7 +470,7 @@ static int launch_logits(const llm42_model* m, int window, float* out_logits, co
   e.window = window;
   e.vocab = m->cfg.vocab;
   const int n_blocks = m->cfg.vocab / 16;
-  const int block = ws.m_pad <= 64 ? 1 : kTiles[pick_tile(LM_HEAD, n_blocks, ws.m_pad, m->cfg.d_model / 32, 1, ws.num_cus).tile].bn;
+  const int block = ws.m_pad <= 64 ? 1 : kTiles[pick_tile(Work{LM_HEAD, n_blocks, m->cfg.d_model / 32, 1, ws.num_cus}, ws.m_pad).tile].bn;
   e.parts = (n_blocks + block - 1) / block;
   e.inv_temp = SAMPLED ? 1.0f / sampling->temperature : 0.f;
   e.seed = SAMPLED ? sampling->seed : 0;

@@ -36,7 +36,7 @@ namespace gemm {
 template <int NW, int FB, int TB, int CH, int R, int F, int NSET, int WGS, bool NT, class Epi>
 __global__ __launch_bounds__(64 * (NW + F), (WGS * (NW + F) + 3) / 4) void gemm_direct_kernel(
     const bf16x8* __restrict__ w, const bf16x8* __restrict__ x, int n_blocks, int k_tiles, int split, int first_plane, int planes,
-    int tiles_n, int tiles_m, const int32_t* __restrict__ live, bool renumber, Epi epi) {
+    int tiles_n, int tiles_m, const int32_t* __restrict__ live, int more_than, bool renumber, Epi epi) {
   constexpr int TBN = NW * FB;
   constexpr int PW = CH * TB / F;                    // activation tiles a fetching wave requests per round
   static_assert(CH * TB % F == 0, "the fetching waves take equal shares");
@@ -49,6 +49,7 @@ __global__ __launch_bounds__(64 * (NW + F), (WGS * (NW + F) + 3) / 4) void gemm_
   // count is a dependent read of 0.7 us that full windows pay for: prefill of 700 tokens by 256 as before.)  `renumber`: launches
   // of more workgroups than CUs also close the gaps.
   const int live_blocks = live ? (live_rows(live) + 15) / 16 : tiles_m * TB;
+  if (live && (live_blocks <= more_than || live_blocks > tiles_m * TB)) return;
   if (renumber) tiles_m = max(1, (live_blocks + TB - 1) / TB);
   const int all = tiles_n * tiles_m, per_xcd = (all * planes + 7) / 8;
   const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
@@ -205,23 +206,23 @@ __global__ __launch_bounds__(64 * (NW + F), (WGS * (NW + F) + 3) / 4) void gemm_
 }
 
 template <int NW, int FB, int TB, int CH, int R, int F, int NSET, int WGS, bool NT, class Epi>
-void launch_tile(const bf16x8* wp, const bf16x8* xp, int n_blocks, const KRange& k, const Workspace& ws, const Epi& epi, hipStream_t st) {
-  const int tiles_n = (n_blocks + NW * FB - 1) / (NW * FB), tiles_m = ws.m_pad / (16 * TB);
+void launch_tile(const bf16x8* wp, const bf16x8* xp, int n_blocks, const Range& k, const Workspace& ws, const Epi& epi, hipStream_t st) {
+  const int tiles_n = (n_blocks + NW * FB - 1) / (NW * FB), tiles_m = k.rows / (16 * TB);
   const int per_xcd = (tiles_n * tiles_m * k.planes + 7) / 8;
   gemm_direct_kernel<NW, FB, TB, CH, R, F, NSET, WGS, NT, Epi><<<8 * per_xcd, 64 * (NW + F), 0, st>>>(
-      wp, xp, n_blocks, k.k_tiles, k.split, k.first_plane, k.planes, tiles_n, tiles_m, ws.live,
+      wp, xp, n_blocks, k.k_tiles, k.split, k.first_plane, k.planes, tiles_n, tiles_m, ws.live, k.more_than / 16,
       ws.live && (long long)tiles_n * tiles_m * k.planes > ws.num_cus, epi);
 }
 
 template <class Epi>
-void launch_direct(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, const KRange& k, const Workspace& ws, const Epi& epi,
+void launch_direct(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, const Range& k, const Workspace& ws, const Epi& epi,
                    hipStream_t st) {
   // TILE_NT: with one token tile no other workgroup reads the weights, and they are marked to be streamed past the caches
   // (gate/up at 128 rows 51.0 -> 48.8 us, at 256 66.7 -> 64.9, LM head at 128 230 -> 215; with several token tiles no gain)
 #define TILE(i, ...) case i: return launch_tile<__VA_ARGS__, false>(wp, xp, n_blocks, k, ws, epi, st)
 #define TILE_NT(i, ...)                                                                                             \
   case i:                                                                                                           \
-    if (ws.m_pad == 16 * kTiles[i].bm) return launch_tile<__VA_ARGS__, true>(wp, xp, n_blocks, k, ws, epi, st);     \
+    if (k.rows == 16 * kTiles[i].bm) return launch_tile<__VA_ARGS__, true>(wp, xp, n_blocks, k, ws, epi, st);     \
     return launch_tile<__VA_ARGS__, false>(wp, xp, n_blocks, k, ws, epi, st)
   switch (tile) {   // feature waves, blocks of each, token blocks | k-tiles of a round, rounds in LDS, fetching waves, register sets, workgroups per CU
     TILE(0, 3, 1, 4, 8, 4, 4, 3, 1);

@@ -1,4 +1,4 @@
 // GEMM of more than 64 rows: QKV projection.
 #include "gemm_direct.h"
 
-template void gemm::launch_direct(int, const bf16x8*, const bf16x8*, int, const KRange&, const Workspace&, const QkvEpi&, hipStream_t);
+template void gemm::launch_direct(int, const bf16x8*, const bf16x8*, int, const Range&, const Workspace&, const QkvEpi&, hipStream_t);

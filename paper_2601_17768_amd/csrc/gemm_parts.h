@@ -327,41 +327,67 @@ struct Choice {
 };
 // The cheapest tile for n_blocks x m_pad rows by k_tiles, `planes` times over.  A launch of more than four rounds does not run
 // them in step: it ends about a quarter of a round behind its share of the CUs' time (14 x 16 blocks, LM head of 768 rows: 6.7
-// rounds take the time of 7; of 1024 rows and 32000 features, 2.2 rounds, that of 3), no later than whole rounds would.  The epilogues of QKV and LM head do much per row, and with 16 token
-// blocks to a wave and few features that counts (QKV at 1024 rows: 16 x 8 blocks 63.6 us, 8 x 16 67.0; LM head of 32000
-// features at 512 rows 114 and 119).
+// rounds take the time of 7; of 1024 rows and 32000 features, 2.2 rounds, that of 3), no later than whole rounds would.  The
+// epilogues of QKV and LM head do much per row, and with 16 token blocks to a wave and few features that counts (QKV at 1024
+// rows: 16 x 8 blocks 63.6 us, 8 x 16 67.0; LM head of 32000 features at 512 rows 114 and 119).
 enum Kind { QKV, PLAIN, LM_HEAD };
-inline Choice pick_tile(Kind kind, int n_blocks, int m_pad, int k_tiles, int planes, long long cus) {
+struct Work {
+  Kind kind;
+  int n_blocks, k_tiles, planes;
+  long long cus;
+};
+// What tile t takes for `rows` rows (negative: it is not for this work).
+inline long long tile_cost(int t, const Work& w, int rows) {
+  const Tile& q = kTiles[t];
+  const long long tiles = (long long)((w.n_blocks + q.bn - 1) / q.bn) * ((rows + 16 * q.bm - 1) / (16 * q.bm)) * w.planes, slots = w.cus * q.per_cu;
+  const long long whole = (tiles + slots - 1) / slots * 64, share = tiles * 64 / slots + 16;   // rounds, in 1/64
+  if (q.per_cu == 2 && (w.kind != LM_HEAD || tiles <= 2 * slots)) return -1;
+  long long round = (long long)q.cost * w.k_tiles + (q.per_cu == 2 ? 500 : (t == kShortRounds ? 2200 : 3000) + 24 * q.bn * q.bm);
+  if (w.kind != PLAIN && q.bm == 16 && q.bn <= 8) round += round / 20;
+  return (whole <= 4 * 64 || whole < share ? whole : share) * round / 64;
+}
+inline Choice pick_tile(const Work& w, int m_pad) {
   Choice best{-1, 0};
   for (int t = 0; t < kTileCount; ++t) {
-    const Tile& q = kTiles[t];
-    if (m_pad % (16 * q.bm)) continue;
-    const long long tiles = (long long)((n_blocks + q.bn - 1) / q.bn) * (m_pad / (16 * q.bm)) * planes, slots = cus * q.per_cu;
-    const long long whole = (tiles + slots - 1) / slots * 64, share = tiles * 64 / slots + 16;   // rounds, in 1/64
-    if (q.per_cu == 2 && (kind != LM_HEAD || tiles <= 2 * slots)) continue;
-    long long round = (long long)q.cost * k_tiles + (q.per_cu == 2 ? 500 : (t == kShortRounds ? 2200 : 3000) + 24 * q.bn * q.bm);
-    if (kind != PLAIN && q.bm == 16 && q.bn <= 8) round += round / 20;
-    const long long cost = (whole <= 4 * 64 || whole < share ? whole : share) * round / 64;
-    if (best.tile < 0 || cost < best.cost) best = Choice{t, cost};
+    if (m_pad % (16 * kTiles[t].bm)) continue;
+    const long long cost = tile_cost(t, w, m_pad);
+    if (cost >= 0 && (best.tile < 0 || cost < best.cost)) best = Choice{t, cost};
   }
   return best;
 }
+// Partly filled windows: how many rows there are only the device knows, and the tile that fits all that there could be is not
+// the one for the half of them that windows of random counts hold.  The number of rows, of 9/16 to 3/4 of all, that are to have
+// a launch of their own beside the one for more (the one that does not apply ends at once, in 4 us): the largest whose tile
+// takes no more than 5 % longer than the best of them, if that saves 15 % against the tile for all on as many rows; else 0.  (8B,
+// us per pass: 516 rows of 999 12682 -> 11126, 440 of 748 12141 -> 11153, 1735 of 3161 33318 -> 29146; with a tenth 1757 of 3549
+// 31191 -> 31444, with 5/8 of all whatever its tile -> 37841.)
+inline int rows_apart(const Work& w, int m_pad, Choice all) {
+  long long least = 0;
+  for (int pass = 0; pass < 2; ++pass)
+    for (int rows = m_pad * 3 / 4 / 128 * 128; rows * 16 >= m_pad * 9; rows -= 128) {
+      const long long cost = pick_tile(w, rows).cost;
+      if (pass == 0) least = least == 0 || cost < least ? cost : least;
+      else if (cost * 100 <= least * 105) return (cost + 4000) * 100 <= tile_cost(all.tile, w, rows) * 85 ? rows : 0;
+    }
+  return 0;
+}
 
-// The k-tiles of a launch: all of them (split == k_tiles), or `planes` halves from `first_plane` on, the second one from k-tile
-// `split` on.
-struct KRange {
-  int k_tiles, split, first_plane, planes;
+// What a launch covers.  k-tiles: all of them (split == k_tiles), or `planes` halves from `first_plane` on, the second one from
+// k-tile `split` on.  Rows: `rows` of the pass's; with packed rows it runs if more than `more_than` and no more than `rows` are
+// there (counted in blocks of 16), else its workgroups leave at once.
+struct Range {
+  int k_tiles, split, first_plane, planes, rows, more_than;
 };
 
 // D = W X with the epilogue, by tile `tile` of kTiles.
 template <class Epi>
-void launch_direct(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, const KRange& k, const Workspace& ws, const Epi& epi,
+void launch_direct(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, const Range& k, const Workspace& ws, const Epi& epi,
                    hipStream_t st);
-extern template void launch_direct(int, const bf16x8*, const bf16x8*, int, const KRange&, const Workspace&, const QkvEpi&, hipStream_t);
-extern template void launch_direct(int, const bf16x8*, const bf16x8*, int, const KRange&, const Workspace&, const SwigluEpi&, hipStream_t);
-extern template void launch_direct(int, const bf16x8*, const bf16x8*, int, const KRange&, const Workspace&, const LogitsEpi<false>&, hipStream_t);
-extern template void launch_direct(int, const bf16x8*, const bf16x8*, int, const KRange&, const Workspace&, const LogitsEpi<true>&, hipStream_t);
-extern template void launch_direct(int, const bf16x8*, const bf16x8*, int, const KRange&, const Workspace&, const StorePartialEpi&, hipStream_t);
-extern template void launch_direct(int, const bf16x8*, const bf16x8*, int, const KRange&, const Workspace&, const ResidualAddEpi&, hipStream_t);
+extern template void launch_direct(int, const bf16x8*, const bf16x8*, int, const Range&, const Workspace&, const QkvEpi&, hipStream_t);
+extern template void launch_direct(int, const bf16x8*, const bf16x8*, int, const Range&, const Workspace&, const SwigluEpi&, hipStream_t);
+extern template void launch_direct(int, const bf16x8*, const bf16x8*, int, const Range&, const Workspace&, const LogitsEpi<false>&, hipStream_t);
+extern template void launch_direct(int, const bf16x8*, const bf16x8*, int, const Range&, const Workspace&, const LogitsEpi<true>&, hipStream_t);
+extern template void launch_direct(int, const bf16x8*, const bf16x8*, int, const Range&, const Workspace&, const StorePartialEpi&, hipStream_t);
+extern template void launch_direct(int, const bf16x8*, const bf16x8*, int, const Range&, const Workspace&, const ResidualAddEpi&, hipStream_t);
 
 }  // namespace gemm

@@ -121,6 +121,7 @@ struct Workspace {
   int32_t *seq_len, *seq_n;          // cached length (-1: takes no part), seq_tag(n, base)
   int32_t *dump_slot;
   const int32_t* live;               // the last sequence's entry of seq_n
+  bool partly_filled;                // packed rows of a verifier pass (a prefill pass's are packed too, but mostly all there)
   int32_t* row_blk;    // physical KV block that holds the row's position (0 for dead rows)
   float2* row_rope;    // [m_pad][head_dim/2] (cos, sin) at the row's position
   float* resid;

@@ -84,6 +84,25 @@ def test_same_bits_among_partly_filled_windows(env, alone, n_seq):
     assert bool(((out >= 0) == live).all())
 
 
+@pytest.mark.parametrize("total", [32, 384, 512, 513, 576, 577, 640, 641, 704, 705, 768, 769, 1024])
+@pytest.mark.parametrize("n_seq", [48, 64])
+def test_same_bits_on_both_sides_of_the_launch_for_fewer_rows(env, alone, n_seq, total):
+    """Partly filled windows of 768 rows and more: a launch for no more rows than a multiple of 128 between 9/16 and 3/4 of
+    all and one for more; exactly one of the two may run, whichever multiple it is."""
+    slot = n_seq // 2
+    total = min(total, n_seq * WINDOW)
+    n_valid = np.full(n_seq, 0)
+    n_valid[slot] = WINDOW
+    rest, others = total - WINDOW, [s for s in range(n_seq) if s != slot]
+    for k, s in enumerate(others):
+        n_valid[s] = (rest * (k + 1)) // len(others) - (rest * k) // len(others)
+    expect = [0 if n else B.LLM42_SEQ_BAD_LENGTH for n in n_valid]           # (a count of 0 is refused: no rows)
+    assert n_valid.sum() == total and n_valid.max() <= WINDOW
+    out, logits, k, v = _run(*env, n_seq, slot, n_valid, expect_status=expect)
+    assert torch.equal(out[slot], alone[0])
+    assert torch.equal(logits, alone[1]) and torch.equal(k, alone[2]) and torch.equal(v, alone[3])
+
+
 @pytest.mark.parametrize("d_model,n_kv_heads", [(1024, 2), (2048, 4)])
 def test_same_bits_with_few_feature_blocks(d_model, n_kv_heads):
     """At most one block of 16 QKV features per CU: up to 64 rows a workgroup takes one block, not two; from 65 rows on the

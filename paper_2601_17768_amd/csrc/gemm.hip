@@ -389,7 +389,7 @@ bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
   }
   constexpr Kind kind = std::is_same<Epi, QkvEpi>::value ? QKV : is_logits<Epi>::value ? LM_HEAD : PLAIN;
   const int h = SPLIT == 2 ? split_point(k_tiles) : k_tiles;
-  const Work one{kind, n_blocks, h, 1, ws.num_cus}, both{kind, n_blocks, h, 2, ws.num_cus};
+  const Work one{kind, n_blocks, h, 1, ws.num_cus, ws.partly_filled}, both{kind, n_blocks, h, 2, ws.num_cus, ws.partly_filled};
   // The two halves in one launch, their sum left to what follows - or one after the other, the second adding the first one's
   // partial and the residual stream in its epilogue, where their workgroups take the same time either way: it saves the norms
   // the halves.  us for the projections and norms of one layer, one launch | two: 8B 1024 rows 199 | 205, 1280 210 | 237, 1536
@@ -470,7 +470,7 @@ static int launch_logits(const llm42_model* m, int window, float* out_logits, co
   e.window = window;
   e.vocab = m->cfg.vocab;
   const int n_blocks = m->cfg.vocab / 16;
-  const int block = ws.m_pad <= 64 ? 1 : kTiles[pick_tile(Work{LM_HEAD, n_blocks, m->cfg.d_model / 32, 1, ws.num_cus}, ws.m_pad).tile].bn;
+  const int block = ws.m_pad <= 64 ? 1 : kTiles[pick_tile(Work{LM_HEAD, n_blocks, m->cfg.d_model / 32, 1, ws.num_cus, ws.partly_filled}, ws.m_pad).tile].bn;
   e.parts = (n_blocks + block - 1) / block;
   e.inv_temp = SAMPLED ? 1.0f / sampling->temperature : 0.f;
   e.seed = SAMPLED ? sampling->seed : 0;

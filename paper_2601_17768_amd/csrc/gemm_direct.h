@@ -251,10 +251,11 @@ void launch_direct(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, c
     TILE(23, 7, 2, 16, 2, 3, 1, 3, 1);
     TILE(24, 7, 4, 10, 1, 6, 1, 2, 1);
     TILE(25, 7, 4, 12, 1, 4, 1, 2, 1);
-    TILE(26, 4, 1, 4, 4, 4, 4, 2, 1);
-    TILE(27, 4, 2, 8, 2, 4, 2, 2, 2);
+    TILE(26, 2, 1, 8, 4, 4, 4, 4, 1);
+    TILE(27, 4, 1, 4, 4, 4, 4, 2, 1);
+    TILE(28, 4, 2, 8, 2, 4, 2, 2, 2);
   }
-  static_assert(kTileCount == 28, "one launch per entry of kTiles");
+  static_assert(kTileCount == 29, "one launch per entry of kTiles");
 #undef TILE
 #undef TILE_NT
 }

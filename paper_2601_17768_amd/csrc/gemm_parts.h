@@ -308,7 +308,11 @@ __device__ __forceinline__ void wait_for_rounds(int ahead) {
 // k-tile, fitted to launches within passes (8B shapes, 128 - 4096 rows) that fill one or more rounds, and 3 us + 24 ns per
 // block of the tile that do not depend on K (O- and down-projection differ in K only: 16 x 10 blocks 41.7 and 117.7 us, 64 and 224
 // k-tiles).  Rounds of fewer workgroups take as long (half of the CUs 0.45 against 0.48 us per k-tile): a CU's own fetches and
-// arithmetic are what a round waits for.  The last two are for small K: the 4 x 4 blocks again in shorter rounds, and 8 x 8 blocks
+// arithmetic are what a round waits for.  Of the last three the first is for split projections of partly filled windows, priced
+// for half of the rows: every workgroup has all token blocks, fetches those that hold rows, and reads weights that no other
+// does, where 4 x 4 blocks leave half of the CUs without rows (8B, us per pass with a quarter, half, three quarters and all of
+// 120 rows there: 4442, 4667, 4607, 4643 -> 4034, 4433, 4692, 4735).
+// The other two are for small K: the 4 x 4 blocks again in shorter rounds, and 8 x 8 blocks
 // two to a CU, where neither's beginning nor end leaves it idle, for the LM head (32 k-tiles x 50304 features: 512 rows
 // 58 us against 61 - 85 with the others, 4096 396 against 436; the heavier epilogue of gate/up gains nothing from it).
 struct Tile {
@@ -317,9 +321,9 @@ struct Tile {
 constexpr Tile kTiles[] = {{3, 4, 115, 1},  {4, 4, 144, 1},  {6, 4, 152, 1},   {3, 6, 140, 1},   {4, 6, 160, 1},   {4, 8, 180, 1},   {6, 6, 185, 1},
                            {8, 6, 215, 1},  {6, 8, 215, 1},  {7, 8, 230, 1},   {8, 8, 242, 1},   {8, 10, 285, 1},  {7, 12, 300, 1},  {6, 12, 300, 1},
                            {8, 12, 326, 1}, {7, 16, 365, 1}, {12, 8, 330, 1},  {16, 8, 376, 1},  {8, 16, 372, 1},  {16, 10, 476, 1}, {14, 12, 480, 1},
-                           {14, 14, 545, 1}, {12, 16, 570, 1}, {14, 16, 605, 1}, {28, 10, 760, 1}, {28, 12, 930, 1}, {4, 4, 170, 1},
-                           {8, 8, 477, 2}};
-constexpr int kTileCount = sizeof kTiles / sizeof kTiles[0], kShortRounds = kTileCount - 2;
+                           {14, 14, 545, 1}, {12, 16, 570, 1}, {14, 16, 605, 1}, {28, 10, 760, 1}, {28, 12, 930, 1}, {2, 8, 95, 1},
+                           {4, 4, 170, 1},  {8, 8, 477, 2}};
+constexpr int kTileCount = sizeof kTiles / sizeof kTiles[0], kShortRounds = kTileCount - 2, kPartly = kTileCount - 3;
 
 struct Choice {
   int tile;
@@ -335,12 +339,14 @@ struct Work {
   Kind kind;
   int n_blocks, k_tiles, planes;
   long long cus;
+  bool partly;   // a verifier pass with partly filled windows
 };
 // What tile t takes for `rows` rows (negative: it is not for this work).
 inline long long tile_cost(int t, const Work& w, int rows) {
   const Tile& q = kTiles[t];
   const long long tiles = (long long)((w.n_blocks + q.bn - 1) / q.bn) * ((rows + 16 * q.bm - 1) / (16 * q.bm)) * w.planes, slots = w.cus * q.per_cu;
   const long long whole = (tiles + slots - 1) / slots * 64, share = tiles * 64 / slots + 16;   // rounds, in 1/64
+  if (t == kPartly && !(w.partly && w.planes == 2)) return -1;
   if (q.per_cu == 2 && (w.kind != LM_HEAD || tiles <= 2 * slots)) return -1;
   long long round = (long long)q.cost * w.k_tiles + (q.per_cu == 2 ? 500 : (t == kShortRounds ? 2200 : 3000) + 24 * q.bn * q.bm);
   if (w.kind != PLAIN && q.bm == 16 && q.bn <= 8) round += round / 20;

@@ -149,8 +149,8 @@ def vendor_gemm_tflops(torch, m, n, k, reps=20):
 
 
 def padded_rows(rows):
-    return 16 if rows <= 16 else 32 if rows <= 32 else 64 if rows <= 64 else \
-        (rows + 127) // 128 * 128 if rows <= 256 else 512 if rows <= 512 else (rows + 255) // 256 * 256
+    return 16 if rows <= 16 else 32 if rows <= 32 else 64 if rows <= 64 else 192 if 128 < rows <= 192 else \
+        (rows + 127) // 128 * 128 if rows <= 1280 else (rows + 255) // 256 * 256
 
 
 def run_workload(name, sess, shape, weights, args, with_cpu_baseline):

@@ -346,9 +346,9 @@ __global__ __launch_bounds__(256) void add_halves_kernel(float* __restrict__ x, 
 }
 
 // The halves in split_part: left to the RMSNorm that follows (true), or added here where that one runs a wave per row over
-// interleaved rows (more than 512, d_model other than 4096), whose pieces of 16 bytes cost more than this launch saves: at
-// 2048 rows the projections with their norms take 298 us a pass of two layers against 338 (d_model 2048), 140 against 153
-// (1024), and at 1280 rows of d_model 8192 1839 against 2037.
+// interleaved rows (more than 512, d_model other than 1024, 2048, 4096 and 8192), whose pieces of 16 bytes cost more than this
+// launch saves: the projections with their norms, us a pass of two layers, added here against left to that norm, taken on widths
+// that ran so then: 2048 rows 298 against 338 (d_model 2048), 140 against 153 (1024), 1280 rows 1839 against 2037 (8192).
 template <class Epi>
 bool halves_pending(const Workspace& ws, int n, const Epi& epi, hipStream_t st) {
   if constexpr (std::is_same<Epi, ResidualEpi>::value) {
@@ -358,7 +358,6 @@ bool halves_pending(const Workspace& ws, int n, const Epi& epi, hipStream_t st) 
   }
   return false;
 }
-
 
 // Returns whether a split GEMM left its two halves in split_part.
 template <int SPLIT, class Epi>

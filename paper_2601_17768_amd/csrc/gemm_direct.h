@@ -29,7 +29,7 @@ namespace gemm {
 //   1536     94.9 -> 78.7   62.2 -> 53.4   180.0 -> 152.3   302.9 -> 262.7    1505 -> 1385
 //   2048    101.6 -> 100.6                                  366.6 -> 354.8    2102 -> 1796
 //   3072    182.0 -> 152.5                                  552.9 -> 530      3145 -> 2747
-//   4096    194.3 -> 185.1 157.1 -> 151.5  411.5 -> 394.6   717.5 -> 703-718  4379 -> 3687
+//   4096    194.3 -> 184.0 157.1 -> 151.5  411.5 -> 394.6   717.5 -> 703-718  4379 -> 3687
 // (gate/up at 4096 rows 1.34 - 1.37 PFLOP/s, where the vendor library's GEMM of the shape runs at 1.32 with such operands.)
 // Other widths, a two-layer pass of 948 calls (d_model 256 - 8192, 1 - 4096 rows): up to 1.5 times as fast, the worst
 // 1.07 times as slow; gate/up of 32 k-tiles x 8192 features is the launch that lost, 63 -> 71 us at 4096 rows.

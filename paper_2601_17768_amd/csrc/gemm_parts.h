@@ -333,7 +333,9 @@ struct Choice {
 // them in step: it ends about a quarter of a round behind its share of the CUs' time (14 x 16 blocks, LM head of 768 rows: 6.7
 // rounds take the time of 7; of 1024 rows and 32000 features, 2.2 rounds, that of 3), no later than whole rounds would.  The
 // epilogues of QKV and LM head do much per row, and with 16 token blocks to a wave and few features that counts (QKV at 1024
-// rows: 16 x 8 blocks 63.6 us, 8 x 16 67.0; LM head of 32000 features at 512 rows 114 and 119).
+// rows: 16 x 8 blocks 63.6 us, 8 x 16 67.0; LM head of 32000 features at 512 rows 114 and 119).  So it does for QKV with 12 x 16
+// blocks in more than one round (against 16 x 8, us: 8B 3328 rows 184 and 174, 4096 195 and 184, 5888 295 and 293, 8192 395 and 368;
+// d_model 2048, 3072 features, 6656 rows 118 and 107, 8192 120 and 114; d_model 8192, 12288 features, 3072 rows 533 and 538).
 enum Kind { QKV, PLAIN, LM_HEAD };
 struct Work {
   Kind kind;
@@ -349,7 +351,7 @@ inline long long tile_cost(int t, const Work& w, int rows) {
   if (t == kPartly && !(w.partly && w.planes == 2)) return -1;
   if (q.per_cu == 2 && (w.kind != LM_HEAD || tiles <= 2 * slots)) return -1;
   long long round = (long long)q.cost * w.k_tiles + (q.per_cu == 2 ? 500 : (t == kShortRounds ? 2200 : 3000) + 24 * q.bn * q.bm);
-  if (w.kind != PLAIN && q.bm == 16 && q.bn <= 8) round += round / 20;
+  if (w.kind != PLAIN && q.bm == 16 && q.bn <= (w.kind == QKV ? 12 : 8)) round += round / 20;
   return (whole <= 4 * 64 || whole < share ? whole : share) * round / 64;
 }
 inline Choice pick_tile(const Work& w, int m_pad) {

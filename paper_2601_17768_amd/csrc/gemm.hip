@@ -299,9 +299,9 @@ __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restri
   }
 }
 
-enum GemmKind { GEMM_QKV = 0, GEMM_RESIDUAL = 1, GEMM_GATE_UP = 2, GEMM_LOGITS = 3 };
-// The split of each GEMM type (part of the reduction schedule, see above).
-constexpr int kSplit[4] = {1, 2, 1, 1};
+// The split of each GEMM type (part of the reduction schedule, see above); the LM head is not split.
+enum GemmKind { GEMM_QKV = 0, GEMM_RESIDUAL = 1, GEMM_GATE_UP = 2 };
+constexpr int kSplit[3] = {1, 2, 1};
 
 template <int SPLIT, class Epi>
 void launch_narrow(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, int n, const Workspace& ws, const Epi& epi,
@@ -359,34 +359,37 @@ bool halves_pending(const Workspace& ws, int n, const Epi& epi, hipStream_t st) 
   return false;
 }
 
-// Returns whether a split GEMM left its two halves in split_part.
+// Up to 64 rows, wide outputs (gate/up, LM head).
+template <class Epi>
+void launch_wide(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, const Workspace& ws, const Epi& epi, hipStream_t st) {
+  // 7 or 8 feature blocks per workgroup: whichever needs less (rounds of 256 workgroups) x (blocks each)
+  const int g8 = (n_blocks + 7) / 8, g7 = (n_blocks + 6) / 7;
+  const bool seven = ((g7 + 255) / 256) * 7 < ((g8 + 255) / 256) * 8;
+  const unsigned gx = (unsigned)(seven ? g7 : g8);
+  if (seven) {
+    if (ws.m_pad == 16) gemm_xshare_kernel<1, 7, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
+    else if (ws.m_pad == 32) gemm_xshare_kernel<2, 7, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
+    else gemm_xshare_kernel<4, 7, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
+  } else {
+    if (ws.m_pad == 16) gemm_xshare_kernel<1, 8, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
+    else if (ws.m_pad == 32) gemm_xshare_kernel<2, 8, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
+    else gemm_xshare_kernel<4, 8, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
+  }
+}
+
+// QKV, gate/up and residual projections.  Returns whether a split GEMM left its two halves in split_part.
 template <int SPLIT, class Epi>
-bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padded, int n, const Workspace& ws,
-                 bool wide, const Epi& epi, hipStream_t st) {
+bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padded, int n, const Workspace& ws, const Epi& epi,
+                 hipStream_t st) {
   const int k_tiles = k_padded / 32, m_pad = ws.m_pad;
   const bf16x8* wp = (const bf16x8*)w;
   const bf16x8* xp = (const bf16x8*)x;
   if (m_pad <= 64) {
-    if (wide && SPLIT == 1) {
-      // 7 or 8 feature blocks per workgroup: whichever needs less (rounds of 256 workgroups) x (blocks each)
-      const int g8 = (n_blocks + 7) / 8, g7 = (n_blocks + 6) / 7;
-      const bool seven = ((g7 + 255) / 256) * 7 < ((g8 + 255) / 256) * 8;
-      const unsigned gx = (unsigned)(seven ? g7 : g8);
-      if (seven) {
-        if (m_pad == 16) gemm_xshare_kernel<1, 7, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
-        else if (m_pad == 32) gemm_xshare_kernel<2, 7, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
-        else gemm_xshare_kernel<4, 7, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
-      } else {
-        if (m_pad == 16) gemm_xshare_kernel<1, 8, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
-        else if (m_pad == 32) gemm_xshare_kernel<2, 8, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
-        else gemm_xshare_kernel<4, 8, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
-      }
-    } else {
-      launch_narrow<SPLIT>(wp, xp, n_blocks, k_tiles, n, ws, epi, st);
-    }
+    if constexpr (std::is_same<Epi, SwigluEpi>::value) launch_wide(wp, xp, n_blocks, k_tiles, ws, epi, st);
+    else launch_narrow<SPLIT>(wp, xp, n_blocks, k_tiles, n, ws, epi, st);
     return SPLIT == 2;
   }
-  constexpr Kind kind = std::is_same<Epi, QkvEpi>::value ? QKV : is_logits<Epi>::value ? LM_HEAD : PLAIN;
+  constexpr Kind kind = std::is_same<Epi, QkvEpi>::value ? QKV : PLAIN;
   const int h = SPLIT == 2 ? split_point(k_tiles) : k_tiles;
   const Work one{kind, n_blocks, h, 1, ws.num_cus, ws.partly_filled}, both{kind, n_blocks, h, 2, ws.num_cus, ws.partly_filled};
   // The two halves in one launch, their sum left to what follows - or one after the other, the second adding the first one's
@@ -413,7 +416,7 @@ bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
       launch_direct(tile, wp, xp, n_blocks, Range{k_tiles, k_tiles, 0, 1, rows, more_than}, ws, epi, st);
     }
   };
-  const int fewer = ws.partly_filled && m_pad >= 768 && kind != LM_HEAD ? rows_apart(work, m_pad, pick_tile(work, m_pad)) : 0;
+  const int fewer = ws.partly_filled && m_pad >= 768 ? rows_apart(work, m_pad, pick_tile(work, m_pad)) : 0;
   if (fewer) launch(fewer, -1);
   launch(m_pad, fewer ? fewer : -1);
   return SPLIT == 2 && !in_turn && halves_pending(ws, n, epi, st);
@@ -439,7 +442,7 @@ void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, 
   e.group = m->group;
   e.window = window;
   e.r_pad = ws.r_pad;
-  launch_gemm<kSplit[GEMM_QKV]>(m->layers[layer].wqkv, ws.normed, m->n_qkv / 16, c.d_model, m->n_qkv, ws, false, e, st);
+  launch_gemm<kSplit[GEMM_QKV]>(m->layers[layer].wqkv, ws.normed, m->n_qkv / 16, c.d_model, m->n_qkv, ws, e, st);
 }
 
 bool launch_gemm_residual(const uint16_t* w, const uint16_t* x, float* resid, int n, int k_padded,
@@ -447,13 +450,13 @@ bool launch_gemm_residual(const uint16_t* w, const uint16_t* x, float* resid, in
   ResidualEpi e{resid, ws.rl, n};
   // Off the fixed schedule (fast path, cost-of-determinism measurement) the split follows the batch,
   // as in an ordinary engine: two halves while there are few rows to spread over the device, none beyond.
-  if (ws.batch_chosen && ws.m_rows > 16) return launch_gemm<1>(w, x, n / 16, k_padded, n, ws, false, e, st);
-  return launch_gemm<kSplit[GEMM_RESIDUAL]>(w, x, n / 16, k_padded, n, ws, false, e, st);
+  if (ws.batch_chosen && ws.m_rows > 16) return launch_gemm<1>(w, x, n / 16, k_padded, n, ws, e, st);
+  return launch_gemm<kSplit[GEMM_RESIDUAL]>(w, x, n / 16, k_padded, n, ws, e, st);
 }
 
 void launch_gemm_swiglu(const llm42_model* m, int layer, const Workspace& ws, hipStream_t st) {
   SwigluEpi e{ws.hidden, m->ffn_k};
-  launch_gemm<kSplit[GEMM_GATE_UP]>(m->layers[layer].wgu, ws.normed, m->gu_blocks, m->cfg.d_model, m->gu_blocks * 16, ws, true, e, st);
+  launch_gemm<kSplit[GEMM_GATE_UP]>(m->layers[layer].wgu, ws.normed, m->gu_blocks, m->cfg.d_model, m->gu_blocks * 16, ws, e, st);
 }
 
 // Returns the number of arg-max partials per row.
@@ -468,13 +471,19 @@ static int launch_logits(const llm42_model* m, int window, float* out_logits, co
   e.amax = ws.amax;
   e.window = window;
   e.vocab = m->cfg.vocab;
-  const int n_blocks = m->cfg.vocab / 16;
-  const int block = ws.m_pad <= 64 ? 1 : kTiles[pick_tile(Work{LM_HEAD, n_blocks, m->cfg.d_model / 32, 1, ws.num_cus, ws.partly_filled}, ws.m_pad).tile].bn;
-  e.parts = (n_blocks + block - 1) / block;
+  const int n_blocks = m->cfg.vocab / 16, k_tiles = m->cfg.d_model / 32;
+  const bf16x8 *wp = (const bf16x8*)m->lm_head, *xp = (const bf16x8*)ws.normed;
   e.inv_temp = SAMPLED ? 1.0f / sampling->temperature : 0.f;
   e.seed = SAMPLED ? sampling->seed : 0;
   e.request_ids = SAMPLED ? sampling->request_ids : nullptr;
-  launch_gemm<kSplit[GEMM_LOGITS]>(m->lm_head, ws.normed, n_blocks, m->cfg.d_model, m->cfg.vocab, ws, true, e, st);
+  if (ws.m_pad <= 64) {
+    e.parts = n_blocks;
+    launch_wide(wp, xp, n_blocks, k_tiles, ws, e, st);
+  } else {
+    const int tile = pick_tile(Work{LM_HEAD, n_blocks, k_tiles, 1, ws.num_cus, ws.partly_filled}, ws.m_pad).tile;
+    e.parts = (n_blocks + kTiles[tile].bn() - 1) / kTiles[tile].bn();
+    launch_direct(tile, wp, xp, n_blocks, Range{k_tiles, k_tiles, 0, 1, ws.m_pad, -1}, ws, e, st);
+  }
   return e.parts;
 }
 

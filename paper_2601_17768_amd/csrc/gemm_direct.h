@@ -1,6 +1,8 @@
 // The GEMM of more than 64 rows: gemm_direct_kernel, its tiles and the rule that chooses among them.  A template of the
 // epilogue; each gemm_direct_*.hip holds the kernels of one.
 #pragma once
+#include <utility>
+
 #include "gemm_parts.h"
 
 namespace gemm {
@@ -205,59 +207,43 @@ __global__ __launch_bounds__(64 * (NW + F), (WGS * (NW + F) + 3) / 4) void gemm_
   }
 }
 
-template <int NW, int FB, int TB, int CH, int R, int F, int NSET, int WGS, bool NT, class Epi>
+template <int T, bool NT, class Epi>
 void launch_tile(const bf16x8* wp, const bf16x8* xp, int n_blocks, const Range& k, const Workspace& ws, const Epi& epi, hipStream_t st) {
-  const int tiles_n = (n_blocks + NW * FB - 1) / (NW * FB), tiles_m = k.rows / (16 * TB);
+  constexpr Tile q = kTiles[T];
+  const int tiles_n = (n_blocks + q.bn() - 1) / q.bn(), tiles_m = k.rows / (16 * q.bm);
   const int per_xcd = (tiles_n * tiles_m * k.planes + 7) / 8;
-  gemm_direct_kernel<NW, FB, TB, CH, R, F, NSET, WGS, NT, Epi><<<8 * per_xcd, 64 * (NW + F), 0, st>>>(
+  gemm_direct_kernel<q.nw, q.fb, q.bm, q.ch, q.r, q.f, q.nset, q.per_cu, NT, Epi><<<8 * per_xcd, 64 * (q.nw + q.f), 0, st>>>(
       wp, xp, n_blocks, k.k_tiles, k.split, k.first_plane, k.planes, tiles_n, tiles_m, ws.live, k.more_than / 16,
       ws.live && (long long)tiles_n * tiles_m * k.planes > ws.num_cus, epi);
+}
+
+// Tile::nt: with one token tile no other workgroup reads the weights, and they are marked to be streamed past the caches
+// (gate/up at 128 rows 51.0 -> 48.8 us, at 256 66.7 -> 64.9, LM head at 128 230 -> 215; with several token tiles no gain)
+template <int T, class Epi>
+bool launch_if(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, const Range& k, const Workspace& ws, const Epi& epi,
+               hipStream_t st) {
+  if (tile != T || k.rows % (16 * kTiles[T].bm)) return false;
+  if constexpr (kTiles[T].nt) {
+    if (k.rows == 16 * kTiles[T].bm) {
+      launch_tile<T, true>(wp, xp, n_blocks, k, ws, epi, st);
+      return true;
+    }
+  }
+  launch_tile<T, false>(wp, xp, n_blocks, k, ws, epi, st);
+  return true;
+}
+
+template <int... T, class Epi>
+bool launch_any(std::integer_sequence<int, T...>, int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, const Range& k,
+                const Workspace& ws, const Epi& epi, hipStream_t st) {
+  return (launch_if<T>(tile, wp, xp, n_blocks, k, ws, epi, st) || ...);
 }
 
 template <class Epi>
 void launch_direct(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, const Range& k, const Workspace& ws, const Epi& epi,
                    hipStream_t st) {
-  // TILE_NT: with one token tile no other workgroup reads the weights, and they are marked to be streamed past the caches
-  // (gate/up at 128 rows 51.0 -> 48.8 us, at 256 66.7 -> 64.9, LM head at 128 230 -> 215; with several token tiles no gain)
-#define TILE(i, ...) case i: return launch_tile<__VA_ARGS__, false>(wp, xp, n_blocks, k, ws, epi, st)
-#define TILE_NT(i, ...)                                                                                             \
-  case i:                                                                                                           \
-    if (k.rows == 16 * kTiles[i].bm) return launch_tile<__VA_ARGS__, true>(wp, xp, n_blocks, k, ws, epi, st);     \
-    return launch_tile<__VA_ARGS__, false>(wp, xp, n_blocks, k, ws, epi, st)
-  switch (tile) {   // feature waves, blocks of each, token blocks | k-tiles of a round, rounds in LDS, fetching waves, register sets, workgroups per CU
-    TILE(0, 3, 1, 4, 8, 4, 4, 3, 1);
-    TILE(1, 4, 1, 4, 8, 4, 4, 3, 1);
-    TILE(2, 6, 1, 4, 8, 4, 4, 2, 1);
-    TILE(3, 3, 1, 6, 4, 5, 4, 3, 1);
-    TILE(4, 4, 1, 6, 4, 5, 4, 3, 1);
-    TILE(5, 4, 1, 8, 4, 4, 4, 2, 1);
-    TILE(6, 6, 1, 6, 4, 5, 4, 3, 1);
-    TILE(7, 8, 1, 6, 4, 5, 4, 3, 1);
-    TILE(8, 6, 1, 8, 4, 4, 4, 2, 1);
-    TILE_NT(9, 7, 1, 8, 4, 4, 4, 2, 1);
-    TILE(10, 8, 1, 8, 4, 4, 4, 2, 1);
-    TILE(11, 8, 1, 10, 2, 5, 4, 3, 1);
-    TILE_NT(12, 7, 1, 12, 2, 4, 4, 3, 1);
-    TILE(13, 6, 1, 12, 2, 4, 2, 4, 1);
-    TILE(14, 4, 2, 12, 2, 4, 4, 3, 1);
-    TILE_NT(15, 7, 1, 16, 2, 4, 4, 2, 1);
-    TILE(16, 6, 2, 8, 4, 4, 2, 2, 1);
-    TILE_NT(17, 8, 2, 8, 4, 4, 4, 2, 1);
-    TILE(18, 4, 2, 16, 2, 4, 4, 2, 1);
-    TILE(19, 8, 2, 10, 2, 5, 4, 2, 1);
-    TILE(20, 7, 2, 12, 2, 4, 1, 3, 1);
-    TILE(21, 7, 2, 14, 2, 4, 1, 3, 1);
-    TILE(22, 6, 2, 16, 2, 3, 1, 3, 1);
-    TILE(23, 7, 2, 16, 2, 3, 1, 3, 1);
-    TILE(24, 7, 4, 10, 1, 6, 1, 2, 1);
-    TILE(25, 7, 4, 12, 1, 4, 1, 2, 1);
-    TILE(26, 2, 1, 8, 4, 4, 4, 4, 1);
-    TILE(27, 4, 1, 4, 4, 4, 4, 2, 1);
-    TILE(28, 4, 2, 8, 2, 4, 2, 2, 2);
-  }
-  static_assert(kTileCount == 29, "one launch per entry of kTiles");
-#undef TILE
-#undef TILE_NT
+  if (!launch_any(std::make_integer_sequence<int, kTileCount>{}, tile, wp, xp, n_blocks, k, ws, epi, st))
+    (void)hipLaunchKernel(nullptr, dim3(1), dim3(1), nullptr, 0, st);   // (fails: no tile of that number, or not for so many rows)
 }
 
 }  // namespace gemm

@@ -316,13 +316,22 @@ __device__ __forceinline__ void wait_for_rounds(int ahead) {
 // two to a CU, where neither's beginning nor end leaves it idle, for the LM head (32 k-tiles x 50304 features: 512 rows
 // 58 us against 61 - 85 with the others, 4096 396 against 436; the heavier epilogue of gate/up gains nothing from it).
 struct Tile {
-  int bn, bm, cost, per_cu;
+  int nw, fb, bm;      // multiplying waves, feature blocks of each; token blocks
+  int ch, r, f, nset;  // k-tiles of a round, rounds in LDS, fetching waves, register sets of weights
+  int per_cu;          // workgroups per CU
+  bool nt;             // with one token tile the weights are streamed past the caches (see launch_tile)
+  int cost;
+  constexpr int bn() const { return nw * fb; }
 };
-constexpr Tile kTiles[] = {{3, 4, 115, 1},  {4, 4, 144, 1},  {6, 4, 152, 1},   {3, 6, 140, 1},   {4, 6, 160, 1},   {4, 8, 180, 1},   {6, 6, 185, 1},
-                           {8, 6, 215, 1},  {6, 8, 215, 1},  {7, 8, 230, 1},   {8, 8, 242, 1},   {8, 10, 285, 1},  {7, 12, 300, 1},  {6, 12, 300, 1},
-                           {8, 12, 326, 1}, {7, 16, 365, 1}, {12, 8, 330, 1},  {16, 8, 376, 1},  {8, 16, 372, 1},  {16, 10, 476, 1}, {14, 12, 480, 1},
-                           {14, 14, 545, 1}, {12, 16, 570, 1}, {14, 16, 605, 1}, {28, 10, 760, 1}, {28, 12, 930, 1}, {2, 8, 95, 1},
-                           {4, 4, 170, 1},  {8, 8, 477, 2}};
+constexpr Tile kTiles[] = {
+    {3, 1, 4, 8, 4, 4, 3, 1, false, 115}, {4, 1, 4, 8, 4, 4, 3, 1, false, 144}, {6, 1, 4, 8, 4, 4, 2, 1, false, 152}, {3, 1, 6, 4, 5, 4, 3, 1, false, 140},
+    {4, 1, 6, 4, 5, 4, 3, 1, false, 160}, {4, 1, 8, 4, 4, 4, 2, 1, false, 180}, {6, 1, 6, 4, 5, 4, 3, 1, false, 185}, {8, 1, 6, 4, 5, 4, 3, 1, false, 215},
+    {6, 1, 8, 4, 4, 4, 2, 1, false, 215}, {7, 1, 8, 4, 4, 4, 2, 1, true, 230}, {8, 1, 8, 4, 4, 4, 2, 1, false, 242}, {8, 1, 10, 2, 5, 4, 3, 1, false, 285},
+    {7, 1, 12, 2, 4, 4, 3, 1, true, 300}, {6, 1, 12, 2, 4, 2, 4, 1, false, 300}, {4, 2, 12, 2, 4, 4, 3, 1, false, 326}, {7, 1, 16, 2, 4, 4, 2, 1, true, 365},
+    {6, 2, 8, 4, 4, 2, 2, 1, false, 330}, {8, 2, 8, 4, 4, 4, 2, 1, true, 376}, {4, 2, 16, 2, 4, 4, 2, 1, false, 372}, {8, 2, 10, 2, 5, 4, 2, 1, false, 476},
+    {7, 2, 12, 2, 4, 1, 3, 1, false, 480}, {7, 2, 14, 2, 4, 1, 3, 1, false, 545}, {6, 2, 16, 2, 3, 1, 3, 1, false, 570}, {7, 2, 16, 2, 3, 1, 3, 1, false, 605},
+    {7, 4, 10, 1, 6, 1, 2, 1, false, 760}, {7, 4, 12, 1, 4, 1, 2, 1, false, 930}, {2, 1, 8, 4, 4, 4, 4, 1, false, 95}, {4, 1, 4, 4, 4, 4, 2, 1, false, 170},
+    {4, 2, 8, 2, 4, 2, 2, 2, false, 477}};
 constexpr int kTileCount = sizeof kTiles / sizeof kTiles[0], kShortRounds = kTileCount - 2, kPartly = kTileCount - 3;
 
 struct Choice {
@@ -346,12 +355,12 @@ struct Work {
 // What tile t takes for `rows` rows (negative: it is not for this work).
 inline long long tile_cost(int t, const Work& w, int rows) {
   const Tile& q = kTiles[t];
-  const long long tiles = (long long)((w.n_blocks + q.bn - 1) / q.bn) * ((rows + 16 * q.bm - 1) / (16 * q.bm)) * w.planes, slots = w.cus * q.per_cu;
+  const long long tiles = (long long)((w.n_blocks + q.bn() - 1) / q.bn()) * ((rows + 16 * q.bm - 1) / (16 * q.bm)) * w.planes, slots = w.cus * q.per_cu;
   const long long whole = (tiles + slots - 1) / slots * 64, share = tiles * 64 / slots + 16;   // rounds, in 1/64
   if (t == kPartly && !(w.partly && w.planes == 2)) return -1;
   if (q.per_cu == 2 && (w.kind != LM_HEAD || tiles <= 2 * slots)) return -1;
-  long long round = (long long)q.cost * w.k_tiles + (q.per_cu == 2 ? 500 : (t == kShortRounds ? 2200 : 3000) + 24 * q.bn * q.bm);
-  if (w.kind != PLAIN && q.bm == 16 && q.bn <= (w.kind == QKV ? 12 : 8)) round += round / 20;
+  long long round = (long long)q.cost * w.k_tiles + (q.per_cu == 2 ? 500 : (t == kShortRounds ? 2200 : 3000) + 24 * q.bn() * q.bm);
+  if (w.kind != PLAIN && q.bm == 16 && q.bn() <= (w.kind == QKV ? 12 : 8)) round += round / 20;
   return (whole <= 4 * 64 || whole < share ? whole : share) * round / 64;
 }
 inline Choice pick_tile(const Work& w, int m_pad) {
@@ -387,7 +396,7 @@ struct Range {
   int k_tiles, split, first_plane, planes, rows, more_than;
 };
 
-// D = W X with the epilogue, by tile `tile` of kTiles.
+// D = W X with the epilogue, by tile `tile` of kTiles.  Without such a tile nothing runs and the error is left for hipGetLastError.
 template <class Epi>
 void launch_direct(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, const Range& k, const Workspace& ws, const Epi& epi,
                    hipStream_t st);

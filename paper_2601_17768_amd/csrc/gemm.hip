@@ -166,7 +166,7 @@ __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restri
                                                           int n_blocks, int k_tiles, Epi epi) {
   // A round is CH k-tiles; NSET register sets of weights: one in use, NSET - 1 in flight (16 KiB per
   // wave whatever the round length).  The round's activation tiles go through LDS, double buffered.
-  constexpr int CH = MB <= 2 ? 16 : MB <= 8 ? 8 : 4, NSET = 16 / CH + 1, NW = 8;
+  constexpr int CH = MB <= 2 ? 16 : 8, NSET = 16 / CH + 1, NW = 8;
   constexpr int XT = MB * CH / NW;                   // activation tiles each wave fetches per round
   static_assert(MB * CH % NW == 0, "a round's activation tiles are dealt evenly to the waves");
   __shared__ bf16x8 xlds[2][MB * CH * 64];
@@ -267,19 +267,11 @@ __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restri
       body(std::integral_constant<int, 0>{}, r);
       body(std::integral_constant<int, 1>{}, r + 1);
       if constexpr (NSET > 2) body(std::integral_constant<int, 2>{}, r + 2);
-      if constexpr (NSET > 3) body(std::integral_constant<int, 3>{}, r + 3);
-      if constexpr (NSET > 4) body(std::integral_constant<int, 4>{}, r + 4);
     }
     if (r < rounds) body(std::integral_constant<int, 0>{}, r);
     if (r + 1 < rounds) body(std::integral_constant<int, 1>{}, r + 1);
-    if constexpr (NSET > 3) {
-      if (r + 2 < rounds) body(std::integral_constant<int, 2>{}, r + 2);
-    }
-    if constexpr (NSET > 4) {
-      if (r + 3 < rounds) body(std::integral_constant<int, 3>{}, r + 3);
-    }
   };
-  static_assert(NSET >= 2 && NSET <= 5, "the groups of rounds are written out for 2 .. 5 register sets");
+  static_assert(NSET == 2 || NSET == 3, "the groups of rounds are written out for 2 and 3 register sets");
   if (rounds > 0) {
     if (owner) run(std::true_type{});
     else run(std::false_type{});

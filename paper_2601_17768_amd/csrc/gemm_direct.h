@@ -222,14 +222,11 @@ void launch_tile(const bf16x8* wp, const bf16x8* xp, int n_blocks, const Range& 
 template <int T, class Epi>
 bool launch_if(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, const Range& k, const Workspace& ws, const Epi& epi,
                hipStream_t st) {
-  if (tile != T || k.rows % (16 * kTiles[T].bm)) return false;
-  if constexpr (kTiles[T].nt) {
-    if (k.rows == 16 * kTiles[T].bm) {
-      launch_tile<T, true>(wp, xp, n_blocks, k, ws, epi, st);
-      return true;
-    }
+  if (!serves<Epi>(T) || tile != T || k.rows % (16 * kTiles[T].bm)) return false;
+  if constexpr (serves<Epi>(T)) {
+    if (kTiles[T].nt && k.rows == 16 * kTiles[T].bm) launch_tile<T, kTiles[T].nt>(wp, xp, n_blocks, k, ws, epi, st);
+    else launch_tile<T, false>(wp, xp, n_blocks, k, ws, epi, st);
   }
-  launch_tile<T, false>(wp, xp, n_blocks, k, ws, epi, st);
   return true;
 }
 
@@ -243,7 +240,7 @@ template <class Epi>
 void launch_direct(int tile, const bf16x8* wp, const bf16x8* xp, int n_blocks, const Range& k, const Workspace& ws, const Epi& epi,
                    hipStream_t st) {
   if (!launch_any(std::make_integer_sequence<int, kTileCount>{}, tile, wp, xp, n_blocks, k, ws, epi, st))
-    (void)hipLaunchKernel(nullptr, dim3(1), dim3(1), nullptr, 0, st);   // (fails: no tile of that number, or not for so many rows)
+    (void)hipLaunchKernel(nullptr, dim3(1), dim3(1), nullptr, 0, st);   // (fails: no such tile for this epilogue and number of rows)
 }
 
 }  // namespace gemm

@@ -334,6 +334,12 @@ constexpr Tile kTiles[] = {
     {4, 2, 8, 2, 4, 2, 2, 2, false, 477}};
 constexpr int kTileCount = sizeof kTiles / sizeof kTiles[0], kShortRounds = kTileCount - 2, kPartly = kTileCount - 3;
 
+// The epilogues that tile t has a kernel for; tile_cost offers it to no other work.
+template <class Epi>
+constexpr bool serves(int t) {
+  return t == kPartly ? std::is_same<Epi, StorePartialEpi>::value : kTiles[t].per_cu == 1 || is_logits<Epi>::value;
+}
+
 struct Choice {
   int tile;
   long long cost;   // ns

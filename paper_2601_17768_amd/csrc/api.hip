@@ -212,10 +212,10 @@ size_t sized_for_up_to(const llm42_model* m, int max_seqs, int window, int max_c
 bool run_mlp(const llm42_model* m, const llm42_model::Layer& ly, const Workspace& ws, hipStream_t st) {
   const llm42_config& c = m->cfg;
   bool pending;
-  TIMED(LLM42_K_O_PROJ, pending = launch_gemm_residual(ly.wo, ws.attn, ws.resid, c.d_model, m->d_attn, ws, st));
+  TIMED(LLM42_K_O_PROJ, pending = launch_gemm_residual(GEMM_O, ly.wo, ws.attn, ws.resid, c.d_model, m->d_attn, ws, st));
   TIMED(LLM42_K_RMSNORM, launch_rmsnorm(pending, ly.ffn_norm, c.d_model, c.rms_eps, ws, st));
   TIMED(LLM42_K_GATE_UP, launch_gemm_swiglu(m, (int)(&ly - m->layers), ws, st));
-  TIMED(LLM42_K_DOWN, pending = launch_gemm_residual(ly.wdown, ws.hidden, ws.resid, c.d_model, m->ffn_k, ws, st));
+  TIMED(LLM42_K_DOWN, pending = launch_gemm_residual(GEMM_DOWN, ly.wdown, ws.hidden, ws.resid, c.d_model, m->ffn_k, ws, st));
   return pending;
 }
 
@@ -240,6 +240,7 @@ llm42_status run_pass(const llm42_model* m, const llm42_kv_cache* kv, const int3
   // launch adds up the counts before it, so not for very many sequences.)
   ws.live = n_valid && num_seqs <= 4096 ? ws.seq_n + num_seqs - 1 : nullptr;
   ws.partly_filled = ws.live && !prefill_pass;
+  plan_gemms(m, ws);
   TIMED(LLM42_K_PREPARE, launch_prepare(m, kv, seq_lens, candidates, n_valid, num_seqs, window, max_context,
                                         dump_seq_ids, n_dump, out_tokens, seq_status, ws, st, prefill_pass));
   if (ws.attn_list) TIMED(LLM42_K_PREPARE, launch_attention_plan(m, num_seqs, max_context, ws, st));
@@ -606,6 +607,7 @@ llm42_status llm42_prefill(const llm42_model* m, const llm42_kv_cache* kv, const
   tail.attn = x.tail_attn;
   tail.resid = x.tail_resid;
   // (the halves of its split GEMMs too: split_part has room for the passes' rows, which are no fewer)
+  plan_gemms(m, tail);
   for (int p = 0; p < passes; ++p) {
     launch_prefill_window(prompt_tokens, prompt_offsets, seq_lens, num_seqs, chunk, p, max_prompt_len, x.cand, x.n_valid,
                           x.lens_now, status, out_next_tokens, st);

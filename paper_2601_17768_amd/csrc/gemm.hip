@@ -291,9 +291,8 @@ __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restri
   }
 }
 
-// The split of each GEMM type (part of the reduction schedule, see above); the LM head is not split.
-enum GemmKind { GEMM_QKV = 0, GEMM_RESIDUAL = 1, GEMM_GATE_UP = 2 };
-constexpr int kSplit[3] = {1, 2, 1};
+// The split of each GEMM type (part of the reduction schedule, see above).
+constexpr int kSplit[GEMM_KINDS] = {1, 2, 1, 2, 1};
 
 template <int SPLIT, class Epi>
 void launch_narrow(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, int n, const Workspace& ws, const Epi& epi,
@@ -369,10 +368,28 @@ void launch_wide(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, 
   }
 }
 
+// How a pass runs a GEMM of more than 64 rows; `split`: in two halves.
+GemmPlan plan_gemm(Kind kind, int n_blocks, int k_tiles, bool split, const Workspace& ws) {
+  const int h = split ? split_point(k_tiles) : k_tiles, m_pad = ws.m_pad;
+  const Work one{kind, n_blocks, h, 1, ws.num_cus, ws.partly_filled}, both{kind, n_blocks, h, 2, ws.num_cus, ws.partly_filled};
+  const Choice alone = pick_tile(one, m_pad), together = split ? pick_tile(both, m_pad) : alone;
+  // The two halves in one launch, their sum left to what follows - or one after the other, the second adding the first one's
+  // partial and the residual stream in its epilogue, where their workgroups take the same time either way: it saves the norms
+  // the halves.  us for the projections and norms of one layer, one launch | two: 8B 1024 rows 199 | 205, 1280 210 | 237, 1536
+  // 260 | 263, 2048 324 | 309, 4096 623 | 606; d_model 8192, 1024 rows 594 | 554, 4096 2246 | 2074; d_model 2048, 4096 rows
+  // 174 | 162.  From 2048 rows on up to a third more is taken for it: the norms are a quarter of the layer there (d_model 2048,
+  // 2048 rows: norms 38 | 26, but 95 | 106 in all; 127 before this kernel).
+  const bool in_turn = split && alone.cost * 2 * 100 <= together.cost * (m_pad < 2048 ? 103 : 135);
+  const Work& work = split && !in_turn ? both : one;
+  const Choice all = split && !in_turn ? together : alone;
+  const int fewer = ws.partly_filled && m_pad >= 768 && kind != LM_HEAD ? rows_apart(work, m_pad, all) : 0;
+  return GemmPlan{all.tile, fewer, fewer ? pick_tile(work, fewer).tile : 0, in_turn};
+}
+
 // QKV, gate/up and residual projections.  Returns whether a split GEMM left its two halves in split_part.
 template <int SPLIT, class Epi>
-bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padded, int n, const Workspace& ws, const Epi& epi,
-                 hipStream_t st) {
+bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padded, int n, const Workspace& ws, const GemmPlan& plan,
+                 const Epi& epi, hipStream_t st) {
   const int k_tiles = k_padded / 32, m_pad = ws.m_pad;
   const bf16x8* wp = (const bf16x8*)w;
   const bf16x8* xp = (const bf16x8*)x;
@@ -381,22 +398,11 @@ bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
     else launch_narrow<SPLIT>(wp, xp, n_blocks, k_tiles, n, ws, epi, st);
     return SPLIT == 2;
   }
-  constexpr Kind kind = std::is_same<Epi, QkvEpi>::value ? QKV : PLAIN;
-  const int h = SPLIT == 2 ? split_point(k_tiles) : k_tiles;
-  const Work one{kind, n_blocks, h, 1, ws.num_cus, ws.partly_filled}, both{kind, n_blocks, h, 2, ws.num_cus, ws.partly_filled};
-  // The two halves in one launch, their sum left to what follows - or one after the other, the second adding the first one's
-  // partial and the residual stream in its epilogue, where their workgroups take the same time either way: it saves the norms
-  // the halves.  us for the projections and norms of one layer, one launch | two: 8B 1024 rows 199 | 205, 1280 210 | 237, 1536
-  // 260 | 263, 2048 324 | 309, 4096 623 | 606; d_model 8192, 1024 rows 594 | 554, 4096 2246 | 2074; d_model 2048, 4096 rows
-  // 174 | 162.  From 2048 rows on up to a third more is taken for it: the norms are a quarter of the layer there (d_model 2048,
-  // 2048 rows: norms 38 | 26, but 95 | 106 in all; 127 before this kernel).
-  const bool in_turn = SPLIT == 2 && pick_tile(one, m_pad).cost * 2 * 100 <= pick_tile(both, m_pad).cost * (m_pad < 2048 ? 103 : 135);
-  const Work& work = SPLIT == 2 && !in_turn ? both : one;
-  const auto launch = [&](int rows, int more_than) {
-    const int tile = pick_tile(work, rows).tile;
+  const auto launch = [&](int tile, int rows, int more_than) {
     if constexpr (SPLIT == 2) {
+      const int h = split_point(k_tiles);
       const StorePartialEpi partial{ws.split_part, ws.rl, n, (size_t)m_pad * n};
-      if (in_turn) {
+      if (plan.in_turn) {
         launch_direct(tile, wp, xp, n_blocks, Range{k_tiles, h, 1, 1, rows, more_than}, ws, partial, st);
         launch_direct(tile, wp, xp, n_blocks, Range{k_tiles, h, 0, 1, rows, more_than}, ws, ResidualAddEpi{epi.resid, ws.split_part, ws.rl, n}, st);
       } else {
@@ -408,13 +414,26 @@ bool launch_gemm(const uint16_t* w, const uint16_t* x, int n_blocks, int k_padde
       launch_direct(tile, wp, xp, n_blocks, Range{k_tiles, k_tiles, 0, 1, rows, more_than}, ws, epi, st);
     }
   };
-  const int fewer = ws.partly_filled && m_pad >= 768 ? rows_apart(work, m_pad, pick_tile(work, m_pad)) : 0;
-  if (fewer) launch(fewer, -1);
-  launch(m_pad, fewer ? fewer : -1);
-  return SPLIT == 2 && !in_turn && halves_pending(ws, n, epi, st);
+  if (plan.fewer) launch(plan.fewer_tile, plan.fewer, -1);
+  launch(plan.tile, m_pad, plan.fewer ? plan.fewer : -1);
+  return SPLIT == 2 && !plan.in_turn && halves_pending(ws, n, epi, st);
 }
 
+// Off the fixed schedule (fast path, cost-of-determinism measurement) the split of the residual projections follows the batch, as
+// in an ordinary engine: two halves while there are few rows to spread over the device, none beyond.
+bool split_residual(const Workspace& ws) { return !(ws.batch_chosen && ws.m_rows > 16); }
+
 }  // namespace
+
+void plan_gemms(const llm42_model* m, Workspace& ws) {
+  if (ws.m_pad <= 64) return;
+  const int d_tiles = m->cfg.d_model / 32, d_blocks = m->cfg.d_model / 16;
+  ws.gemm[GEMM_QKV] = plan_gemm(QKV, m->n_qkv / 16, d_tiles, false, ws);
+  ws.gemm[GEMM_O] = plan_gemm(PLAIN, d_blocks, m->d_attn / 32, split_residual(ws), ws);
+  ws.gemm[GEMM_GATE_UP] = plan_gemm(PLAIN, m->gu_blocks, d_tiles, false, ws);
+  ws.gemm[GEMM_DOWN] = plan_gemm(PLAIN, d_blocks, m->ffn_k / 32, split_residual(ws), ws);
+  ws.gemm[GEMM_LM_HEAD] = plan_gemm(LM_HEAD, m->cfg.vocab / 16, d_tiles, false, ws);
+}
 
 void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, int window, const Workspace& ws,
                      hipStream_t st) {
@@ -434,21 +453,19 @@ void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, 
   e.group = m->group;
   e.window = window;
   e.r_pad = ws.r_pad;
-  launch_gemm<kSplit[GEMM_QKV]>(m->layers[layer].wqkv, ws.normed, m->n_qkv / 16, c.d_model, m->n_qkv, ws, e, st);
+  launch_gemm<kSplit[GEMM_QKV]>(m->layers[layer].wqkv, ws.normed, m->n_qkv / 16, c.d_model, m->n_qkv, ws, ws.gemm[GEMM_QKV], e, st);
 }
 
-bool launch_gemm_residual(const uint16_t* w, const uint16_t* x, float* resid, int n, int k_padded,
+bool launch_gemm_residual(GemmKind kind, const uint16_t* w, const uint16_t* x, float* resid, int n, int k_padded,
                           const Workspace& ws, hipStream_t st) {
   ResidualEpi e{resid, ws.rl, n};
-  // Off the fixed schedule (fast path, cost-of-determinism measurement) the split follows the batch,
-  // as in an ordinary engine: two halves while there are few rows to spread over the device, none beyond.
-  if (ws.batch_chosen && ws.m_rows > 16) return launch_gemm<1>(w, x, n / 16, k_padded, n, ws, e, st);
-  return launch_gemm<kSplit[GEMM_RESIDUAL]>(w, x, n / 16, k_padded, n, ws, e, st);
+  if (!split_residual(ws)) return launch_gemm<1>(w, x, n / 16, k_padded, n, ws, ws.gemm[kind], e, st);
+  return launch_gemm<kSplit[GEMM_O]>(w, x, n / 16, k_padded, n, ws, ws.gemm[kind], e, st);
 }
 
 void launch_gemm_swiglu(const llm42_model* m, int layer, const Workspace& ws, hipStream_t st) {
   SwigluEpi e{ws.hidden, m->ffn_k};
-  launch_gemm<kSplit[GEMM_GATE_UP]>(m->layers[layer].wgu, ws.normed, m->gu_blocks, m->cfg.d_model, m->gu_blocks * 16, ws, e, st);
+  launch_gemm<kSplit[GEMM_GATE_UP]>(m->layers[layer].wgu, ws.normed, m->gu_blocks, m->cfg.d_model, m->gu_blocks * 16, ws, ws.gemm[GEMM_GATE_UP], e, st);
 }
 
 // Returns the number of arg-max partials per row.
@@ -472,7 +489,7 @@ static int launch_logits(const llm42_model* m, int window, float* out_logits, co
     e.parts = n_blocks;
     launch_wide(wp, xp, n_blocks, k_tiles, ws, e, st);
   } else {
-    const int tile = pick_tile(Work{LM_HEAD, n_blocks, k_tiles, 1, ws.num_cus, ws.partly_filled}, ws.m_pad).tile;
+    const int tile = ws.gemm[GEMM_LM_HEAD].tile;
     e.parts = (n_blocks + kTiles[tile].bn() - 1) / kTiles[tile].bn();
     launch_direct(tile, wp, xp, n_blocks, Range{k_tiles, k_tiles, 0, 1, ws.m_pad, -1}, ws, e, st);
   }

@@ -100,6 +100,14 @@ __host__ __device__ inline int tag_base(int tag) { return tag >> 10; }
 // Packed rows end where those of the last sequence do (its tag, Workspace::live, says where).
 __device__ inline int live_rows(const int32_t* live) { return tag_base(*live) + tag_rows(*live); }
 
+// How a pass of more than 64 rows runs one of its GEMMs (see plan_gemms): tile, the number of rows that have a launch of their
+// own beside it (0: none) and the tile of that one, and whether the halves of a split one follow each other.
+struct GemmPlan {
+  int tile, fewer, fewer_tile;
+  bool in_turn;
+};
+enum GemmKind { GEMM_QKV, GEMM_O, GEMM_GATE_UP, GEMM_DOWN, GEMM_LM_HEAD, GEMM_KINDS };
+
 // Workspace carving, identical in llm42_workspace_bytes and llm42_verify_window.
 struct Workspace {
   int num_cus;    // compute units of the device
@@ -121,6 +129,7 @@ struct Workspace {
   int32_t *seq_len, *seq_n;          // cached length (-1: takes no part), seq_tag(n, base)
   int32_t *dump_slot;
   const int32_t* live;               // the last sequence's entry of seq_n
+  GemmPlan gemm[GEMM_KINDS];
   bool partly_filled;                // packed rows of a verifier pass (a prefill pass's are packed too, but mostly all there)
   int32_t* row_blk;    // physical KV block that holds the row's position (0 for dead rows)
   float2* row_rope;    // [m_pad][head_dim/2] (cos, sin) at the row's position
@@ -162,10 +171,13 @@ inline bool norm_adds_halves(int m_pad, int d) { return m_pad <= 512 || d == 102
 // pending: the last residual GEMM left its halves in split_part (what launch_gemm_residual returned)
 void launch_rmsnorm(bool pending, const uint16_t* gain, int d, float eps, const Workspace& ws, hipStream_t st);
 
+// Fills ws.gemm: the same for every layer, so chosen once per pass (the rule takes 0.3 us a GEMM, and with partly filled windows
+// 1 - 13 us at 1024 - 16384 rows; a layer's ten launches take about 40).
+void plan_gemms(const llm42_model* m, Workspace& ws);
 void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, int window, const Workspace& ws,
                      hipStream_t st);
 // true: the residual stream is not complete yet; the halves are in split_part, for the RMSNorm that follows
-bool launch_gemm_residual(const uint16_t* w, const uint16_t* x, float* resid, int n, int k_padded,
+bool launch_gemm_residual(GemmKind kind, const uint16_t* w, const uint16_t* x, float* resid, int n, int k_padded,
                           const Workspace& ws, hipStream_t st);
 void launch_gemm_swiglu(const llm42_model* m, int layer, const Workspace& ws, hipStream_t st);
 // Returns the number of arg-max partials per row that it leaves in amax.

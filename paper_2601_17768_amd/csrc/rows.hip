@@ -199,24 +199,29 @@ __device__ inline void emit_normed(uint4* yr, int f, const f32x4 a, const f32x4 
 }
 
 // The pending halves of a split GEMM added to U tiles (t0, t0 + 16, ...) of a row's residual stream, which go back to
-// memory: old + (p0 + p1), as everywhere.
-template <int U>
+// memory: old + (p0 + p1), as everywhere.  G tiles at a time: both halves of all 16 tiles of d 8192 do not fit the registers.
+template <int U, int G = (U > 8 ? 4 : U)>
 __device__ __forceinline__ void add_pending(float* __restrict__ xr, const float* __restrict__ p0, const float* __restrict__ p1,
                                             int fs, int t0, int g, f32x4 (&a)[U], f32x4 (&b)[U]) {
-  f32x4 q0[U], q1[U];
+  static_assert(U % G == 0, "whole groups of tiles");
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int o = ((t0 + u * 16) * 8 + g * 2) * fs;
-    q0[u] = *(const f32x4*)(p0 + o) + *(const f32x4*)(p1 + o);
-    q1[u] = *(const f32x4*)(p0 + o + fs) + *(const f32x4*)(p1 + o + fs);
-  }
+  for (int v = 0; v < U; v += G) {
+    f32x4 q0[G], q1[G];
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int o = ((t0 + u * 16) * 8 + g * 2) * fs;
-    a[u] = a[u] + q0[u];
-    b[u] = b[u] + q1[u];
-    *(f32x4*)(xr + o) = a[u];
-    *(f32x4*)(xr + o + fs) = b[u];
+    for (int u = 0; u < G; ++u) {
+      const int o = ((t0 + (v + u) * 16) * 8 + g * 2) * fs;
+      q0[u] = *(const f32x4*)(p0 + o) + *(const f32x4*)(p1 + o);
+      q1[u] = *(const f32x4*)(p0 + o + fs) + *(const f32x4*)(p1 + o + fs);
+    }
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const int o = ((t0 + (v + u) * 16) * 8 + g * 2) * fs;
+      a[v + u] = a[v + u] + q0[u];
+      b[v + u] = b[v + u] + q1[u];
+      *(f32x4*)(xr + o) = a[v + u];
+      *(f32x4*)(xr + o + fs) = b[v + u];
+    }
+    if (v + G < U) __builtin_amdgcn_sched_barrier(0);
   }
 }
 
@@ -332,6 +337,7 @@ __global__ __launch_bounds__(64 * R) void rmsnorm_block_kernel(float* __restrict
                                                                const int32_t* __restrict__ live) {
   if (live && (int)blockIdx.x * R >= live_rows(live)) return;      // packed rows: only what pads (workgroup-uniform)
   constexpr int D = 512 * U;                             // U tiles of 32 features per thread: t = u * 16 + w
+  constexpr bool kLateGain = PEND && U > 8;              // (the gains of d 8192 have no registers before the halves are added)
   __shared__ float part[64][R];
   __shared__ float inv_s[R];
   const int r = threadIdx.x % R, wg = threadIdx.x / R, w = wg >> 2, g = wg & 3;
@@ -347,9 +353,14 @@ __global__ __launch_bounds__(64 * R) void rmsnorm_block_kernel(float* __restrict
     const int f = (u * 16 + w) * 32 + g * 8;
     a[u] = *(const f32x4*)(xr + (f >> 2) * fs);
     b[u] = *(const f32x4*)(xr + (f >> 2) * fs + fs);
-    gv[u] = *(const uint4*)(gain + f);
+    if (!kLateGain) gv[u] = *(const uint4*)(gain + f);
   }
   if (PEND) add_pending<U>(xr, p0 + ro, p1 + ro, fs, w, g, a, b);
+  if (kLateGain) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) gv[u] = *(const uint4*)(gain + (u * 16 + w) * 32 + g * 8);
+  }
   float ss = 0.f;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -426,7 +437,8 @@ static void launch_norm(float* x, const float* p0, const float* p1, ResidLayout 
   // the length of the runs that they read and write.
   // The widths 1024, 2048 and 8192 follow beyond 512 rows, where a wave per row reads pieces of 16 bytes (norms of one layer and
   // the final one, halves of two projections left to two of the three, wave per row with the halves added before -> this with
-  // them: 2048 rows d 2048 44.6 + 2 adding launches -> 38.3, d 8192 197.7 + 2 -> 148.9, d 1024 27.4 + 2 -> 26.8).
+  // them: 2048 rows d 2048 44.6 + 2 adding launches -> 38.3, d 8192 197.7 + 2 -> 148.9, d 1024 27.4 + 2 -> 26.8; d 8192 with the
+  // halves added in groups that leave no register spilled, two layers of 528 rows 119 -> 107, of 768 128 -> 120).
   const bool rows8 = m_pad > 512;
   auto block8 = [&](auto u) { rmsnorm_block_kernel<8, decltype(u)::value, PEND><<<m_pad / 8, 512, 0, st>>>(x, p0, p1, rl, gain, y, eps, live); };
   if (rows8 && d == 1024) block8(std::integral_constant<int, 2>{});

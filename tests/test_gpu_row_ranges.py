@@ -118,6 +118,24 @@ def test_same_bits_with_few_feature_blocks(d_model, n_kv_heads):
     sess.close()
 
 
+@pytest.mark.parametrize("n_seq", [33, 48, 96])
+@pytest.mark.parametrize("d_model", [1024, 2048, 8192])
+def test_same_bits_with_norms_of_eight_rows_per_workgroup(d_model, n_seq):
+    """Beyond 512 rows the norms of these widths are a kernel of their own that also adds the halves of the split projections
+    (by the tile rule both projections leave theirs to it at 528 and 768 rows, and up to d_model 2048 at 1536)."""
+    shape = wl.LLAMA_8B.replace(n_layers=1, d_model=d_model, n_q_heads=8, n_kv_heads=2, d_ffn=1024, vocab=1024)
+    sess = VerifierSession(shape, wl.make_weights(shape, seed=53), max_position=128, device=DEV)
+    want = _run(shape, sess, 1, 0)
+    assert torch.isfinite(want[1]).all()
+    n_valid = wl.rng_for(53, n_seq).integers(1, WINDOW + 1, size=n_seq)
+    n_valid[n_seq - 1] = WINDOW
+    for counts in (None, n_valid):
+        out, logits, k, v = _run(shape, sess, n_seq, n_seq - 1, counts)
+        assert torch.equal(out[n_seq - 1], want[0][0]) and torch.equal(logits, want[1])
+        assert torch.equal(k, want[2]) and torch.equal(v, want[3])
+    sess.close()
+
+
 @pytest.fixture(scope="module")
 def ragged():
     """28, 449 and 14 k-tiles (halves of 225 and 224, of 7 and 7), feature blocks that no tile divides: partial rounds and partial

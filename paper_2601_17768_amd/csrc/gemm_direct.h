@@ -153,8 +153,12 @@ __global__ __launch_bounds__(64 * (NW + F), (WGS * (NW + F) + 3) / 4) void gemm_
   if constexpr (NSET > 3) {
     if (r + 3 < rounds) round(Set3{}, std::false_type{}, r + 3);
   }
-  // epilogue, EG token blocks at a time: what they need from memory is requested together
-  constexpr int EG = TB % 4 == 0 && FB <= 2 ? 4 : 2;
+  // epilogue, EG token blocks at a time: what they need from memory is requested together.  kTight: beside 192 accumulators the 8
+  // operands for each of four feature blocks have registers for one at a time, and offsets are not worked out ahead of the loop.
+  constexpr bool kTight = FB * TB >= 48 && std::is_same<Epi, ResidualAddEpi>::value;
+  constexpr int EG = kTight ? 1 : TB % 4 == 0 && FB <= 2 ? 4 : 2;
+  int el = lane;
+  if constexpr (kTight) asm volatile("" : "+v"(el));
   static_assert(TB % EG == 0, "whole groups of token blocks");
   constexpr bool kLogits = is_logits<Epi>::value;
   float2* best = (float2*)ring;                      // LM head: [NW][16 TB] best of a wave's features
@@ -165,10 +169,10 @@ __global__ __launch_bounds__(64 * (NW + F), (WGS * (NW + F) + 3) / 4) void gemm_
     typename Epi::Pre pre[EG][FB];
 #pragma unroll
     for (int j = 0; j < EG; ++j) {
-      const int row = (m0 + j0 + j) * 16 + (lane & 15);
+      const int row = (m0 + j0 + j) * 16 + (el & 15);
       info[j] = epi.row_info(row);
 #pragma unroll
-      for (int i = 0; i < FB; ++i) pre[j][i] = epi.pre(min(n0 + wave * FB + i, n_blocks - 1), lane, row, info[j]);
+      for (int i = 0; i < FB; ++i) pre[j][i] = epi.pre(min(n0 + wave * FB + i, n_blocks - 1), el, row, info[j]);
     }
 #pragma unroll
     for (int j = 0; j < EG; ++j) {
@@ -177,15 +181,15 @@ __global__ __launch_bounds__(64 * (NW + F), (WGS * (NW + F) + 3) / 4) void gemm_
 #pragma unroll
         for (int i = 0; i < FB; ++i) {
           const int nb = n0 + wave * FB + i;
-          if (nb < n_blocks) epi.rank(nb, lane, acc[i][j0 + j], info[j], b);
+          if (nb < n_blocks) epi.rank(nb, el, acc[i][j0 + j], info[j], b);
         }
         b = Epi::over_lanes(b);
-        if (lane < 16) best[wave * 16 * TB + (j0 + j) * 16 + lane] = make_float2(b.v, __int_as_float(b.i));
+        if (el < 16) best[wave * 16 * TB + (j0 + j) * 16 + el] = make_float2(b.v, __int_as_float(b.i));
       } else {
 #pragma unroll
         for (int i = 0; i < FB; ++i) {
           const int nb = n0 + wave * FB + i;
-          if (nb < n_blocks) epi(nb, lane, (m0 + j0 + j) * 16 + (lane & 15), acc[i][j0 + j], pre[j][i]);
+          if (nb < n_blocks) epi(nb, el, (m0 + j0 + j) * 16 + (el & 15), acc[i][j0 + j], pre[j][i]);
         }
       }
     }

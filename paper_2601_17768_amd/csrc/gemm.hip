@@ -379,7 +379,10 @@ GemmPlan plan_gemm(Kind kind, int n_blocks, int k_tiles, bool split, const Works
   // 260 | 263, 2048 324 | 309, 4096 623 | 606; d_model 8192, 1024 rows 594 | 554, 4096 2246 | 2074; d_model 2048, 4096 rows
   // 174 | 162.  From 2048 rows on up to a third more is taken for it: the norms are a quarter of the layer there (d_model 2048,
   // 2048 rows: norms 38 | 26, but 95 | 106 in all; 127 before this kernel).
-  const bool in_turn = split && alone.cost * 2 * 100 <= together.cost * (m_pad < 2048 ? 103 : 135);
+  // (The tile of short rounds has less than a launch's own time in its price: with it counted so here, d_model 512 at 2048 rows takes
+  // 237 us a pass of two layers, in turn 244.)
+  const long long apart = 2 * (alone.cost + (alone.tile == kShortRounds ? 1300 : 0));
+  const bool in_turn = split && apart * 100 <= together.cost * (m_pad < 2048 ? 103 : 135);
   const Work& work = split && !in_turn ? both : one;
   const Choice all = split && !in_turn ? together : alone;
   const int fewer = ws.partly_filled && m_pad >= 768 && kind != LM_HEAD ? rows_apart(work, m_pad, all) : 0;

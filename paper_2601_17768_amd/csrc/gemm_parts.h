@@ -312,7 +312,11 @@ __device__ __forceinline__ void wait_for_rounds(int ahead) {
 // for half of the rows: every workgroup has all token blocks, fetches those that hold rows, and reads weights that no other
 // does, where 4 x 4 blocks leave half of the CUs without rows (8B, us per pass with a quarter, half, three quarters and all of
 // 120 rows there: 4442, 4667, 4607, 4643 -> 4034, 4433, 4692, 4735).
-// The other two are for small K: the 4 x 4 blocks again in shorter rounds, and 8 x 8 blocks
+// The other two are for small K.  One is the 4 x 4 blocks again in rounds of four k-tiles, two register sets: the others' rounds
+// left over behind the last whole group of them take about 1 us more, in code of their own, and 900 ns where they have 3000 puts it
+// ahead up to about 40 k-tiles (us for two launches, the tile at 2200 ns -> this: 128 rows of d_model 1024 O 16.6 -> 12.9 and gate/up
+// 19.3 -> 16.6, at 512 rows down 25.8 -> 21.8; 128 rows of d_model 512 gate/up 17.0 -> 13.2; of 24 launches that it now takes at
+// d_model 512 - 4096 none is slower but QKV of 24 k-tiles at 128 - 192 rows, 16.5 - 17.0 -> 17.0 - 17.6).  The other is 8 x 8 blocks
 // two to a CU, where neither's beginning nor end leaves it idle, for the LM head (32 k-tiles x 50304 features: 512 rows
 // 58 us against 61 - 85 with the others, 4096 396 against 436; the heavier epilogue of gate/up gains nothing from it).
 struct Tile {
@@ -365,7 +369,7 @@ inline long long tile_cost(int t, const Work& w, int rows) {
   const long long whole = (tiles + slots - 1) / slots * 64, share = tiles * 64 / slots + 16;   // rounds, in 1/64
   if (t == kPartly && !(w.partly && w.planes == 2)) return -1;
   if (q.per_cu == 2 && (w.kind != LM_HEAD || tiles <= 2 * slots)) return -1;
-  long long round = (long long)q.cost * w.k_tiles + (q.per_cu == 2 ? 500 : (t == kShortRounds ? 2200 : 3000) + 24 * q.bn() * q.bm);
+  long long round = (long long)q.cost * w.k_tiles + (q.per_cu == 2 ? 500 : (t == kShortRounds ? 900 : 3000) + 24 * q.bn() * q.bm);
   if (w.kind != PLAIN && q.bm == 16 && q.bn() <= (w.kind == QKV ? 12 : 8)) round += round / 20;
   return (whole <= 4 * 64 || whole < share ? whole : share) * round / 64;
 }

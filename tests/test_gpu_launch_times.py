@@ -105,6 +105,18 @@ def test_few_tiles_are_made_smaller_at_any_row_count():
     sess.close()
 
 
+def test_projections_of_few_k_tiles_by_the_tile_of_short_rounds():
+    """O-projection, 128 rows: halves of 16 k-tiles at d_model 1024 cost what halves of 12 do at 768 (1.23 times as much while the
+    tile whose rounds do not divide 16 k-tiles was taken)."""
+    t = {}
+    for d in (768, 1024):
+        shape, sess = _session(64, d_model=d, n_q_heads=d // 64, n_kv_heads=d // 64, head_dim=64, d_ffn=1024, vocab=1024)
+        t[d] = _times(shape, sess, 8, 16, 16)["o_proj"]
+        sess.close()
+    print(f"O-projection at 128 rows: d_model 768 {t[768]:.1f} us, 1024 {t[1024]:.1f} us")
+    assert t[1024] <= 1.1 * t[768]
+
+
 def test_unsplit_residual_projections_of_many_features():
     """512 blocks of 16 output features, 32 rows: the fast path's unsplit projections cost what the split ones do (1.2 times as
     much with a workgroup per block)."""

@@ -385,7 +385,7 @@ GemmPlan plan_gemm(Kind kind, int n_blocks, int k_tiles, bool split, const Works
   const bool in_turn = split && apart * 100 <= together.cost * (m_pad < 2048 ? 103 : 135);
   const Work& work = split && !in_turn ? both : one;
   const Choice all = split && !in_turn ? together : alone;
-  const int fewer = ws.partly_filled && m_pad >= 768 && kind != LM_HEAD ? rows_apart(work, m_pad, all) : 0;
+  const int fewer = ws.partly_filled && m_pad >= 768 ? rows_apart(work, m_pad, all) : 0;
   return GemmPlan{all.tile, fewer, fewer ? pick_tile(work, fewer).tile : 0, in_turn};
 }
 
@@ -435,7 +435,8 @@ void plan_gemms(const llm42_model* m, Workspace& ws) {
   ws.gemm[GEMM_O] = plan_gemm(PLAIN, d_blocks, m->d_attn / 32, split_residual(ws), ws);
   ws.gemm[GEMM_GATE_UP] = plan_gemm(PLAIN, m->gu_blocks, d_tiles, false, ws);
   ws.gemm[GEMM_DOWN] = plan_gemm(PLAIN, d_blocks, m->ffn_k / 32, split_residual(ws), ws);
-  ws.gemm[GEMM_LM_HEAD] = plan_gemm(LM_HEAD, m->cfg.vocab / 16, d_tiles, false, ws);
+  const Work head{LM_HEAD, m->cfg.vocab / 16, d_tiles, 1, ws.num_cus, ws.partly_filled};
+  ws.gemm[GEMM_LM_HEAD] = GemmPlan{ws.partly_filled ? pick_partly_filled(head, ws.m_pad) : pick_tile(head, ws.m_pad).tile, 0, 0, false};
 }
 
 void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, int window, const Workspace& ws,

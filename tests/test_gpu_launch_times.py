@@ -20,7 +20,7 @@ def _session(max_position, **dims):
     return shape, VerifierSession(shape, wl.make_weights(shape, seed=57), max_position=max_position, device=DEV)
 
 
-def _times(shape, sess, n_seq, window, context, max_context=None, decode=False):
+def _times(shape, sess, n_seq, window, context, max_context=None, decode=False, n_valid=None):
     """Microseconds per pass of every launch class (median of 9 passes, behind 3 that are not counted)."""
     rng = wl.rng_for(57, n_seq, window)
     table, blocks = wl.make_block_table(rng, np.full(n_seq, context + window), 16, max_blocks_per_seq=(max(max_context or 0, context + window) + 15) // 16)
@@ -32,12 +32,13 @@ def _times(shape, sess, n_seq, window, context, max_context=None, decode=False):
     out = torch.empty((n_seq, window), dtype=torch.int32, device=DEV)
     max_context = max_context or context + window
     ws = sess.workspace(n_seq, window, max_context)
+    counts = None if n_valid is None else torch.as_tensor(np.asarray(n_valid, dtype=np.int32), device=DEV)
 
     def one():
         if decode:
             B.llm42_decode_step(sess.model, kv, blocks, bt, lens, cand.view(-1), max_context, out.view(-1), ws)
         else:
-            B.llm42_verify_window(sess.model, kv, blocks, bt, lens, cand, window, None, max_context, out, ws)
+            B.llm42_verify_window(sess.model, kv, blocks, bt, lens, cand, window, counts, max_context, out, ws)
     for _ in range(3):
         one()
     torch.cuda.synchronize()
@@ -115,6 +116,15 @@ def test_projections_of_few_k_tiles_by_the_tile_of_short_rounds():
         sess.close()
     print(f"O-projection at 128 rows: d_model 768 {t[768]:.1f} us, 1024 {t[1024]:.1f} us")
     assert t[1024] <= 1.1 * t[768]
+
+
+def test_lm_head_of_half_filled_windows():
+    """768 rows, every other token there: less than with all of them (as much as that while the tile was the best one for all)."""
+    shape, sess = _session(64, d_model=2048, d_ffn=2048, vocab=32000)
+    full, half = (_times(shape, sess, 48, 16, 16, n_valid=[n] * 48)["lm_head"] for n in (16, 8))
+    print(f"LM head at 768 rows: all there {full:.1f} us, half {half:.1f} us")
+    assert half <= 0.85 * full
+    sess.close()
 
 
 def test_unsplit_residual_projections_of_many_features():

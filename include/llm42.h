@@ -209,7 +209,7 @@ llm42_status llm42_commit_rollback(
  * temperature == 0 (or a NULL llm42_sampling) is the greedy sampler.  out_logits, if asked for,
  * always receives the unperturbed logits. */
 typedef struct {
-  float          temperature;         /* >= 0                                             */
+  float          temperature;         /* >= 0; infinity: the noise alone is ranked        */
   uint64_t       seed;
   const int64_t* request_ids;         /* dev [num_seqs]; NULL: the index in the call      */
 } llm42_sampling;

@@ -63,3 +63,15 @@ def test_unsplit_projections_by_value(d_model, d_ffn):
         # 8.4e-3, bounded at about four times that.  A stale or missing k-tile moves the logits by the order of their size.
         assert rel <= 3e-3 and worst <= 3e-2
     sess.close()
+
+
+@pytest.mark.parametrize("d_model", [768, 2048])
+def test_unsplit_projections_of_many_rows(d_model):
+    """One accumulator per element whatever the tile: the same bits from 32 to 4096 rows."""
+    shape = wl.LLAMA_8B.replace(n_layers=1, d_model=d_model, n_q_heads=16, n_kv_heads=8, d_ffn=2064, vocab=2048)
+    sess = VerifierSession(shape, wl.make_weights(shape, seed=62), max_position=128, device=DEV)
+    want = _logits(shape, sess, 2, 16, True)
+    assert torch.isfinite(want).all()
+    for n_seq in (5, 12, 16, 24, 32, 40, 48, 56, 64, 72, 80, 96, 128, 192, 256):
+        assert torch.equal(_logits(shape, sess, n_seq, 16, True), want), n_seq
+    sess.close()

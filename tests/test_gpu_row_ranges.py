@@ -65,10 +65,11 @@ def test_same_bits_at_every_row_count(env, alone, n_seq):
     assert torch.equal(logits, alone[1]) and torch.equal(k, alone[2]) and torch.equal(v, alone[3])
 
 
-@pytest.mark.parametrize("n_seq", [4, 9, 20, 41, 65, 97, 130, 200, 256, 300])
+@pytest.mark.parametrize("n_seq", [4, 5, 6, 7, 8, 9, 20, 41, 65, 97, 130, 200, 256, 300])
 def test_same_bits_among_partly_filled_windows(env, alone, n_seq):
     """Partly filled windows are packed: the target's rows begin wherever the counts before it end (odd offsets, across
-    tiles), sequences that fail a check have no rows or dead ones, and what lies behind the last row is skipped."""
+    tiles), sequences that fail a check have no rows or dead ones, and what lies behind the last row is skipped.  65 to 128 rows
+    (5 - 8 sequences) take the 32 x 128 tile of partly filled windows for the split projections."""
     rng = wl.rng_for(47, 5, n_seq)
     n_valid = rng.integers(1, WINDOW + 1, size=n_seq)
     slot = n_seq - 2
@@ -84,13 +85,17 @@ def test_same_bits_among_partly_filled_windows(env, alone, n_seq):
     assert bool(((out >= 0) == live).all())
 
 
-@pytest.mark.parametrize("total", [32, 384, 512, 513, 576, 577, 640, 641, 704, 705, 768, 769, 1024])
-@pytest.mark.parametrize("n_seq", [48, 64])
+_TOTALS = [32, 384, 512, 513, 576, 577, 640, 641, 704, 705, 768, 769, 1024]
+
+
+@pytest.mark.parametrize("n_seq,total", [(48, t) for t in _TOTALS if t <= 768] + [(64, t) for t in _TOTALS] +
+                         [(128, t) for t in (16, 1280, 1281, 2047, 2048)] + [(256, t) for t in (2304, 2305, 2560, 2561, 4096)])
 def test_same_bits_on_both_sides_of_the_launch_for_fewer_rows(env, alone, n_seq, total):
     """Partly filled windows of 768 rows and more: a launch for no more rows than a multiple of 128 between 9/16 and 3/4 of
-    all and one for more; exactly one of the two may run, whichever multiple it is."""
+    all and one for more; exactly one of the two may run, whichever multiple it is.  (At 2048 rows the rule has it at 1280 for all
+    four projections, at 4096 at 2304 for QKV and 2560 for O and down; the halves of those two follow each other there, so each
+    side is two launches, the second of which adds the first one's partial.)"""
     slot = n_seq // 2
-    total = min(total, n_seq * WINDOW)
     n_valid = np.full(n_seq, 0)
     n_valid[slot] = WINDOW
     rest, others = total - WINDOW, [s for s in range(n_seq) if s != slot]
@@ -154,6 +159,48 @@ def test_same_bits_with_partial_rounds_and_tiles(ragged, n_seq):
     out, logits, k, v = _run(shape, sess, n_seq, n_seq - 1)
     assert torch.equal(out[n_seq - 1], want[0][0]) and torch.equal(logits, want[1])
     assert torch.equal(k, want[2]) and torch.equal(v, want[3])
+
+
+@pytest.mark.parametrize("n_seq", [5, 8, 12, 16, 24, 32, 48, 64, 128])
+def test_same_bits_with_partial_rounds_and_tiles_among_partly_filled_windows(ragged, n_seq):
+    """Odd halves of the split projections by the 32 x 128 tile (5, 8, 16 - 32 sequences), and the LM head's tile of two
+    workgroups per CU (from 32 sequences on) with rows left out."""
+    shape, sess, want = ragged
+    n_valid = wl.rng_for(50, n_seq).integers(1, WINDOW + 1, size=n_seq)
+    n_valid[n_seq - 1] = WINDOW
+    out, logits, k, v = _run(shape, sess, n_seq, n_seq - 1, n_valid)
+    assert torch.equal(out[n_seq - 1], want[0][0]) and torch.equal(logits, want[1])
+    assert torch.equal(k, want[2]) and torch.equal(v, want[3])
+
+
+# Chosen by the tile rule: with the models above and the unsplit projections of test_gpu_batch_chosen.py, 122 of the 137 kernels of
+# more than 64 rows (tile x epilogue, the sampled LM head aside) run in some test.
+@pytest.mark.parametrize("d_model,heads,kv_heads,d_ffn,vocab,calls", [
+    (256, 16, 8, 1024, 4096, [(24, False)]),
+    (256, 16, 2, 1024, 4096, [(80, False)]),
+    (256, 16, 8, 2048, 4096, [(80, False)]),
+    (256, 4, 2, 8192, 4096, [(5, False)]),
+    (256, 32, 4, 1024, 4096, [(80, False)]),
+    (768, 32, 4, 1024, 4096, [(192, True)]),
+    (768, 16, 8, 1024, 16384, [(48, False), (72, False)]),
+    (1024, 4, 2, 8192, 4096, [(192, False)]),
+    (1536, 4, 2, 1024, 50304, [(5, False), (40, False)]),
+    (1536, 4, 2, 8192, 4096, [(192, True)]),
+    (3072, 4, 2, 1024, 4096, [(24, False), (32, False), (128, False), (320, False)]),
+    (3072, 32, 4, 1024, 4096, [(112, True), (256, True)]),
+])
+def test_same_bits_by_the_other_tiles(d_model, heads, kv_heads, d_ffn, vocab, calls):
+    shape = wl.LLAMA_8B.replace(n_layers=1, d_model=d_model, n_q_heads=heads, n_kv_heads=kv_heads, d_ffn=d_ffn, vocab=vocab)
+    sess = VerifierSession(shape, wl.make_weights(shape, seed=54), max_position=128, device=DEV)
+    want = _run(shape, sess, 1, 0)
+    assert torch.isfinite(want[1]).all()
+    for n_seq, partly in calls:
+        n_valid = wl.rng_for(54, n_seq).integers(1, WINDOW + 1, size=n_seq)
+        n_valid[n_seq - 1] = WINDOW
+        out, logits, k, v = _run(shape, sess, n_seq, n_seq - 1, n_valid if partly else None)
+        assert torch.equal(out[n_seq - 1], want[0][0]) and torch.equal(logits, want[1])
+        assert torch.equal(k, want[2]) and torch.equal(v, want[3])
+    sess.close()
 
 
 @pytest.mark.timeout(300)

@@ -121,3 +121,19 @@ def test_loop_with_sampling_reproduces_the_verifier_only_stream(tiny):
     assert torch.equal(toks[0], ref)
     greedy_ref = dvr.generate_verifier_only(sess, *state(prompts[:1]), new)[0]
     assert not torch.equal(ref, greedy_ref)
+
+
+def test_infinite_temperature_ranks_the_noise_alone(tiny, scenario):
+    """logit / infinity is 0: what the definition of the sampler and the checker say (the greedy sampler is temperature 0)."""
+    shape, w, sess = tiny
+    sc = scenario
+    kv, bt, lens, cand = _gpu_state(sess, sc)
+    out, _, _ = sess.verify(kv, bt, lens, cand, sampling=B.make_sampling(float("inf"), 77, None))
+    decided = 0
+    for s in range(4):
+        for i in range(sc.window):
+            noise = torch.from_numpy(orc.gumbel_noise(77, s, int(sc.lens[s]) + i, shape.vocab))[None]
+            if float(orc.top2_margin(noise)) > 1e-4:              # (noise up to 17, in fp32: errors of some 1e-6)
+                assert int(out[s, i]) == int(noise.argmax()), (s, i)
+                decided += 1
+    assert decided >= 28

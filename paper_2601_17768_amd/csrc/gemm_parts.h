@@ -315,8 +315,8 @@ __device__ __forceinline__ void wait_for_rounds(int ahead) {
 // The other two are for small K.  One is the 4 x 4 blocks again in rounds of four k-tiles, two register sets: the others' rounds
 // left over behind the last whole group of them take about 1 us more, in code of their own, and 900 ns where they have 3000 puts it
 // ahead up to about 40 k-tiles (us for two launches, the tile at 2200 ns -> this: 128 rows of d_model 1024 O 16.6 -> 12.9 and gate/up
-// 19.3 -> 16.6, at 512 rows down 25.8 -> 21.8; 128 rows of d_model 512 gate/up 17.0 -> 13.2; of 24 launches that it now takes at
-// d_model 512 - 4096 none is slower but QKV of 24 k-tiles at 128 - 192 rows, 16.5 - 17.0 -> 17.0 - 17.6).  The other is 8 x 8 blocks
+// 19.3 -> 16.6, at 512 rows down 25.8 -> 21.8; 128 rows of d_model 512 gate/up 17.0 -> 13.2; of the 34 launches that it now
+// takes at d_model 512 - 4096 29 are faster, and QKV of 24 k-tiles at 128 - 192 rows is not, 16.5 - 17.0 -> 17.0 - 17.6).  The other is 8 x 8 blocks
 // two to a CU, where neither's beginning nor end leaves it idle, for the LM head (32 k-tiles x 50304 features: 512 rows
 // 58 us against 61 - 85 with the others, 4096 396 against 436; the heavier epilogue of gate/up gains nothing from it).
 struct Tile {
@@ -350,8 +350,12 @@ struct Choice {
 };
 // The cheapest tile for n_blocks x m_pad rows by k_tiles, `planes` times over.  A launch of more than four rounds does not run
 // them in step: it ends about a quarter of a round behind its share of the CUs' time (14 x 16 blocks, LM head of 768 rows: 6.7
-// rounds take the time of 7; of 1024 rows and 32000 features, 2.2 rounds, that of 3), no later than whole rounds would.  The
-// epilogues of QKV and LM head do much per row, and with 16 token blocks to a wave and few features that counts (QKV at 1024
+// rounds take the time of 7; of 1024 rows and 32000 features, 2.2 rounds, that of 3), no later than whole rounds would.  Two
+// workgroups to a CU are never in step (LM head of 50304 features x 1024 and x 768, 3.1 rounds at 512 rows that were priced as 4: 59
+// and 51 us by 14 x 16 blocks, 57 and 47 by 8 x 8; with half of the rows there 61 and 52 against 46 and 38).  With up to two rounds of
+// them the other tiles are the better ones where all rows are there (32000 x 2048, 384 and 512 rows 58 and 65 us against 59 and 74),
+// not where half are (50304 x 1024, 256 rows 33 against 25, with all of them 34 and 38).
+// The epilogues of QKV and LM head do much per row, and with 16 token blocks to a wave and few features that counts (QKV at 1024
 // rows: 16 x 8 blocks 63.6 us, 8 x 16 67.0; LM head of 32000 features at 512 rows 114 and 119).  So it does for QKV with 12 x 16
 // blocks in more than one round (against 16 x 8, us: 8B 3328 rows 184 and 174, 4096 195 and 184, 5888 295 and 293, 8192 395 and 368;
 // d_model 2048, 3072 features, 6656 rows 118 and 107, 8192 120 and 114; d_model 8192, 12288 features, 3072 rows 533 and 538).
@@ -369,10 +373,10 @@ inline long long tile_cost(int t, const Work& w, int rows, int of = 0) {
   const long long whole = (tiles + slots - 1) / slots * 64, share = tiles * 64 / slots + 16;   // rounds, in 1/64
   if (t == kPartly && !(w.partly && w.planes == 2)) return -1;
   const long long launched = of ? tiles_n * (of / (16 * q.bm)) : tiles;
-  if (q.per_cu == 2 && (w.kind != LM_HEAD || launched <= 2 * slots)) return -1;
+  if (q.per_cu == 2 && (w.kind != LM_HEAD || launched <= (w.partly ? 1 : 2) * slots)) return -1;
   long long round = (long long)q.cost * w.k_tiles + (q.per_cu == 2 ? 500 : (t == kShortRounds ? 900 : 3000) + 24 * q.bn() * q.bm);
   if (w.kind != PLAIN && q.bm == 16 && q.bn() <= (w.kind == QKV ? 12 : 8)) round += round / 20;
-  return (whole <= 4 * 64 || whole < share ? whole : share) * round / 64;
+  return ((whole <= 4 * 64 && q.per_cu == 1) || whole < share ? whole : share) * round / 64;
 }
 inline Choice pick_tile(const Work& w, int m_pad) {
   Choice best{-1, 0};

@@ -118,11 +118,13 @@ def test_projections_of_few_k_tiles_by_the_tile_of_short_rounds():
     assert t[1024] <= 1.1 * t[768]
 
 
-def test_lm_head_of_half_filled_windows():
-    """768 rows, every other token there: less than with all of them (as much as that while the tile was the best one for all)."""
-    shape, sess = _session(64, d_model=2048, d_ffn=2048, vocab=32000)
-    full, half = (_times(shape, sess, 48, 16, 16, n_valid=[n] * 48)["lm_head"] for n in (16, 8))
-    print(f"LM head at 768 rows: all there {full:.1f} us, half {half:.1f} us")
+@pytest.mark.parametrize("d_model,vocab,n_seq", [(2048, 32000, 48), (1024, 50304, 16)])
+def test_lm_head_of_half_filled_windows(d_model, vocab, n_seq):
+    """768 and 256 rows, every other token there: less than with all of them (as much as that while the tile was the best one
+    for all)."""
+    shape, sess = _session(64, d_model=d_model, d_ffn=2048, vocab=vocab)
+    full, half = (_times(shape, sess, n_seq, 16, 16, n_valid=[n] * n_seq)["lm_head"] for n in (16, 8))
+    print(f"LM head at {16 * n_seq} rows: all there {full:.1f} us, half {half:.1f} us")
     assert half <= 0.85 * full
     sess.close()
 

@@ -31,10 +31,12 @@ namespace gemm {
 //   1536     94.9 -> 78.7   62.2 -> 53.4   180.0 -> 152.3   302.9 -> 262.7    1505 -> 1385
 //   2048    101.6 -> 100.6                                  366.6 -> 354.8    2102 -> 1796
 //   3072    182.0 -> 152.5                                  552.9 -> 530      3145 -> 2747
-//   4096    194.3 -> 184.0 157.1 -> 151.5  411.5 -> 394.6   717.5 -> 703-718  4379 -> 3687
-// (gate/up at 4096 rows 1.34 - 1.37 PFLOP/s, where the vendor library's GEMM of the shape runs at 1.32 with such operands.)
-// Other widths, a two-layer pass of 948 calls (d_model 256 - 8192, 1 - 4096 rows): up to 1.5 times as fast, the worst
-// 1.07 times as slow; gate/up of 32 k-tiles x 8192 features is the launch that lost, 63 -> 71 us at 4096 rows.
+//   4096    194.3 -> 184.0 157.1 -> 151.5  411.5 -> 394.6   717.5 ->  720    4379 -> 3687
+// (gate/up at 4096 rows 1.32 - 1.34 PFLOP/s, 1 % below the vendor library's GEMM of the shape in the same runs.)
+// Other widths (d_model 512 - 8192, 80 - 6144 rows), passes of two layers against the kernels before this one: 189 calls with full
+// windows take 0.71 - 1.01 of their time, 0.88 on average, 532 with partly filled ones 0.71 - 1.05, 0.89 on average.  What takes
+// longer: a quarter of 1280 - 3072 rows there (up to 1.05: the halves that follow each other, in tiles for 9/16 of the rows, leave CUs
+// idle); and within calls that take less, gate/up of 32 k-tiles x 8192 features at 4096 rows (66 -> 76 us).
 template <int NW, int FB, int TB, int CH, int R, int F, int NSET, int WGS, bool NT, class Epi>
 __global__ __launch_bounds__(64 * (NW + F), (WGS * (NW + F) + 3) / 4) void gemm_direct_kernel(
     const bf16x8* __restrict__ w, const bf16x8* __restrict__ x, int n_blocks, int k_tiles, int split, int first_plane, int planes,

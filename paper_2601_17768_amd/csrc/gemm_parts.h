@@ -348,11 +348,14 @@ struct Choice {
   int tile;
   long long cost;   // ns
 };
-// The cheapest tile for n_blocks x m_pad rows by k_tiles, `planes` times over.  A launch of more than four rounds does not run
-// them in step: it ends about a quarter of a round behind its share of the CUs' time (14 x 16 blocks, LM head of 768 rows: 6.7
-// rounds take the time of 7; of 1024 rows and 32000 features, 2.2 rounds, that of 3), no later than whole rounds would.  Two
-// workgroups to a CU are never in step (LM head of 50304 features x 1024 and x 768, 3.1 rounds at 512 rows that were priced as 4: 59
-// and 51 us by 14 x 16 blocks, 57 and 47 by 8 x 8; with half of the rows there 61 and 52 against 46 and 38).  With up to two rounds of
+// The cheapest tile for n_blocks x m_pad rows by k_tiles, `planes` times over.  A launch takes whole rounds however many there are:
+// QKV of 12288 features x 4096 by 14 x 16 blocks 3.0 rounds 365 us, 3.4 368, 4.3 457, 5.2 557, 6.0 643, 6.9 661, gate/up of 8192
+// features x 4096 2.9 rounds 257, 3.5 329, 4.05 411, 4.6 414.  (Priced as their share and a quarter of a round beyond four rounds, the
+// tile with a few workgroups too many won: that QKV at 6144 rows 557 us, 510 by 6.9 rounds of 14 x 12 blocks; at 5120 rows 457 -> 411;
+// that gate/up at 7168 rows 411 -> 364; of 27 launches at d_model 768 - 8192 and 1152 - 8192 rows that take another tile now 25 are
+// 1 - 13 % faster, two 0.4 and 1.9 % slower.)
+// Two workgroups to a CU are never in step and take their share and a quarter (LM head of 50304 features x 1024 and x 768, 3.1 rounds
+// at 512 rows: 59 and 51 us by 14 x 16 blocks, 57 and 47 by 8 x 8; with half of the rows there 61 and 52 against 46 and 38).  With up to two rounds of
 // them the other tiles are the better ones where all rows are there (32000 x 2048, 384 and 512 rows 58 and 65 us against 59 and 74),
 // not where half are (50304 x 1024, 256 rows 33 against 25, with all of them 34 and 38).
 // The epilogues of QKV and LM head do much per row, and with 16 token blocks to a wave and few features that counts (QKV at 1024
@@ -376,7 +379,7 @@ inline long long tile_cost(int t, const Work& w, int rows, int of = 0) {
   if (q.per_cu == 2 && (w.kind != LM_HEAD || launched <= (w.partly ? 1 : 2) * slots)) return -1;
   long long round = (long long)q.cost * w.k_tiles + (q.per_cu == 2 ? 500 : (t == kShortRounds ? 900 : 3000) + 24 * q.bn() * q.bm);
   if (w.kind != PLAIN && q.bm == 16 && q.bn() <= (w.kind == QKV ? 12 : 8)) round += round / 20;
-  return ((whole <= 4 * 64 && q.per_cu == 1) || whole < share ? whole : share) * round / 64;
+  return (q.per_cu == 2 && share < whole ? share : whole) * round / 64;
 }
 inline Choice pick_tile(const Work& w, int m_pad) {
   Choice best{-1, 0};
@@ -388,11 +391,11 @@ inline Choice pick_tile(const Work& w, int m_pad) {
   return best;
 }
 // The LM head of partly filled windows has one launch, for the merge reads its partials by the tile.  The best tile for all of the
-// rows gives way to one that takes no more than 3 % longer there and a twentieth less on average over eight counts from 19/64 to 61/64
+// rows gives way to one that takes no more than 5 % longer there and a twentieth less on average over eight counts from 19/64 to 61/64
 // of them: its workgroups may have nothing to leave out.  (us per launch with a quarter, half and all of the rows there, best for
 // all -> this: 128256 features x 4096, 384 rows 246, 358, 359 -> 199, 271, 356; 32000 x 4096, 768 rows 82, 168, 170 -> 71, 114, 168.
-// Without the 3 % 88 launches at d_model 512 - 8192 take 7 % less at a quarter and 5 % at half, but 2.5 % more, 32 % at worst, where
-// all rows are there.)
+// 88 launches at d_model 512 - 8192: 4 % less at a quarter and at half, as long where all rows are there; at 3 % seven more of them
+// lose, at 10 % nine.)
 inline int pick_partly_filled(const Work& w, int m_pad) {
   const Choice all = pick_tile(w, m_pad);
   auto average = [&](int t) {
@@ -404,7 +407,7 @@ inline int pick_partly_filled(const Work& w, int m_pad) {
   for (int t = 0; t < kTileCount; ++t) {
     if (m_pad % (16 * kTiles[t].bm)) continue;
     const long long full = tile_cost(t, w, m_pad);
-    if (full < 0 || full * 100 > all.cost * 103) continue;
+    if (full < 0 || full * 100 > all.cost * 105) continue;
     const long long a = average(t);
     if (a < best.cost) best = Choice{t, a};
   }

@@ -21,7 +21,7 @@ def _session(max_position, **dims):
 
 
 def _times(shape, sess, n_seq, window, context, max_context=None, decode=False, n_valid=None):
-    """Microseconds per pass of every launch class (median of 9 passes, behind 3 that are not counted)."""
+    """Microseconds per pass of every launch class (least of three medians of 9 passes, behind 3 that are not counted)."""
     rng = wl.rng_for(57, n_seq, window)
     table, blocks = wl.make_block_table(rng, np.full(n_seq, context + window), 16, max_blocks_per_seq=(max(max_context or 0, context + window) + 15) // 16)
     bt = torch.as_tensor(table, device=DEV)
@@ -43,15 +43,19 @@ def _times(shape, sess, n_seq, window, context, max_context=None, decode=False, 
         one()
     torch.cuda.synchronize()
     passes = 9
-    B.llm42_profile_enable(None, passes * 64)
-    for _ in range(passes):
-        one()
-    got = B.llm42_profile_collect(passes * 64)
-    per = len(got) // passes
-    assert per * passes == len(got)
-    kinds = {k for k, _ in got}
-    return {k: statistics.median(1e3 * sum(ms for kk, ms in got[p * per:(p + 1) * per] if kk == k) for p in range(passes))
-            for k in kinds}
+
+    def medians():
+        B.llm42_profile_enable(None, passes * 64)
+        for _ in range(passes):
+            one()
+        got = B.llm42_profile_collect(passes * 64)
+        per = len(got) // passes
+        assert per * passes == len(got)
+        return {k: statistics.median(1e3 * sum(ms for kk, ms in got[p * per:(p + 1) * per] if kk == k) for p in range(passes))
+                for k in {k for k, _ in got}}
+    # (a process's first passes run up to 15 % slower than those that follow, at either of two builds compared)
+    sets = [medians() for _ in range(3)]
+    return {k: min(t[k] for t in sets) for k in sets[0]}
 
 
 @pytest.mark.parametrize("n_seq,context", [(128, 250), (256, 100), (64, 500)])
@@ -116,6 +120,16 @@ def test_projections_of_few_k_tiles_by_the_tile_of_short_rounds():
         sess.close()
     print(f"O-projection at 128 rows: d_model 768 {t[768]:.1f} us, 1024 {t[1024]:.1f} us")
     assert t[1024] <= 1.1 * t[768]
+
+
+def test_a_round_of_few_workgroups_is_a_round():
+    """QKV of 12288 x 4096: 5120 rows cost no more than 1.25 times what 4096 do (1.19; 1.31 while a tile was taken for them whose
+    workgroups fill 4.3 rounds, which last five)."""
+    shape, sess = _session(64, n_kv_heads=32, d_ffn=512, vocab=1024)
+    t = {rows: _times(shape, sess, rows // 16, 16, 16)["qkv"] for rows in (4096, 5120)}
+    print(f"QKV at 4096 rows {t[4096]:.1f} us, at 5120 {t[5120]:.1f} us")
+    assert t[5120] <= 1.25 * t[4096]
+    sess.close()
 
 
 @pytest.mark.parametrize("d_model,vocab,n_seq", [(2048, 32000, 48), (1024, 50304, 16)])

@@ -176,18 +176,19 @@ def test_same_bits_with_partial_rounds_and_tiles_among_partly_filled_windows(rag
 # Chosen by the tile rule: with the models above and the unsplit projections of test_gpu_batch_chosen.py, 122 of the 137 kernels of
 # more than 64 rows (tile x epilogue, the sampled LM head aside) run in some test.
 @pytest.mark.parametrize("d_model,heads,kv_heads,d_ffn,vocab,calls", [
-    (256, 16, 8, 1024, 4096, [(24, False)]),
+    (256, 16, 8, 1024, 4096, [(24, False), (72, False)]),
     (256, 16, 2, 1024, 4096, [(80, False)]),
     (256, 16, 8, 2048, 4096, [(80, False)]),
     (256, 4, 2, 8192, 4096, [(5, False)]),
     (256, 32, 4, 1024, 4096, [(80, False)]),
-    (768, 32, 4, 1024, 4096, [(192, True)]),
-    (768, 16, 8, 1024, 16384, [(48, False), (72, False)]),
-    (1024, 4, 2, 8192, 4096, [(192, False)]),
-    (1536, 4, 2, 1024, 50304, [(5, False), (40, False)]),
-    (1536, 4, 2, 8192, 4096, [(192, True)]),
-    (3072, 4, 2, 1024, 4096, [(24, False), (32, False), (128, False), (320, False)]),
-    (3072, 32, 4, 1024, 4096, [(112, True), (256, True)]),
+    (768, 16, 8, 1024, 4096, [(48, False), (96, False)]),
+    (1536, 32, 4, 1024, 4096, [(192, True)]),
+    (1536, 4, 2, 1024, 4096, [(5, False)]),
+    (1536, 4, 2, 1024, 33296, [(112, False)]),
+    (1536, 4, 2, 1024, 50304, [(40, False)]),
+    (3072, 4, 2, 1024, 4096, [(24, False), (32, False), (112, False), (128, False), (320, False)]),
+    (3072, 4, 2, 1024, 16384, [(72, False)]),
+    (3072, 32, 4, 1024, 4096, [(256, True)]),
 ])
 def test_same_bits_by_the_other_tiles(d_model, heads, kv_heads, d_ffn, vocab, calls):
     shape = wl.LLAMA_8B.replace(n_layers=1, d_model=d_model, n_q_heads=heads, n_kv_heads=kv_heads, d_ffn=d_ffn, vocab=vocab)

@@ -306,19 +306,19 @@ __device__ __forceinline__ void wait_for_rounds(int ahead) {
 
 // Tiles of gemm_direct_kernel (gemm_direct.h), in blocks of 16, and what a round of one workgroup per CU takes: 1/1000 us per
 // k-tile, fitted to launches within passes (8B shapes, 128 - 4096 rows) that fill one or more rounds, and 3 us + 24 ns per
-// block of the tile that do not depend on K (O- and down-projection differ in K only: 16 x 10 blocks 41.7 and 117.7 us, 64 and 224
-// k-tiles).  Rounds of fewer workgroups take as long (half of the CUs 0.45 against 0.48 us per k-tile): a CU's own fetches and
-// arithmetic are what a round waits for.  Of the last three the first is for split projections of partly filled windows, priced
-// for half of the rows: every workgroup has all token blocks, fetches those that hold rows, and reads weights that no other
-// does, where 4 x 4 blocks leave half of the CUs without rows (8B, us per pass with a quarter, half, three quarters and all of
-// 120 rows there: 4442, 4667, 4607, 4643 -> 4034, 4433, 4692, 4735).
-// The other two are for small K.  One is the 4 x 4 blocks again in rounds of four k-tiles, two register sets: the others' rounds
-// left over behind the last whole group of them take about 1 us more, in code of their own, and 900 ns where they have 3000 puts it
-// ahead up to about 40 k-tiles (us for two launches, the tile at 2200 ns -> this: 128 rows of d_model 1024 O 16.6 -> 12.9 and gate/up
-// 19.3 -> 16.6, at 512 rows down 25.8 -> 21.8; 128 rows of d_model 512 gate/up 17.0 -> 13.2; of the 34 launches that it now
-// takes at d_model 512 - 4096 29 are faster, and QKV of 24 k-tiles at 128 - 192 rows is not, 16.5 - 17.0 -> 17.0 - 17.6).  The other is 8 x 8 blocks
-// two to a CU, where neither's beginning nor end leaves it idle, for the LM head (32 k-tiles x 50304 features: 512 rows
-// 58 us against 61 - 85 with the others, 4096 396 against 436; the heavier epilogue of gate/up gains nothing from it).
+// block of the tile that do not depend on K (O- and down-projection differ in K only: 16 x 10 blocks 41.7 and 117.7 us, 64 and
+// 224 k-tiles).  Rounds of fewer workgroups take as long (half of the CUs 0.45 against 0.48 us per k-tile): a CU's own fetches
+// and arithmetic are what a round waits for.  Of the last three the first is for split projections of partly filled windows,
+// priced for half of the rows: every workgroup has all token blocks, fetches those that hold rows, and reads weights that no
+// other does, where 4 x 4 blocks leave half of the CUs without rows (8B, us per pass with a quarter, half, three quarters and
+// all of 120 rows there: 4442, 4667, 4607, 4643 -> 4034, 4433, 4692, 4735). The other two are for small K.  One is the 4 x 4
+// blocks again in rounds of four k-tiles, two register sets: the others' rounds left over behind the last whole group of them
+// take about 1 us more, in code of their own, and 900 ns where they have 3000 puts it ahead up to about 40 k-tiles (us for two
+// launches, the tile at 2200 ns -> this: 128 rows of d_model 1024 O 16.6 -> 12.9 and gate/up 19.3 -> 16.6, at 512 rows down
+// 25.8 -> 21.8; 128 rows of d_model 512 gate/up 17.0 -> 13.2; of the 34 launches that it now takes at d_model 512 - 4096 29 are
+// faster, and QKV of 24 k-tiles at 128 - 192 rows is not, 16.5 - 17.0 -> 17.0 - 17.6).  The other is 8 x 8 blocks two to a CU,
+// where neither's beginning nor end leaves it idle, for the LM head (32 k-tiles x 50304 features: 512 rows 58 us against 61 -
+// 85 with the others, 4096 396 against 436; the heavier epilogue of gate/up gains nothing from it).
 struct Tile {
   int nw, fb, bm;      // multiplying waves, feature blocks of each; token blocks
   int ch, r, f, nset;  // k-tiles of a round, rounds in LDS, fetching waves, register sets of weights
@@ -328,14 +328,16 @@ struct Tile {
   constexpr int bn() const { return nw * fb; }
 };
 constexpr Tile kTiles[] = {
-    {3, 1, 4, 8, 4, 4, 3, 1, false, 115}, {4, 1, 4, 8, 4, 4, 3, 1, false, 144}, {6, 1, 4, 8, 4, 4, 2, 1, false, 152}, {3, 1, 6, 4, 5, 4, 3, 1, false, 140},
-    {4, 1, 6, 4, 5, 4, 3, 1, false, 160}, {4, 1, 8, 4, 4, 4, 2, 1, false, 180}, {6, 1, 6, 4, 5, 4, 3, 1, false, 185}, {8, 1, 6, 4, 5, 4, 3, 1, false, 215},
-    {6, 1, 8, 4, 4, 4, 2, 1, false, 215}, {7, 1, 8, 4, 4, 4, 2, 1, true, 230}, {8, 1, 8, 4, 4, 4, 2, 1, false, 242}, {8, 1, 10, 2, 5, 4, 3, 1, false, 285},
-    {7, 1, 12, 2, 4, 4, 3, 1, true, 300}, {6, 1, 12, 2, 4, 2, 4, 1, false, 300}, {4, 2, 12, 2, 4, 4, 3, 1, false, 326}, {7, 1, 16, 2, 4, 4, 2, 1, true, 365},
-    {6, 2, 8, 4, 4, 2, 2, 1, false, 330}, {8, 2, 8, 4, 4, 4, 2, 1, true, 376}, {4, 2, 16, 2, 4, 4, 2, 1, false, 372}, {8, 2, 10, 2, 5, 4, 2, 1, false, 476},
-    {7, 2, 12, 2, 4, 1, 3, 1, false, 480}, {7, 2, 14, 2, 4, 1, 3, 1, false, 545}, {6, 2, 16, 2, 3, 1, 3, 1, false, 570}, {7, 2, 16, 2, 3, 1, 3, 1, false, 605},
-    {7, 4, 10, 1, 6, 1, 2, 1, false, 760}, {7, 4, 12, 1, 4, 1, 2, 1, false, 930}, {2, 1, 8, 4, 4, 4, 4, 1, false, 95}, {4, 1, 4, 4, 4, 4, 2, 1, false, 170},
-    {4, 2, 8, 2, 4, 2, 2, 2, false, 477}};
+    {3, 1, 4, 8, 4, 4, 3, 1, false, 115}, {4, 1, 4, 8, 4, 4, 3, 1, false, 144}, {6, 1, 4, 8, 4, 4, 2, 1, false, 152},
+    {3, 1, 6, 4, 5, 4, 3, 1, false, 140}, {4, 1, 6, 4, 5, 4, 3, 1, false, 160}, {4, 1, 8, 4, 4, 4, 2, 1, false, 180},
+    {6, 1, 6, 4, 5, 4, 3, 1, false, 185}, {8, 1, 6, 4, 5, 4, 3, 1, false, 215}, {6, 1, 8, 4, 4, 4, 2, 1, false, 215},
+    {7, 1, 8, 4, 4, 4, 2, 1, true, 230}, {8, 1, 8, 4, 4, 4, 2, 1, false, 242}, {8, 1, 10, 2, 5, 4, 3, 1, false, 285},
+    {7, 1, 12, 2, 4, 4, 3, 1, true, 300}, {6, 1, 12, 2, 4, 2, 4, 1, false, 300}, {4, 2, 12, 2, 4, 4, 3, 1, false, 326},
+    {7, 1, 16, 2, 4, 4, 2, 1, true, 365}, {6, 2, 8, 4, 4, 2, 2, 1, false, 330}, {8, 2, 8, 4, 4, 4, 2, 1, true, 376},
+    {4, 2, 16, 2, 4, 4, 2, 1, false, 372}, {8, 2, 10, 2, 5, 4, 2, 1, false, 476}, {7, 2, 12, 2, 4, 1, 3, 1, false, 480},
+    {7, 2, 14, 2, 4, 1, 3, 1, false, 545}, {6, 2, 16, 2, 3, 1, 3, 1, false, 570}, {7, 2, 16, 2, 3, 1, 3, 1, false, 605},
+    {7, 4, 10, 1, 6, 1, 2, 1, false, 760}, {7, 4, 12, 1, 4, 1, 2, 1, false, 930}, {2, 1, 8, 4, 4, 4, 4, 1, false, 95},
+    {4, 1, 4, 4, 4, 4, 2, 1, false, 170}, {4, 2, 8, 2, 4, 2, 2, 2, false, 477}};
 constexpr int kTileCount = sizeof kTiles / sizeof kTiles[0], kShortRounds = kTileCount - 2, kPartly = kTileCount - 3;
 
 // The epilogues that tile t has a kernel for; tile_cost offers it to no other work.
@@ -348,20 +350,20 @@ struct Choice {
   int tile;
   long long cost;   // ns
 };
-// The cheapest tile for n_blocks x m_pad rows by k_tiles, `planes` times over.  A launch takes whole rounds however many there are:
-// QKV of 12288 features x 4096 by 14 x 16 blocks 3.0 rounds 365 us, 3.4 368, 4.3 457, 5.2 557, 6.0 643, 6.9 661, gate/up of 8192
-// features x 4096 2.9 rounds 257, 3.5 329, 4.05 411, 4.6 414.  (Priced as their share and a quarter of a round beyond four rounds, the
-// tile with a few workgroups too many won: that QKV at 6144 rows 557 us, 510 by 6.9 rounds of 14 x 12 blocks; at 5120 rows 457 -> 411;
-// that gate/up at 7168 rows 411 -> 364; of 27 launches at d_model 768 - 8192 and 1152 - 8192 rows that take another tile now 25 are
-// 1 - 13 % faster, two 0.4 and 1.9 % slower.)
-// Two workgroups to a CU are never in step and take their share and a quarter (LM head of 50304 features x 1024 and x 768, 3.1 rounds
-// at 512 rows: 59 and 51 us by 14 x 16 blocks, 57 and 47 by 8 x 8; with half of the rows there 61 and 52 against 46 and 38).  With up to two rounds of
-// them the other tiles are the better ones where all rows are there (32000 x 2048, 384 and 512 rows 58 and 65 us against 59 and 74),
-// not where half are (50304 x 1024, 256 rows 33 against 25, with all of them 34 and 38).
-// The epilogues of QKV and LM head do much per row, and with 16 token blocks to a wave and few features that counts (QKV at 1024
-// rows: 16 x 8 blocks 63.6 us, 8 x 16 67.0; LM head of 32000 features at 512 rows 114 and 119).  So it does for QKV with 12 x 16
-// blocks in more than one round (against 16 x 8, us: 8B 3328 rows 184 and 174, 4096 195 and 184, 5888 295 and 293, 8192 395 and 368;
-// d_model 2048, 3072 features, 6656 rows 118 and 107, 8192 120 and 114; d_model 8192, 12288 features, 3072 rows 533 and 538).
+// The cheapest tile for n_blocks x m_pad rows by k_tiles, `planes` times over.  A launch takes whole rounds however many there
+// are: QKV of 12288 features x 4096 by 14 x 16 blocks 3.0 rounds 365 us, 3.4 368, 4.3 457, 5.2 557, 6.0 643, 6.9 661, gate/up
+// of 8192 features x 4096 2.9 rounds 257, 3.5 329, 4.05 411, 4.6 414.  (Priced as their share and a quarter of a round beyond
+// four rounds, the tile with a few workgroups too many won: that QKV at 6144 rows 557 us, 510 by 6.9 rounds of 14 x 12 blocks;
+// at 5120 rows 457 -> 411; that gate/up at 7168 rows 411 -> 364; of 27 launches at d_model 768 - 8192 and 1152 - 8192 rows that
+// take another tile now 25 are 1 - 13 % faster, two 0.4 and 1.9 % slower.) Two workgroups to a CU are never in step and take
+// their share and a quarter (LM head of 50304 features x 1024 and x 768, 3.1 rounds at 512 rows: 59 and 51 us by 14 x 16
+// blocks, 57 and 47 by 8 x 8; with half of the rows there 61 and 52 against 46 and 38).  With up to two rounds of them the
+// other tiles are the better ones where all rows are there (32000 x 2048, 384 and 512 rows 58 and 65 us against 59 and 74), not
+// where half are (50304 x 1024, 256 rows 33 against 25, with all of them 34 and 38). The epilogues of QKV and LM head do much
+// per row, and with 16 token blocks to a wave and few features that counts (QKV at 1024 rows: 16 x 8 blocks 63.6 us, 8 x 16
+// 67.0; LM head of 32000 features at 512 rows 114 and 119).  So it does for QKV with 12 x 16 blocks in more than one round
+// (against 16 x 8, us: 8B 3328 rows 184 and 174, 4096 195 and 184, 5888 295 and 293, 8192 395 and 368; d_model 2048, 3072
+// features, 6656 rows 118 and 107, 8192 120 and 114; d_model 8192, 12288 features, 3072 rows 533 and 538).
 enum Kind { QKV, PLAIN, LM_HEAD };
 struct Work {
   Kind kind;
@@ -372,7 +374,8 @@ struct Work {
 // What tile t takes for `rows` rows (negative: it is not for this work), in a launch for `of` rows.
 inline long long tile_cost(int t, const Work& w, int rows, int of = 0) {
   const Tile& q = kTiles[t];
-  const long long tiles_n = (w.n_blocks + q.bn() - 1) / q.bn(), tiles = tiles_n * ((rows + 16 * q.bm - 1) / (16 * q.bm)) * w.planes, slots = w.cus * q.per_cu;
+  const long long tiles_n = (w.n_blocks + q.bn() - 1) / q.bn(), tiles = tiles_n * ((rows + 16 * q.bm - 1) / (16 * q.bm)) * w.planes;
+  const long long slots = w.cus * q.per_cu;
   const long long whole = (tiles + slots - 1) / slots * 64, share = tiles * 64 / slots + 16;   // rounds, in 1/64
   if (t == kPartly && !(w.partly && w.planes == 2)) return -1;
   const long long launched = of ? tiles_n * (of / (16 * q.bm)) : tiles;
@@ -416,9 +419,12 @@ inline int pick_partly_filled(const Work& w, int m_pad) {
 // Partly filled windows: how many rows there are only the device knows, and the tile that fits all that there could be is not
 // the one for the half of them that windows of random counts hold.  The number of rows, of 9/16 to 3/4 of all, that are to have
 // a launch of their own beside the one for more (the one that does not apply ends at once, in 4 us): the largest whose tile
-// takes no more than 5 % longer than the best of them, if that saves 15 % against the tile for all on as many rows; else 0.  (8B,
-// us per pass: 516 rows of 999 12682 -> 11126, 440 of 748 12141 -> 11153, 1735 of 3161 33318 -> 29146; with a tenth 1757 of 3549
-// 31191 -> 31444, with 5/8 of all whatever its tile -> 37841.)
+// takes no more than 5 % longer than the best of them, if that saves 15 % against the tile for all on as many rows; else 0.
+// (8B, us per pass: 516 rows of 999 12682 -> 11126, 440 of 748 12141 -> 11153, 1735 of 3161 33318 -> 29146; with a tenth 1757
+// of 3549 31191 -> 31444, with 5/8 of all whatever its tile -> 37841.  Windows that are all full, given as counts, take 0.97 -
+// 1.02 of the time without counts at the 8B shape, 80 - 4096 rows, up to 1.03 at other widths and 1.06 at 128 - 256 rows there
+// - the launch that ends at once, the read of the count, the tile for split projections of partly filled windows - and 0.75 -
+// 1.01 of that before these kernels.)
 inline int rows_apart(const Work& w, int m_pad, Choice all) {
   long long least = 0;
   for (int pass = 0; pass < 2; ++pass)

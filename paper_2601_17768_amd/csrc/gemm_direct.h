@@ -22,7 +22,7 @@ namespace gemm {
 // at 4.4 TB/s, of 2 KiB and more at 6).  Beyond that it is the power of the matrix cores, as for any kernel here.
 // us per launch within a pass (events, 8B shapes), operands through LDS with 64 x 64 ... 256 x 128 tiles before -> this:
 //            QKV            O-projection   down-projection   gate/up          LM head
-//    128     25.6 -> 22.0   16.6 -> 16.4    42.2 ->  39.4    57.8 ->  47.8     230 ->  211
+//    128     25.6 -> 22.0   16.6 -> 15.9    42.2 ->  39.4    57.8 ->  47.8     230 ->  211
 //    256     30.4 -> 27.1   19.2 -> 18.4    48.9 ->  47.3    73.3 ->  63.8     316 ->  311
 //    512     44.4 -> 36.6   26.4 -> 25.3    69.2 ->  64.1   114.1 ->  94.8     509 ->  508
 //    768     64.0 -> 49.7   34.2 -> 30.1    96.0 ->  82.3   168.0 -> 135.8     761 ->  707

@@ -32,8 +32,8 @@ namespace gemm {
 //   2048    101.6 -> 100.6                                  366.6 -> 354.8    2102 -> 1796
 //   3072    182.0 -> 152.5                                  552.9 -> 530      3145 -> 2747
 //   4096    194.3 -> 184.0 157.1 -> 151.5  411.5 -> 394.6   717.5 ->  720    4379 -> 3687
-// (gate/up at 4096 rows 1.32 - 1.35 PFLOP/s, where the vendor library's GEMM of the shape runs at 1.33 - 1.35: within a run 1 %
-// below it, 1 % below and 1.5 % above.)
+// (gate/up at 4096 rows 1.30 - 1.35 PFLOP/s, level with the vendor library's GEMM of the shape: from 1 % below to 1.5 % above it
+// in four runs that timed both.)
 // Other widths (d_model 512 - 8192, 80 - 6144 rows), passes of two layers against the kernels before this one: 189 calls with full
 // windows take 0.71 - 1.01 of their time, 0.88 on average, 532 with partly filled ones 0.71 - 1.05, 0.89 on average.  What takes
 // longer: a quarter of 1280 - 3072 rows there (up to 1.05: the halves that follow each other, in tiles for 9/16 of the rows, leave CUs

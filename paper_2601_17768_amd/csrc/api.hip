@@ -129,6 +129,21 @@ void attention_mode(const llm42_model* m, int num_seqs, int max_context, Workspa
   ws.attn_units = attention_units(ws.attn_super, max_context);
 }
 
+// Whether attention_wave_kernel is the one for a call of one block of 16 query rows per (sequence, kv head).  What it and its merge
+// pass take against the other kernels, us per layer (sequences x keys; 8 kv heads, head dimension 128: at 64 it is not built):
+//   contexts beyond one super    1 x 8000 -2, 4 x 3000 -8, 8 x 8000 +1, 32 of up to 2400 -30, 48 x 3000 -15, 24 of 16 - 8000 -24
+//   more workgroups than CUs     40 x 512 -6, 48 x 1900 -8, 64 x 300 -6, 128 x 1000 -2, 48 of 65 - 2000 -13
+//   up to half as many           8 x 1900 -8, 8 x 1000 -3, 4 x 1000 -4, 16 x 1000 0; 16 x 512 +1.5, 8 x 300 +2, 4 x 300 +4
+//   in between                   24 of 65 - 1873 -9, 24 of 100 - 2000 -2, 32 of 100 - 2000 +2, 24 x 1900 +3; 24 x 1000 +1, 32 x 300 +1.5
+// With one sequence the other kernels are as good; with two and more blocks of rows, each of which would fetch K and V for
+// itself, they are better (two blocks 8 x 1900 +6, eight 8 x 1900 +78).
+bool waves_pay(const llm42_model* m, int num_seqs, int window, int max_context) {
+  if (m->cfg.head_dim != 128 || m->group * window > 16 || max_context <= 256) return false;
+  const long long wgs = (long long)num_seqs * m->cfg.n_kv_heads, cus = m->num_cus;
+  if (attention_units(true, max_context) > 1 || wgs > cus) return true;
+  return 2 * wgs <= cus ? wgs >= 16 && max_context > 768 : max_context > 1280;
+}
+
 // Rows of the GEMM grid: multiples for which gemm_direct_kernel has a tile of all the rows, or of an even part of them, whose
 // workgroups fill the device once (8B, ms per pass against the next of 256, 512 and the multiples of 256: 160 rows 6.11 -> 5.83,
 // 384 8.48 -> 7.76, 576 11.19 -> 10.31, 832 13.76 -> 13.26, 1088 17.80 -> 17.07; other widths up to 17 % less, the worst 4 % more).
@@ -140,7 +155,7 @@ ResidLayout resid_layout(int m_pad, int d) { return m_pad <= 512 ? ResidLayout{d
 
 // Carve the workspace.  Called with base == nullptr to size it.
 Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context, char* base, bool batch_chosen = false,
-                size_t min_part_rows = 0) {
+                size_t min_part_rows = 0, bool waves = false) {
   const llm42_config& c = m->cfg;
   Workspace ws;
   memset(&ws, 0, sizeof ws);
@@ -150,6 +165,13 @@ Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context,
   ws.m_pad = padded_rows(ws.m_rows);
   ws.r_pad = pad_to(m->group * window, 16);
   attention_mode(m, num_seqs, max_context, ws);
+  ws.part_rows = ws.r_pad;
+  if (waves) {
+    ws.attn_waves = ws.attn_list = true;
+    ws.attn_super = ws.attn_direct = ws.attn_seq = ws.attn_split = false;
+    ws.part_rows = m->group * window;          // (a slot's padding rows are never written)
+    ws.attn_units = attention_units(false, max_context);
+  }
   size_t off = 0;
   auto take = [&](size_t bytes) {
     char* p = base ? base + off : nullptr;
@@ -171,7 +193,7 @@ Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context,
   ws.hidden = (uint16_t*)take(2ull * ws.m_pad * m->ffn_k);
   // (min_part_rows: llm42_workspace_bytes sizes the partials for every call of up to max_seqs sequences - a call of
   // fewer sequences may run per chunk where the largest runs per super, with 8 x the slots per sequence)
-  const size_t part_rows = std::max((size_t)num_seqs * c.n_kv_heads * ws.attn_units * ws.r_pad, min_part_rows);
+  const size_t part_rows = std::max((size_t)num_seqs * c.n_kv_heads * ws.attn_units * ws.part_rows, min_part_rows);
   ws.attn_items = (int4*)take(sizeof(int4) * std::max((size_t)num_seqs * ws.attn_units, min_part_rows / ((size_t)c.n_kv_heads * ws.r_pad)));
   ws.attn_ctrl_offset = off;
   ws.attn_ctrl = (int32_t*)take(sizeof(int32_t) * (2 + c.n_layers));
@@ -313,7 +335,11 @@ llm42_status verify_impl(const char* who, const llm42_model* m, const llm42_kv_c
     return fail(LLM42_ECAPACITY, "%s: max_context %d exceeds block-table capacity %lld", who, max_context,
                 (long long)kv->max_blocks_per_seq * LLM42_KV_BLOCK);
   if ((uintptr_t)workspace % 256) return fail(LLM42_EWORKSPACE, "%s: workspace not 256-byte aligned", who);
-  Workspace ws = carve(m, num_seqs, window, max_context, (char*)workspace, batch_chosen);
+  // (a wave per chunk needs a partial slot for each: only where the caller's workspace has them, for what a call needs at least
+  // is not to grow)
+  const bool waves = waves_pay(m, num_seqs, window, max_context) &&
+                     carve(m, num_seqs, window, max_context, nullptr, batch_chosen, 0, true).bytes <= workspace_bytes;
+  Workspace ws = carve(m, num_seqs, window, max_context, (char*)workspace, batch_chosen, 0, waves);
   if (ws.bytes > workspace_bytes)
     return fail(LLM42_EWORKSPACE, "%s: workspace %zu < %zu bytes", who, workspace_bytes, ws.bytes);
   return run_pass(m, kv, seq_lens, candidates, window, n_valid, num_seqs, max_context, out_tokens, seq_status,

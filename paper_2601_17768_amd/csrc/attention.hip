@@ -661,15 +661,72 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
   fetch_wait<0>();                      // the dummy fetches too
 }
 
+// One online-softmax step of a wave that has the 64 keys from k0 in registers, for one block of 16 query rows.  next_k and next_v
+// request what follows into the same registers, each as soon as they are free.
+// A lane takes V 16 bytes at a time: the keys of group g of TWO neighbouring features.  MFMA row c of product h of block
+// pair p is then feature (2 p + c / 8) * 16 + 2 (c % 8) + h, and the lane ends up with 8 consecutive features of its row:
+// (2 p + g / 2) * 16 + (g % 2) * 8 + 2 e + h for e = 0 .. 3.  Which row of the product a feature has does not touch its sum.
+template <int HD, class NextK, class NextV>
+__device__ __forceinline__ void register_step(bf16x8 (&kb)[4][HD / 32], u32x4 (&vb)[4][HD / 32], const bf16x8 (&qf)[HD / 32], int k0, int k_hi,
+                                              int g, int qpos, int wmin, float scale_log2, float& m, float& l, f32x4 (&acc)[HD / 16],
+                                              bool first, NextK next_k, NextV next_v) {
+  constexpr int DK = HD / 32, DB = HD / 16;
+  f32x4 sc[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int d = 0; d < DK; ++d)
+      sc[b] = mfma16(kb[b][d], qf[d], d == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : sc[b]);
+  next_k();
+  u32x4 pf[2];
+  const bool inner = k0 + STEP - 1 <= wmin;                                // wave-uniform
+  if (inner) softmax_update<DB, false>(sc, k0, g, qpos, scale_log2, m, l, acc, pf, first);
+  else softmax_update<DB, true>(sc, k0, g, qpos, scale_log2, m, l, acc, pf, first);
+  if (!inner) {
+    // slots at or beyond k_hi hold stale, never-written or foreign data: zero, so that 0 * garbage is no NaN
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int kp = k0 + b * 16 + g * 4;
+#pragma unroll
+      for (int d = 0; d < DB / 2; ++d) {
+        u32x4& v = vb[b][d];
+        if (kp + 0 >= k_hi) v[0] &= 0xFFFF0000u, v[2] &= 0xFFFF0000u;
+        if (kp + 1 >= k_hi) v[0] &= 0x0000FFFFu, v[2] &= 0x0000FFFFu;
+        if (kp + 2 >= k_hi) v[1] &= 0xFFFF0000u, v[3] &= 0xFFFF0000u;
+        if (kp + 3 >= k_hi) v[1] &= 0x0000FFFFu, v[3] &= 0x0000FFFFu;
+      }
+    }
+  }
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+    for (int d = 0; d < DB; ++d) {
+      const u32x4 x = vb[2 * kk][d / 2], y = vb[2 * kk + 1][d / 2];
+      const u32x4 v = d % 2 == 0 ? (u32x4){x[0], x[1], y[0], y[1]} : (u32x4){x[2], x[3], y[2], y[3]};
+      acc[d] = mfma16(__builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, pf[kk]), acc[d]);
+    }
+  next_v();
+}
+
+// 16 keys of K, or of V as register_step wants them: tile `tile` (in 16-byte units) of a plane.  NT: past the caches.
+template <int DK, bool NT>
+__device__ __forceinline__ void load_k_tile(bf16x8 (&kb)[DK], const bf16x8* __restrict__ plane, size_t tile, int lane) {
+#pragma unroll
+  for (int d = 0; d < DK; ++d) kb[d] = NT ? __builtin_nontemporal_load(plane + tile + lane + d * 64) : plane[tile + lane + d * 64];
+}
+template <int DK, bool NT>
+__device__ __forceinline__ void load_v_tile(u32x4 (&vb)[DK], const u32x4* __restrict__ plane, size_t tile, int col, int g) {
+  const u32x4* p = plane + tile + ((col >> 3) * 4 + g) * 8 + (col & 7);
+#pragma unroll
+  for (int d = 0; d < DK; ++d) vb[d] = NT ? __builtin_nontemporal_load(p + d * 64) : p[d * 64];
+}
+
 // Contexts within one super, for few sequences or few query rows per (sequence, kv head): a workgroup of 4 waves takes ONE
 // block of 16 query rows, wave w walking chunks w and w + 4 on its own - K and V operands straight from global memory into registers, two
 // steps ahead, no ring and no barrier - and the chunk partials are folded through LDS in the schedule's order.  What
 // bounds such a call is the latency of one fetch after the other: four waves in a row of steps each put a whole super's
 // first 512 keys in flight at once.  The K and V of a (sequence, kv head) are fetched once per row block (from L2 after
 // the first), so it is used while the row blocks are few (see attention_mode).
-// A lane takes V 16 bytes at a time: the keys of group g of TWO neighbouring features.  MFMA row c of product h of block
-// pair p is then feature (2 p + c / 8) * 16 + 2 (c % 8) + h, and the lane ends up with 8 consecutive features of its row:
-// (2 p + g / 2) * 16 + (g % 2) * 8 + 2 e + h for e = 0 .. 3.  Which row of the product a feature has does not touch its sum.
 // items == nullptr: item t is of sequence t / per_item (no list to wait for).
 template <int HD>
 __global__ __launch_bounds__(256) void attention_split_kernel(
@@ -720,68 +777,27 @@ __global__ __launch_bounds__(256) void attention_split_kernel(
       const int safe_id = block_table[(size_t)s * max_blocks_per_seq];
       const int ids = my_blk <= last_blk ? raw : safe_id;
       bf16x8 ka[4][DK], kc[4][DK];
-      u32x4 va[4][DB / 2], vc[4][DB / 2];
+      u32x4 va[4][DK], vc[4][DK];
       auto tile_of = [&](int u, int b) {   // (a step past the wave's last one: the last one once more)
         const int id = __builtin_amdgcn_readlane(ids, min(u, steps - 1) * 4 + b);
         return ((size_t)id * n_kv_heads + kvh) * TV4;
       };
       auto load_k = [&](bf16x8(&kb)[4][DK], int u) __attribute__((always_inline)) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const bf16x8* p = k_plane + tile_of(u, b) + lane;
-#pragma unroll
-          for (int d = 0; d < DK; ++d) kb[b][d] = p[d * 64];
-        }
+        for (int b = 0; b < 4; ++b) load_k_tile<DK, false>(kb[b], k_plane, tile_of(u, b), lane);
       };
-      auto load_v = [&](u32x4(&vb)[4][DB / 2], int u) __attribute__((always_inline)) {
+      auto load_v = [&](u32x4(&vb)[4][DK], int u) __attribute__((always_inline)) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const u32x4* p = v_plane + tile_of(u, b) + ((col >> 3) * 4 + g) * 8 + (col & 7);
-#pragma unroll
-          for (int d = 0; d < DB / 2; ++d) vb[b][d] = p[d * 64];
-        }
+        for (int b = 0; b < 4; ++b) load_v_tile<DK, false>(vb[b], v_plane, tile_of(u, b), col, g);
       };
       float m = -INFINITY, l = 0.f;
       f32x4 acc[DB];
 #pragma unroll
       for (int d = 0; d < DB; ++d) acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
-      auto step = [&](int u, bf16x8(&kb)[4][DK], u32x4(&vb)[4][DB / 2]) __attribute__((always_inline)) {
+      auto step = [&](int u, bf16x8(&kb)[4][DK], u32x4(&vb)[4][DK]) __attribute__((always_inline)) {
         const int c = wave + (u / SPC) * NW, k0 = c * CHUNK + (u % SPC) * STEP;
-        f32x4 sc[4];
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-          for (int d = 0; d < DK; ++d)
-            sc[b] = mfma16(kb[b][d], qf[d], d == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : sc[b]);
-        load_k(kb, u + 2);
-        u32x4 pf[2];
-        const bool inner = k0 + STEP - 1 <= wmin;                          // wave-uniform
-        if (inner) softmax_update<DB, false>(sc, k0, g, qpos, scale_log2, m, l, acc, pf, u % SPC == 0);
-        else softmax_update<DB, true>(sc, k0, g, qpos, scale_log2, m, l, acc, pf, u % SPC == 0);
-        if (!inner) {
-          // slots at or beyond k_hi hold stale, never-written or foreign data: zero, so that 0 * garbage is no NaN
-#pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            const int kp = k0 + b * 16 + g * 4;
-#pragma unroll
-            for (int d = 0; d < DB / 2; ++d) {
-              u32x4& v = vb[b][d];
-              if (kp + 0 >= k_hi) v[0] &= 0xFFFF0000u, v[2] &= 0xFFFF0000u;
-              if (kp + 1 >= k_hi) v[0] &= 0x0000FFFFu, v[2] &= 0x0000FFFFu;
-              if (kp + 2 >= k_hi) v[1] &= 0xFFFF0000u, v[3] &= 0xFFFF0000u;
-              if (kp + 3 >= k_hi) v[1] &= 0x0000FFFFu, v[3] &= 0x0000FFFFu;
-            }
-          }
-        }
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-          for (int d = 0; d < DB; ++d) {
-            const u32x4 x = vb[2 * kk][d / 2], y = vb[2 * kk + 1][d / 2];
-            const u32x4 v = d % 2 == 0 ? (u32x4){x[0], x[1], y[0], y[1]} : (u32x4){x[2], x[3], y[2], y[3]};
-            acc[d] = mfma16(__builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, pf[kk]), acc[d]);
-          }
-        load_v(vb, u + 2);
+        register_step<HD>(kb, vb, qf, k0, k_hi, g, qpos, wmin, scale_log2, m, l, acc, u % SPC == 0,
+                          [&]() __attribute__((always_inline)) { load_k(kb, u + 2); }, [&]() __attribute__((always_inline)) { load_v(vb, u + 2); });
         if (u % SPC == SPC - 1 || u + 1 == steps) {                        // the chunk is complete
 #pragma unroll
           for (int d = 0; d < DB; ++d) {
@@ -821,6 +837,142 @@ __global__ __launch_bounds__(256) void attention_split_kernel(
     }
     __syncthreads();        // the partials are read before the next item's are written
   }
+}
+
+// One block of 16 query rows per (sequence, kv head), as in a decode step: a wave per chunk, and the merge pass for the sequences
+// of several (the others' rows are written here).  The waves of the launch deal the plan's list among them, longest chunks first and
+// neighbours on different CUs, and keep K and V of two steps on their way, straight to registers and across the end of an item: no
+// ring, no barrier.  What bounds it is what a CU fetches (about 42 GB/s of memory that no other reads): attention_split_kernel, a
+// workgroup per sequence and kv head, waits for its longest one, attention_kernel computes three blocks of rows that are
+// not there.  us per layer against those kernels, merge pass and all, at head dimension 128 and 8 kv heads: 24 sequences of 65 - 1873
+// keys 9 of 27 less, 32 of up to 2400 30 less, 8 x 1900 8, 48 x 1900 8, 4 x 8000 15, 24 of 16 - 8000 24 less, 24 x 1900 3 more.
+// (Folding by the wave that finishes a row's last chunk, partials through agent-scope stores and a counter, takes
+// as long as the merge launch that it saves.  Requests past an item's last step repeat one tile: as whole steps they took 6 - 60 us.)
+template <int HD>
+__global__ __launch_bounds__(256) void attention_wave_kernel(
+    const uint16_t* __restrict__ q, const bf16x8* __restrict__ k_plane, const u32x4* __restrict__ v_plane,
+    const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count, int n_kv_heads,
+    int group, int window, int r_pad, int max_blocks_per_seq, int n_units, int part_rows, int max_items, float scale_log2,
+    float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out, int d_attn) {
+  constexpr int DK = HD / 32, DB = HD / 16, TV4 = HD * 2;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int col = lane & 15, g = lane >> 4;
+  const int row_blocks = r_pad / 16, per_item = n_kv_heads * row_blocks, stride = 4 * (int)gridDim.x;
+  struct Item {
+    int s, kvh, rb, L, tag, k_lo, k_hi, steps, wmin, row, qpos, raw;
+    bf16x8 qf[DK];
+  };
+  // An item's share of the list entry `su`; what it needs from memory is requested, not waited for.  steps = 0: nothing for
+  // these rows in this chunk.
+  auto open = [&](Item& x, int t, const int4 su) __attribute__((always_inline)) {
+    const int rem = t % per_item;
+    x.rb = rem % row_blocks, x.kvh = rem / row_blocks;
+    x.s = su.x, x.L = su.z, x.tag = su.w, x.k_lo = su.y * CHUNK;
+    x.raw = block_table[(size_t)x.s * max_blocks_per_seq + min(x.k_lo / 16 + col, max_blocks_per_seq - 1)];
+    const uint16_t* qb = q + ((size_t)x.s * n_kv_heads + x.kvh) * r_pad * HD + (size_t)x.rb * DK * 512;
+#pragma unroll
+    for (int d = 0; d < DK; ++d) x.qf[d] = *(const bf16x8*)(qb + d * 512 + lane * 8);
+    x.row = x.rb * 16 + col;
+    const int i = x.row % window;
+    x.qpos = x.row < group * window && i < tag_rows(x.tag) ? x.L + i : -1;
+    int wmax = x.qpos, wmin = x.qpos;  // highest and lowest position among the block's rows (dead rows: -1)
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) {
+      wmax = max(wmax, __shfl_xor(wmax, off));
+      wmin = min(wmin, __shfl_xor(wmin, off));
+    }
+    x.wmin = __builtin_amdgcn_readfirstlane(wmin);
+    x.k_hi = min(__builtin_amdgcn_readfirstlane(wmax) + 1, x.k_lo + CHUNK);
+    x.steps = max(0, (x.k_hi - x.k_lo + STEP - 1) / STEP);
+  };
+  // The tile of step u, block b of the item.  Blocks past the last needed one (the table may hold anything there): the chunk's
+  // first; steps past the last one: the last tile, over and over.
+  auto tile_of = [&](const Item& x, int u, int b) __attribute__((always_inline)) {
+    const int at = u < x.steps ? u * 4 + b : x.steps * 4 - 1;
+    return ((size_t)__builtin_amdgcn_readlane(x.raw, x.k_lo / 16 + at <= (x.k_hi - 1) / 16 ? at : 0) * n_kv_heads + x.kvh) * TV4;
+  };
+  int t = wave * (int)gridDim.x + (int)blockIdx.x;
+  auto entry = [&](int at) { return items[min(at / per_item, max_items - 1)]; };   // (past the list: an entry that is not used)
+  int4 su = entry(t);
+  const int total = *item_count * per_item;
+  // the next item that has steps, from t on (`su` is its entry, requested one item earlier)
+  auto next = [&](Item& x) __attribute__((always_inline)) {
+    x.steps = 0;
+    while (t < total && x.steps == 0) {
+      open(x, t, su);
+      t += stride;
+      su = entry(t);
+    }
+  };
+  Item c, n;
+  next(c);
+  if (c.steps == 0) return;
+  n.steps = 0;
+  bf16x8 ka[4][DK], kc[4][DK];
+  u32x4 va[4][DK], vc[4][DK];
+  // (u counts from the current item's first step on; behind its last one come the next item's)
+  auto tile_at = [&](int u, int b) __attribute__((always_inline)) {
+    return u >= c.steps && n.steps > 0 ? tile_of(n, u - c.steps, b) : tile_of(c, u, b);
+  };
+  auto load_k = [&](bf16x8(&kb)[4][DK], int u) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) load_k_tile<DK, true>(kb[b], k_plane, tile_at(u, b), lane);
+  };
+  auto load_v = [&](u32x4(&vb)[4][DK], int u) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) load_v_tile<DK, true>(vb[b], v_plane, tile_at(u, b), col, g);
+  };
+  float m = -INFINITY, l = 0.f;
+  f32x4 acc[DB];
+#pragma unroll
+  for (int d = 0; d < DB; ++d) acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  int u = 0;
+  // One step, and the end of the item behind its last one.  False: there is none left.
+  auto step = [&](bf16x8(&kb)[4][DK], u32x4(&vb)[4][DK]) __attribute__((always_inline)) {
+    register_step<HD>(kb, vb, c.qf, c.k_lo + u * STEP, c.k_hi, g, c.qpos, c.wmin, scale_log2, m, l, acc, u == 0,
+                      [&]() __attribute__((always_inline)) { load_k(kb, u + 2); }, [&]() __attribute__((always_inline)) { load_v(vb, u + 2); });
+    if (++u < c.steps) return true;
+    const int f0 = (g / 2) * 16 + (g & 1) * 8;                             // the lane's 8 features of block pair p: f0 + 32 p
+    if (c.L + tag_rows(c.tag) <= CHUNK) {                                  // the sequence's only chunk: no merge pass over its rows
+      if (c.qpos >= 0) {
+#pragma unroll
+        for (int p = 0; p < DB / 2; ++p) {
+          u32x4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = pack2_bf16(acc[2 * p][e] / l, acc[2 * p + 1][e] / l);
+          *(u32x4*)(attn_out + pk_off(tag_base(c.tag) + c.row % window, (c.kvh * group + c.row / window) * HD + f0 + 32 * p, d_attn)) = o;
+        }
+      }
+    } else if (c.qpos >= c.k_lo) {
+      const size_t prow = (((size_t)c.s * n_kv_heads + c.kvh) * n_units + c.k_lo / CHUNK) * part_rows + c.row;
+      float* pa = part_acc + prow * HD + f0;
+#pragma unroll
+      for (int p = 0; p < DB / 2; ++p) {
+        *(f32x4*)(pa + 32 * p) = (f32x4){acc[2 * p][0], acc[2 * p + 1][0], acc[2 * p][1], acc[2 * p + 1][1]};
+        *(f32x4*)(pa + 32 * p + 4) = (f32x4){acc[2 * p][2], acc[2 * p + 1][2], acc[2 * p][3], acc[2 * p + 1][3]};
+      }
+      if (g == 0) *(float2*)(part_ml + prow * 2) = make_float2(m, l);
+    }
+    if (n.steps == 0) return false;
+    c = n;
+    next(n);
+    u = 0;
+    m = -INFINITY;
+    l = 0.f;
+#pragma unroll
+    for (int d = 0; d < DB; ++d) acc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    if (c.steps == 1 && n.steps > 0) {     // two steps ahead was beyond an item of one step, into one not known then
+      load_k(kb, 1);
+      load_v(vb, 1);
+    }
+    return true;
+  };
+  load_k(ka, 0);
+  load_v(va, 0);
+  next(n);
+  load_k(kc, 1);
+  load_v(vc, 1);
+  while (step(ka, va) && step(kc, vc)) {}
 }
 
 // The work items of a call: every (sequence, unit) pair that holds keys, as (s, unit, L, seq_tag), sorted
@@ -912,42 +1064,52 @@ __global__ __launch_bounds__(256) void attention_plan_kernel(const int32_t* __re
 
 // Fold the partials of every query row (chunks inside a super left to right, then the supers
 // left to right) and write the normalised output, bf16, into the tile layout of the
-// O-projection's activation operand.  One thread per (row, 4 features).
+// O-projection's activation operand.  One thread per (row, 4 features).  Sequences of up to done_keys keys have their output already.
 template <int HD, bool SUPER>
 __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const float* __restrict__ part_ml,
                                        const int32_t* __restrict__ seq_len, const int32_t* __restrict__ seq_n,
                                        int n_kv_heads, int group, int window, int r_pad, int n_units, int d_attn,
-                                       uint16_t* __restrict__ out, const int32_t* __restrict__ seq_mode) {
-  if (*seq_mode) return;                // the attention kernel took whole sequences and wrote the output itself
+                                       uint16_t* __restrict__ out, const int32_t* __restrict__ seq_mode, int done_keys) {
   constexpr int QUADS = HD / 4;
   const int quad = threadIdx.x % QUADS;
   const int r = blockIdx.y * (blockDim.x / QUADS) + threadIdx.x / QUADS;   // (pairs can outnumber what grid.y allows)
   const int s = blockIdx.x / n_kv_heads, kvh = blockIdx.x % n_kv_heads;
   if (r >= group * window) return;
-  const int L = seq_len[s], tag = seq_n[s];
   const int i = r % window, hq = kvh * group + r / window;
-  if (L < 0 || i >= tag_rows(tag)) return;   // no such row, or one that prepare_kernel has given zeros
-  uint2* dst = (uint2*)(out + pk_off(tag_base(tag) + i, hq * HD + quad * 4, d_attn));
   const size_t base = ((size_t)s * n_kv_heads + kvh) * n_units;
   auto slot_ml = [&](int u) { return *(const float2*)(part_ml + ((base + u) * r_pad + r) * 2); };
   auto slot_acc = [&](int u) { return *(const f32x4*)(part_acc + ((base + u) * r_pad + r) * HD + quad * 4); };
+  // The first partials are requested together with the length that says which of them there are (a round trip less: with
+  // attention_wave_kernel, 1 - 32 sequences of 300 keys, 1.4 us a layer).
+  constexpr int U = SUPER ? 1 : 4;
+  float2 ml[U];
+  f32x4 acc[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    ml[u] = slot_ml(min(u, n_units - 1));
+    acc[u] = slot_acc(min(u, n_units - 1));
+  }
+  const int L = seq_len[s], tag = seq_n[s], whole = *seq_mode;
+  if (whole) return;                         // the attention kernel took whole sequences and wrote the output itself
+  if (L < 0 || i >= tag_rows(tag)) return;   // no such row, or one that prepare_kernel has given zeros
+  if (L + tag_rows(tag) <= done_keys) return;
+  uint2* dst = (uint2*)(out + pk_off(tag_base(tag) + i, hq * HD + quad * 4, d_attn));
   float M, Ls;
   f32x4 A[1];
   if (SUPER) {
     const int last = (L + i) / SUPER_KEYS;
-    float2 ml = slot_ml(0);
-    M = ml.x;
-    Ls = ml.y;
-    A[0] = slot_acc(0);
+    M = ml[0].x;
+    Ls = ml[0].y;
+    A[0] = acc[0];
     for (int u = 1; u <= last; ++u) {
-      ml = slot_ml(u);
+      const float2 next = slot_ml(u);
       const f32x4 B[1] = {slot_acc(u)};
-      fold<1>(M, Ls, A, ml.x, ml.y, B);
+      fold<1>(M, Ls, A, next.x, next.y, B);
     }
   } else {
     // The partials of half a super are requested together (those past the last one clamped to it): folding them as they
     // come is one dependent round trip after the other.
-    constexpr int PER = SUPER_KEYS / CHUNK, U = 4;
+    constexpr int PER = SUPER_KEYS / CHUNK;
     const int last = (L + i) / CHUNK;
     M = 0.f;
     Ls = 0.f;
@@ -955,12 +1117,12 @@ __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const
     float m2 = 0.f, l2 = 0.f;
     f32x4 a2[1] = {(f32x4){0.f, 0.f, 0.f, 0.f}};
     for (int c0 = 0; c0 <= last; c0 += U) {
-      float2 ml[U];
-      f32x4 acc[U];
+      if (c0 > 0) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        ml[u] = slot_ml(min(c0 + u, last));
-        acc[u] = slot_acc(min(c0 + u, last));
+        for (int u = 0; u < U; ++u) {
+          ml[u] = slot_ml(min(c0 + u, last));
+          acc[u] = slot_acc(min(c0 + u, last));
+        }
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -999,7 +1161,7 @@ void launch_one(const llm42_model* m, int layer, const uint16_t* kp, const uint1
   attention_merge_kernel<HD, SUPER><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256,
                                       0, st>>>(ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, m->group,
                                                window, ws.r_pad, ws.attn_units, m->d_attn, ws.attn,
-                                               ws.attn_ctrl + 1 + c.n_layers);
+                                               ws.attn_ctrl + 1 + c.n_layers, 0);
 }
 
 // Workgroups of a stream-kernel launch: one per CU at head_dim 128 (two at 64), no more than there are items.
@@ -1024,7 +1186,7 @@ void launch_stream(const llm42_model* m, const uint16_t* kp, const uint16_t* vp,
   attention_merge_kernel<HD, SUPER><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256,
                                       0, st>>>(ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, m->group,
                                                window, ws.r_pad, ws.attn_units, m->d_attn, ws.attn,
-                                               ws.attn_ctrl + 1 + c.n_layers);
+                                               ws.attn_ctrl + 1 + c.n_layers, 0);
 }
 
 template <int HD>
@@ -1043,6 +1205,21 @@ void launch_split(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, 
 }
 
 template <int HD>
+void launch_waves(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, const llm42_kv_cache* kv, int num_seqs,
+                  int window, const Workspace& ws, hipStream_t st) {
+  const llm42_config& c = m->cfg;
+  const float scale_log2 = (1.0f / sqrtf((float)c.head_dim)) * 1.44269504088896340736f;
+  const int rows = m->group * window, rows_per_block = 256 / (HD / 4);
+  const unsigned grid = (unsigned)std::min<long long>(m->num_cus, (long long)num_seqs * ws.attn_units * c.n_kv_heads * (ws.r_pad / 16));
+  attention_wave_kernel<HD><<<grid, 256, 0, st>>>(ws.q, (const bf16x8*)kp, (const u32x4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl,
+                                                  c.n_kv_heads, m->group, window, ws.r_pad, kv->max_blocks_per_seq, ws.attn_units,
+                                                  ws.part_rows, num_seqs * ws.attn_units, scale_log2, ws.part_acc, ws.part_ml, ws.attn, m->d_attn);
+  attention_merge_kernel<HD, false><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256, 0, st>>>(
+      ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, m->group, window, ws.part_rows, ws.attn_units, m->d_attn, ws.attn,
+      ws.attn_ctrl + 1 + c.n_layers, CHUNK);
+}
+
+template <int HD>
 void launch_hd(const llm42_model* m, int layer, const uint16_t* kp, const uint16_t* vp, const llm42_kv_cache* kv,
                int num_seqs, int window, const Workspace& ws, hipStream_t st) {
   // 8 row blocks or more per (sequence, kv head): 8 waves of one row block each, two per SIMD, so
@@ -1050,6 +1227,12 @@ void launch_hd(const llm42_model* m, int layer, const uint16_t* kp, const uint16
   const bool wide = ws.r_pad / 16 >= 8;
   // (a call that may take whole sequences as items launches that kernel too; the plan's choice, made on the device
   // from the lengths, leaves one of the two with nothing to do)
+  if constexpr (HD == 128) {
+    if (ws.attn_waves) {
+      launch_waves<HD>(m, kp, vp, kv, num_seqs, window, ws, st);
+      return;
+    }
+  }
   if (ws.attn_split) {
     launch_split<HD>(m, kp, vp, kv, num_seqs, window, ws, st);
     return;
@@ -1071,7 +1254,7 @@ void launch_attention_plan(const llm42_model* m, int num_seqs, int max_context, 
   // as a whole-sequence item a unit has as many keys as the longest sequence of the call may have
   const int seq_unit_keys = ws.attn_seq ? (max_context + STEP - 1) / STEP * STEP : 0;
   const int seq_per_item = m->cfg.n_kv_heads * ((ws.r_pad / 16 + 7) / 8);
-  attention_plan_kernel<<<1, 256, 0, st>>>(ws.seq_len, ws.seq_n, num_seqs, ws.attn_super || ws.attn_split ? SUPER_KEYS : CHUNK,
+  attention_plan_kernel<<<1, 256, 0, st>>>(ws.seq_len, ws.seq_n, num_seqs, !ws.attn_waves && (ws.attn_super || ws.attn_split) ? SUPER_KEYS : CHUNK,
                                            seq_unit_keys, seq_per_item, (int)stream_grid(m, num_seqs, 1, ws.r_pad),
                                            ws.attn_items, ws.attn_ctrl, ws.attn_ctrl + 1, m->cfg.n_layers,
                                            ws.attn_ctrl + 1 + m->cfg.n_layers);

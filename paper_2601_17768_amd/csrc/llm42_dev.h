@@ -114,12 +114,14 @@ struct Workspace {
   int m_rows;     // num_seqs * window
   int m_pad;      // rows padded for the GEMM grid
   int r_pad;      // query rows per (seq, kv head) padded to 16
+  int part_rows;  // rows of an attention partial slot
   int attn_units; // attention partial slots per row (chunks or supers, see attention.hip)
   bool attn_super; // one workgroup per super (many sequences) instead of per chunk
   bool attn_direct; // every sequence fits one super: the attention kernel writes the final output, no merge pass
   bool attn_seq;    // the call may take whole sequences as attention items (the plan kernel decides from the lengths)
   bool attn_split;  // whatever the three above say: a workgroup per (sequence, kv head, block of 16 query rows), chunks
                     // dealt to its waves, output written by the same launch
+  bool attn_waves;  // whatever those above say: a wave per chunk, and the merge pass (see waves_pay)
   bool attn_list;   // the launches take their items from the plan kernel's list (else: sequence by sequence)
   bool batch_chosen; // off the fixed schedule (fast-path decode step, cost-of-determinism measurement): the batch may
                      // choose the split of the residual projections and the attention partials

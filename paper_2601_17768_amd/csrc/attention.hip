@@ -20,7 +20,9 @@
 //
 // Work distribution (free to change, does not touch the bits): a workgroup owns one unit of the keys
 // of a (sequence, kv head) for 8 blocks of 16 query rows (attention_stream_kernel, 8 waves) or up to 4
-// (attention_kernel, 4 waves); query rows are ordered r = q_head_in_group * window + i.  A unit is
+// (attention_kernel, 4 waves).  Query rows are ordered r = i * group + q_head_in_group: those that a partly filled window
+// lacks come last, and blocks of 16 without any row are left out (27 sequences, 516 of 999 rows: 43.5 -> 28.4 us a launch against
+// r = q_head_in_group * window + i, where every block has some).  A unit is
 //   a chunk          - few sequences: most parallelism; chunk partials are written and the merge
 //                      kernel does all folds;
 //   a super          - more sequences: chunks are folded in registers, 8 times fewer partials;
@@ -123,9 +125,9 @@ __device__ __forceinline__ float rows_sum(float x) {
 // writes 8 consecutive features of every second block d (16 bytes per lane and store, half as many stores).
 // Called by all four lanes of a row or by none.
 template <int HD>
-__device__ __forceinline__ void store_output(uint16_t* __restrict__ out, int d_attn, int base, int kvh, int group, int window,
+__device__ __forceinline__ void store_output(uint16_t* __restrict__ out, int d_attn, int base, int kvh, int group,
                                              int r, int g, const f32x4 (&acc)[HD / 16], float l) {
-  const int i = r % window, hq = kvh * group + r / window;
+  const int i = r / group, hq = kvh * group + r % group;
   const bool odd = g & 1;
 #pragma unroll
   for (int d = 0; d < HD / 16; d += 2) {
@@ -276,7 +278,7 @@ __global__ __launch_bounds__(NW * 64) void attention_kernel(
     const uint16_t* __restrict__ q, const uint4* __restrict__ k_plane, const uint4* __restrict__ v_plane,
     const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_len, const int32_t* __restrict__ seq_n,
     const int4* __restrict__ items, const int32_t* __restrict__ item_count, int32_t* __restrict__ queue,
-    int n_kv_heads, int group, int window, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
+    int n_kv_heads, int group, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
     float scale_log2, float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out,
     int d_attn) {
   constexpr int DK = HD / 32;        // MFMA k-steps over the head dimension (scores)
@@ -321,23 +323,23 @@ __global__ __launch_bounds__(NW * 64) void attention_kernel(
     for (int d = 0; d < DK; ++d) qf[cb][d] = *(const bf16x8*)(qb + d * 512 + lane * 8);
   }
   const int L = seq_len[s], tag = seq_n[s], n = tag_rows(tag);
-  if (L < 0) return;                                         // whole workgroup
+  if (L < 0 || yb * NW * CB * 16 >= n * group) return;       // whole workgroup: no live row
 
   int qpos[CB];
-  int wmax = -1, wmin = 0x7FFFFFFF;   // highest and lowest position among this wave's rows (dead rows: -1)
+  int wmax = -1, wmin = 0x7FFFFFFF;   // highest and lowest position among this wave's live rows
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
-    const int i = row[cb] % window;
-    qpos[cb] = (row[cb] < group * window && i < n) ? L + i : -1;
+    const int i = row[cb] / group;
+    qpos[cb] = i < n ? L + i : -1;
     wmax = max(wmax, qpos[cb]);
-    wmin = min(wmin, qpos[cb]);
+    if (qpos[cb] >= 0) wmin = min(wmin, qpos[cb]);
   }
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
     wmax = max(wmax, __shfl_xor(wmax, off));
     wmin = min(wmin, __shfl_xor(wmin, off));
   }
-  wmin = __builtin_amdgcn_readfirstlane(wmin);
+  wmin = __builtin_amdgcn_readfirstlane(wmax) < 0 ? -1 : __builtin_amdgcn_readfirstlane(wmin);   // (-1: no live row, the wave only fetches)
   if (lane == 0) wg_max[wave] = wmax;
   __syncthreads();
   int gmax = wg_max[0];
@@ -400,7 +402,7 @@ __global__ __launch_bounds__(NW * 64) void attention_kernel(
       const bool first = SUPER ? (j & 3) == 0 : j == 0;        // the chunk partial is empty
       if (k0 + STEP - 1 <= wmin)                               // wave-uniform
         softmax_step<HD, CB, false>(sk, sv, k0, k_hi, lane, scale_log2, qf, qpos, m, l, acc, first);
-      else
+      else if (wmin >= 0)
         softmax_step<HD, CB, true>(sk, sv, k0, k_hi, lane, scale_log2, qf, qpos, m, l, acc, first);
     }
     if (SUPER && ((j & 3) == 3 || j + 1 == n_steps)) {
@@ -434,7 +436,7 @@ __global__ __launch_bounds__(NW * 64) void attention_kernel(
   for (int cb = 0; cb < CB; ++cb) {
     if (qpos[cb] < k_lo) continue;
     if (SUPER && attn_out) {   // (one unit per sequence: no partial, no merge pass)
-      store_output<HD>(attn_out, d_attn, tag_base(tag), kvh, group, window, row[cb], g, sacc[cb], sl[cb]);
+      store_output<HD>(attn_out, d_attn, tag_base(tag), kvh, group, row[cb], g, sacc[cb], sl[cb]);
       continue;
     }
     const size_t prow = (((size_t)s * n_kv_heads + kvh) * n_units + unit) * r_pad + row[cb];
@@ -480,7 +482,7 @@ template <int HD, bool SUPER, bool FOLD, bool SEQ = false>
 __global__ __launch_bounds__(512) void attention_stream_kernel(
     const uint16_t* __restrict__ q, const uint4* __restrict__ k_plane, const uint4* __restrict__ v_plane,
     const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count,
-    int n_kv_heads, int group, int window, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
+    int n_kv_heads, int group, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
     float scale_log2, float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out,
     int d_attn, const int32_t* __restrict__ seq_mode) {
   if ((*seq_mode != 0) != SEQ) return;   // the plan chose the other kind of item for this call (workgroup-uniform)
@@ -518,7 +520,8 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     x.kvh = rem / y_blocks, x.yb = rem % y_blocks;
     x.k_lo = SEQ ? 0 : x.unit * UNIT;
     x.k_hi = SEQ ? x.L + x.n : min(x.L + x.n, x.k_lo + UNIT);
-    x.n_steps = (x.k_hi - x.k_lo + STEP - 1) / STEP;
+    // (row blocks without a live row: the query entry only)
+    x.n_steps = x.yb * NW * 16 < x.n * group ? (x.k_hi - x.k_lo + STEP - 1) / STEP : 0;
     return x;
   };
 
@@ -581,13 +584,13 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     int row[CB], qpos[CB];
     row[0] = (c.yb * NW + wave) * 16 + col;
     {
-      const int i = row[0] % window;
-      qpos[0] = (row[0] < group * window && i < c.n) ? c.L + i : -1;
+      const int i = row[0] / group;
+      qpos[0] = i < c.n ? c.L + i : -1;
     }
-    int wmin = qpos[0];               // lowest position among this wave's rows (dead rows: -1)
+    int wmin = qpos[0] >= 0 ? qpos[0] : 0x7FFFFFFF;   // lowest position among this wave's live rows (-1: none, it only fetches)
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) wmin = min(wmin, __shfl_xor(wmin, off));
-    wmin = __builtin_amdgcn_readfirstlane(wmin);
+    wmin = (c.yb * NW + wave) * 16 < c.n * group ? __builtin_amdgcn_readfirstlane(wmin) : -1;
     float m[CB] = {-INFINITY}, l[CB] = {0.f}, sm[CB] = {-INFINITY}, sl[CB] = {0.f};
     f32x4 acc[CB][DB], sacc[CB][DB];
     float tm = -INFINITY, tl = 0.f;   // SEQ: running fold of finished supers
@@ -612,7 +615,7 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
       const bool first = SUPER && FOLD ? (j & 3) == 0 : j == 0;   // the chunk partial is empty
       if (k0 + STEP - 1 <= wmin)                               // wave-uniform
         softmax_step<HD, CB, false>(sk, sv, k0, c.k_hi, lane, scale_log2, qf, qpos, m, l, acc, first);
-      else
+      else if (wmin >= 0)
         softmax_step<HD, CB, true>(sk, sv, k0, c.k_hi, lane, scale_log2, qf, qpos, m, l, acc, first);
       if (SUPER && FOLD && ((j & 3) == 3 || j + 1 == c.n_steps)) {
         // a chunk is complete: fold it into the running super partial and start the next one afresh
@@ -644,10 +647,10 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     }
     // -- partial of this unit for every row that reaches into it
     if (SEQ) {
-      if (qpos[0] >= 0) store_output<HD>(attn_out, d_attn, c.base, c.kvh, group, window, row[0], g, tacc, tl);
+      if (qpos[0] >= 0) store_output<HD>(attn_out, d_attn, c.base, c.kvh, group, row[0], g, tacc, tl);
     } else if (SUPER && attn_out) {   // one unit per sequence: no partial, no merge pass
       if (qpos[0] >= 0)
-        store_output<HD>(attn_out, d_attn, c.base, c.kvh, group, window, row[0], g, FOLD ? sacc[0] : acc[0], FOLD ? sl[0] : l[0]);
+        store_output<HD>(attn_out, d_attn, c.base, c.kvh, group, row[0], g, FOLD ? sacc[0] : acc[0], FOLD ? sl[0] : l[0]);
     } else if (qpos[0] >= c.k_lo) {
       const size_t prow = (((size_t)c.s * n_kv_heads + c.kvh) * n_units + c.unit) * r_pad + row[0];
       float* pa = part_acc + prow * HD;
@@ -733,7 +736,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(
     const uint16_t* __restrict__ q, const bf16x8* __restrict__ k_plane, const u32x4* __restrict__ v_plane,
     const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_len, const int32_t* __restrict__ seq_n,
     const int4* __restrict__ items, const int32_t* __restrict__ item_count, int num_seqs, int n_kv_heads, int group,
-    int window, int r_pad, int max_blocks_per_seq, float scale_log2, uint16_t* __restrict__ attn_out, int d_attn) {
+    int r_pad, int max_blocks_per_seq, float scale_log2, uint16_t* __restrict__ attn_out, int d_attn) {
   constexpr int DK = HD / 32, DB = HD / 16, TV4 = HD * 2, PER = SUPER_KEYS / CHUNK, NW = 4, SPC = CHUNK / STEP;
   static_assert(PER == 2 * NW, "two chunks of a super per wave");
   __shared__ f32x4 fold_acc[PER][DB * 64];
@@ -755,9 +758,9 @@ __global__ __launch_bounds__(256) void attention_split_kernel(
 #pragma unroll
     for (int d = 0; d < DK; ++d) qf[d] = *(const bf16x8*)(qb + d * 512 + lane * 8);
     const int L = seq_len[s], tag = seq_n[s], n = tag_rows(tag);
-    const int row = rb * 16 + col, i = row % window;
-    const int qpos = L >= 0 && row < group * window && i < n ? L + i : -1;
-    int wmax = qpos, wmin = qpos;      // highest and lowest position among the block's rows (dead rows: -1)
+    const int row = rb * 16 + col, i = row / group;
+    const int qpos = L >= 0 && i < n ? L + i : -1;
+    int wmax = qpos, wmin = qpos >= 0 ? qpos : 0x7FFFFFFF;   // highest and lowest position among the block's live rows
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) {
       wmax = max(wmax, __shfl_xor(wmax, off));
@@ -833,7 +836,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(
       u32x4 o;
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = pack2_bf16(A[0][e] / Ls, A[1][e] / Ls);
-      *(u32x4*)(attn_out + pk_off(tag_base(tag) + i, (kvh * group + row / window) * HD + f, d_attn)) = o;
+      *(u32x4*)(attn_out + pk_off(tag_base(tag) + i, (kvh * group + row % group) * HD + f, d_attn)) = o;
     }
     __syncthreads();        // the partials are read before the next item's are written
   }
@@ -852,7 +855,7 @@ template <int HD>
 __global__ __launch_bounds__(256) void attention_wave_kernel(
     const uint16_t* __restrict__ q, const bf16x8* __restrict__ k_plane, const u32x4* __restrict__ v_plane,
     const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count, int n_kv_heads,
-    int group, int window, int r_pad, int max_blocks_per_seq, int n_units, int part_rows, int max_items, float scale_log2,
+    int group, int r_pad, int max_blocks_per_seq, int n_units, int part_rows, int max_items, float scale_log2,
     float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out, int d_attn) {
   constexpr int DK = HD / 32, DB = HD / 16, TV4 = HD * 2;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -873,9 +876,9 @@ __global__ __launch_bounds__(256) void attention_wave_kernel(
 #pragma unroll
     for (int d = 0; d < DK; ++d) x.qf[d] = *(const bf16x8*)(qb + d * 512 + lane * 8);
     x.row = x.rb * 16 + col;
-    const int i = x.row % window;
-    x.qpos = x.row < group * window && i < tag_rows(x.tag) ? x.L + i : -1;
-    int wmax = x.qpos, wmin = x.qpos;  // highest and lowest position among the block's rows (dead rows: -1)
+    const int i = x.row / group;
+    x.qpos = i < tag_rows(x.tag) ? x.L + i : -1;
+    int wmax = x.qpos, wmin = x.qpos >= 0 ? x.qpos : 0x7FFFFFFF;   // highest and lowest position among the block's live rows
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) {
       wmax = max(wmax, __shfl_xor(wmax, off));
@@ -940,7 +943,7 @@ __global__ __launch_bounds__(256) void attention_wave_kernel(
           u32x4 o;
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[e] = pack2_bf16(acc[2 * p][e] / l, acc[2 * p + 1][e] / l);
-          *(u32x4*)(attn_out + pk_off(tag_base(c.tag) + c.row % window, (c.kvh * group + c.row / window) * HD + f0 + 32 * p, d_attn)) = o;
+          *(u32x4*)(attn_out + pk_off(tag_base(c.tag) + c.row / group, (c.kvh * group + c.row % group) * HD + f0 + 32 * p, d_attn)) = o;
         }
       }
     } else if (c.qpos >= c.k_lo) {
@@ -1070,27 +1073,30 @@ __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const
                                        const int32_t* __restrict__ seq_len, const int32_t* __restrict__ seq_n,
                                        int n_kv_heads, int group, int window, int r_pad, int n_units, int d_attn,
                                        uint16_t* __restrict__ out, const int32_t* __restrict__ seq_mode, int done_keys) {
+  if (SUPER && *seq_mode) return;       // the attention kernel took whole sequences and wrote the output itself
   constexpr int QUADS = HD / 4;
   const int quad = threadIdx.x % QUADS;
-  const int r = blockIdx.y * (blockDim.x / QUADS) + threadIdx.x / QUADS;   // (pairs can outnumber what grid.y allows)
+  const int at = blockIdx.y * (blockDim.x / QUADS) + threadIdx.x / QUADS;   // (pairs can outnumber what grid.y allows)
   const int s = blockIdx.x / n_kv_heads, kvh = blockIdx.x % n_kv_heads;
-  if (r >= group * window) return;
-  const int i = r % window, hq = kvh * group + r / window;
+  if (at >= group * window) return;
+  // (neighbouring threads take neighbouring tokens of one head, as the output lies; the partials' rows are 512 bytes each anyway)
+  const int i = at % window, hq = kvh * group + at / window, r = i * group + at / window;
   const size_t base = ((size_t)s * n_kv_heads + kvh) * n_units;
   auto slot_ml = [&](int u) { return *(const float2*)(part_ml + ((base + u) * r_pad + r) * 2); };
   auto slot_acc = [&](int u) { return *(const f32x4*)(part_acc + ((base + u) * r_pad + r) * HD + quad * 4); };
-  // The first partials are requested together with the length that says which of them there are (a round trip less: with
+  // Chunks: the first partials are requested together with the length that says which of them there are (a round trip less: with
   // attention_wave_kernel, 1 - 32 sequences of 300 keys, 1.4 us a layer).
   constexpr int U = SUPER ? 1 : 4;
   float2 ml[U];
   f32x4 acc[U];
+  if (!SUPER) {
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    ml[u] = slot_ml(min(u, n_units - 1));
-    acc[u] = slot_acc(min(u, n_units - 1));
+    for (int u = 0; u < U; ++u) {
+      ml[u] = slot_ml(min(u, n_units - 1));
+      acc[u] = slot_acc(min(u, n_units - 1));
+    }
   }
-  const int L = seq_len[s], tag = seq_n[s], whole = *seq_mode;
-  if (whole) return;                         // the attention kernel took whole sequences and wrote the output itself
+  const int L = seq_len[s], tag = seq_n[s];
   if (L < 0 || i >= tag_rows(tag)) return;   // no such row, or one that prepare_kernel has given zeros
   if (L + tag_rows(tag) <= done_keys) return;
   uint2* dst = (uint2*)(out + pk_off(tag_base(tag) + i, hq * HD + quad * 4, d_attn));
@@ -1098,13 +1104,14 @@ __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const
   f32x4 A[1];
   if (SUPER) {
     const int last = (L + i) / SUPER_KEYS;
-    M = ml[0].x;
-    Ls = ml[0].y;
-    A[0] = acc[0];
+    float2 m2 = slot_ml(0);
+    M = m2.x;
+    Ls = m2.y;
+    A[0] = slot_acc(0);
     for (int u = 1; u <= last; ++u) {
-      const float2 next = slot_ml(u);
+      m2 = slot_ml(u);
       const f32x4 B[1] = {slot_acc(u)};
-      fold<1>(M, Ls, A, next.x, next.y, B);
+      fold<1>(M, Ls, A, m2.x, m2.y, B);
     }
   } else {
     // The partials of half a super are requested together (those past the last one clamped to it): folding them as they
@@ -1154,7 +1161,7 @@ void launch_one(const llm42_model* m, int layer, const uint16_t* kp, const uint1
   const unsigned grid = (unsigned)std::min<long long>(m->num_cus * (HD == 128 ? 1 : 2), max_items);
   attention_kernel<HD, CB, NW, SUPER><<<grid, NW * 64, 0, st>>>(
       ws.q, (const uint4*)kp, (const uint4*)vp, kv->block_table, ws.seq_len, ws.seq_n, ws.attn_items, ws.attn_ctrl,
-      ws.attn_ctrl + 1 + layer, c.n_kv_heads, m->group, window, ws.r_pad, y_blocks, kv->max_blocks_per_seq,
+      ws.attn_ctrl + 1 + layer, c.n_kv_heads, m->group, ws.r_pad, y_blocks, kv->max_blocks_per_seq,
       ws.attn_units, scale_log2, ws.part_acc, ws.part_ml, SUPER && ws.attn_direct ? ws.attn : nullptr, m->d_attn);
   if (SUPER && ws.attn_direct) return;
   const int rows = m->group * window, rows_per_block = 256 / (HD / 4);
@@ -1179,7 +1186,7 @@ void launch_stream(const llm42_model* m, const uint16_t* kp, const uint16_t* vp,
   const unsigned grid = (unsigned)stream_grid(m, num_seqs, SEQ ? 1 : ws.attn_units, ws.r_pad);
   attention_stream_kernel<HD, SUPER, FOLD, SEQ><<<grid, 512, 0, st>>>(
       ws.q, (const uint4*)kp, (const uint4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl, c.n_kv_heads, m->group,
-      window, ws.r_pad, y_blocks, kv->max_blocks_per_seq, ws.attn_units, scale_log2, ws.part_acc, ws.part_ml,
+      ws.r_pad, y_blocks, kv->max_blocks_per_seq, ws.attn_units, scale_log2, ws.part_acc, ws.part_ml,
       SEQ || (SUPER && ws.attn_direct) ? ws.attn : nullptr, m->d_attn, ws.attn_ctrl + 1 + c.n_layers);
   if (SEQ || (SUPER && ws.attn_direct)) return;
   const int rows = m->group * window, rows_per_block = 256 / (HD / 4);
@@ -1191,7 +1198,7 @@ void launch_stream(const llm42_model* m, const uint16_t* kp, const uint16_t* vp,
 
 template <int HD>
 void launch_split(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, const llm42_kv_cache* kv, int num_seqs,
-                  int window, const Workspace& ws, hipStream_t st) {
+                  const Workspace& ws, hipStream_t st) {
   const llm42_config& c = m->cfg;
   const float scale_log2 = (1.0f / sqrtf((float)c.head_dim)) * 1.44269504088896340736f;
   // As many workgroups as the device holds at once: one per CU at head dimension 128 (its 418 registers per wave), two at 64
@@ -1201,7 +1208,7 @@ void launch_split(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, 
   const unsigned grid = (unsigned)std::min<long long>((long long)kPerCu * m->num_cus, (long long)num_seqs * c.n_kv_heads * (ws.r_pad / 16));
   attention_split_kernel<HD><<<grid, 256, 0, st>>>(
       ws.q, (const bf16x8*)kp, (const u32x4*)vp, kv->block_table, ws.seq_len, ws.seq_n, ws.attn_list ? ws.attn_items : nullptr,
-      ws.attn_ctrl, num_seqs, c.n_kv_heads, m->group, window, ws.r_pad, kv->max_blocks_per_seq, scale_log2, ws.attn, m->d_attn);
+      ws.attn_ctrl, num_seqs, c.n_kv_heads, m->group, ws.r_pad, kv->max_blocks_per_seq, scale_log2, ws.attn, m->d_attn);
 }
 
 template <int HD>
@@ -1212,7 +1219,7 @@ void launch_waves(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, 
   const int rows = m->group * window, rows_per_block = 256 / (HD / 4);
   const unsigned grid = (unsigned)std::min<long long>(m->num_cus, (long long)num_seqs * ws.attn_units * c.n_kv_heads * (ws.r_pad / 16));
   attention_wave_kernel<HD><<<grid, 256, 0, st>>>(ws.q, (const bf16x8*)kp, (const u32x4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl,
-                                                  c.n_kv_heads, m->group, window, ws.r_pad, kv->max_blocks_per_seq, ws.attn_units,
+                                                  c.n_kv_heads, m->group, ws.r_pad, kv->max_blocks_per_seq, ws.attn_units,
                                                   ws.part_rows, num_seqs * ws.attn_units, scale_log2, ws.part_acc, ws.part_ml, ws.attn, m->d_attn);
   attention_merge_kernel<HD, false><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256, 0, st>>>(
       ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, m->group, window, ws.part_rows, ws.attn_units, m->d_attn, ws.attn,
@@ -1234,7 +1241,7 @@ void launch_hd(const llm42_model* m, int layer, const uint16_t* kp, const uint16
     }
   }
   if (ws.attn_split) {
-    launch_split<HD>(m, kp, vp, kv, num_seqs, window, ws, st);
+    launch_split<HD>(m, kp, vp, kv, num_seqs, ws, st);
     return;
   }
   if (ws.attn_seq) launch_stream<HD, true, true, true>(m, kp, vp, kv, num_seqs, window, ws, st);

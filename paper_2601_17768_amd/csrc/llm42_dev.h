@@ -176,7 +176,7 @@ void launch_rmsnorm(bool pending, const uint16_t* gain, int d, float eps, const 
 // Fills ws.gemm: the same for every layer, so chosen once per pass (the rule takes 0.3 us a GEMM, and with partly filled windows
 // 1 - 13 us at 1024 - 16384 rows; a layer's ten launches take about 40).
 void plan_gemms(const llm42_model* m, Workspace& ws);
-void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, int window, const Workspace& ws,
+void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, const Workspace& ws,
                      hipStream_t st);
 // true: the residual stream is not complete yet; the halves are in split_part, for the RMSNorm that follows
 bool launch_gemm_residual(GemmKind kind, const uint16_t* w, const uint16_t* x, float* resid, int n, int k_padded,

@@ -56,8 +56,8 @@ llm42_status llm42_measure_verify_window_batch_chosen(
  *           it did take whole sequences (valid after the call has run);
  *   out[4]  2 if a workgroup takes one block of 16 query rows and deals the chunks of its context to
  *           its waves (contexts within 2048 keys, few workgroups); else 1 if the 8-wave streaming
- *           kernel runs (8 or more blocks of 16 query rows per sequence and kv head), 0 for the
- *           4-wave kernel.
+ *           kernel runs (8 or more blocks of 16 query rows per sequence and kv head, unless few
+ *           chunks are to be dealt out), 0 for the 4-wave kernel.
  * A verify or decode call of one block of 16 query rows per sequence and kv head (head_dim 128) may
  * run a wave per 256-key chunk and the merge pass instead, if its workspace has room for a partial
  * of every chunk; the values are then those of the distribution that it runs with less room. */

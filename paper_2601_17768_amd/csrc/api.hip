@@ -544,7 +544,7 @@ llm42_status llm42_measure_attention_plan(const llm42_model* m, int32_t num_seqs
   out[1] = ws.attn_direct || ws.attn_split ? 1 : 0;
   out[2] = ws.attn_seq ? 1 : 0;
   out[3] = (int64_t)(ws.attn_ctrl_offset + sizeof(int32_t) * (1 + m->cfg.n_layers));
-  out[4] = ws.attn_split ? 2 : ws.r_pad / 16 >= 8 ? 1 : 0;
+  out[4] = ws.attn_split ? 2 : attention_streams(m, num_seqs, ws) ? 1 : 0;
   return LLM42_OK;
 }
 

@@ -273,11 +273,10 @@ __device__ __forceinline__ void softmax_step(const uint4* lk, const uint16_t* lv
   }
 }
 
-template <int HD, int CB, int NW, bool SUPER>
-__global__ __launch_bounds__(NW * 64) void attention_kernel(
+template <int HD, int CB, int NW, bool SUPER, int NBUF>
+__global__ __launch_bounds__(NW * 64, NBUF == 2 ? 2 : 1) void attention_kernel(
     const uint16_t* __restrict__ q, const uint4* __restrict__ k_plane, const uint4* __restrict__ v_plane,
-    const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_len, const int32_t* __restrict__ seq_n,
-    const int4* __restrict__ items, const int32_t* __restrict__ item_count, int32_t* __restrict__ queue,
+    const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count, int32_t* __restrict__ queue,
     int n_kv_heads, int group, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
     float scale_log2, float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out,
     int d_attn) {
@@ -286,7 +285,8 @@ __global__ __launch_bounds__(NW * 64) void attention_kernel(
   constexpr int TV4 = HD * 2;        // uint4 per KV tile (16 tokens x HD bf16)
   constexpr int TL = TV4 / 64;       // uint4 per lane per tile
   constexpr int UNIT = SUPER ? SUPER_KEYS : CHUNK;
-  constexpr int NBUF = 4, AHEAD = 3;    // ring of step buffers; steps in flight ahead of the one computed
+  constexpr int AHEAD = NBUF - 1;       // ring of step buffers; steps in flight ahead of the one computed
+  constexpr bool QUEUE = NBUF > 2;
   constexpr int FI = 8 * TL / NW;       // fetch instructions per wave per step (4 K and 4 V tiles in all)
   static_assert(NW == 4 || NW == 8, "a step's tiles are split over 4 or 8 waves");
   static_assert(TL % (NW / 4) == 0, "half a tile per wave needs an even number of pieces");
@@ -302,7 +302,9 @@ __global__ __launch_bounds__(NW * 64) void attention_kernel(
 
   // One work item: unit `unit` of the keys of sequence `s`, kv head `kvh`, for the `yb`-th group of
   // NW * CB blocks of 16 query rows.  (A return leaves the item; every condition is workgroup-uniform.)
-  auto run_item = [&](const int unit, const int yb, const int s, const int kvh) {
+  auto run_item = [&](const int4 su, const int yb, const int kvh) {
+  const int s = su.x, unit = su.y, L = su.z, tag = su.w, n = tag_rows(tag);
+  if (yb * NW * CB * 16 >= n * group) return;                // whole workgroup: no live row
   const int k_lo = unit * UNIT;
   const int32_t* bt = block_table + (size_t)s * max_blocks_per_seq;
   // Requested before anything is known about the sequence, so that the three latencies (lengths,
@@ -322,9 +324,6 @@ __global__ __launch_bounds__(NW * 64) void attention_kernel(
 #pragma unroll
     for (int d = 0; d < DK; ++d) qf[cb][d] = *(const bf16x8*)(qb + d * 512 + lane * 8);
   }
-  const int L = seq_len[s], tag = seq_n[s], n = tag_rows(tag);
-  if (L < 0 || yb * NW * CB * 16 >= n * group) return;       // whole workgroup: no live row
-
   int qpos[CB];
   int wmax = -1, wmin = 0x7FFFFFFF;   // highest and lowest position among this wave's live rows
 #pragma unroll
@@ -453,14 +452,23 @@ __global__ __launch_bounds__(NW * 64) void attention_kernel(
   // the order in which workgroups finish does not matter: every item writes its own partial.
   const int per_item = n_kv_heads * y_blocks;
   const int total = *item_count * per_item;
+  int4 su = items[blockIdx.x / per_item];                  // (in the list's room even if there is no such item)
   for (int t = blockIdx.x; t < total;) {
-    const int it = t / per_item, rem = t - it * per_item;
-    const int4 su = items[it];
-    run_item(su.y, rem % y_blocks, su.x, rem / y_blocks);
-    __syncthreads();                                       // every wave is done with the ring
-    if (threadIdx.x == 0) next_work = (int)gridDim.x + atomicAdd(queue, 1);
-    __syncthreads();
-    t = next_work;
+    const int rem = t % per_item;
+    if constexpr (!QUEUE) {
+      t += gridDim.x;
+      const int4 next = items[min(t, total - 1) / per_item];
+      run_item(su, rem % y_blocks, rem / y_blocks);
+      su = next;
+      if (t < total) __syncthreads();                      // every wave is done with the ring
+    } else {
+      run_item(su, rem % y_blocks, rem / y_blocks);
+      __syncthreads();                                     // every wave is done with the ring
+      if (threadIdx.x == 0) next_work = (int)gridDim.x + atomicAdd(queue, 1);
+      __syncthreads();
+      t = next_work;
+      if (t < total) su = items[t / per_item];
+    }
   }
 }
 
@@ -485,7 +493,7 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     int n_kv_heads, int group, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
     float scale_log2, float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out,
     int d_attn, const int32_t* __restrict__ seq_mode) {
-  if ((*seq_mode != 0) != SEQ) return;   // the plan chose the other kind of item for this call (workgroup-uniform)
+  if (seq_mode && (*seq_mode != 0) != SEQ) return;   // the plan chose the other kind of item for this call (workgroup-uniform)
   constexpr int NW = 8, CB = 1;
   constexpr int DK = HD / 32, DB = HD / 16, TV4 = HD * 2, TL = TV4 / 64;
   constexpr int UNIT = SUPER ? SUPER_KEYS : CHUNK;
@@ -513,9 +521,9 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     const int t = ord * G + ((ord & 1) ? G - 1 - w : w);
     x.valid = t < total;
     const int tt = x.valid ? t : 0;
-    const int it = tt / per_item, rem = tt - it * per_item;
+    const int rem = tt % per_item;
     // (past the end: a harmless stand-in, so that the dummy fetches read valid memory)
-    const int4 su = x.valid ? items[it] : make_int4(0, 0, 0, seq_tag(1, 0));
+    const int4 su = x.valid ? items[tt / per_item] : make_int4(0, 0, 0, seq_tag(1, 0));
     x.s = su.x, x.unit = su.y, x.L = su.z, x.n = tag_rows(su.w), x.base = tag_base(su.w);
     x.kvh = rem / y_blocks, x.yb = rem % y_blocks;
     x.k_lo = SEQ ? 0 : x.unit * UNIT;
@@ -1068,12 +1076,12 @@ __global__ __launch_bounds__(256) void attention_plan_kernel(const int32_t* __re
 // Fold the partials of every query row (chunks inside a super left to right, then the supers
 // left to right) and write the normalised output, bf16, into the tile layout of the
 // O-projection's activation operand.  One thread per (row, 4 features).  Sequences of up to done_keys keys have their output already.
-template <int HD, bool SUPER>
+template <int HD, bool SUPER, bool EARLY = false>
 __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const float* __restrict__ part_ml,
                                        const int32_t* __restrict__ seq_len, const int32_t* __restrict__ seq_n,
                                        int n_kv_heads, int group, int window, int r_pad, int n_units, int d_attn,
                                        uint16_t* __restrict__ out, const int32_t* __restrict__ seq_mode, int done_keys) {
-  if (SUPER && *seq_mode) return;       // the attention kernel took whole sequences and wrote the output itself
+  if (SUPER && seq_mode && *seq_mode) return;       // the attention kernel took whole sequences and wrote the output itself
   constexpr int QUADS = HD / 4;
   const int quad = threadIdx.x % QUADS;
   const int at = blockIdx.y * (blockDim.x / QUADS) + threadIdx.x / QUADS;   // (pairs can outnumber what grid.y allows)
@@ -1084,12 +1092,12 @@ __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const
   const size_t base = ((size_t)s * n_kv_heads + kvh) * n_units;
   auto slot_ml = [&](int u) { return *(const float2*)(part_ml + ((base + u) * r_pad + r) * 2); };
   auto slot_acc = [&](int u) { return *(const f32x4*)(part_acc + ((base + u) * r_pad + r) * HD + quad * 4); };
-  // Chunks: the first partials are requested together with the length that says which of them there are (a round trip less: with
-  // attention_wave_kernel, 1 - 32 sequences of 300 keys, 1.4 us a layer).
+  // EARLY: the first partials are requested together with the length that says which of them there are (a round trip less: behind
+  // attention_wave_kernel, 1 - 32 sequences of 300 keys, 1.4 us a layer; with 128 rows each the ones too many cost 1 us).
   constexpr int U = SUPER ? 1 : 4;
   float2 ml[U];
   f32x4 acc[U];
-  if (!SUPER) {
+  if (EARLY) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       ml[u] = slot_ml(min(u, n_units - 1));
@@ -1124,7 +1132,7 @@ __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const
     float m2 = 0.f, l2 = 0.f;
     f32x4 a2[1] = {(f32x4){0.f, 0.f, 0.f, 0.f}};
     for (int c0 = 0; c0 <= last; c0 += U) {
-      if (c0 > 0) {
+      if (!EARLY || c0 > 0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           ml[u] = slot_ml(min(c0 + u, last));
@@ -1149,7 +1157,14 @@ __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const
   *dst = o;
 }
 
-template <int HD, int CB, int NW, bool SUPER>
+// Entries of attention_kernel's ring for chunk items: two at head dimension 128, so that a CU holds two workgroups and one
+// computes while the other waits for its item's first tiles, and the items dealt out in turn instead of by a counter whose answer is
+// waited for.  us per layer less than with one workgroup, four entries and the counter: 2 row blocks, 2 sequences of up to 16000 keys
+// 8.6; 4 row blocks, 8 x 1900 keys 7.8, 4 x 1900 2.1, 1 x 1900 0.9.
+template <int HD>
+constexpr int kChunkRing = HD == 128 ? 2 : 4;
+
+template <int HD, int CB, int NW, bool SUPER, int NBUF = 4>
 void launch_one(const llm42_model* m, int layer, const uint16_t* kp, const uint16_t* vp, const llm42_kv_cache* kv,
                 int num_seqs, int window, const Workspace& ws, hipStream_t st) {
   const llm42_config& c = m->cfg;
@@ -1158,17 +1173,16 @@ void launch_one(const llm42_model* m, int layer, const uint16_t* kp, const uint1
   const int y_blocks = (col_blocks + NW * CB - 1) / (NW * CB);
   // one workgroup per CU (the KV ring takes 128 KiB of LDS at head_dim 128), but no more than there can be items
   const long long max_items = (long long)num_seqs * ws.attn_units * c.n_kv_heads * y_blocks;
-  const unsigned grid = (unsigned)std::min<long long>(m->num_cus * (HD == 128 ? 1 : 2), max_items);
-  attention_kernel<HD, CB, NW, SUPER><<<grid, NW * 64, 0, st>>>(
-      ws.q, (const uint4*)kp, (const uint4*)vp, kv->block_table, ws.seq_len, ws.seq_n, ws.attn_items, ws.attn_ctrl,
-      ws.attn_ctrl + 1 + layer, c.n_kv_heads, m->group, ws.r_pad, y_blocks, kv->max_blocks_per_seq,
+  const unsigned grid = (unsigned)std::min<long long>(m->num_cus * (HD == 128 ? 1 : 2) * (NBUF == 2 ? 2 : 1), max_items);
+  attention_kernel<HD, CB, NW, SUPER, NBUF><<<grid, NW * 64, 0, st>>>(
+      ws.q, (const uint4*)kp, (const uint4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl, ws.attn_ctrl + 1 + layer, c.n_kv_heads, m->group, ws.r_pad, y_blocks, kv->max_blocks_per_seq,
       ws.attn_units, scale_log2, ws.part_acc, ws.part_ml, SUPER && ws.attn_direct ? ws.attn : nullptr, m->d_attn);
   if (SUPER && ws.attn_direct) return;
   const int rows = m->group * window, rows_per_block = 256 / (HD / 4);
   attention_merge_kernel<HD, SUPER><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256,
                                       0, st>>>(ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, m->group,
                                                window, ws.r_pad, ws.attn_units, m->d_attn, ws.attn,
-                                               ws.attn_ctrl + 1 + c.n_layers, 0);
+                                               ws.attn_seq ? ws.attn_ctrl + 1 + c.n_layers : nullptr, 0);
 }
 
 // Workgroups of a stream-kernel launch: one per CU at head_dim 128 (two at 64), no more than there are items.
@@ -1187,13 +1201,13 @@ void launch_stream(const llm42_model* m, const uint16_t* kp, const uint16_t* vp,
   attention_stream_kernel<HD, SUPER, FOLD, SEQ><<<grid, 512, 0, st>>>(
       ws.q, (const uint4*)kp, (const uint4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl, c.n_kv_heads, m->group,
       ws.r_pad, y_blocks, kv->max_blocks_per_seq, ws.attn_units, scale_log2, ws.part_acc, ws.part_ml,
-      SEQ || (SUPER && ws.attn_direct) ? ws.attn : nullptr, m->d_attn, ws.attn_ctrl + 1 + c.n_layers);
+      SEQ || (SUPER && ws.attn_direct) ? ws.attn : nullptr, m->d_attn, ws.attn_seq ? ws.attn_ctrl + 1 + c.n_layers : nullptr);
   if (SEQ || (SUPER && ws.attn_direct)) return;
   const int rows = m->group * window, rows_per_block = 256 / (HD / 4);
   attention_merge_kernel<HD, SUPER><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256,
                                       0, st>>>(ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, m->group,
                                                window, ws.r_pad, ws.attn_units, m->d_attn, ws.attn,
-                                               ws.attn_ctrl + 1 + c.n_layers, 0);
+                                               ws.attn_seq ? ws.attn_ctrl + 1 + c.n_layers : nullptr, 0);
 }
 
 template <int HD>
@@ -1221,17 +1235,15 @@ void launch_waves(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, 
   attention_wave_kernel<HD><<<grid, 256, 0, st>>>(ws.q, (const bf16x8*)kp, (const u32x4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl,
                                                   c.n_kv_heads, m->group, ws.r_pad, kv->max_blocks_per_seq, ws.attn_units,
                                                   ws.part_rows, num_seqs * ws.attn_units, scale_log2, ws.part_acc, ws.part_ml, ws.attn, m->d_attn);
-  attention_merge_kernel<HD, false><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256, 0, st>>>(
+  attention_merge_kernel<HD, false, true><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256, 0, st>>>(
       ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, m->group, window, ws.part_rows, ws.attn_units, m->d_attn, ws.attn,
-      ws.attn_ctrl + 1 + c.n_layers, CHUNK);
+      nullptr, CHUNK);
 }
 
 template <int HD>
 void launch_hd(const llm42_model* m, int layer, const uint16_t* kp, const uint16_t* vp, const llm42_kv_cache* kv,
                int num_seqs, int window, const Workspace& ws, hipStream_t st) {
-  // 8 row blocks or more per (sequence, kv head): 8 waves of one row block each, two per SIMD, so
-  // that one wave's MFMAs run under the other's softmax arithmetic, as one stream per CU; fewer: 4 waves.
-  const bool wide = ws.r_pad / 16 >= 8;
+  const bool wide = attention_streams(m, num_seqs, ws);
   // (a call that may take whole sequences as items launches that kernel too; the plan's choice, made on the device
   // from the lengths, leaves one of the two with nothing to do)
   if constexpr (HD == 128) {
@@ -1251,7 +1263,7 @@ void launch_hd(const llm42_model* m, int layer, const uint16_t* kp, const uint16
     else launch_one<HD, 1, 4, true>(m, layer, kp, vp, kv, num_seqs, window, ws, st);
   } else {
     if (wide) launch_stream<HD, false, true>(m, kp, vp, kv, num_seqs, window, ws, st);
-    else launch_one<HD, 1, 4, false>(m, layer, kp, vp, kv, num_seqs, window, ws, st);
+    else launch_one<HD, 1, 4, false, kChunkRing<HD>>(m, layer, kp, vp, kv, num_seqs, window, ws, st);
   }
 }
 
@@ -1265,6 +1277,16 @@ void launch_attention_plan(const llm42_model* m, int num_seqs, int max_context, 
                                            seq_unit_keys, seq_per_item, (int)stream_grid(m, num_seqs, 1, ws.r_pad),
                                            ws.attn_items, ws.attn_ctrl, ws.attn_ctrl + 1, m->cfg.n_layers,
                                            ws.attn_ctrl + 1 + m->cfg.n_layers);
+}
+
+// 8 row blocks or more per (sequence, kv head): 8 waves of one row block each, two per SIMD, so that one wave's MFMAs run under the
+// other's softmax arithmetic, as one stream per CU; fewer: 4 waves.  So do chunks of which there are no more than four row blocks'
+// worth for two workgroups a CU (us per layer less: prefill of 700 tokens by 256 2.3, 4 x 32 behind 512 keys 2.2, 1 x 64 behind
+// 1900 1.4; where there are more they take longer, 8 x 32 behind 1900 7.3: K and V are fetched twice).
+bool attention_streams(const llm42_model* m, int num_seqs, const Workspace& ws) {
+  const int blocks = ws.r_pad / 16;
+  const long long items = (long long)num_seqs * ws.attn_units * m->cfg.n_kv_heads * ((blocks + 3) / 4);
+  return blocks >= 8 && (ws.attn_super || m->cfg.head_dim != 128 || items > 2LL * m->num_cus);
 }
 
 int attention_units(bool super_mode, int max_context) {

@@ -187,6 +187,7 @@ int launch_gemm_logits(const llm42_model* m, int window, float* out_logits, cons
                        const Workspace& ws, hipStream_t st);
 
 int attention_units(bool super_mode, int max_context);
+bool attention_streams(const llm42_model* m, int num_seqs, const Workspace& ws);   // by the 8-wave kernel
 void launch_attention_plan(const llm42_model* m, int num_seqs, int max_context, const Workspace& ws, hipStream_t st);
 void launch_attention(const llm42_model* m, int layer, const llm42_kv_cache* kv, int num_seqs, int window,
                       int max_context, const Workspace& ws, hipStream_t st);

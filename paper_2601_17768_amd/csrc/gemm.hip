@@ -15,6 +15,15 @@ using namespace gemm;
 
 namespace {
 
+// Byte offset, in an activation operand, of what lane `lane` takes of a tile of token block `block` at k-tile 0: its row's 16 bytes, or
+// those of the last row that there is.  Rows that only pad are not fetched then (a line holds 8 rows): every workgroup reads all
+// activations, at 32 rows twice as many bytes as its share of the weights (8B, us a decode step: 1 row 3244 -> 3141, 24 rows
+// 3854 -> 3721).
+__device__ __forceinline__ uint32_t row_offset(int block, int lane, int last_row, int k_tiles) {
+  const int row = min(block * 16 + (lane & 15), last_row);
+  return (uint32_t)(row >> 4) * (uint32_t)k_tiles * 1024u + (uint32_t)((lane >> 4) * 16 + (row & 15)) * 16u;
+}
+
 // Small-batch kernel for narrow outputs (at most 64 tokens): bound by the weight stream, with one workgroup on every CU.  A
 // workgroup owns NBW blocks of 16 features over one k range (a half of a split GEMM: blockIdx.y) and all MB token blocks.
 // F waves do nothing but fetch: per k-tile the NBW weight and MB activation tiles go from global memory straight into a ring
@@ -28,7 +37,7 @@ namespace {
 template <int NBW, int MB, int CH, int R, int F, class Epi>
 __global__ __launch_bounds__(64 * (NBW * MB + F)) void gemm_narrow_kernel(const bf16x8* __restrict__ w,
                                                                          const bf16x8* __restrict__ x, int n_blocks,
-                                                                         int k_tiles, int split, Epi epi) {
+                                                                         int k_tiles, int split, int last_row, Epi epi) {
   constexpr int ST = NBW + MB;                       // operand tiles per k-tile
   constexpr int PW = CH * ST / F;                    // tiles a fetching wave requests per round
   static_assert(CH * ST % F == 0, "the fetching waves take equal shares");
@@ -43,16 +52,18 @@ __global__ __launch_bounds__(64 * (NBW * MB + F)) void gemm_narrow_kernel(const 
     const uint32_t dst = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0][0];
     const bf16x8* src[PW];
     int kt[PW];
+    uint32_t at[PW];
 #pragma unroll
     for (int i = 0; i < PW; ++i) {
       const int q = fw * PW + i, op = q % ST;
       kt[i] = q / ST;
-      src[i] = (op < NBW ? w + (size_t)min(n0 + op, n_blocks - 1) * k_tiles * 64 : x + (size_t)(op - NBW) * k_tiles * 64) + (size_t)k_begin * 64;
+      src[i] = (op < NBW ? w + (size_t)min(n0 + op, n_blocks - 1) * k_tiles * 64 : x) + (size_t)k_begin * 64;
+      at[i] = op < NBW ? lane * 16u : row_offset(op - NBW, lane, last_row, k_tiles);
     }
     auto fetch = [&](int r) {
 #pragma unroll
       for (int i = 0; i < PW; ++i) {
-        const uint32_t off = (uint32_t)min(r * CH + kt[i], k_count - 1) * 1024u + lane * 16u;
+        const uint32_t off = (uint32_t)min(r * CH + kt[i], k_count - 1) * 1024u + at[i];
         const uint32_t d = dst + (uint32_t)(((r % R) * CH * ST + fw * PW + i) * 1024);
         if ((fw * PW + i) % ST < NBW) lds_fetch_1k<true>(src[i], off, d);
         else lds_fetch_1k(src[i], off, d);
@@ -96,7 +107,7 @@ __global__ __launch_bounds__(64 * (NBW * MB + F)) void gemm_narrow_kernel(const 
 // gemm_narrow_kernel, on half the CUs here, takes 37 and 45.
 template <int MB, int CH, int R, int F, class Epi>
 __global__ __launch_bounds__(64 * (MB + F)) void gemm_ring_kernel(const bf16x8* __restrict__ w,
-                                                                  const bf16x8* __restrict__ x, int k_tiles, Epi epi) {
+                                                                  const bf16x8* __restrict__ x, int k_tiles, int last_row, Epi epi) {
   constexpr int PW = CH / F;                         // weight tiles a fetching wave requests per round
   static_assert(CH % F == 0, "the fetching waves take equal shares");
   __shared__ bf16x8 ring[R][CH * 64];
@@ -121,7 +132,7 @@ __global__ __launch_bounds__(64 * (MB + F)) void gemm_ring_kernel(const bf16x8* 
       if (r + R - 1 < rounds) fetch(r + R - 1);   // into the slot of round r - 1
     }
   } else {
-    const bf16x8* xp = x + (size_t)wave * k_tiles * 64 + lane;
+    const bf16x8* xp = x + row_offset(wave, lane, last_row, k_tiles) / 16;
     const int row = wave * 16 + (lane & 15);
     bf16x8 xa[CH], xb[CH];
     auto load_x = [&](bf16x8(&dst)[CH], int r) __attribute__((always_inline)) {
@@ -163,7 +174,7 @@ __global__ __launch_bounds__(64 * (MB + F)) void gemm_ring_kernel(const bf16x8* 
 // activations (this makes the grid of the 8B gate/up GEMM exactly one workgroup per CU).
 template <int MB, int NBW, class Epi>
 __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restrict__ w, const bf16x8* __restrict__ x,
-                                                          int n_blocks, int k_tiles, Epi epi) {
+                                                          int n_blocks, int k_tiles, int last_row, Epi epi) {
   // A round is CH k-tiles; NSET register sets of weights: one in use, NSET - 1 in flight (16 KiB per
   // wave whatever the round length).  The round's activation tiles go through LDS, double buffered.
   constexpr int CH = MB <= 2 ? 16 : 8, NSET = 16 / CH + 1, NW = 8;
@@ -174,7 +185,9 @@ __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restri
   const bool owner = wave < NBW && blockIdx.x * NBW + wave < n_blocks;   // other waves only fetch activations
   const int nb = owner ? blockIdx.x * NBW + wave : 0;
   const bf16x8* wp = w + (size_t)nb * k_tiles * 64 + lane;
-  const bf16x8* xp = x + lane;
+  const bf16x8* xp[MB];                              // this lane's share of the token blocks' first tiles
+#pragma unroll
+  for (int b = 0; b < MB; ++b) xp[b] = x + row_offset(b, lane, last_row, k_tiles) / 16;
   f32x4 acc[MB];
 #pragma unroll
   for (int b = 0; b < MB; ++b) acc[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -193,7 +206,7 @@ __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restri
 #pragma unroll
     for (int i = 0; i < XT; ++i) {
       const int q = i * NW + wave;
-      xg[i] = xp[((size_t)(q / CH) * k_tiles + r * CH + q % CH) * 64];
+      xg[i] = xp[i * NW / CH][(size_t)(r * CH + q % CH) * 64];
     }
   };
   auto store_x = [&](int buf) {
@@ -279,7 +292,7 @@ __global__ __launch_bounds__(512) void gemm_xshare_kernel(const bf16x8* __restri
   for (int kt = rounds * CH; owner && kt < k_tiles; ++kt) {   // tail of fewer than CH tiles: tile by tile
     const bf16x8 a = wp[(size_t)kt * 64];
 #pragma unroll
-    for (int b = 0; b < MB; ++b) acc[b] = mfma16(a, xp[((size_t)b * k_tiles + kt) * 64], acc[b]);
+    for (int b = 0; b < MB; ++b) acc[b] = mfma16(a, xp[b][(size_t)kt * 64], acc[b]);
   }
   if (owner) {
 #pragma unroll
@@ -306,12 +319,12 @@ void launch_narrow(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles
     // and 121 by the ring, 5120 x 13824 42 and 48 against 49 and 58.
     if (n_blocks <= ws.num_cus) {
       if constexpr (std::is_same<Epi, ResidualEpi>::value) {
-        if (ws.m_pad == 32) gemm_ring_kernel<2, 16, 5, 2, Epi><<<n_blocks, 64 * 4, 0, st>>>(wp, xp, k_tiles, epi);
-        else gemm_ring_kernel<4, 16, 5, 2, Epi><<<n_blocks, 64 * 6, 0, st>>>(wp, xp, k_tiles, epi);
+        if (ws.m_pad == 32) gemm_ring_kernel<2, 16, 5, 2, Epi><<<n_blocks, 64 * 4, 0, st>>>(wp, xp, k_tiles, ws.m_rows - 1, epi);
+        else gemm_ring_kernel<4, 16, 5, 2, Epi><<<n_blocks, 64 * 6, 0, st>>>(wp, xp, k_tiles, ws.m_rows - 1, epi);
       } else {
-        if (ws.m_pad == 16) gemm_narrow_kernel<1, 1, 8, 4, 4, Epi><<<n_blocks, 64 * 5, 0, st>>>(wp, xp, n_blocks, k_tiles, split, epi);
-        else if (ws.m_pad == 32) gemm_narrow_kernel<1, 2, 4, 5, 4, Epi><<<n_blocks, 64 * 6, 0, st>>>(wp, xp, n_blocks, k_tiles, split, epi);
-        else gemm_narrow_kernel<1, 4, 4, 6, 4, Epi><<<n_blocks, 64 * 8, 0, st>>>(wp, xp, n_blocks, k_tiles, split, epi);
+        if (ws.m_pad == 16) gemm_narrow_kernel<1, 1, 8, 4, 4, Epi><<<n_blocks, 64 * 5, 0, st>>>(wp, xp, n_blocks, k_tiles, split, ws.m_rows - 1, epi);
+        else if (ws.m_pad == 32) gemm_narrow_kernel<1, 2, 4, 5, 4, Epi><<<n_blocks, 64 * 6, 0, st>>>(wp, xp, n_blocks, k_tiles, split, ws.m_rows - 1, epi);
+        else gemm_narrow_kernel<1, 4, 4, 6, 4, Epi><<<n_blocks, 64 * 8, 0, st>>>(wp, xp, n_blocks, k_tiles, split, ws.m_rows - 1, epi);
       }
       return;
     }
@@ -320,9 +333,9 @@ void launch_narrow(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles
   auto go = [&](const auto& e) {
     using E = std::decay_t<decltype(e)>;
     // (ring depths within a few percent of each other: what counts is four fetching waves and few barriers)
-    if (ws.m_pad == 16) gemm_narrow_kernel<2, 1, 8, 4, 4, E><<<grid, 64 * 6, 0, st>>>(wp, xp, n_blocks, k_tiles, split, e);
-    else if (ws.m_pad == 32) gemm_narrow_kernel<2, 2, 4, 5, 4, E><<<grid, 64 * 8, 0, st>>>(wp, xp, n_blocks, k_tiles, split, e);
-    else gemm_narrow_kernel<2, 4, 4, 6, 4, E><<<grid, 64 * 12, 0, st>>>(wp, xp, n_blocks, k_tiles, split, e);
+    if (ws.m_pad == 16) gemm_narrow_kernel<2, 1, 8, 4, 4, E><<<grid, 64 * 6, 0, st>>>(wp, xp, n_blocks, k_tiles, split, ws.m_rows - 1, e);
+    else if (ws.m_pad == 32) gemm_narrow_kernel<2, 2, 4, 5, 4, E><<<grid, 64 * 8, 0, st>>>(wp, xp, n_blocks, k_tiles, split, ws.m_rows - 1, e);
+    else gemm_narrow_kernel<2, 4, 4, 6, 4, E><<<grid, 64 * 12, 0, st>>>(wp, xp, n_blocks, k_tiles, split, ws.m_rows - 1, e);
   };
   if constexpr (SPLIT == 2) go(StorePartialEpi{ws.split_part, ws.rl, n, (size_t)ws.m_pad * n});
   else go(epi);
@@ -358,13 +371,13 @@ void launch_wide(const bf16x8* wp, const bf16x8* xp, int n_blocks, int k_tiles, 
   const bool seven = ((g7 + 255) / 256) * 7 < ((g8 + 255) / 256) * 8;
   const unsigned gx = (unsigned)(seven ? g7 : g8);
   if (seven) {
-    if (ws.m_pad == 16) gemm_xshare_kernel<1, 7, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
-    else if (ws.m_pad == 32) gemm_xshare_kernel<2, 7, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
-    else gemm_xshare_kernel<4, 7, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
+    if (ws.m_pad == 16) gemm_xshare_kernel<1, 7, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, ws.m_rows - 1, epi);
+    else if (ws.m_pad == 32) gemm_xshare_kernel<2, 7, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, ws.m_rows - 1, epi);
+    else gemm_xshare_kernel<4, 7, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, ws.m_rows - 1, epi);
   } else {
-    if (ws.m_pad == 16) gemm_xshare_kernel<1, 8, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
-    else if (ws.m_pad == 32) gemm_xshare_kernel<2, 8, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
-    else gemm_xshare_kernel<4, 8, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, epi);
+    if (ws.m_pad == 16) gemm_xshare_kernel<1, 8, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, ws.m_rows - 1, epi);
+    else if (ws.m_pad == 32) gemm_xshare_kernel<2, 8, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, ws.m_rows - 1, epi);
+    else gemm_xshare_kernel<4, 8, Epi><<<gx, 512, 0, st>>>(wp, xp, n_blocks, k_tiles, ws.m_rows - 1, epi);
   }
 }
 

@@ -271,7 +271,7 @@ llm42_status run_pass(const llm42_model* m, const llm42_kv_cache* kv, const int3
   for (int l = 0; l < c.n_layers; ++l) {
     const llm42_model::Layer& ly = m->layers[l];
     TIMED(LLM42_K_RMSNORM, launch_rmsnorm(pending, ly.attn_norm, c.d_model, c.rms_eps, ws, st));
-    TIMED(LLM42_K_QKV, launch_gemm_qkv(m, l, kv, ws, st));
+    TIMED(LLM42_K_QKV, launch_gemm_qkv(m, l, kv, window, ws, st));
     TIMED(LLM42_K_ATTENTION, launch_attention(m, l, kv, num_seqs, window, max_context, ws, st));
     if (prefill_pass && l + 1 == c.n_layers) return LLM42_OK;   // the rest is run once, for the rows that need it (see llm42_prefill)
     pending = run_mlp(m, ly, ws, st);

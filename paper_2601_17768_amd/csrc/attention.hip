@@ -20,7 +20,7 @@
 //
 // Work distribution (free to change, does not touch the bits): a workgroup owns one unit of the keys
 // of a (sequence, kv head) for 8 blocks of 16 query rows (attention_stream_kernel, 8 waves) or up to 4
-// (attention_kernel, 4 waves).  Query rows are ordered r = i * group + q_head_in_group: those that a partly filled window
+// (attention_kernel, 4 waves).  Query rows are ordered by token (RowOrder): those that a partly filled window
 // lacks come last, and blocks of 16 without any row are left out (27 sequences, 516 of 999 rows: 43.5 -> 28.4 us a launch against
 // r = q_head_in_group * window + i, where every block has some).  A unit is
 //   a chunk          - few sequences: most parallelism; chunk partials are written and the merge
@@ -125,9 +125,9 @@ __device__ __forceinline__ float rows_sum(float x) {
 // writes 8 consecutive features of every second block d (16 bytes per lane and store, half as many stores).
 // Called by all four lanes of a row or by none.
 template <int HD>
-__device__ __forceinline__ void store_output(uint16_t* __restrict__ out, int d_attn, int base, int kvh, int group,
+__device__ __forceinline__ void store_output(uint16_t* __restrict__ out, int d_attn, int base, int kvh, RowOrder order,
                                              int r, int g, const f32x4 (&acc)[HD / 16], float l) {
-  const int i = r / group, hq = kvh * group + r % group;
+  const int i = order.token(r), hq = kvh * order.group + order.head(r);
   const bool odd = g & 1;
 #pragma unroll
   for (int d = 0; d < HD / 16; d += 2) {
@@ -277,7 +277,7 @@ template <int HD, int CB, int NW, bool SUPER, int NBUF>
 __global__ __launch_bounds__(NW * 64, NBUF == 2 ? 2 : 1) void attention_kernel(
     const uint16_t* __restrict__ q, const uint4* __restrict__ k_plane, const uint4* __restrict__ v_plane,
     const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count, int32_t* __restrict__ queue,
-    int n_kv_heads, int group, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
+    int n_kv_heads, RowOrder order, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
     float scale_log2, float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out,
     int d_attn) {
   constexpr int DK = HD / 32;        // MFMA k-steps over the head dimension (scores)
@@ -304,7 +304,7 @@ __global__ __launch_bounds__(NW * 64, NBUF == 2 ? 2 : 1) void attention_kernel(
   // NW * CB blocks of 16 query rows.  (A return leaves the item; every condition is workgroup-uniform.)
   auto run_item = [&](const int4 su, const int yb, const int kvh) {
   const int s = su.x, unit = su.y, L = su.z, tag = su.w, n = tag_rows(tag);
-  if (yb * NW * CB * 16 >= n * group) return;                // whole workgroup: no live row
+  if (yb * NW * CB * 16 >= n * order.group) return;                // whole workgroup: no live row
   const int k_lo = unit * UNIT;
   const int32_t* bt = block_table + (size_t)s * max_blocks_per_seq;
   // Requested before anything is known about the sequence, so that the three latencies (lengths,
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(NW * 64, NBUF == 2 ? 2 : 1) void attention_kernel(
   int wmax = -1, wmin = 0x7FFFFFFF;   // highest and lowest position among this wave's live rows
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
-    const int i = row[cb] / group;
+    const int i = order.token(row[cb]);
     qpos[cb] = i < n ? L + i : -1;
     wmax = max(wmax, qpos[cb]);
     if (qpos[cb] >= 0) wmin = min(wmin, qpos[cb]);
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(NW * 64, NBUF == 2 ? 2 : 1) void attention_kernel(
   for (int cb = 0; cb < CB; ++cb) {
     if (qpos[cb] < k_lo) continue;
     if (SUPER && attn_out) {   // (one unit per sequence: no partial, no merge pass)
-      store_output<HD>(attn_out, d_attn, tag_base(tag), kvh, group, row[cb], g, sacc[cb], sl[cb]);
+      store_output<HD>(attn_out, d_attn, tag_base(tag), kvh, order, row[cb], g, sacc[cb], sl[cb]);
       continue;
     }
     const size_t prow = (((size_t)s * n_kv_heads + kvh) * n_units + unit) * r_pad + row[cb];
@@ -490,7 +490,7 @@ template <int HD, bool SUPER, bool FOLD, bool SEQ = false>
 __global__ __launch_bounds__(512) void attention_stream_kernel(
     const uint16_t* __restrict__ q, const uint4* __restrict__ k_plane, const uint4* __restrict__ v_plane,
     const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count,
-    int n_kv_heads, int group, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
+    int n_kv_heads, RowOrder order, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
     float scale_log2, float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out,
     int d_attn, const int32_t* __restrict__ seq_mode) {
   if (seq_mode && (*seq_mode != 0) != SEQ) return;   // the plan chose the other kind of item for this call (workgroup-uniform)
@@ -529,7 +529,7 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     x.k_lo = SEQ ? 0 : x.unit * UNIT;
     x.k_hi = SEQ ? x.L + x.n : min(x.L + x.n, x.k_lo + UNIT);
     // (row blocks without a live row: the query entry only)
-    x.n_steps = x.yb * NW * 16 < x.n * group ? (x.k_hi - x.k_lo + STEP - 1) / STEP : 0;
+    x.n_steps = x.yb * NW * 16 < x.n * order.group ? (x.k_hi - x.k_lo + STEP - 1) / STEP : 0;
     return x;
   };
 
@@ -592,13 +592,13 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     int row[CB], qpos[CB];
     row[0] = (c.yb * NW + wave) * 16 + col;
     {
-      const int i = row[0] / group;
+      const int i = order.token(row[0]);
       qpos[0] = i < c.n ? c.L + i : -1;
     }
     int wmin = qpos[0] >= 0 ? qpos[0] : 0x7FFFFFFF;   // lowest position among this wave's live rows (-1: none, it only fetches)
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) wmin = min(wmin, __shfl_xor(wmin, off));
-    wmin = (c.yb * NW + wave) * 16 < c.n * group ? __builtin_amdgcn_readfirstlane(wmin) : -1;
+    wmin = (c.yb * NW + wave) * 16 < c.n * order.group ? __builtin_amdgcn_readfirstlane(wmin) : -1;
     float m[CB] = {-INFINITY}, l[CB] = {0.f}, sm[CB] = {-INFINITY}, sl[CB] = {0.f};
     f32x4 acc[CB][DB], sacc[CB][DB];
     float tm = -INFINITY, tl = 0.f;   // SEQ: running fold of finished supers
@@ -610,8 +610,14 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
       tacc[d] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
     entry_done();
-    // -- one entry per step
-    for (int j = 0; j < c.n_steps; ++j) {
+    // -- one entry per step.  A wave without live rows only fetches, in a loop of its own: as a branch around the masked step it
+    // changed the registers of the loop below (whole sequences 232 -> 216, others 200 -> 183).
+    if (wmin < 0) {
+      for (int j = 0; j < c.n_steps; ++j) {
+        fetch_next(gidx + AHEAD);
+        entry_done();
+      }
+    } else for (int j = 0; j < c.n_steps; ++j) {
       fetch_next(gidx + AHEAD);
       const int k0 = c.k_lo + j * STEP;
       const uint4* sk = &ring[gidx & (NBUF - 1)][0];
@@ -623,7 +629,7 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
       const bool first = SUPER && FOLD ? (j & 3) == 0 : j == 0;   // the chunk partial is empty
       if (k0 + STEP - 1 <= wmin)                               // wave-uniform
         softmax_step<HD, CB, false>(sk, sv, k0, c.k_hi, lane, scale_log2, qf, qpos, m, l, acc, first);
-      else if (wmin >= 0)
+      else
         softmax_step<HD, CB, true>(sk, sv, k0, c.k_hi, lane, scale_log2, qf, qpos, m, l, acc, first);
       if (SUPER && FOLD && ((j & 3) == 3 || j + 1 == c.n_steps)) {
         // a chunk is complete: fold it into the running super partial and start the next one afresh
@@ -655,10 +661,10 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     }
     // -- partial of this unit for every row that reaches into it
     if (SEQ) {
-      if (qpos[0] >= 0) store_output<HD>(attn_out, d_attn, c.base, c.kvh, group, row[0], g, tacc, tl);
+      if (qpos[0] >= 0) store_output<HD>(attn_out, d_attn, c.base, c.kvh, order, row[0], g, tacc, tl);
     } else if (SUPER && attn_out) {   // one unit per sequence: no partial, no merge pass
       if (qpos[0] >= 0)
-        store_output<HD>(attn_out, d_attn, c.base, c.kvh, group, row[0], g, FOLD ? sacc[0] : acc[0], FOLD ? sl[0] : l[0]);
+        store_output<HD>(attn_out, d_attn, c.base, c.kvh, order, row[0], g, FOLD ? sacc[0] : acc[0], FOLD ? sl[0] : l[0]);
     } else if (qpos[0] >= c.k_lo) {
       const size_t prow = (((size_t)c.s * n_kv_heads + c.kvh) * n_units + c.unit) * r_pad + row[0];
       float* pa = part_acc + prow * HD;
@@ -743,7 +749,7 @@ template <int HD>
 __global__ __launch_bounds__(256) void attention_split_kernel(
     const uint16_t* __restrict__ q, const bf16x8* __restrict__ k_plane, const u32x4* __restrict__ v_plane,
     const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_len, const int32_t* __restrict__ seq_n,
-    const int4* __restrict__ items, const int32_t* __restrict__ item_count, int num_seqs, int n_kv_heads, int group,
+    const int4* __restrict__ items, const int32_t* __restrict__ item_count, int num_seqs, int n_kv_heads, RowOrder order,
     int r_pad, int max_blocks_per_seq, float scale_log2, uint16_t* __restrict__ attn_out, int d_attn) {
   constexpr int DK = HD / 32, DB = HD / 16, TV4 = HD * 2, PER = SUPER_KEYS / CHUNK, NW = 4, SPC = CHUNK / STEP;
   static_assert(PER == 2 * NW, "two chunks of a super per wave");
@@ -766,7 +772,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(
 #pragma unroll
     for (int d = 0; d < DK; ++d) qf[d] = *(const bf16x8*)(qb + d * 512 + lane * 8);
     const int L = seq_len[s], tag = seq_n[s], n = tag_rows(tag);
-    const int row = rb * 16 + col, i = row / group;
+    const int row = rb * 16 + col, i = order.token(row);
     const int qpos = L >= 0 && i < n ? L + i : -1;
     int wmax = qpos, wmin = qpos >= 0 ? qpos : 0x7FFFFFFF;   // highest and lowest position among the block's live rows
 #pragma unroll
@@ -844,7 +850,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(
       u32x4 o;
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = pack2_bf16(A[0][e] / Ls, A[1][e] / Ls);
-      *(u32x4*)(attn_out + pk_off(tag_base(tag) + i, (kvh * group + row % group) * HD + f, d_attn)) = o;
+      *(u32x4*)(attn_out + pk_off(tag_base(tag) + i, (kvh * order.group + order.head(row)) * HD + f, d_attn)) = o;
     }
     __syncthreads();        // the partials are read before the next item's are written
   }
@@ -863,7 +869,7 @@ template <int HD>
 __global__ __launch_bounds__(256) void attention_wave_kernel(
     const uint16_t* __restrict__ q, const bf16x8* __restrict__ k_plane, const u32x4* __restrict__ v_plane,
     const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count, int n_kv_heads,
-    int group, int r_pad, int max_blocks_per_seq, int n_units, int part_rows, int max_items, float scale_log2,
+    RowOrder order, int r_pad, int max_blocks_per_seq, int n_units, int part_rows, int max_items, float scale_log2,
     float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out, int d_attn) {
   constexpr int DK = HD / 32, DB = HD / 16, TV4 = HD * 2;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -884,7 +890,7 @@ __global__ __launch_bounds__(256) void attention_wave_kernel(
 #pragma unroll
     for (int d = 0; d < DK; ++d) x.qf[d] = *(const bf16x8*)(qb + d * 512 + lane * 8);
     x.row = x.rb * 16 + col;
-    const int i = x.row / group;
+    const int i = order.token(x.row);
     x.qpos = i < tag_rows(x.tag) ? x.L + i : -1;
     int wmax = x.qpos, wmin = x.qpos >= 0 ? x.qpos : 0x7FFFFFFF;   // highest and lowest position among the block's live rows
 #pragma unroll
@@ -951,7 +957,7 @@ __global__ __launch_bounds__(256) void attention_wave_kernel(
           u32x4 o;
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[e] = pack2_bf16(acc[2 * p][e] / l, acc[2 * p + 1][e] / l);
-          *(u32x4*)(attn_out + pk_off(tag_base(c.tag) + c.row / group, (c.kvh * group + c.row % group) * HD + f0 + 32 * p, d_attn)) = o;
+          *(u32x4*)(attn_out + pk_off(tag_base(c.tag) + order.token(c.row), (c.kvh * order.group + order.head(c.row)) * HD + f0 + 32 * p, d_attn)) = o;
         }
       }
     } else if (c.qpos >= c.k_lo) {
@@ -1079,16 +1085,16 @@ __global__ __launch_bounds__(256) void attention_plan_kernel(const int32_t* __re
 template <int HD, bool SUPER, bool EARLY = false>
 __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const float* __restrict__ part_ml,
                                        const int32_t* __restrict__ seq_len, const int32_t* __restrict__ seq_n,
-                                       int n_kv_heads, int group, int window, int r_pad, int n_units, int d_attn,
+                                       int n_kv_heads, RowOrder order, int window, int r_pad, int n_units, int d_attn,
                                        uint16_t* __restrict__ out, const int32_t* __restrict__ seq_mode, int done_keys) {
   if (SUPER && seq_mode && *seq_mode) return;       // the attention kernel took whole sequences and wrote the output itself
   constexpr int QUADS = HD / 4;
   const int quad = threadIdx.x % QUADS;
   const int at = blockIdx.y * (blockDim.x / QUADS) + threadIdx.x / QUADS;   // (pairs can outnumber what grid.y allows)
   const int s = blockIdx.x / n_kv_heads, kvh = blockIdx.x % n_kv_heads;
-  if (at >= group * window) return;
+  if (at >= order.group * window) return;
   // (neighbouring threads take neighbouring tokens of one head, as the output lies; the partials' rows are 512 bytes each anyway)
-  const int i = at % window, hq = kvh * group + at / window, r = i * group + at / window;
+  const int i = at % window, hq = kvh * order.group + at / window, r = order.row(i, at / window);
   const size_t base = ((size_t)s * n_kv_heads + kvh) * n_units;
   auto slot_ml = [&](int u) { return *(const float2*)(part_ml + ((base + u) * r_pad + r) * 2); };
   auto slot_acc = [&](int u) { return *(const f32x4*)(part_acc + ((base + u) * r_pad + r) * HD + quad * 4); };
@@ -1175,12 +1181,12 @@ void launch_one(const llm42_model* m, int layer, const uint16_t* kp, const uint1
   const long long max_items = (long long)num_seqs * ws.attn_units * c.n_kv_heads * y_blocks;
   const unsigned grid = (unsigned)std::min<long long>(m->num_cus * (HD == 128 ? 1 : 2) * (NBUF == 2 ? 2 : 1), max_items);
   attention_kernel<HD, CB, NW, SUPER, NBUF><<<grid, NW * 64, 0, st>>>(
-      ws.q, (const uint4*)kp, (const uint4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl, ws.attn_ctrl + 1 + layer, c.n_kv_heads, m->group, ws.r_pad, y_blocks, kv->max_blocks_per_seq,
+      ws.q, (const uint4*)kp, (const uint4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl, ws.attn_ctrl + 1 + layer, c.n_kv_heads, row_order(m->group, window), ws.r_pad, y_blocks, kv->max_blocks_per_seq,
       ws.attn_units, scale_log2, ws.part_acc, ws.part_ml, SUPER && ws.attn_direct ? ws.attn : nullptr, m->d_attn);
   if (SUPER && ws.attn_direct) return;
   const int rows = m->group * window, rows_per_block = 256 / (HD / 4);
   attention_merge_kernel<HD, SUPER><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256,
-                                      0, st>>>(ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, m->group,
+                                      0, st>>>(ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, row_order(m->group, window),
                                                window, ws.r_pad, ws.attn_units, m->d_attn, ws.attn,
                                                ws.attn_seq ? ws.attn_ctrl + 1 + c.n_layers : nullptr, 0);
 }
@@ -1199,20 +1205,20 @@ void launch_stream(const llm42_model* m, const uint16_t* kp, const uint16_t* vp,
   const int y_blocks = (ws.r_pad / 16 + 7) / 8;
   const unsigned grid = (unsigned)stream_grid(m, num_seqs, SEQ ? 1 : ws.attn_units, ws.r_pad);
   attention_stream_kernel<HD, SUPER, FOLD, SEQ><<<grid, 512, 0, st>>>(
-      ws.q, (const uint4*)kp, (const uint4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl, c.n_kv_heads, m->group,
+      ws.q, (const uint4*)kp, (const uint4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl, c.n_kv_heads, row_order(m->group, window),
       ws.r_pad, y_blocks, kv->max_blocks_per_seq, ws.attn_units, scale_log2, ws.part_acc, ws.part_ml,
       SEQ || (SUPER && ws.attn_direct) ? ws.attn : nullptr, m->d_attn, ws.attn_seq ? ws.attn_ctrl + 1 + c.n_layers : nullptr);
   if (SEQ || (SUPER && ws.attn_direct)) return;
   const int rows = m->group * window, rows_per_block = 256 / (HD / 4);
   attention_merge_kernel<HD, SUPER><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256,
-                                      0, st>>>(ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, m->group,
+                                      0, st>>>(ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, row_order(m->group, window),
                                                window, ws.r_pad, ws.attn_units, m->d_attn, ws.attn,
                                                ws.attn_seq ? ws.attn_ctrl + 1 + c.n_layers : nullptr, 0);
 }
 
 template <int HD>
 void launch_split(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, const llm42_kv_cache* kv, int num_seqs,
-                  const Workspace& ws, hipStream_t st) {
+                  int window, const Workspace& ws, hipStream_t st) {
   const llm42_config& c = m->cfg;
   const float scale_log2 = (1.0f / sqrtf((float)c.head_dim)) * 1.44269504088896340736f;
   // As many workgroups as the device holds at once: one per CU at head dimension 128 (its 418 registers per wave), two at 64
@@ -1222,7 +1228,7 @@ void launch_split(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, 
   const unsigned grid = (unsigned)std::min<long long>((long long)kPerCu * m->num_cus, (long long)num_seqs * c.n_kv_heads * (ws.r_pad / 16));
   attention_split_kernel<HD><<<grid, 256, 0, st>>>(
       ws.q, (const bf16x8*)kp, (const u32x4*)vp, kv->block_table, ws.seq_len, ws.seq_n, ws.attn_list ? ws.attn_items : nullptr,
-      ws.attn_ctrl, num_seqs, c.n_kv_heads, m->group, ws.r_pad, kv->max_blocks_per_seq, scale_log2, ws.attn, m->d_attn);
+      ws.attn_ctrl, num_seqs, c.n_kv_heads, row_order(m->group, window), ws.r_pad, kv->max_blocks_per_seq, scale_log2, ws.attn, m->d_attn);
 }
 
 template <int HD>
@@ -1233,10 +1239,10 @@ void launch_waves(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, 
   const int rows = m->group * window, rows_per_block = 256 / (HD / 4);
   const unsigned grid = (unsigned)std::min<long long>(m->num_cus, (long long)num_seqs * ws.attn_units * c.n_kv_heads * (ws.r_pad / 16));
   attention_wave_kernel<HD><<<grid, 256, 0, st>>>(ws.q, (const bf16x8*)kp, (const u32x4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl,
-                                                  c.n_kv_heads, m->group, ws.r_pad, kv->max_blocks_per_seq, ws.attn_units,
+                                                  c.n_kv_heads, row_order(m->group, window), ws.r_pad, kv->max_blocks_per_seq, ws.attn_units,
                                                   ws.part_rows, num_seqs * ws.attn_units, scale_log2, ws.part_acc, ws.part_ml, ws.attn, m->d_attn);
   attention_merge_kernel<HD, false, true><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256, 0, st>>>(
-      ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, m->group, window, ws.part_rows, ws.attn_units, m->d_attn, ws.attn,
+      ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, row_order(m->group, window), window, ws.part_rows, ws.attn_units, m->d_attn, ws.attn,
       nullptr, CHUNK);
 }
 
@@ -1253,7 +1259,7 @@ void launch_hd(const llm42_model* m, int layer, const uint16_t* kp, const uint16
     }
   }
   if (ws.attn_split) {
-    launch_split<HD>(m, kp, vp, kv, num_seqs, ws, st);
+    launch_split<HD>(m, kp, vp, kv, num_seqs, window, ws, st);
     return;
   }
   if (ws.attn_seq) launch_stream<HD, true, true, true>(m, kp, vp, kv, num_seqs, window, ws, st);

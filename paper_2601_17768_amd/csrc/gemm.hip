@@ -452,7 +452,7 @@ void plan_gemms(const llm42_model* m, Workspace& ws) {
   ws.gemm[GEMM_LM_HEAD] = GemmPlan{ws.partly_filled ? pick_partly_filled(head, ws.m_pad) : pick_tile(head, ws.m_pad).tile, 0, 0, false};
 }
 
-void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, const Workspace& ws,
+void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, int window, const Workspace& ws,
                      hipStream_t st) {
   const llm42_config& c = m->cfg;
   const size_t plane = (size_t)kv->num_blocks * c.n_kv_heads * 16 * c.head_dim;
@@ -467,7 +467,7 @@ void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, 
   e.n_q_heads = c.n_q_heads;
   e.n_kv_heads = c.n_kv_heads;
   e.head_dim = c.head_dim;
-  e.group = m->group;
+  e.order = row_order(m->group, window);
   e.r_pad = ws.r_pad;
   launch_gemm<kSplit[GEMM_QKV]>(m->layers[layer].wqkv, ws.normed, m->n_qkv / 16, c.d_model, m->n_qkv, ws, ws.gemm[GEMM_QKV], e, st);
 }

@@ -14,10 +14,11 @@ struct QkvEpi {
   const int32_t* __restrict__ row_pos;
   const int32_t* __restrict__ row_seq;
   const int32_t* __restrict__ row_blk;    // physical KV block of the row's position
-  uint16_t* q;               // [seq][kv head][r_pad][head_dim] tile layout, r = i * group + q-head-in-group: rows that are not there come last
+  uint16_t* q;               // [seq][kv head][r_pad][head_dim] tile layout, r: see RowOrder
   uint16_t* k_plane;         // this layer's K tiles [block][kv head][16*head_dim]
   uint16_t* v_plane;
-  int n_q_heads, n_kv_heads, head_dim, group, r_pad;
+  int n_q_heads, n_kv_heads, head_dim, r_pad;
+  RowOrder order;
 
   // What the epilogue needs from memory besides the accumulators; requested when the kernel
   // starts so that its latency hides behind the weight stream.  Everything is indexed by the row
@@ -65,7 +66,7 @@ struct QkvEpi {
     }
     const uint32_t lo = pack2_bf16(lo0, lo1), hi = pack2_bf16(hi0, hi1);
     if (head < n_q_heads) {
-      const int kvh = head / group, r = tag_index(p.tag) * group + head % group;
+      const int kvh = head / order.group, r = order.row(tag_index(p.tag), head % order.group);
       uint16_t* base = q + ((size_t)s * n_kv_heads + kvh) * r_pad * head_dim;
       *(uint32_t*)(base + pk_off(r, j0, head_dim)) = lo;
       *(uint32_t*)(base + pk_off(r, j0 + half, head_dim)) = hi;

@@ -91,6 +91,21 @@ struct llm42_model {
 };
 
 // (at most 65536 rows, windows of at most 512)
+// Order of the query rows of a (sequence, kv head): `t` tokens at a time (a power of two that divides the window, and t * group
+// divides 16; else 1), heads outside: rows that a partly filled window lacks come last, and neighbouring tokens of a head, which
+// the QKV projection computes together, lie side by side (in the plain order of tokens, then heads, Q was written in 16-byte pieces:
+// 128 sequences x window 32, us a layer: attention 556, QKV 195.6; so 540 and 192.4).
+struct RowOrder {
+  int group, t;
+  __host__ __device__ int row(int i, int h) const { return (i & -t) * group + h * t + (i & (t - 1)); }
+  __host__ __device__ int token(int r) const { return r / (t * group) * t + (r & (t - 1)); }
+  __host__ __device__ int head(int r) const { return r % (t * group) / t; }
+};
+inline RowOrder row_order(int group, int window) {
+  int t = 16;
+  while (t > 1 && (16 % (t * group) || window % t)) t /= 2;
+  return {group, t};
+}
 __host__ __device__ inline int row_tag(int s, int i) { return s << 10 | i; }
 __host__ __device__ inline int tag_seq(int tag) { return tag >> 10; }
 __host__ __device__ inline int tag_index(int tag) { return tag & 1023; }
@@ -176,7 +191,7 @@ void launch_rmsnorm(bool pending, const uint16_t* gain, int d, float eps, const 
 // Fills ws.gemm: the same for every layer, so chosen once per pass (the rule takes 0.3 us a GEMM, and with partly filled windows
 // 1 - 13 us at 1024 - 16384 rows; a layer's ten launches take about 40).
 void plan_gemms(const llm42_model* m, Workspace& ws);
-void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, const Workspace& ws,
+void launch_gemm_qkv(const llm42_model* m, int layer, const llm42_kv_cache* kv, int window, const Workspace& ws,
                      hipStream_t st);
 // true: the residual stream is not complete yet; the halves are in split_part, for the RMSNorm that follows
 bool launch_gemm_residual(GemmKind kind, const uint16_t* w, const uint16_t* x, float* resid, int n, int k_padded,

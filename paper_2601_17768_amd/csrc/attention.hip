@@ -516,6 +516,7 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     bool valid;
     int s, kvh, yb, unit, L, n, base, k_lo, k_hi, n_steps;
   };
+  const int item_tokens = (NW * 16 + order.group - 1) / order.group;   // (at least those that an item's rows span)
   auto work_of = [&](int ord) {
     Work x;
     const int t = ord * G + ((ord & 1) ? G - 1 - w : w);
@@ -527,9 +528,12 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     x.s = su.x, x.unit = su.y, x.L = su.z, x.n = tag_rows(su.w), x.base = tag_base(su.w);
     x.kvh = rem / y_blocks, x.yb = rem % y_blocks;
     x.k_lo = SEQ ? 0 : x.unit * UNIT;
-    x.k_hi = SEQ ? x.L + x.n : min(x.L + x.n, x.k_lo + UNIT);
-    // (row blocks without a live row: the query entry only)
-    x.n_steps = x.yb * NW * 16 < x.n * order.group ? (x.k_hi - x.k_lo + STEP - 1) / STEP : 0;
+    // Keys behind the last token of these rows are masked for all of them, and a masked step changes no state: left out (prefill of
+    // 8 x 2048 tokens by 512: 0.995 -> 1.007 of the speed with rows by heads).
+    const int end = x.L + min(x.n, (x.yb + 1) * item_tokens);
+    x.k_hi = SEQ ? end : min(end, x.k_lo + UNIT);
+    // (row blocks without a live row, or whose keys all lie before this unit: the query entry only)
+    x.n_steps = x.yb * NW * 16 < x.n * order.group ? max(0, (x.k_hi - x.k_lo + STEP - 1) / STEP) : 0;
     return x;
   };
 

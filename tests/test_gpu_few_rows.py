@@ -1,6 +1,6 @@
 """Passes of up to 64 rows fetch only the activation rows that there are: at row counts around the edges of a line (8 rows), a
 token block (16) and a pass's padding (16, 32, 64) every row has the bits that it has among more sequences.  The larger group
-takes other GEMM kernels; those are held to the checker elsewhere, and the schedule is fixed, so the comparison is exact."""
+takes other GEMM kernels; those are held to the oracle elsewhere, and the schedule is fixed, so the comparison is exact."""
 import numpy as np
 import pytest
 import torch

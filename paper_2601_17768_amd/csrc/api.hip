@@ -335,13 +335,15 @@ llm42_status verify_impl(const char* who, const llm42_model* m, const llm42_kv_c
     return fail(LLM42_ECAPACITY, "%s: max_context %d exceeds block-table capacity %lld", who, max_context,
                 (long long)kv->max_blocks_per_seq * LLM42_KV_BLOCK);
   if ((uintptr_t)workspace % 256) return fail(LLM42_EWORKSPACE, "%s: workspace not 256-byte aligned", who);
-  // (a wave per chunk needs a partial slot for each: only where the caller's workspace has them, for what a call needs at least
-  // is not to grow)
-  const bool waves = waves_pay(m, num_seqs, window, max_context) &&
-                     carve(m, num_seqs, window, max_context, nullptr, batch_chosen, 0, true).bytes <= workspace_bytes;
-  Workspace ws = carve(m, num_seqs, window, max_context, (char*)workspace, batch_chosen, 0, waves);
+  // What a call needs at least is its carve without a wave per chunk, whichever of the two is smaller: the partials of a wave
+  // per chunk are used where they fit as well.
+  Workspace ws = carve(m, num_seqs, window, max_context, (char*)workspace, batch_chosen);
   if (ws.bytes > workspace_bytes)
     return fail(LLM42_EWORKSPACE, "%s: workspace %zu < %zu bytes", who, workspace_bytes, ws.bytes);
+  if (waves_pay(m, num_seqs, window, max_context)) {
+    const Workspace waves = carve(m, num_seqs, window, max_context, (char*)workspace, batch_chosen, 0, true);
+    if (waves.bytes <= workspace_bytes) ws = waves;
+  }
   return run_pass(m, kv, seq_lens, candidates, window, n_valid, num_seqs, max_context, out_tokens, seq_status,
                   n_dump > 0 ? out_logits : nullptr, dump_seq_ids, n_dump, ws, (hipStream_t)hip_stream, sampling, false);
 }

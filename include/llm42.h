@@ -121,7 +121,9 @@ llm42_status llm42_kv_bytes(const llm42_model* model, int64_t num_blocks, size_t
 
 /* Workspace (device scratch, 256-byte aligned) needed by llm42_verify_window for
  * any call of 1 .. max_seqs sequences, the given window and contexts
- * (seq_len + n_valid) up to max_context. */
+ * (seq_len + n_valid) up to max_context.  Some calls need less and are accepted with
+ * less, but may then run a slower work split (the results are the same bits): with
+ * this size, or more, every such call runs the split that is meant for it. */
 llm42_status llm42_workspace_bytes(const llm42_model* model, int32_t max_seqs, int32_t window,
                                    int32_t max_context, size_t* out_bytes);
 
@@ -167,7 +169,7 @@ llm42_status llm42_verify_window(
  * area of LLM42_STATIC_SCRATCH_BYTES that is part of the library's device image (each GPU on which
  * a model was created holds one copy until the process ends; its device address is looked up once
  * per device in llm42_model_create).  The call allocates nothing and frees nothing.
- * LLM42_EWORKSPACE if the call needs more than the area holds (what it needs is
+ * LLM42_EWORKSPACE if the call needs more than the area holds (it never needs more than
  * llm42_workspace_bytes of its own num_seqs, window and max_context); LLM42_EINVAL if the model's
  * device is not the current one.  All calls on one GPU share the one area, which keeps the
  * previous call's contents (every pass rewrites what it reads, nothing has to start at zero):

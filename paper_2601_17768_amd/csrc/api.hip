@@ -155,7 +155,7 @@ ResidLayout resid_layout(int m_pad, int d) { return m_pad <= 512 ? ResidLayout{d
 
 // Carve the workspace.  Called with base == nullptr to size it.
 Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context, char* base, bool batch_chosen = false,
-                size_t min_part_rows = 0, bool waves = false) {
+                size_t min_part_rows = 0, size_t min_items = 0, bool waves = false) {
   const llm42_config& c = m->cfg;
   Workspace ws;
   memset(&ws, 0, sizeof ws);
@@ -191,10 +191,10 @@ Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context,
   ws.q = (uint16_t*)take(2ull * num_seqs * c.n_kv_heads * ws.r_pad * c.head_dim);
   ws.attn = (uint16_t*)take(2ull * ws.m_pad * m->d_attn);
   ws.hidden = (uint16_t*)take(2ull * ws.m_pad * m->ffn_k);
-  // (min_part_rows: llm42_workspace_bytes sizes the partials for every call of up to max_seqs sequences - a call of
+  // (min_part_rows, min_items: llm42_workspace_bytes sizes the partials for every call of up to max_seqs sequences - a call of
   // fewer sequences may run per chunk where the largest runs per super, with 8 x the slots per sequence)
   const size_t part_rows = std::max((size_t)num_seqs * c.n_kv_heads * ws.attn_units * ws.part_rows, min_part_rows);
-  ws.attn_items = (int4*)take(sizeof(int4) * std::max((size_t)num_seqs * ws.attn_units, min_part_rows / ((size_t)c.n_kv_heads * ws.r_pad)));
+  ws.attn_items = (int4*)take(sizeof(int4) * std::max((size_t)num_seqs * ws.attn_units, min_items));
   ws.attn_ctrl_offset = off;
   ws.attn_ctrl = (int32_t*)take(sizeof(int32_t) * (2 + c.n_layers));
   const size_t partials = off;
@@ -215,18 +215,24 @@ Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context,
 
 // Bytes that serve every call of 1 .. max_seqs sequences: everything but the attention partials grows with the
 // number of sequences; the partials depend on the work split as well (a few sequences run per 256-key chunk where many
-// run per 2048-key super), so their slots are counted for every n.
+// run per 2048-key super), so their slots are counted for every n, and those of a wave per chunk with them: which kernel a call
+// runs is then the same for every workspace of this size or more, whatever else it was sized for.
 size_t sized_for_up_to(const llm42_model* m, int max_seqs, int window, int max_context) {
   Workspace w;
   memset(&w, 0, sizeof w);
   w.num_cus = m->num_cus;
   w.r_pad = pad_to(m->group * window, 16);
-  size_t part_rows = 0;
+  size_t part_rows = 0, items = 0;
+  auto count = [&](int n, int units, int rows) {
+    part_rows = std::max(part_rows, (size_t)n * m->cfg.n_kv_heads * units * rows);
+    items = std::max(items, (size_t)n * units);
+  };
   for (int n = 1; n <= max_seqs; ++n) {
     attention_mode(m, n, max_context, w);
-    part_rows = std::max(part_rows, (size_t)n * m->cfg.n_kv_heads * w.attn_units * w.r_pad);
+    count(n, w.attn_units, w.r_pad);
+    if (waves_pay(m, n, window, max_context)) count(n, attention_units(false, max_context), m->group * window);
   }
-  return carve(m, max_seqs, window, max_context, nullptr, false, part_rows).bytes;
+  return carve(m, max_seqs, window, max_context, nullptr, false, part_rows, items).bytes;
 }
 
 // Layer `ly` behind its attention.  Returns whether the residual stream still lacks the down-projection (see
@@ -341,7 +347,7 @@ llm42_status verify_impl(const char* who, const llm42_model* m, const llm42_kv_c
   if (ws.bytes > workspace_bytes)
     return fail(LLM42_EWORKSPACE, "%s: workspace %zu < %zu bytes", who, workspace_bytes, ws.bytes);
   if (waves_pay(m, num_seqs, window, max_context)) {
-    const Workspace waves = carve(m, num_seqs, window, max_context, (char*)workspace, batch_chosen, 0, true);
+    const Workspace waves = carve(m, num_seqs, window, max_context, (char*)workspace, batch_chosen, 0, 0, true);
     if (waves.bytes <= workspace_bytes) ws = waves;
   }
   return run_pass(m, kv, seq_lens, candidates, window, n_valid, num_seqs, max_context, out_tokens, seq_status,

@@ -1,4 +1,4 @@
-"""What a call's workspace must hold: the least that is accepted."""
+"""What a call's workspace must hold: the least that is accepted, and what llm42_workspace_bytes counts."""
 import numpy as np
 import pytest
 import torch
@@ -51,3 +51,15 @@ def test_the_least_workspace_is_that_of_the_work_split_without_a_wave_per_chunk(
         run(ws[:need - 256])
     assert e.value.status == B.LLM42_EWORKSPACE
     assert int(run(ws).min()) >= 0
+
+
+@pytest.mark.parametrize("n,window,max_context", [(40, 4, 2044), (40, 3, 1500)])
+def test_workspace_bytes_has_room_for_a_wave_per_chunk(sess, n, window, max_context):
+    """One block of query rows and more sequences than a workgroup each would fit the device: the calls that run a wave per
+    256-key chunk, with a partial of every query row (accumulators, maximum and sum in 32 bits) per chunk."""
+    rows, chunks = 4 * window, (max_context + 255) // 256
+    partials = n * SHAPE.n_kv_heads * chunks * rows * (SHAPE.head_dim * 4 + 8)
+    queries = n * SHAPE.n_kv_heads * 16 * SHAPE.head_dim * 2
+    assert B.llm42_workspace_bytes(sess.model, n, window, max_context) >= partials + queries
+    for fewer in (1, n // 2, n - 1):
+        assert B.llm42_workspace_bytes(sess.model, fewer, window, max_context) <= B.llm42_workspace_bytes(sess.model, n, window, max_context)

@@ -54,13 +54,14 @@ llm42_status llm42_measure_verify_window_batch_chosen(
  *           lengths whether they deal out evenly enough;
  *   out[3]  byte offset, in the call's workspace, of the int32 that the device sets to 1 when
  *           it did take whole sequences (valid after the call has run);
- *   out[4]  2 if a workgroup takes one block of 16 query rows and deals the chunks of its context to
- *           its waves (contexts within 2048 keys, few workgroups); else 1 if the 8-wave streaming
- *           kernel runs (8 or more blocks of 16 query rows per sequence and kv head, unless few
- *           chunks are to be dealt out), 0 for the 4-wave kernel.
- * A verify or decode call of one block of 16 query rows per sequence and kv head (head_dim 128) may
- * run a wave per 256-key chunk and the merge pass instead, if its workspace has room for a partial
- * of every chunk; the values are then those of the distribution that it runs with less room. */
+ *   out[4]  3 if a wave takes a 256-key chunk of one block of 16 query rows and the merge pass folds the
+ *           chunks (verify and decode calls; a prefill pass runs what is named next); 2 if a workgroup
+ *           takes one block of 16 query rows and deals the chunks of its context to its waves
+ *           (contexts within 2048 keys, few workgroups); else 1 if the 8-wave streaming kernel runs
+ *           (8 or more blocks of 16 query rows per sequence and kv head, unless few chunks are to be
+ *           dealt out), 0 for the 4-wave kernel.
+ * The values are those of a call whose workspace has the llm42_workspace_bytes of its own num_seqs,
+ * window and max_context, or more; with less room than that a wave per chunk may not fit. */
 llm42_status llm42_measure_attention_plan(const llm42_model* model, int32_t num_seqs, int32_t window,
                                           int32_t max_context, int64_t* out);
 

@@ -235,6 +235,15 @@ size_t sized_for_up_to(const llm42_model* m, int max_seqs, int window, int max_c
   return carve(m, max_seqs, window, max_context, nullptr, false, part_rows, items).bytes;
 }
 
+// The workspace of a verify or decode call that is given `have` bytes.  What it needs at least is its carve without a wave per
+// chunk, whichever of the two is smaller: the partials of a wave per chunk are used where they fit as well.
+Workspace call_workspace(const llm42_model* m, int num_seqs, int window, int max_context, char* base, size_t have, bool batch_chosen) {
+  const Workspace ws = carve(m, num_seqs, window, max_context, base, batch_chosen);
+  if (ws.bytes > have || !waves_pay(m, num_seqs, window, max_context)) return ws;
+  const Workspace waves = carve(m, num_seqs, window, max_context, base, batch_chosen, 0, 0, true);
+  return waves.bytes <= have ? waves : ws;
+}
+
 // Layer `ly` behind its attention.  Returns whether the residual stream still lacks the down-projection (see
 // launch_gemm_residual).
 bool run_mlp(const llm42_model* m, const llm42_model::Layer& ly, const Workspace& ws, hipStream_t st) {
@@ -341,15 +350,9 @@ llm42_status verify_impl(const char* who, const llm42_model* m, const llm42_kv_c
     return fail(LLM42_ECAPACITY, "%s: max_context %d exceeds block-table capacity %lld", who, max_context,
                 (long long)kv->max_blocks_per_seq * LLM42_KV_BLOCK);
   if ((uintptr_t)workspace % 256) return fail(LLM42_EWORKSPACE, "%s: workspace not 256-byte aligned", who);
-  // What a call needs at least is its carve without a wave per chunk, whichever of the two is smaller: the partials of a wave
-  // per chunk are used where they fit as well.
-  Workspace ws = carve(m, num_seqs, window, max_context, (char*)workspace, batch_chosen);
+  Workspace ws = call_workspace(m, num_seqs, window, max_context, (char*)workspace, workspace_bytes, batch_chosen);
   if (ws.bytes > workspace_bytes)
     return fail(LLM42_EWORKSPACE, "%s: workspace %zu < %zu bytes", who, workspace_bytes, ws.bytes);
-  if (waves_pay(m, num_seqs, window, max_context)) {
-    const Workspace waves = carve(m, num_seqs, window, max_context, (char*)workspace, batch_chosen, 0, 0, true);
-    if (waves.bytes <= workspace_bytes) ws = waves;
-  }
   return run_pass(m, kv, seq_lens, candidates, window, n_valid, num_seqs, max_context, out_tokens, seq_status,
                   n_dump > 0 ? out_logits : nullptr, dump_seq_ids, n_dump, ws, (hipStream_t)hip_stream, sampling, false);
 }
@@ -547,12 +550,12 @@ llm42_status llm42_measure_attention_plan(const llm42_model* m, int32_t num_seqs
   if (num_seqs < 1 || window < 1 || window > LLM42_MAX_WINDOW || max_context < 1 ||
       (int64_t)num_seqs * window > LLM42_MAX_ROWS)
     return fail(LLM42_EINVAL, "measure_attention_plan: num_seqs/window/max_context out of range");
-  const Workspace ws = carve(m, num_seqs, window, max_context, nullptr);
+  const Workspace ws = call_workspace(m, num_seqs, window, max_context, nullptr, sized_for_up_to(m, num_seqs, window, max_context), false);
   out[0] = ws.attn_super && !ws.attn_split ? 2048 : 256;
   out[1] = ws.attn_direct || ws.attn_split ? 1 : 0;
   out[2] = ws.attn_seq ? 1 : 0;
   out[3] = (int64_t)(ws.attn_ctrl_offset + sizeof(int32_t) * (1 + m->cfg.n_layers));
-  out[4] = ws.attn_split ? 2 : attention_streams(m, num_seqs, ws) ? 1 : 0;
+  out[4] = ws.attn_waves ? 3 : ws.attn_split ? 2 : attention_streams(m, num_seqs, ws) ? 1 : 0;
   return LLM42_OK;
 }
 

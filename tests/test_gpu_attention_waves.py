@@ -1,6 +1,7 @@
 """The attention kernel of decode steps and of windows of a few rows (a wave per 256-key chunk, one block of 16 query rows per
-sequence and kv head) gives the same bits as the kernels that such a call runs when its workspace has no room for a partial of
-every chunk.  Those are held to the checker in test_gpu_attention_modes.py; the schedule is fixed, so the comparison is exact."""
+sequence and kv head) gives the same bits as the kernels of larger windows, of which the same rows are the first ones.  Those are held
+to the checker in test_gpu_attention_modes.py; the schedule is fixed, so the comparison is exact.  Every case makes sure which
+kernel ran: by the plan, and by the items that the call has listed in its workspace, which are chunks of 256 keys."""
 import numpy as np
 import pytest
 import torch
@@ -11,73 +12,76 @@ from paper_2601_17768_amd import binding as B
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-SHAPE = wl.TINY.replace(d_model=512, n_q_heads=32, n_kv_heads=8, head_dim=128)
 
 
 @pytest.fixture(scope="module")
-def sess():
-    s = VerifierSession(SHAPE, wl.make_weights(SHAPE, seed=53), max_position=4608, device=DEV)
-    yield s
-    s.close()
+def sessions():
+    made = {}
+
+    def get(group):
+        if group not in made:
+            shape = wl.TINY.replace(d_model=512, n_q_heads=8 * group, n_kv_heads=8, head_dim=128)
+            made[group] = shape, VerifierSession(shape, wl.make_weights(shape, seed=53), max_position=4608, device=DEV)
+        return made[group]
+
+    yield get
+    for _, s in made.values():
+        s.close()
 
 
-def _least(call, bytes_):
-    """The smallest workspace that the call accepts (it is refused on the host, before anything runs)."""
-    lo, hi = 0, bytes_ // 256
-    while lo + 1 < hi:
-        mid = (lo + hi) // 2
-        try:
-            call(mid * 256)
-            hi = mid
-        except B.Llm42Error:
-            lo = mid
-    return hi * 256
+# query heads per kv head, window, cached lengths.  Chunk and step edges: contexts of one chunk (no merge), of whole chunks, of a last
+# chunk of one to four steps, past one super; sequences x 8 kv heads: fewer items than waves (1024), several per wave with
+# short ones last; 4, 8, 12, 14, 15 and 16 query rows, neighbouring tokens side by side and not
+CASES = [(4, 1, [0, 254, 255, 256, 257, 319, 320, 511, 512, 1023, 2000]),
+         (4, 1, [2047, 63, 64, 127, 128, 191, 192, 1, 0, 300, 1279, 1280, 1281]), (4, 1, [2048, 4095] + [2047, 0, 255, 256, 3000] * 3),
+         (4, 1, "uniform:0:700:60"), (4, 1, "uniform:2500:4000:14"), (4, 1, "uniform:257:300:150"), (4, 1, "uniform:0:1300:40"),
+         (4, 4, [0, 251, 252, 253, 508, 1276, 2040, 2044]), (4, 4, "uniform:1:2040:40"), (4, 3, "uniform:1:2000:8"),
+         (5, 3, [0, 252, 253, 254, 509, 1277, 2044, 2045]), (7, 2, "uniform:1:2040:9"), (8, 2, "uniform:1:2040:38"), (8, 1, "uniform:1:4000:13"),
+         (3, 5, [250, 251, 252, 2000, 2043, 1, 0, 700])]
 
 
-# chunk and step edges: contexts of one chunk (no merge), of whole chunks, of a last chunk of one to four steps, past one super;
-# sequences x 8 kv heads: fewer items than waves, several per wave with short ones last (1024 waves), windows of one and four rows
-CASES = [(1, [2047]), (1, [2048, 4100]), (1, [0, 254, 255, 256, 257, 319, 320, 511, 512, 1023, 2000]), (4, [0, 251, 252, 253, 508, 2044, 2045, 4200]),
-         (1, "uniform:0:1300:17"), (1, "uniform:0:700:60"), (4, "uniform:1:2100:40"), (1, "uniform:4000:4500:12"), (1, "uniform:257:300:150")]
-
-
-@pytest.mark.parametrize("window,lens", CASES, ids=[str(c) for c in CASES])
-def test_same_bits_with_and_without_room_for_the_partials(sess, window, lens):
-    rng = wl.rng_for(53, window, len(lens))
+@pytest.mark.parametrize("group,window,lens", CASES, ids=[f"{g}-{w}-{c}" for g, w, c in CASES])
+def test_same_bits_as_the_first_rows_of_a_larger_window(sessions, group, window, lens):
+    shape, sess = sessions(group)
+    rng = wl.rng_for(53, group, window, len(lens))
     if isinstance(lens, str):
         _, lo, hi, n = lens.split(":")
         lens = rng.integers(int(lo), int(hi) + 1, size=int(n))
         lens[-1] = int(hi)
     lens = np.array(lens, dtype=np.int32)
-    n = len(lens)
+    n, larger = len(lens), 16 // group + 1                                            # two blocks of query rows
     rows = rng.integers(1, window + 1, size=n).astype(np.int32)
     rows[0] = window
-    table, blocks = wl.make_block_table(rng, lens + window, 16, spare_blocks=2)       # unused entries are -1
+    table, blocks = wl.make_block_table(rng, lens + larger, 16, spare_blocks=2)       # unused entries are -1
     d = lambda a: torch.as_tensor(a, device=DEV)
-    bt, sl, nv = d(table), d(lens), d(rows) if window > 1 else None
-    cand = d(wl.random_tokens(rng, n * window, SHAPE.vocab).reshape(n, window))
+    bt, sl, nv = d(table), d(lens), d(rows)
+    cand = d(wl.random_tokens(rng, n * larger, shape.vocab).reshape(n, larger))
     kv0 = sess.kv_cache(blocks)
     kv0.normal_(generator=torch.Generator(device=DEV).manual_seed(3))
     for s in range(n):                                                                # nothing behind a context is ever read
-        last = (int(lens[s]) + window + 15) // 16
+        last = (int(lens[s]) + larger + 15) // 16
         kv0[:, :, bt[s, (int(lens[s]) + 15) // 16:last].long()] = float("nan")
-    max_context = int(lens.max()) + window
-    ample = B.llm42_workspace_bytes(sess.model, max(n, 15), window, max_context) * 8
-    ws = torch.empty(ample, dtype=torch.uint8, device=DEV)
 
-    def run(nbytes):
-        kv = kv0.clone()
-        out = torch.full((n, window), -1, dtype=torch.int32, device=DEV)
+    def run(w, counts):
+        max_context = int(lens.max()) + w
+        plan = B.llm42_measure_attention_plan(sess.model, n, w, max_context)
+        ws = torch.full((B.llm42_workspace_bytes(sess.model, n, w, max_context),), 0xFF, dtype=torch.uint8, device=DEV)   # NaN partials
+        kv, out = kv0.clone(), torch.full((n, w), -1, dtype=torch.int32, device=DEV)
         status = torch.empty(n, dtype=torch.int32, device=DEV)
-        logits = torch.zeros((n, window, SHAPE.vocab), device=DEV)
-        ws.fill_(0xFF)                                                                # NaN in every partial that is not written
-        B.llm42_verify_window(sess.model, kv, blocks, bt, sl, cand, window, nv, max_context, out, ws[:nbytes], status, logits,
+        logits = torch.zeros((n, w, shape.vocab), device=DEV)
+        B.llm42_verify_window(sess.model, kv, blocks, bt, sl, cand[:, :w].contiguous(), w, counts, max_context, out, ws, status, logits,
                               torch.arange(n, dtype=torch.int32, device=DEV))
-        return out, status, logits, kv
+        torch.cuda.synchronize()
+        # the items' count lies in front of a counter per layer and of the flag whose place the plan names
+        at = plan["sequences_flag_offset"] - 4 * (1 + shape.n_layers)
+        listed = int(ws[at:at + 4].view(torch.int32)[0])
+        return plan, listed, out, status, logits, kv
 
-    few = run(_least(lambda b: run(b), ample))
-    many = run(ample)
-    torch.cuda.synchronize()
-    assert int(many[1].abs().max()) == 0 and torch.isfinite(many[2]).all()
-    for a, b in zip(few[:3], many[:3]):
-        assert torch.equal(a, b)
-    assert torch.equal(few[3].view(torch.int16), many[3].view(torch.int16))           # (NaN where nothing was written)
+    plan, listed, out, status, logits, kv = run(window, nv if window > 1 else None)
+    assert plan["waves"] and listed == int(((lens + rows + 255) // 256).sum())
+    ref = run(larger, nv)
+    assert not ref[0]["waves"]
+    assert int(status.abs().max()) == 0 and torch.isfinite(logits).all()
+    assert torch.equal(out, ref[2][:, :window]) and torch.equal(status, ref[3])
+    assert torch.equal(logits, ref[4][:, :window])                                    # (rows that are not there stay as they were)
+    assert torch.equal(kv.view(torch.int16), ref[5].view(torch.int16))                # (NaN where nothing was written)

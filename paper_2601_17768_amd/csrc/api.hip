@@ -129,19 +129,35 @@ void attention_mode(const llm42_model* m, int num_seqs, int max_context, Workspa
   ws.attn_units = attention_units(ws.attn_super, max_context);
 }
 
-// Whether attention_wave_kernel is the one for a call of one block of 16 query rows per (sequence, kv head).  What it and its merge
-// pass take against the other kernels, us per layer (sequences x keys; 8 kv heads, head dimension 128: at 64 it is not built):
-//   contexts beyond one super    1 x 8000 -2, 4 x 3000 -8, 8 x 8000 +1, 32 of up to 2400 -30, 48 x 3000 -15, 24 of 16 - 8000 -24
-//   more workgroups than CUs     40 x 512 -6, 48 x 1900 -8, 64 x 300 -6, 128 x 1000 -2, 48 of 65 - 2000 -13
-//   up to half as many           8 x 1900 -8, 8 x 1000 -3, 4 x 1000 -4, 16 x 1000 0; 16 x 512 +1.5, 8 x 300 +2, 4 x 300 +4
-//   in between                   24 of 65 - 1873 -9, 24 of 100 - 2000 -2, 32 of 100 - 2000 +2, 24 x 1900 +3; 24 x 1000 +1, 32 x 300 +1.5
-// With one sequence the other kernels are as good; with two and more blocks of rows, each of which would fetch K and V for
-// itself, they are better (two blocks 8 x 1900 +6, eight 8 x 1900 +78).
+// Whether attention_wave_kernel is the one for a call of one block of 16 query rows per (sequence, kv head).  us per layer with its merge
+// pass / with the kernels that the call runs otherwise (sequences x keys, 8 kv heads, 4 query rows; head dimension 128: at 64 it is not built):
+//   one super, more workgroups than CUs, which leave a round of the split kernel nearly empty:  33 x 1270 41 / 57, 40 x 500 25 / 29,
+//     40 x 1900 64 / 76, 48 of 65 - 1873 49 / 58, 64 x 1000 54 / 59, 64 x 1700 87 / 88; 40 of 16 - 500 19.2 / 18.3, 56 x 1700 81 / 80;
+//     beyond two per CU the others take supers, better from 1270 keys on:  96 x 1000 78 / 84, 128 x 1030 108 / 112; 96 x 1270 96 / 95, 128 x 1900 186 / 174
+//   one super, up to half as many workgroups, and the waves of the split kernel walk two chunks:  2 x 1270 15.5 / 18.7, 8 x 1900 20 / 27,
+//     12 x 1500 24 / 25, 16 x 1270 24.5 / 26.6, 16 x 1900 31 / 32, 16 of 16 - 2040 20 / 25; 8 x 1000 16.5 / 15.1, 8 x 1030 17.3 / 16.3, and
+//     where few sequences have their chunks dealt out anyway 2 x 1900 15.7 / 14.2
+//   in between the lengths decide, which only the device knows, so not at all:  24 of 65 - 1873 29 / 32, 20 of 16 - 2040 25 / 31;
+//     20 x 1700 38 / 33, 24 x 1500 39 / 34, 24 of 1000 - 2040 40 / 37.5
+//   two supers, from where the others take supers on, to as many workgroups as CUs:  12 x 2500 32 / 43, 16 of 16 - 4000 30 / 43,
+//     18 x 4090 63 / 81, 24 x 3000 61 / 65, 32 of 16 - 2500 42.5 / 45.5; 16 x 4090 55 / 51, 32 x 3500 89 / 83; fewer 4 x 3000 20 / 18, more
+//     48 x 3500 132 / 121; three supers and beyond 20 x 4500 73 / 83, but 8 x 8000 57 / 51, 24 x 8000 151 / 136, 128 x 8000 761 / 657
+// A partial has all of a call's query rows: at 8 rows 40 x 1900 68 / 75 but 64 x 1900 102 / 97, 16 of 16 - 4000 40 / 44 but 28 x 3000 73 / 68;
+// at 16 rows 40 x 1400 56 / 62 and 8 x 1900 22 / 26.5, but 48 x 1900 86 / 80, 16 x 2040 36 / 34, 128 x 8000 872 / 717.  With two and more
+// blocks of rows, each of which would fetch K and V for itself, the others are better (two blocks 8 x 1900 +6, eight 8 x 1900 +78).
 bool waves_pay(const llm42_model* m, int num_seqs, int window, int max_context) {
-  if (m->cfg.head_dim != 128 || m->group * window > 16 || max_context <= 256) return false;
+  const int rows = m->group * window;
+  if (m->cfg.head_dim != 128 || rows > 16 || max_context <= 256) return false;
+  Workspace other;                                                     // the work split that the call has otherwise
+  memset(&other, 0, sizeof other);
+  other.num_cus = m->num_cus;
+  other.r_pad = 16;
+  attention_mode(m, num_seqs, max_context, other);
   const long long wgs = (long long)num_seqs * m->cfg.n_kv_heads, cus = m->num_cus;
-  if (attention_units(true, max_context) > 1 || wgs > cus) return true;
-  return 2 * wgs <= cus ? wgs >= 16 && max_context > 768 : max_context > 1280;
+  const int supers = attention_units(true, max_context);
+  if (supers > 1) return supers == 2 && other.attn_super && wgs * rows <= 4 * cus;
+  if (wgs > cus) return rows <= 4 ? wgs <= 2 * cus || max_context <= 1152 : 4 * wgs <= 5 * cus;
+  return 2 * wgs <= cus && wgs >= 16 && other.attn_split && max_context > 1152 && wgs * rows <= 6 * cus;
 }
 
 // Rows of the GEMM grid: multiples for which gemm_direct_kernel has a tile of all the rows, or of an even part of them, whose

@@ -70,6 +70,11 @@ def test_same_bits_as_in_a_large_group(env, L, window, rows):
     assert torch.equal(alone[0], crowd[0]) and torch.equal(alone[1], crowd[1])
 
 
+def one_block(shape, window):
+    """Fewer sequences of one row block at head dimension 128 take a wave per chunk at such contexts (test_gpu_attention_waves.py)."""
+    return shape.head_dim == 128 and window == 1
+
+
 @pytest.mark.parametrize("L", [1279, 1281, 1535, 1536, 1791, 1792, 2040])
 @pytest.mark.parametrize("window,rows", [(1, 1), (8, 8), (8, 3)])
 def test_second_chunk_of_every_wave(env, L, window, rows):
@@ -78,6 +83,16 @@ def test_second_chunk_of_every_wave(env, L, window, rows):
     shape, sess = env
     merged = _run(shape, sess, L, window, rows, 0, 0, max(L + window, 1281), split=False)
     assert torch.isfinite(merged[1]).all()
-    one_block = shape.head_dim == 128 and window == 1   # (such a call takes a wave per chunk: test_gpu_attention_waves.py)
-    among = _run(shape, sess, L, window, rows, 60, 20, L + window, split=not one_block)
+    among = _run(shape, sess, L, window, rows, 199 if one_block(shape, window) else 60, 20, L + window, split=True)
     assert torch.equal(merged[0], among[0]) and torch.equal(merged[1], among[1])
+
+
+@pytest.mark.parametrize("L", [1281, 1536, 1791, 2040])
+def test_second_chunk_of_items_from_the_list(env, L):
+    """One row block and more workgroups than CUs: the split kernel takes its items from the plan's list."""
+    shape, sess = env
+    if shape.head_dim != 128:
+        pytest.skip("the other kernels take such a call at head dimension 64")
+    merged = _run(shape, sess, L, 4, 3, 0, 0, L + 4, split=False)
+    listed = _run(shape, sess, L, 4, 3, 400, 20, L + 4, split=True)
+    assert torch.equal(merged[0], listed[0]) and torch.equal(merged[1], listed[1])

@@ -85,3 +85,18 @@ def test_same_bits_as_the_first_rows_of_a_larger_window(sessions, group, window,
     assert torch.equal(out, ref[2][:, :window]) and torch.equal(status, ref[3])
     assert torch.equal(logits, ref[4][:, :window])                                    # (rows that are not there stay as they were)
     assert torch.equal(kv.view(torch.int16), ref[5].view(torch.int16))                # (NaN where nothing was written)
+
+
+# sequences, window, longest context: 4 query rows per token and kv head, 8 kv heads; measured to be slower with a wave per chunk, or not
+SLOWER = [(24, 1, 1500), (20, 1, 1700), (24, 1, 1901), (32, 1, 1281), (8, 1, 1001), (16, 1, 1001), (2, 1, 1901), (1, 1, 8001), (4, 1, 3001),
+          (24, 1, 8001), (64, 1, 4501), (128, 1, 8001), (128, 1, 1901), (64, 3, 1902), (64, 4, 1004), (128, 4, 8004), (32, 4, 3004), (16, 4, 2044)]
+FASTER = [(40, 1, 501), (48, 1, 1874), (64, 1, 1001), (8, 1, 1901), (2, 1, 1271), (16, 1, 2041), (16, 1, 4001), (24, 1, 3001), (40, 2, 1902),
+          (16, 2, 4002), (40, 4, 1404), (8, 4, 1904), (128, 1, 1001)]
+
+
+@pytest.mark.parametrize("n,window,max_context,waves", [(*c, False) for c in SLOWER] + [(*c, True) for c in FASTER])
+def test_a_wave_per_chunk_only_where_it_is_not_slower(sessions, n, window, max_context, waves):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("measured with 256 CUs")
+    shape, sess = sessions(4)
+    assert B.llm42_measure_attention_plan(sess.model, n, window, max_context)["waves"] == waves

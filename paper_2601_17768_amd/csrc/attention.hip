@@ -1290,13 +1290,20 @@ void launch_attention_plan(const llm42_model* m, int num_seqs, int max_context, 
 }
 
 // 8 row blocks or more per (sequence, kv head): 8 waves of one row block each, two per SIMD, so that one wave's MFMAs run under the
-// other's softmax arithmetic, as one stream per CU; fewer: 4 waves.  So do chunks of which there are no more than four row blocks'
-// worth for two workgroups a CU (us per layer less: prefill of 700 tokens by 256 2.3, 4 x 32 behind 512 keys 2.2, 1 x 64 behind
-// 1900 1.4; where there are more they take longer, 8 x 32 behind 1900 7.3: K and V are fetched twice).
+// other's softmax arithmetic, as one stream per CU; fewer: 4 waves.  So do chunks while there are few of them for two workgroups a CU,
+// and few per sequence: four row blocks' worth of a chunk per workgroup, K and V are fetched twice.  us per layer, 4 waves / 8
+// (sequences x window behind keys, 8 kv heads, 4 query heads each):
+//   up to 5 chunks  8 x 32 / 300 18.6 / 20.8, 5 x 32 / 512 18.3 / 20.4, 4 x 32 / 1000 20.4 / 21.6, 2 x 64 / 1000 21.1 / 22.8,
+//                   1 x 256 / 300 20.3 / 23.5, 1 x 256 / 512 22.8 / 23.6; 6 x 32 / 1000 23.1 / 23.4, 3 x 64 / 1000 24.0 / 23.9
+//   6 - 8           1 x 32 / 1900 17.8 / 18.8, 1 x 64 / 1500 20.4 / 22.1; 2 x 32 / 1900 21.8 / 20.6, 4 x 32 / 1900 25.4 / 24.7, 1 x 128 / 1900 28.8 / 26.3
+//   more            1 x 32 / 4500 24.9 / 22.0, 1 x 32 / 8000 31.8 / 26.8, 2 x 32 / 3000 27.1 / 23.3, 1 x 64 / 3000 27.1 / 26.2
+// Where the 8 waves' last row group is at most half full, the 4 waves fetch less: 1 x 48 / 4500 28.8 / 34.6, 3 x 48 / 1500 24.0 / 30.7.
 bool attention_streams(const llm42_model* m, int num_seqs, const Workspace& ws) {
-  const int blocks = ws.r_pad / 16;
-  const long long items = (long long)num_seqs * ws.attn_units * m->cfg.n_kv_heads * ((blocks + 3) / 4);
-  return blocks >= 8 && (ws.attn_super || m->cfg.head_dim != 128 || items > 2LL * m->num_cus);
+  const int blocks = ws.r_pad / 16, groups = (blocks + 3) / 4, units = ws.attn_units;
+  if (blocks < 8) return false;
+  if (ws.attn_super || m->cfg.head_dim != 128) return true;
+  const long long items = (long long)num_seqs * units * m->cfg.n_kv_heads * groups, cus = m->num_cus;
+  return items > (groups % 2 ? 2 * cus : units <= 5 ? 7 * cus / 4 : units <= 8 ? cus - 1 : 0);
 }
 
 int attention_units(bool super_mode, int max_context) {

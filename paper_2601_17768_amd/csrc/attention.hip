@@ -483,10 +483,16 @@ __global__ __launch_bounds__(NW * 64, NBUF == 2 ? 2 : 1) void attention_kernel(
 // fetches is ever counted by vmcnt between the first and the last entry.  Past the last item the
 // fetch cursor issues dummy fetches into slots nothing reads, which keeps the wait count constant.
 // FOLD = false (measurement only): no chunk partials inside a super, one straight accumulation.
+// FULL: every window of the call is full, a multiple of 128 query rows, and no item lacks keys that others have (see
+// Workspace::full): nothing is tested for rows that are not there.  The loop is bound by instruction issue with every scalar register
+// taken, and those tests' scalars cost 2 - 4 % of it: us a layer before there were any, with them for every call and now, 16 sequences x
+// window 32 behind 1900 keys 56.7, 57.9, 56.5, 32 x 64 behind 1900 117.1, 121.4, 117.6, of 16 - 8000 316.7, 325.3, 315.2, 16 x 32
+// behind 4500 85.2, 87.6, 85.0, 2 x 128 behind 3000 53.3, 54.7, 53.7; the same windows given as counts 0.5 - 2 % more, partly filled
+// 10 - 15 % less than before.
 // SEQ: an item is a whole sequence (all of its supers); the supers' partials are folded in registers, in the order
 // of the merge pass, and the kernel writes the output rows itself.  The query operands then stay in LDS instead of
 // registers (the third accumulator level needs theirs).
-template <int HD, bool SUPER, bool FOLD, bool SEQ = false>
+template <int HD, bool SUPER, bool FOLD, bool SEQ, bool FULL>
 __global__ __launch_bounds__(512) void attention_stream_kernel(
     const uint16_t* __restrict__ q, const uint4* __restrict__ k_plane, const uint4* __restrict__ v_plane,
     const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count,
@@ -511,35 +517,43 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
   const int per_item = n_kv_heads * y_blocks;
   const int total = *item_count * per_item;
 
-  // the ord-th piece of work of this workgroup (wave-uniform; scalar loads)
+  // a piece of work of this workgroup (wave-uniform; scalar loads)
   struct Work {
     bool valid;
     int s, kvh, yb, unit, L, n, base, k_lo, k_hi, n_steps;
   };
   const int item_tokens = (NW * 16 + order.group - 1) / order.group;   // (at least those that an item's rows span)
-  auto work_of = [&](int ord) {
+  // the list's entry of the ord-th piece; past the end: t = total, and a harmless stand-in, so that the dummy fetches read valid memory
+  struct Entry {
+    int t;
+    int4 su;
+  };
+  auto entry_of = [&](int ord) {
+    Entry e;
+    e.t = min(ord * G + ((ord & 1) ? G - 1 - w : w), total);
+    e.su = e.t < total ? items[e.t / per_item] : make_int4(0, 0, 0, seq_tag(1, 0));
+    return e;
+  };
+  auto work_of = [&](const Entry e) {
     Work x;
-    const int t = ord * G + ((ord & 1) ? G - 1 - w : w);
-    x.valid = t < total;
-    const int tt = x.valid ? t : 0;
-    const int rem = tt % per_item;
-    // (past the end: a harmless stand-in, so that the dummy fetches read valid memory)
-    const int4 su = x.valid ? items[tt / per_item] : make_int4(0, 0, 0, seq_tag(1, 0));
-    x.s = su.x, x.unit = su.y, x.L = su.z, x.n = tag_rows(su.w), x.base = tag_base(su.w);
+    x.valid = e.t < total;
+    const int rem = e.t % per_item;
+    x.s = e.su.x, x.unit = e.su.y, x.L = e.su.z, x.n = tag_rows(e.su.w), x.base = tag_base(e.su.w);
     x.kvh = rem / y_blocks, x.yb = rem % y_blocks;
     x.k_lo = SEQ ? 0 : x.unit * UNIT;
     // Keys behind the last token of these rows are masked for all of them, and a masked step changes no state: left out (prefill of
     // 8 x 2048 tokens by 512: 0.995 -> 1.007 of the speed with rows by heads).
-    const int end = x.L + min(x.n, (x.yb + 1) * item_tokens);
+    const int end = x.L + (FULL ? x.n : min(x.n, (x.yb + 1) * item_tokens));
     x.k_hi = SEQ ? end : min(end, x.k_lo + UNIT);
+    x.n_steps = (x.k_hi - x.k_lo + STEP - 1) / STEP;
     // (row blocks without a live row, or whose keys all lie before this unit: the query entry only)
-    x.n_steps = x.yb * NW * 16 < x.n * order.group ? max(0, (x.k_hi - x.k_lo + STEP - 1) / STEP) : 0;
+    if (!FULL) x.n_steps = x.yb * NW * 16 < x.n * order.group ? max(0, x.n_steps) : 0;
     return x;
   };
 
   // ---- fetch cursor ----------------------------------------------------------------------------
   int f_ord = 0, f_entry = 0;           // entry 0 = query operands, entry e > 0 = step e - 1
-  Work f = work_of(0);
+  Work f = work_of(entry_of(0));
   int f_id = 0;                         // block id this wave needs for the entry at the cursor (steps only)
   const int blk = wave >> 1, part = wave & 1;
   auto id_for = [&](const Work& x, int e) {   // physical block of this wave's 16 keys of step e - 1
@@ -562,7 +576,7 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     }
     if (f.valid) {
       if (++f_entry > f.n_steps) {
-        f = work_of(++f_ord);
+        f = work_of(entry_of(++f_ord));
         f_entry = 0;
       } else {
         f_id = id_for(f, f_entry);      // requested one entry ahead of its use
@@ -581,9 +595,9 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     __syncthreads();                    // ... for every wave, and every wave is done with this entry's slot
     ++gidx;
   };
-  Work c = work_of(0);
+  Work c = work_of(entry_of(0));
   for (int ord = 0; c.valid; ++ord) {
-    const Work c_next = work_of(ord + 1);   // requested now, needed when this item is done
+    const Entry next = entry_of(ord + 1);   // requested now, needed when this item is done (as a Work it took 6 registers more)
     // -- entry 0: query operands; per-lane row data
     fetch_next(gidx + AHEAD);
     bf16x8 qf[CB][DK];
@@ -602,7 +616,7 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     int wmin = qpos[0] >= 0 ? qpos[0] : 0x7FFFFFFF;   // lowest position among this wave's live rows (-1: none, it only fetches)
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) wmin = min(wmin, __shfl_xor(wmin, off));
-    wmin = (c.yb * NW + wave) * 16 < c.n * order.group ? __builtin_amdgcn_readfirstlane(wmin) : -1;
+    wmin = FULL || (c.yb * NW + wave) * 16 < c.n * order.group ? __builtin_amdgcn_readfirstlane(wmin) : -1;
     float m[CB] = {-INFINITY}, l[CB] = {0.f}, sm[CB] = {-INFINITY}, sl[CB] = {0.f};
     f32x4 acc[CB][DB], sacc[CB][DB];
     float tm = -INFINITY, tl = 0.f;   // SEQ: running fold of finished supers
@@ -616,7 +630,7 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
     entry_done();
     // -- one entry per step.  A wave without live rows only fetches, in a loop of its own: as a branch around the masked step it
     // changed the registers of the loop below (whole sequences 232 -> 216, others 200 -> 183).
-    if (wmin < 0) {
+    if (!FULL && wmin < 0) {
       for (int j = 0; j < c.n_steps; ++j) {
         fetch_next(gidx + AHEAD);
         entry_done();
@@ -677,7 +691,7 @@ __global__ __launch_bounds__(512) void attention_stream_kernel(
       if (g == 0)
         *(float2*)(part_ml + prow * 2) = SUPER && FOLD ? make_float2(sm[0], sl[0]) : make_float2(m[0], l[0]);
     }
-    c = c_next;
+    c = work_of(next);
   }
   fetch_wait<0>();                      // the dummy fetches too
 }
@@ -1208,7 +1222,8 @@ void launch_stream(const llm42_model* m, const uint16_t* kp, const uint16_t* vp,
   const float scale_log2 = (1.0f / sqrtf((float)c.head_dim)) * 1.44269504088896340736f;
   const int y_blocks = (ws.r_pad / 16 + 7) / 8;
   const unsigned grid = (unsigned)stream_grid(m, num_seqs, SEQ ? 1 : ws.attn_units, ws.r_pad);
-  attention_stream_kernel<HD, SUPER, FOLD, SEQ><<<grid, 512, 0, st>>>(
+  auto* const kernel = ws.full ? attention_stream_kernel<HD, SUPER, FOLD, SEQ, true> : attention_stream_kernel<HD, SUPER, FOLD, SEQ, false>;
+  kernel<<<grid, 512, 0, st>>>(
       ws.q, (const uint4*)kp, (const uint4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl, c.n_kv_heads, row_order(m->group, window),
       ws.r_pad, y_blocks, kv->max_blocks_per_seq, ws.attn_units, scale_log2, ws.part_acc, ws.part_ml,
       SEQ || (SUPER && ws.attn_direct) ? ws.attn : nullptr, m->d_attn, ws.attn_seq ? ws.attn_ctrl + 1 + c.n_layers : nullptr);

@@ -138,6 +138,7 @@ struct Workspace {
                     // dealt to its waves, output written by the same launch
   bool attn_waves;  // whatever those above say: a wave per chunk, and the merge pass (see waves_pay)
   bool attn_list;   // the launches take their items from the plan kernel's list (else: sequence by sequence)
+  bool full;        // every window of the call is full: attention by 8 waves need not test for rows that are not there
   bool batch_chosen; // off the fixed schedule (fast-path decode step, cost-of-determinism measurement): the batch may
                      // choose the split of the residual projections and the attention partials
   // Rows of a pass: sequence s has rows base(s) .. base(s) + n(s) - 1.  With n_valid the rows are packed - base(s) is the sum

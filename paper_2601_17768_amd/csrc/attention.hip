@@ -276,8 +276,8 @@ __device__ __forceinline__ void softmax_step(const uint4* lk, const uint16_t* lv
 template <int HD, int CB, int NW, bool SUPER, int NBUF>
 __global__ __launch_bounds__(NW * 64, NBUF == 2 ? 2 : 1) void attention_kernel(
     const uint16_t* __restrict__ q, const uint4* __restrict__ k_plane, const uint4* __restrict__ v_plane,
-    const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count, int32_t* __restrict__ queue,
-    int n_kv_heads, RowOrder order, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
+    const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count,
+    int32_t* __restrict__ queue, int n_kv_heads, RowOrder order, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
     float scale_log2, float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out,
     int d_attn) {
   constexpr int DK = HD / 32;        // MFMA k-steps over the head dimension (scores)
@@ -887,28 +887,25 @@ template <int HD>
 __global__ __launch_bounds__(256) void attention_wave_kernel(
     const uint16_t* __restrict__ q, const bf16x8* __restrict__ k_plane, const u32x4* __restrict__ v_plane,
     const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count, int n_kv_heads,
-    RowOrder order, int r_pad, int max_blocks_per_seq, int n_units, int part_rows, int max_items, float scale_log2,
+    RowOrder order, int max_blocks_per_seq, int n_units, int part_rows, int max_items, float scale_log2,
     float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out, int d_attn) {
   constexpr int DK = HD / 32, DB = HD / 16, TV4 = HD * 2;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int col = lane & 15, g = lane >> 4;
-  const int row_blocks = r_pad / 16, per_item = n_kv_heads * row_blocks, stride = 4 * (int)gridDim.x;
+  const int stride = 4 * (int)gridDim.x;
   struct Item {
-    int s, kvh, rb, L, tag, k_lo, k_hi, steps, wmin, row, qpos, raw;
+    int s, kvh, L, tag, k_lo, k_hi, steps, wmin, qpos, raw;
     bf16x8 qf[DK];
   };
   // An item's share of the list entry `su`; what it needs from memory is requested, not waited for.  steps = 0: nothing for
   // these rows in this chunk.
   auto open = [&](Item& x, int t, const int4 su) __attribute__((always_inline)) {
-    const int rem = t % per_item;
-    x.rb = rem % row_blocks, x.kvh = rem / row_blocks;
-    x.s = su.x, x.L = su.z, x.tag = su.w, x.k_lo = su.y * CHUNK;
+    x.kvh = t % n_kv_heads, x.s = su.x, x.L = su.z, x.tag = su.w, x.k_lo = su.y * CHUNK;
     x.raw = block_table[(size_t)x.s * max_blocks_per_seq + min(x.k_lo / 16 + col, max_blocks_per_seq - 1)];
-    const uint16_t* qb = q + ((size_t)x.s * n_kv_heads + x.kvh) * r_pad * HD + (size_t)x.rb * DK * 512;
+    const uint16_t* qb = q + ((size_t)x.s * n_kv_heads + x.kvh) * 16 * HD;
 #pragma unroll
     for (int d = 0; d < DK; ++d) x.qf[d] = *(const bf16x8*)(qb + d * 512 + lane * 8);
-    x.row = x.rb * 16 + col;
-    const int i = order.token(x.row);
+    const int i = order.token(col);
     x.qpos = i < tag_rows(x.tag) ? x.L + i : -1;
     int wmax = x.qpos, wmin = x.qpos >= 0 ? x.qpos : 0x7FFFFFFF;   // highest and lowest position among the block's live rows
 #pragma unroll
@@ -927,9 +924,9 @@ __global__ __launch_bounds__(256) void attention_wave_kernel(
     return ((size_t)__builtin_amdgcn_readlane(x.raw, x.k_lo / 16 + at <= (x.k_hi - 1) / 16 ? at : 0) * n_kv_heads + x.kvh) * TV4;
   };
   int t = wave * (int)gridDim.x + (int)blockIdx.x;
-  auto entry = [&](int at) { return items[min(at / per_item, max_items - 1)]; };   // (past the list: an entry that is not used)
+  auto entry = [&](int at) { return items[min(at / n_kv_heads, max_items - 1)]; };   // (past the list: an entry that is not used)
   int4 su = entry(t);
-  const int total = *item_count * per_item;
+  const int total = *item_count * n_kv_heads;
   // the next item that has steps, from t on (`su` is its entry, requested one item earlier)
   auto next = [&](Item& x) __attribute__((always_inline)) {
     x.steps = 0;
@@ -975,11 +972,12 @@ __global__ __launch_bounds__(256) void attention_wave_kernel(
           u32x4 o;
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[e] = pack2_bf16(acc[2 * p][e] / l, acc[2 * p + 1][e] / l);
-          *(u32x4*)(attn_out + pk_off(tag_base(c.tag) + order.token(c.row), (c.kvh * order.group + order.head(c.row)) * HD + f0 + 32 * p, d_attn)) = o;
+          const int feature = (c.kvh * order.group + order.head(col)) * HD + f0 + 32 * p;
+          *(u32x4*)(attn_out + pk_off(tag_base(c.tag) + order.token(col), feature, d_attn)) = o;
         }
       }
     } else if (c.qpos >= c.k_lo) {
-      const size_t prow = (((size_t)c.s * n_kv_heads + c.kvh) * n_units + c.k_lo / CHUNK) * part_rows + c.row;
+      const size_t prow = (((size_t)c.s * n_kv_heads + c.kvh) * n_units + c.k_lo / CHUNK) * part_rows + col;
       float* pa = part_acc + prow * HD + f0;
 #pragma unroll
       for (int p = 0; p < DB / 2; ++p) {
@@ -1199,8 +1197,9 @@ void launch_one(const llm42_model* m, int layer, const uint16_t* kp, const uint1
   const long long max_items = (long long)num_seqs * ws.attn_units * c.n_kv_heads * y_blocks;
   const unsigned grid = (unsigned)std::min<long long>(m->num_cus * (HD == 128 ? 1 : 2) * (NBUF == 2 ? 2 : 1), max_items);
   attention_kernel<HD, CB, NW, SUPER, NBUF><<<grid, NW * 64, 0, st>>>(
-      ws.q, (const uint4*)kp, (const uint4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl, ws.attn_ctrl + 1 + layer, c.n_kv_heads, row_order(m->group, window), ws.r_pad, y_blocks, kv->max_blocks_per_seq,
-      ws.attn_units, scale_log2, ws.part_acc, ws.part_ml, SUPER && ws.attn_direct ? ws.attn : nullptr, m->d_attn);
+      ws.q, (const uint4*)kp, (const uint4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl, ws.attn_ctrl + 1 + layer,
+      c.n_kv_heads, row_order(m->group, window), ws.r_pad, y_blocks, kv->max_blocks_per_seq, ws.attn_units, scale_log2, ws.part_acc,
+      ws.part_ml, SUPER && ws.attn_direct ? ws.attn : nullptr, m->d_attn);
   if (SUPER && ws.attn_direct) return;
   const int rows = m->group * window, rows_per_block = 256 / (HD / 4);
   attention_merge_kernel<HD, SUPER><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256,
@@ -1256,13 +1255,13 @@ void launch_waves(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, 
   const llm42_config& c = m->cfg;
   const float scale_log2 = (1.0f / sqrtf((float)c.head_dim)) * 1.44269504088896340736f;
   const int rows = m->group * window, rows_per_block = 256 / (HD / 4);
-  const unsigned grid = (unsigned)std::min<long long>(m->num_cus, (long long)num_seqs * ws.attn_units * c.n_kv_heads * (ws.r_pad / 16));
+  const unsigned grid = (unsigned)std::min<long long>(m->num_cus, (long long)num_seqs * ws.attn_units * c.n_kv_heads);
   attention_wave_kernel<HD><<<grid, 256, 0, st>>>(ws.q, (const bf16x8*)kp, (const u32x4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl,
-                                                  c.n_kv_heads, row_order(m->group, window), ws.r_pad, kv->max_blocks_per_seq, ws.attn_units,
+                                                  c.n_kv_heads, row_order(m->group, window), kv->max_blocks_per_seq, ws.attn_units,
                                                   ws.part_rows, num_seqs * ws.attn_units, scale_log2, ws.part_acc, ws.part_ml, ws.attn, m->d_attn);
   attention_merge_kernel<HD, false, true><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256, 0, st>>>(
-      ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, row_order(m->group, window), window, ws.part_rows, ws.attn_units, m->d_attn, ws.attn,
-      nullptr, CHUNK);
+      ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, row_order(m->group, window), window, ws.part_rows, ws.attn_units,
+      m->d_attn, ws.attn, nullptr, CHUNK);
 }
 
 template <int HD>
@@ -1298,9 +1297,10 @@ void launch_attention_plan(const llm42_model* m, int num_seqs, int max_context, 
   // as a whole-sequence item a unit has as many keys as the longest sequence of the call may have
   const int seq_unit_keys = ws.attn_seq ? (max_context + STEP - 1) / STEP * STEP : 0;
   const int seq_per_item = m->cfg.n_kv_heads * ((ws.r_pad / 16 + 7) / 8);
-  attention_plan_kernel<<<1, 256, 0, st>>>(ws.seq_len, ws.seq_n, num_seqs, !ws.attn_waves && (ws.attn_super || ws.attn_split) ? SUPER_KEYS : CHUNK,
-                                           seq_unit_keys, seq_per_item, (int)stream_grid(m, num_seqs, 1, ws.r_pad),
-                                           ws.attn_items, ws.attn_ctrl, ws.attn_ctrl + 1, m->cfg.n_layers,
+  const int unit_keys = !ws.attn_waves && (ws.attn_super || ws.attn_split) ? SUPER_KEYS : CHUNK;
+  attention_plan_kernel<<<1, 256, 0, st>>>(ws.seq_len, ws.seq_n, num_seqs, unit_keys, seq_unit_keys, seq_per_item,
+                                           (int)stream_grid(m, num_seqs, 1, ws.r_pad), ws.attn_items, ws.attn_ctrl, ws.attn_ctrl + 1,
+                                           m->cfg.n_layers,
                                            ws.attn_ctrl + 1 + m->cfg.n_layers);
 }
 

@@ -53,10 +53,12 @@ llm42_status llm42_measure_verify_window_batch_chosen(
  *   out[2]  1 if the call may take whole sequences as work items - the device decides from the
  *           lengths whether they deal out evenly enough;
  *   out[3]  byte offset, in the call's workspace, of the int32 that the device sets to 1 when
- *           it did take whole sequences (valid after the call has run);
+ *           it did take whole sequences, or with out[4] == 4 a wave per chunk (valid after the
+ *           call has run);
  *   out[4]  3 if a wave takes a 256-key chunk of one block of 16 query rows and the merge pass folds the
- *           chunks (verify and decode calls; a prefill pass runs what is named next); 2 if a workgroup
- *           takes one block of 16 query rows and deals the chunks of its context to its waves
+ *           chunks, 4 if the device decides from the lengths whether it does or a workgroup takes a
+ *           super (both verify and decode calls; a prefill pass runs what is named next); 2 if a
+ *           workgroup takes one block of 16 query rows and deals the chunks of its context to its waves
  *           (contexts within 2048 keys, few workgroups); else 1 if the 8-wave streaming kernel runs
  *           (8 or more blocks of 16 query rows per sequence and kv head, unless few chunks are to be
  *           dealt out), 0 for the 4-wave kernel.

@@ -304,7 +304,7 @@ def llm42_measure_attention_plan(model: int, num_seqs: int, window: int, max_con
     out = (ctypes.c_int64 * 5)()
     _check(load_library().llm42_measure_attention_plan(model, num_seqs, window, max_context, out))
     return {"item_keys": out[0], "direct": bool(out[1]), "may_take_sequences": bool(out[2]),
-            "sequences_flag_offset": out[3], "streaming": out[4] == 1, "split": out[4] == 2, "waves": out[4] == 3}
+            "sequences_flag_offset": out[3], "streaming": out[4] == 1, "split": out[4] == 2, "waves": out[4] == 3, "may_take_waves": out[4] == 4}
 
 
 def llm42_profile_enable(kind, max_launches: int) -> None:

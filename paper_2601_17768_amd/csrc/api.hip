@@ -137,27 +137,31 @@ void attention_mode(const llm42_model* m, int num_seqs, int max_context, Workspa
 //   one super, up to half as many workgroups, and the waves of the split kernel walk two chunks:  2 x 1270 15.5 / 18.7, 8 x 1900 20 / 27,
 //     12 x 1500 24 / 25, 16 x 1270 24.5 / 26.6, 16 x 1900 31 / 32, 16 of 16 - 2040 20 / 25; 8 x 1000 16.5 / 15.1, 8 x 1030 17.3 / 16.3, and
 //     where few sequences have their chunks dealt out anyway 2 x 1900 15.7 / 14.2
-//   in between the lengths decide, which only the device knows, so not at all:  24 of 65 - 1873 29 / 32, 20 of 16 - 2040 25 / 31;
-//     20 x 1700 38 / 33, 24 x 1500 39 / 34, 24 of 1000 - 2040 40 / 37.5
-//   two supers, from where the others take supers on, to as many workgroups as CUs:  12 x 2500 32 / 43, 16 of 16 - 4000 30 / 43,
-//     18 x 4090 63 / 81, 24 x 3000 61 / 65, 32 of 16 - 2500 42.5 / 45.5; 16 x 4090 55 / 51, 32 x 3500 89 / 83; fewer 4 x 3000 20 / 18, more
-//     48 x 3500 132 / 121; three supers and beyond 20 x 4500 73 / 83, but 8 x 8000 57 / 51, 24 x 8000 151 / 136, 128 x 8000 761 / 657
+//   in between, to 7/8 (beyond, hardly any call has a chunk or none for each wave), where uneven lengths leave most of the split kernel's
+//     waves idle: by the lengths, which only the device knows.  Waves / split kernel /
+//     as the device decides, merge pass that leaves at once and all:  24 of 65 - 1873 28.7 / 31.9 / 28.8, 20 of 16 - 2040 25 / 31 / 25,
+//     20 x 1700 38 / 32.6 / 34, 24 x 1500 39 / 34 / 35, 28 of 500 - 2040 37.2 / 37.2 / 38.6 (before there was a choice 33.7, 35.3, 37.7)
+//   two supers and beyond, from where the others take supers on: by the lengths, at no cost (both have a merge pass), while few enough
+//     rows are written:  12 x 2500 32 / 43, 16 of 16 - 4000 30 / 43, 20 x 4500 73 / 83; 16 x 4090 55 / 51, 24 x 8000 151 / 136; fewer or
+//     more, never:  4 x 3000 20 / 18, 96 x 3000 219 / 199, 128 x 8000 761 / 657
 // A partial has all of a call's query rows: at 8 rows 40 x 1900 68 / 75 but 64 x 1900 102 / 97, 16 of 16 - 4000 40 / 44 but 28 x 3000 73 / 68;
 // at 16 rows 40 x 1400 56 / 62 and 8 x 1900 22 / 26.5, but 48 x 1900 86 / 80, 16 x 2040 36 / 34, 128 x 8000 872 / 717.  With two and more
 // blocks of rows, each of which would fetch K and V for itself, the others are better (two blocks 8 x 1900 +6, eight 8 x 1900 +78).
-bool waves_pay(const llm42_model* m, int num_seqs, int window, int max_context) {
+enum class WaveUse { NO, YES, BY_LENGTHS };
+WaveUse wave_use(const llm42_model* m, int num_seqs, int window, int max_context) {
   const int rows = m->group * window;
-  if (m->cfg.head_dim != 128 || rows > 16 || max_context <= 256) return false;
+  if (m->cfg.head_dim != 128 || rows > 16 || max_context <= 256) return WaveUse::NO;
   Workspace other;                                                     // the work split that the call has otherwise
   memset(&other, 0, sizeof other);
   other.num_cus = m->num_cus;
   other.r_pad = 16;
   attention_mode(m, num_seqs, max_context, other);
   const long long wgs = (long long)num_seqs * m->cfg.n_kv_heads, cus = m->num_cus;
-  const int supers = attention_units(true, max_context);
-  if (supers > 1) return supers == 2 && other.attn_super && wgs * rows <= 4 * cus;
-  if (wgs > cus) return rows <= 4 ? wgs <= 2 * cus || max_context <= 1152 : 4 * wgs <= 5 * cus;
-  return 2 * wgs <= cus && wgs >= 16 && other.attn_split && max_context > 1152 && wgs * rows <= 6 * cus;
+  if (attention_units(true, max_context) > 1) return other.attn_super && wgs * rows <= 8 * cus ? WaveUse::BY_LENGTHS : WaveUse::NO;
+  if (wgs > cus) return (rows <= 4 ? wgs <= 2 * cus || max_context <= 1152 : 4 * wgs <= 5 * cus) ? WaveUse::YES : WaveUse::NO;
+  if (!other.attn_split || max_context <= 1152) return WaveUse::NO;
+  if (2 * wgs > cus) return 8 * wgs <= 7 * cus && rows <= 8 && max_context > 1280 ? WaveUse::BY_LENGTHS : WaveUse::NO;
+  return wgs >= 16 && wgs * rows <= 6 * cus ? WaveUse::YES : WaveUse::NO;
 }
 
 // Rows of the GEMM grid: multiples for which gemm_direct_kernel has a tile of all the rows, or of an even part of them, whose
@@ -171,7 +175,7 @@ ResidLayout resid_layout(int m_pad, int d) { return m_pad <= 512 ? ResidLayout{d
 
 // Carve the workspace.  Called with base == nullptr to size it.
 Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context, char* base, bool batch_chosen = false,
-                size_t min_part_rows = 0, size_t min_items = 0, bool waves = false) {
+                size_t min_part_rows = 0, size_t min_items = 0, WaveUse waves = WaveUse::NO) {
   const llm42_config& c = m->cfg;
   Workspace ws;
   memset(&ws, 0, sizeof ws);
@@ -182,9 +186,12 @@ Workspace carve(const llm42_model* m, int num_seqs, int window, int max_context,
   ws.r_pad = pad_to(m->group * window, 16);
   attention_mode(m, num_seqs, max_context, ws);
   ws.part_rows = ws.r_pad;
-  if (waves) {
-    ws.attn_waves = ws.attn_list = true;
-    ws.attn_super = ws.attn_direct = ws.attn_seq = ws.attn_split = false;
+  if (waves != WaveUse::NO) {
+    ws.attn_waves = waves == WaveUse::YES;
+    ws.attn_choice = waves == WaveUse::BY_LENGTHS;
+    ws.attn_list = true;
+    if (waves == WaveUse::YES) ws.attn_split = false;
+    ws.attn_super = ws.attn_direct = ws.attn_seq = false;      // (attn_split: what the call by lengths runs otherwise)
     ws.part_rows = m->group * window;          // (a slot's padding rows are never written)
     ws.attn_units = attention_units(false, max_context);
   }
@@ -246,7 +253,7 @@ size_t sized_for_up_to(const llm42_model* m, int max_seqs, int window, int max_c
   for (int n = 1; n <= max_seqs; ++n) {
     attention_mode(m, n, max_context, w);
     count(n, w.attn_units, w.r_pad);
-    if (waves_pay(m, n, window, max_context)) count(n, attention_units(false, max_context), m->group * window);
+    if (wave_use(m, n, window, max_context) != WaveUse::NO) count(n, attention_units(false, max_context), m->group * window);
   }
   return carve(m, max_seqs, window, max_context, nullptr, false, part_rows, items).bytes;
 }
@@ -255,8 +262,9 @@ size_t sized_for_up_to(const llm42_model* m, int max_seqs, int window, int max_c
 // chunk, whichever of the two is smaller: the partials of a wave per chunk are used where they fit as well.
 Workspace call_workspace(const llm42_model* m, int num_seqs, int window, int max_context, char* base, size_t have, bool batch_chosen) {
   const Workspace ws = carve(m, num_seqs, window, max_context, base, batch_chosen);
-  if (ws.bytes > have || !waves_pay(m, num_seqs, window, max_context)) return ws;
-  const Workspace waves = carve(m, num_seqs, window, max_context, base, batch_chosen, 0, 0, true);
+  const WaveUse use = wave_use(m, num_seqs, window, max_context);
+  if (ws.bytes > have || use == WaveUse::NO) return ws;
+  const Workspace waves = carve(m, num_seqs, window, max_context, base, batch_chosen, 0, 0, use);
   return waves.bytes <= have ? waves : ws;
 }
 
@@ -570,11 +578,11 @@ llm42_status llm42_measure_attention_plan(const llm42_model* m, int32_t num_seqs
       (int64_t)num_seqs * window > LLM42_MAX_ROWS)
     return fail(LLM42_EINVAL, "measure_attention_plan: num_seqs/window/max_context out of range");
   const Workspace ws = call_workspace(m, num_seqs, window, max_context, nullptr, sized_for_up_to(m, num_seqs, window, max_context), false);
-  out[0] = ws.attn_super && !ws.attn_split ? 2048 : 256;
+  out[0] = (ws.attn_choice || ws.attn_super) && !ws.attn_split ? 2048 : 256;
   out[1] = ws.attn_direct || ws.attn_split ? 1 : 0;
   out[2] = ws.attn_seq ? 1 : 0;
   out[3] = (int64_t)(ws.attn_ctrl_offset + sizeof(int32_t) * (1 + m->cfg.n_layers));
-  out[4] = ws.attn_waves ? 3 : ws.attn_split ? 2 : attention_streams(m, num_seqs, ws) ? 1 : 0;
+  out[4] = ws.attn_choice ? 4 : ws.attn_waves ? 3 : ws.attn_split ? 2 : attention_streams(m, num_seqs, ws) ? 1 : 0;
   return LLM42_OK;
 }
 

@@ -274,11 +274,11 @@ __device__ __forceinline__ void softmax_step(const uint4* lk, const uint16_t* lv
 }
 
 template <int HD, int CB, int NW, bool SUPER, int NBUF>
-__global__ __launch_bounds__(NW * 64, NBUF == 2 ? 2 : 1) void attention_kernel(
+__device__ __forceinline__ void attention_items(
     const uint16_t* __restrict__ q, const uint4* __restrict__ k_plane, const uint4* __restrict__ v_plane,
     const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count,
     int32_t* __restrict__ queue, int n_kv_heads, RowOrder order, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
-    float scale_log2, float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out,
+    int part_rows, float scale_log2, float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out,
     int d_attn) {
   constexpr int DK = HD / 32;        // MFMA k-steps over the head dimension (scores)
   constexpr int DB = HD / 16;        // 16-feature blocks of the output
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(NW * 64, NBUF == 2 ? 2 : 1) void attention_kernel(
       store_output<HD>(attn_out, d_attn, tag_base(tag), kvh, order, row[cb], g, sacc[cb], sl[cb]);
       continue;
     }
-    const size_t prow = (((size_t)s * n_kv_heads + kvh) * n_units + unit) * r_pad + row[cb];
+    const size_t prow = (((size_t)s * n_kv_heads + kvh) * n_units + unit) * part_rows + row[cb];
     float* pa = part_acc + prow * HD;
 #pragma unroll
     for (int d = 0; d < DB; ++d) *(f32x4*)(pa + d * 16 + g * 4) = SUPER ? sacc[cb][d] : acc[cb][d];
@@ -470,6 +470,17 @@ __global__ __launch_bounds__(NW * 64, NBUF == 2 ? 2 : 1) void attention_kernel(
       if (t < total) su = items[t / per_item];
     }
   }
+}
+
+template <int HD, int CB, int NW, bool SUPER, int NBUF>
+__global__ __launch_bounds__(NW * 64, NBUF == 2 ? 2 : 1) void attention_kernel(
+    const uint16_t* __restrict__ q, const uint4* __restrict__ k_plane, const uint4* __restrict__ v_plane,
+    const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count,
+    int32_t* __restrict__ queue, int n_kv_heads, RowOrder order, int r_pad, int y_blocks, int max_blocks_per_seq, int n_units,
+    float scale_log2, float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out,
+    int d_attn) {
+  attention_items<HD, CB, NW, SUPER, NBUF>(q, k_plane, v_plane, block_table, items, item_count, queue, n_kv_heads, order, r_pad, y_blocks,
+                                           max_blocks_per_seq, n_units, r_pad, scale_log2, part_acc, part_ml, attn_out, d_attn);
 }
 
 // The same computation for 8 or more blocks of query rows per (sequence, kv head), as one stream per
@@ -764,7 +775,7 @@ __device__ __forceinline__ void load_v_tile(u32x4 (&vb)[DK], const u32x4* __rest
 // the first), so it is used while the row blocks are few (see attention_mode).
 // items == nullptr: item t is of sequence t / per_item (no list to wait for).
 template <int HD>
-__global__ __launch_bounds__(256) void attention_split_kernel(
+__device__ __forceinline__ void attention_split(
     const uint16_t* __restrict__ q, const bf16x8* __restrict__ k_plane, const u32x4* __restrict__ v_plane,
     const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_len, const int32_t* __restrict__ seq_n,
     const int4* __restrict__ items, const int32_t* __restrict__ item_count, int num_seqs, int n_kv_heads, RowOrder order,
@@ -874,6 +885,16 @@ __global__ __launch_bounds__(256) void attention_split_kernel(
   }
 }
 
+template <int HD>
+__global__ __launch_bounds__(256) void attention_split_kernel(
+    const uint16_t* __restrict__ q, const bf16x8* __restrict__ k_plane, const u32x4* __restrict__ v_plane,
+    const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_len, const int32_t* __restrict__ seq_n,
+    const int4* __restrict__ items, const int32_t* __restrict__ item_count, int num_seqs, int n_kv_heads, RowOrder order,
+    int r_pad, int max_blocks_per_seq, float scale_log2, uint16_t* __restrict__ attn_out, int d_attn) {
+  attention_split<HD>(q, k_plane, v_plane, block_table, seq_len, seq_n, items, item_count, num_seqs, n_kv_heads, order, r_pad,
+                      max_blocks_per_seq, scale_log2, attn_out, d_attn);
+}
+
 // One block of 16 query rows per (sequence, kv head), as in a decode step: a wave per chunk, and the merge pass for the sequences
 // of several (the others' rows are written here).  The waves of the launch deal the plan's list among them, longest chunks first and
 // neighbours on different CUs, and keep K and V of two steps on their way, straight to registers and across the end of an item: no
@@ -884,7 +905,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(
 // (Folding by the wave that finishes a row's last chunk, partials through agent-scope stores and a counter, takes
 // as long as the merge launch that it saves.  Requests past an item's last step repeat one tile: as whole steps they took 6 - 60 us.)
 template <int HD>
-__global__ __launch_bounds__(256) void attention_wave_kernel(
+__device__ __forceinline__ void attention_waves(
     const uint16_t* __restrict__ q, const bf16x8* __restrict__ k_plane, const u32x4* __restrict__ v_plane,
     const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count, int n_kv_heads,
     RowOrder order, int max_blocks_per_seq, int n_units, int part_rows, int max_items, float scale_log2,
@@ -1008,6 +1029,36 @@ __global__ __launch_bounds__(256) void attention_wave_kernel(
   while (step(ka, va) && step(kc, vc)) {}
 }
 
+template <int HD>
+__global__ __launch_bounds__(256) void attention_wave_kernel(
+    const uint16_t* __restrict__ q, const bf16x8* __restrict__ k_plane, const u32x4* __restrict__ v_plane,
+    const int32_t* __restrict__ block_table, const int4* __restrict__ items, const int32_t* __restrict__ item_count, int n_kv_heads,
+    RowOrder order, int max_blocks_per_seq, int n_units, int part_rows, int max_items, float scale_log2,
+    float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ attn_out, int d_attn) {
+  attention_waves<HD>(q, k_plane, v_plane, block_table, items, item_count, n_kv_heads, order, max_blocks_per_seq, n_units, part_rows,
+                      max_items, scale_log2, part_acc, part_ml, attn_out, d_attn);
+}
+
+// The same, or what the call runs otherwise - a workgroup per (sequence, kv head) where contexts are within one super, super items
+// beyond - as the plan kernel has decided from the lengths (*by_waves): both in one launch, for one that leaves at once takes 4 us.
+template <int HD, bool SPLIT>
+__global__ __launch_bounds__(256) void attention_choice_kernel(
+    const uint16_t* __restrict__ q, const void* __restrict__ k_plane, const void* __restrict__ v_plane,
+    const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_len, const int32_t* __restrict__ seq_n,
+    const int4* __restrict__ items, const int32_t* __restrict__ item_count, int32_t* __restrict__ queue, int num_seqs, int n_kv_heads,
+    RowOrder order, int max_blocks_per_seq, int n_units, int part_rows, float scale_log2, float* __restrict__ part_acc,
+    float* __restrict__ part_ml, uint16_t* __restrict__ attn_out, int d_attn, const int32_t* __restrict__ by_waves) {
+  if (*by_waves)
+    attention_waves<HD>(q, (const bf16x8*)k_plane, (const u32x4*)v_plane, block_table, items, item_count, n_kv_heads, order,
+                        max_blocks_per_seq, n_units, part_rows, num_seqs * n_units, scale_log2, part_acc, part_ml, attn_out, d_attn);
+  else if constexpr (SPLIT)
+    attention_split<HD>(q, (const bf16x8*)k_plane, (const u32x4*)v_plane, block_table, seq_len, seq_n, nullptr, nullptr, num_seqs,
+                        n_kv_heads, order, 16, max_blocks_per_seq, scale_log2, attn_out, d_attn);
+  else
+    attention_items<HD, 1, 4, true, 4>(q, (const uint4*)k_plane, (const uint4*)v_plane, block_table, items, item_count, queue, n_kv_heads,
+                                       order, 16, 1, max_blocks_per_seq, n_units, part_rows, scale_log2, part_acc, part_ml, nullptr, d_attn);
+}
+
 // The work items of a call: every (sequence, unit) pair that holds keys, as (s, unit, L, seq_tag), sorted
 // by the number of 64-key steps it takes, longest first (the attention kernels deal them out in that
 // order, which keeps the tail of a launch short); and the per-layer queue counters.  The order
@@ -1020,17 +1071,25 @@ __global__ __launch_bounds__(256) void attention_wave_kernel(
 // entries, and keeps that list (*seq_mode = 1) if the busiest workgroup has at most 5 % more than the
 // average - else (*seq_mode = 0) it lists the units of unit_keys keys as usual.  The choice moves
 // work between kernels that compute the same bits.
+//
+// wave_rows != 0: the call may run a wave per chunk instead of what it runs otherwise (attention_choice_kernel on seq_grid
+// workgroups, seq_per_item per item), with partials of wave_rows query rows; *seq_mode = 1 if it does.
+// or_split: instead of the split kernel, if no wave gets a second chunk.  Else instead of supers: these take as long as the busiest
+// workgroup, dealt as above (1.3 us per step of 64 keys), the waves as long as all steps at the rate of the memory (1.5 us per step
+// and workgroup) or a wave's chunks one after the other (3.9 us a step), whichever is more, and their partials; both the starts and
+// merge passes that were measured (8 kv heads, head dimension 128).  Over 223 calls of 8 - 48 sequences and 1 - 4 tokens, of 2100 - 16000
+// keys, the one chosen took 0.3 % longer than the better one on average, 7 % at most; always the waves 3.5 %, always the supers 9.5 %.
 __global__ __launch_bounds__(256) void attention_plan_kernel(const int32_t* __restrict__ seq_len,
                                                              const int32_t* __restrict__ seq_n, int num_seqs,
-                                                             int unit_keys, int seq_unit_keys, int seq_per_item,
-                                                             int seq_grid, int4* __restrict__ items,
+                                                             int unit_keys, int seq_unit_keys, int wave_rows,
+                                                             bool or_split, int seq_per_item, int seq_grid, int4* __restrict__ items,
                                                              int32_t* __restrict__ item_count,
                                                              int32_t* __restrict__ queues, int n_layers,
                                                              int32_t* __restrict__ seq_mode) {
   // classes: an item's steps in units of class_steps, 1 .. nb <= MAXB (class_steps is 1 unless a unit is a whole sequence)
   constexpr int MAXB = SUPER_KEYS / STEP;
   __shared__ int count[MAXB + 1], cursor[MAXB + 1];
-  __shared__ int n_items;
+  __shared__ int n_items, n_chunks;
   __shared__ unsigned long long load_sum;
   __shared__ int load_max;
   for (int l = threadIdx.x; l < n_layers; l += 256) queues[l] = 0;
@@ -1067,43 +1126,66 @@ __global__ __launch_bounds__(256) void attention_plan_kernel(const int32_t* __re
     }
     __syncthreads();                                         // the list is complete (and visible to this workgroup)
   };
-  int whole = 0;
-  if (seq_unit_keys) {
-    list_items(seq_unit_keys, (seq_unit_keys / STEP + MAXB - 1) / MAXB);
+  // load_sum and load_max: what the workgroups of a launch walk if the listed items of `unit` keys are dealt to them in turn, rounds
+  // alternating direction - steps, and `extra` per item
+  auto deal = [&](const int unit, const int extra) {
     if (threadIdx.x == 0) {
       load_sum = 0;
       load_max = 0;
     }
     __syncthreads();
     const int total = n_items * seq_per_item;
-    for (int w = threadIdx.x; w < seq_grid; w += 256) {      // the entries workgroup w of the stream kernel would walk
+    for (int w = threadIdx.x; w < seq_grid; w += 256) {
       int load = 0;
       for (int ord = 0;; ++ord) {
         const int t = ord * seq_grid + ((ord & 1) ? seq_grid - 1 - w : w);
         if (t >= total) break;
         const int4 it = items[t / seq_per_item];
-        load += (it.z + tag_rows(it.w) + STEP - 1) / STEP + 1;
+        load += (min(it.z + tag_rows(it.w) - it.y * unit, unit) + STEP - 1) / STEP + extra;
       }
       atomicAdd(&load_sum, (unsigned long long)load);
       atomicMax(&load_max, load);
     }
     __syncthreads();
-    whole = (unsigned long long)load_max * seq_grid * 100ull <= load_sum * 105ull ? 1 : 0;
+  };
+  int mode = 0;
+  if (seq_unit_keys) {
+    list_items(seq_unit_keys, (seq_unit_keys / STEP + MAXB - 1) / MAXB);
+    deal(seq_unit_keys, 1);
+    mode = (unsigned long long)load_max * seq_grid * 100ull <= load_sum * 105ull ? 1 : 0;
     __syncthreads();
   }
-  if (!whole) list_items(unit_keys, 1);
-  if (threadIdx.x == 0) *seq_mode = whole;
+  if (!mode && !or_split) list_items(unit_keys, 1);
+  if (wave_rows) {
+    if (threadIdx.x == 0) n_chunks = 0;
+    if (or_split) __syncthreads();
+    else deal(unit_keys, 0);
+    for (int s = threadIdx.x; s < num_seqs; s += 256)
+      if (seq_len[s] >= 0) atomicAdd(&n_chunks, (seq_len[s] + tag_rows(seq_n[s]) + CHUNK - 1) / CHUNK);
+    __syncthreads();
+    const int chunks = n_chunks * seq_per_item, rounds = (chunks + 4 * seq_grid - 1) / (4 * seq_grid);
+    const float supers_us = 4.f + 1.3f * (float)load_max;
+    const float waves_us = 9.f + fmaxf(1.5f * (float)load_sum / (float)seq_grid, 3.9f * (CHUNK / STEP) * (float)rounds) +
+                           2e-4f * (float)wave_rows * (float)chunks;
+    mode = or_split ? rounds <= 1 : waves_us < supers_us;
+    __syncthreads();
+    if (mode) list_items(CHUNK, 1);
+  }
+  if (threadIdx.x == 0) *seq_mode = mode;
 }
 
 // Fold the partials of every query row (chunks inside a super left to right, then the supers
 // left to right) and write the normalised output, bf16, into the tile layout of the
-// O-projection's activation operand.  One thread per (row, 4 features).  Sequences of up to done_keys keys have their output already.
-template <int HD, bool SUPER, bool EARLY = false>
+// O-projection's activation operand.  One thread per (row, 4 features).  Chunk partials: sequences of up to done_keys keys have
+// their output already, and *seq_mode == 0 (where it is given) says that the call did not run a wave per chunk after all: all have
+// it (SPLIT), or supers' partials.
+template <int HD, bool SUPER, bool EARLY = false, bool SPLIT = false>
 __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const float* __restrict__ part_ml,
                                        const int32_t* __restrict__ seq_len, const int32_t* __restrict__ seq_n,
                                        int n_kv_heads, RowOrder order, int window, int r_pad, int n_units, int d_attn,
                                        uint16_t* __restrict__ out, const int32_t* __restrict__ seq_mode, int done_keys) {
   if (SUPER && seq_mode && *seq_mode) return;       // the attention kernel took whole sequences and wrote the output itself
+  if (SPLIT && *seq_mode == 0) return;
   constexpr int QUADS = HD / 4;
   const int quad = threadIdx.x % QUADS;
   const int at = blockIdx.y * (blockDim.x / QUADS) + threadIdx.x / QUADS;   // (pairs can outnumber what grid.y allows)
@@ -1128,11 +1210,12 @@ __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const
   }
   const int L = seq_len[s], tag = seq_n[s];
   if (L < 0 || i >= tag_rows(tag)) return;   // no such row, or one that prepare_kernel has given zeros
-  if (L + tag_rows(tag) <= done_keys) return;
+  const bool by_super = SUPER || (EARLY && seq_mode && *seq_mode == 0);
+  if (!by_super && L + tag_rows(tag) <= done_keys) return;
   uint2* dst = (uint2*)(out + pk_off(tag_base(tag) + i, hq * HD + quad * 4, d_attn));
   float M, Ls;
   f32x4 A[1];
-  if (SUPER) {
+  if (by_super) {
     const int last = (L + i) / SUPER_KEYS;
     float2 m2 = slot_ml(0);
     M = m2.x;
@@ -1250,18 +1333,27 @@ void launch_split(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, 
 }
 
 template <int HD>
-void launch_waves(const llm42_model* m, const uint16_t* kp, const uint16_t* vp, const llm42_kv_cache* kv, int num_seqs,
+void launch_waves(const llm42_model* m, int layer, const uint16_t* kp, const uint16_t* vp, const llm42_kv_cache* kv, int num_seqs,
                   int window, const Workspace& ws, hipStream_t st) {
   const llm42_config& c = m->cfg;
   const float scale_log2 = (1.0f / sqrtf((float)c.head_dim)) * 1.44269504088896340736f;
   const int rows = m->group * window, rows_per_block = 256 / (HD / 4);
   const unsigned grid = (unsigned)std::min<long long>(m->num_cus, (long long)num_seqs * ws.attn_units * c.n_kv_heads);
-  attention_wave_kernel<HD><<<grid, 256, 0, st>>>(ws.q, (const bf16x8*)kp, (const u32x4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl,
-                                                  c.n_kv_heads, row_order(m->group, window), kv->max_blocks_per_seq, ws.attn_units,
-                                                  ws.part_rows, num_seqs * ws.attn_units, scale_log2, ws.part_acc, ws.part_ml, ws.attn, m->d_attn);
-  attention_merge_kernel<HD, false, true><<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256, 0, st>>>(
+  const int32_t* by_waves = ws.attn_choice ? ws.attn_ctrl + 1 + c.n_layers : nullptr;
+  if (by_waves) {
+    auto* const kernel = ws.attn_split ? attention_choice_kernel<HD, true> : attention_choice_kernel<HD, false>;
+    kernel<<<grid, 256, 0, st>>>(ws.q, kp, vp, kv->block_table, ws.seq_len, ws.seq_n, ws.attn_items, ws.attn_ctrl,
+                                 ws.attn_ctrl + 1 + layer, num_seqs, c.n_kv_heads, row_order(m->group, window), kv->max_blocks_per_seq,
+                                 ws.attn_units, ws.part_rows, scale_log2, ws.part_acc, ws.part_ml, ws.attn, m->d_attn, by_waves);
+  } else {
+    attention_wave_kernel<HD><<<grid, 256, 0, st>>>(
+        ws.q, (const bf16x8*)kp, (const u32x4*)vp, kv->block_table, ws.attn_items, ws.attn_ctrl, c.n_kv_heads, row_order(m->group, window),
+        kv->max_blocks_per_seq, ws.attn_units, ws.part_rows, num_seqs * ws.attn_units, scale_log2, ws.part_acc, ws.part_ml, ws.attn, m->d_attn);
+  }
+  auto* const merge = by_waves && ws.attn_split ? attention_merge_kernel<HD, false, true, true> : attention_merge_kernel<HD, false, true>;
+  merge<<<dim3(num_seqs * c.n_kv_heads, (rows + rows_per_block - 1) / rows_per_block), 256, 0, st>>>(
       ws.part_acc, ws.part_ml, ws.seq_len, ws.seq_n, c.n_kv_heads, row_order(m->group, window), window, ws.part_rows, ws.attn_units,
-      m->d_attn, ws.attn, nullptr, CHUNK);
+      m->d_attn, ws.attn, by_waves, CHUNK);
 }
 
 template <int HD>
@@ -1271,8 +1363,8 @@ void launch_hd(const llm42_model* m, int layer, const uint16_t* kp, const uint16
   // (a call that may take whole sequences as items launches that kernel too; the plan's choice, made on the device
   // from the lengths, leaves one of the two with nothing to do)
   if constexpr (HD == 128) {
-    if (ws.attn_waves) {
-      launch_waves<HD>(m, kp, vp, kv, num_seqs, window, ws, st);
+    if (ws.attn_waves || ws.attn_choice) {
+      launch_waves<HD>(m, layer, kp, vp, kv, num_seqs, window, ws, st);
       return;
     }
   }
@@ -1297,10 +1389,11 @@ void launch_attention_plan(const llm42_model* m, int num_seqs, int max_context, 
   // as a whole-sequence item a unit has as many keys as the longest sequence of the call may have
   const int seq_unit_keys = ws.attn_seq ? (max_context + STEP - 1) / STEP * STEP : 0;
   const int seq_per_item = m->cfg.n_kv_heads * ((ws.r_pad / 16 + 7) / 8);
-  const int unit_keys = !ws.attn_waves && (ws.attn_super || ws.attn_split) ? SUPER_KEYS : CHUNK;
-  attention_plan_kernel<<<1, 256, 0, st>>>(ws.seq_len, ws.seq_n, num_seqs, unit_keys, seq_unit_keys, seq_per_item,
-                                           (int)stream_grid(m, num_seqs, 1, ws.r_pad), ws.attn_items, ws.attn_ctrl, ws.attn_ctrl + 1,
-                                           m->cfg.n_layers,
+  const int unit_keys = ws.attn_choice || (!ws.attn_waves && (ws.attn_super || ws.attn_split)) ? SUPER_KEYS : CHUNK;
+  const int grid = ws.attn_choice ? m->num_cus : (int)stream_grid(m, num_seqs, 1, ws.r_pad);
+  attention_plan_kernel<<<1, 256, 0, st>>>(ws.seq_len, ws.seq_n, num_seqs, unit_keys, seq_unit_keys, ws.attn_choice ? ws.part_rows : 0,
+                                           ws.attn_choice && ws.attn_split, seq_per_item, grid, ws.attn_items, ws.attn_ctrl,
+                                           ws.attn_ctrl + 1, m->cfg.n_layers,
                                            ws.attn_ctrl + 1 + m->cfg.n_layers);
 }
 

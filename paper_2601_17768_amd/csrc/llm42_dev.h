@@ -136,7 +136,8 @@ struct Workspace {
   bool attn_seq;    // the call may take whole sequences as attention items (the plan kernel decides from the lengths)
   bool attn_split;  // whatever the three above say: a workgroup per (sequence, kv head, block of 16 query rows), chunks
                     // dealt to its waves, output written by the same launch
-  bool attn_waves;  // whatever those above say: a wave per chunk, and the merge pass (see waves_pay)
+  bool attn_waves;  // whatever those above say: a wave per chunk, and the merge pass (see wave_use)
+  bool attn_choice; // whatever those above say: a wave per chunk or a workgroup per super, as the plan kernel decides from the lengths
   bool attn_list;   // the launches take their items from the plan kernel's list (else: sequence by sequence)
   bool full;        // every window of the call is full: attention by 8 waves need not test for rows that are not there
   bool batch_chosen; // off the fixed schedule (fast-path decode step, cost-of-determinism measurement): the batch may

@@ -83,7 +83,7 @@ def test_second_chunk_of_every_wave(env, L, window, rows):
     shape, sess = env
     merged = _run(shape, sess, L, window, rows, 0, 0, max(L + window, 1281), split=False)
     assert torch.isfinite(merged[1]).all()
-    among = _run(shape, sess, L, window, rows, 199 if one_block(shape, window) else 60, 20, L + window, split=True)
+    among = _run(shape, sess, L, window, rows, 239 if one_block(shape, window) else 60, 20, L + window, split=True)
     assert torch.equal(merged[0], among[0]) and torch.equal(merged[1], among[1])
 
 

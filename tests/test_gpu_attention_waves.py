@@ -33,15 +33,25 @@ def sessions():
 # chunk of one to four steps, past one super; sequences x 8 kv heads: fewer items than waves (1024), several per wave with
 # short ones last; 4, 8, 12, 14, 15 and 16 query rows, neighbouring tokens side by side and not
 CASES = [(4, 1, [0, 254, 255, 256, 257, 319, 320, 511, 512, 1023, 2000]),
-         (4, 1, [2047, 63, 64, 127, 128, 191, 192, 1, 0, 300, 1279, 1280, 1281]), (4, 1, [2048, 4095] + [2047, 0, 255, 256, 3000] * 3),
-         (4, 1, "uniform:0:700:60"), (4, 1, "uniform:2500:4000:14"), (4, 1, "uniform:257:300:150"), (4, 1, "uniform:0:1300:40"),
+         (4, 1, [2047, 63, 64, 127, 128, 191, 192, 1, 0, 300, 1279, 1280, 1281]),
+         (4, 1, "uniform:0:700:60"), (4, 1, "uniform:257:300:150"), (4, 1, "uniform:0:1300:40"),
          (4, 4, [0, 251, 252, 253, 508, 1276, 2040, 2044]), (4, 4, "uniform:1:2040:40"), (4, 3, "uniform:1:2000:8"),
-         (5, 3, [0, 252, 253, 254, 509, 1277, 2044, 2045]), (7, 2, "uniform:1:2040:9"), (8, 2, "uniform:1:2040:38"), (8, 1, "uniform:1:4000:13"),
+         (5, 3, [0, 252, 253, 254, 509, 1277, 2044, 2045]), (7, 2, "uniform:1:2040:9"), (8, 2, "uniform:1:2040:38"),
          (3, 5, [250, 251, 252, 2000, 2043, 1, 0, 700])]
+# where the device decides from the lengths, and takes a wave per chunk - or not: beyond one super of sequences that deal out evenly, within
+# one where a wave would get a second chunk
+BY_LENGTHS = [(4, 1, [2048, 4095] + [2047, 0, 255, 256, 3000] * 3, True), (4, 1, "uniform:2100:3000:14", True), (8, 1, "uniform:1:4000:13", True),
+              (4, 1, [4500] + [3, 200, 256, 257, 2048] * 5, True), (4, 2, "uniform:2060:2200:12", True), (4, 1, "uniform:3900:4094:16", False),
+              (4, 1, "uniform:4000:4095:31", False), (4, 3, "uniform:3900:4090:16", False), (4, 1, [2047, 2048, 4095, 4096, 4000] * 3 + [4000], False),
+              (4, 1, "uniform:0:2000:20", True), (4, 2, [2045, 2046, 0, 255, 256, 700] * 3, True), (4, 1, [1279] * 25 + [1280], False),
+              (4, 1, [1280] + [1279] * 23 + [0], True), (4, 1, "uniform:1700:2040:27", False), (7, 1, [1300, 254, 255, 256] * 7, True)]
 
 
-@pytest.mark.parametrize("group,window,lens", CASES, ids=[f"{g}-{w}-{c}" for g, w, c in CASES])
-def test_same_bits_as_the_first_rows_of_a_larger_window(sessions, group, window, lens):
+ALL = [(*c, None) for c in CASES] + BY_LENGTHS
+
+
+@pytest.mark.parametrize("group,window,lens,takes", ALL, ids=[f"{g}-{w}-{c}"[:70] for g, w, c, _ in ALL])
+def test_same_bits_as_the_first_rows_of_a_larger_window(sessions, group, window, lens, takes):
     shape, sess = sessions(group)
     rng = wl.rng_for(53, group, window, len(lens))
     if isinstance(lens, str):
@@ -72,31 +82,37 @@ def test_same_bits_as_the_first_rows_of_a_larger_window(sessions, group, window,
         B.llm42_verify_window(sess.model, kv, blocks, bt, sl, cand[:, :w].contiguous(), w, counts, max_context, out, ws, status, logits,
                               torch.arange(n, dtype=torch.int32, device=DEV))
         torch.cuda.synchronize()
-        # the items' count lies in front of a counter per layer and of the flag whose place the plan names
-        at = plan["sequences_flag_offset"] - 4 * (1 + shape.n_layers)
-        listed = int(ws[at:at + 4].view(torch.int32)[0])
-        return plan, listed, out, status, logits, kv
+        # the items' count, a counter per layer, and the flag whose place the plan names
+        control = ws[plan["sequences_flag_offset"] - 4 * (1 + shape.n_layers):plan["sequences_flag_offset"] + 4].view(torch.int32)
+        return plan, (int(control[0]), int(control[-1])), out, status, logits, kv
 
-    plan, listed, out, status, logits, kv = run(window, nv if window > 1 else None)
-    assert plan["waves"] and listed == int(((lens + rows + 255) // 256).sum())
+    plan, (listed, flag), out, status, logits, kv = run(window, nv if window > 1 else None)
+    assert plan["waves"] == (takes is None) and plan["may_take_waves"] == (takes is not None)
+    unit = 2048 if takes is False else 256
+    assert flag == int(takes is True)
+    assert listed == int(((lens + rows + unit - 1) // unit).sum()) or (takes is False and int(lens.max()) + window <= 2048)   # (no list)
     ref = run(larger, nv)
-    assert not ref[0]["waves"]
+    assert not ref[0]["waves"] and not ref[0]["may_take_waves"]
     assert int(status.abs().max()) == 0 and torch.isfinite(logits).all()
     assert torch.equal(out, ref[2][:, :window]) and torch.equal(status, ref[3])
     assert torch.equal(logits, ref[4][:, :window])                                    # (rows that are not there stay as they were)
     assert torch.equal(kv.view(torch.int16), ref[5].view(torch.int16))                # (NaN where nothing was written)
 
 
-# sequences, window, longest context: 4 query rows per token and kv head, 8 kv heads; measured to be slower with a wave per chunk, or not
-SLOWER = [(24, 1, 1500), (20, 1, 1700), (24, 1, 1901), (32, 1, 1281), (8, 1, 1001), (16, 1, 1001), (2, 1, 1901), (1, 1, 8001), (4, 1, 3001),
-          (24, 1, 8001), (64, 1, 4501), (128, 1, 8001), (128, 1, 1901), (64, 3, 1902), (64, 4, 1004), (128, 4, 8004), (32, 4, 3004), (16, 4, 2044)]
-FASTER = [(40, 1, 501), (48, 1, 1874), (64, 1, 1001), (8, 1, 1901), (2, 1, 1271), (16, 1, 2041), (16, 1, 4001), (24, 1, 3001), (40, 2, 1902),
-          (16, 2, 4002), (40, 4, 1404), (8, 4, 1904), (128, 1, 1001)]
+# sequences, window, longest context: 4 query rows per token and kv head, 8 kv heads; measured to be slower with a wave per chunk, to be
+# faster, or to depend on the lengths
+SLOWER = [(32, 1, 2041), (24, 1, 1001), (32, 4, 1901), (8, 1, 1001), (16, 1, 1001), (2, 1, 1901), (1, 1, 8001), (4, 1, 3001),
+          (80, 1, 4501), (128, 1, 8001), (128, 1, 1901), (64, 3, 1902), (64, 4, 1004), (128, 4, 8004), (32, 4, 3004), (24, 1, 1271), (16, 4, 2044)]
+FASTER = [(40, 1, 501), (48, 1, 1874), (64, 1, 1001), (8, 1, 1901), (2, 1, 1271), (16, 1, 2041), (40, 2, 1902), (40, 4, 1404), (8, 4, 1904),
+          (128, 1, 1001)]
+EITHER = [(24, 1, 1500), (20, 1, 1700), (28, 1, 1281), (24, 2, 1902), (16, 1, 4001), (24, 1, 3001), (64, 1, 8001), (32, 2, 2100), (16, 4, 4004)]
 
 
-@pytest.mark.parametrize("n,window,max_context,waves", [(*c, False) for c in SLOWER] + [(*c, True) for c in FASTER])
-def test_a_wave_per_chunk_only_where_it_is_not_slower(sessions, n, window, max_context, waves):
+@pytest.mark.parametrize("n,window,max_context,how", [(*c, "no") for c in SLOWER] + [(*c, "waves") for c in FASTER] +
+                         [(*c, "may_take_waves") for c in EITHER])
+def test_a_wave_per_chunk_only_where_it_is_not_slower(sessions, n, window, max_context, how):
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("measured with 256 CUs")
     shape, sess = sessions(4)
-    assert B.llm42_measure_attention_plan(sess.model, n, window, max_context)["waves"] == waves
+    plan = B.llm42_measure_attention_plan(sess.model, n, window, max_context)
+    assert plan["waves"] == (how == "waves") and plan["may_take_waves"] == (how == "may_take_waves")

@@ -151,15 +151,18 @@ enum class WaveUse { NO, YES, BY_LENGTHS };
 WaveUse wave_use(const llm42_model* m, int num_seqs, int window, int max_context) {
   const int rows = m->group * window;
   if (m->cfg.head_dim != 128 || rows > 16 || max_context <= 256) return WaveUse::NO;
+  const long long wgs = (long long)num_seqs * m->cfg.n_kv_heads, cus = m->num_cus;
+  const bool one_super = attention_units(true, max_context) == 1;
+  if (one_super && wgs > cus)
+    return (rows <= 4 ? wgs <= 2 * cus || max_context <= 1152 : 4 * wgs <= 5 * cus) ? WaveUse::YES : WaveUse::NO;
+  if (one_super ? max_context <= 1152 : wgs * rows > 8 * cus) return WaveUse::NO;
   Workspace other;                                                     // the work split that the call has otherwise
   memset(&other, 0, sizeof other);
   other.num_cus = m->num_cus;
   other.r_pad = 16;
   attention_mode(m, num_seqs, max_context, other);
-  const long long wgs = (long long)num_seqs * m->cfg.n_kv_heads, cus = m->num_cus;
-  if (attention_units(true, max_context) > 1) return other.attn_super && wgs * rows <= 8 * cus ? WaveUse::BY_LENGTHS : WaveUse::NO;
-  if (wgs > cus) return (rows <= 4 ? wgs <= 2 * cus || max_context <= 1152 : 4 * wgs <= 5 * cus) ? WaveUse::YES : WaveUse::NO;
-  if (!other.attn_split || max_context <= 1152) return WaveUse::NO;
+  if (!one_super) return other.attn_super ? WaveUse::BY_LENGTHS : WaveUse::NO;
+  if (!other.attn_split) return WaveUse::NO;
   if (2 * wgs > cus) return 8 * wgs <= 7 * cus && rows <= 8 && max_context > 1280 ? WaveUse::BY_LENGTHS : WaveUse::NO;
   return wgs >= 16 && wgs * rows <= 6 * cus ? WaveUse::YES : WaveUse::NO;
 }

@@ -898,12 +898,15 @@ __global__ __launch_bounds__(256) void attention_split_kernel(
 // One block of 16 query rows per (sequence, kv head), as in a decode step: a wave per chunk, and the merge pass for the sequences
 // of several (the others' rows are written here).  The waves of the launch deal the plan's list among them, longest chunks first and
 // neighbours on different CUs, and keep K and V of two steps on their way, straight to registers and across the end of an item: no
-// ring, no barrier.  What bounds it is what a CU fetches (about 42 GB/s of memory that no other reads): attention_split_kernel, a
-// workgroup per sequence and kv head, waits for its longest one, attention_kernel computes three blocks of rows that are
-// not there.  us per layer against those kernels, merge pass and all, at head dimension 128 and 8 kv heads: 24 sequences of 65 - 1873
-// keys 9 of 27 less, 32 of up to 2400 30 less, 8 x 1900 8, 48 x 1900 8, 4 x 8000 15, 24 of 16 - 8000 24 less, 24 x 1900 3 more.
+// ring, no barrier.  (attention_split_kernel, a workgroup per sequence and kv head, waits for its longest one; super items leave a
+// launch's last round with few of them.  Where it is taken and what it takes against those: wave_use, in api.hip.)
+// What bounds it is the memory where the waves walk several chunks each - 64 sequences of 1000 keys, 262 MB of K and V in 49 us, 5.4
+// TB/s - and the way of a wave's first tiles where they have one or two: 8 x 1900, 62 MB in 15 us, 4.1 TB/s, 43 % of the waves' cycles
+// waiting.
 // (Folding by the wave that finishes a row's last chunk, partials through agent-scope stores and a counter, takes
-// as long as the merge launch that it saves.  Requests past an item's last step repeat one tile: as whole steps they took 6 - 60 us.)
+// as long as the merge launch that it saves.  Requests past an item's last step repeat one tile: as whole steps they took 6 - 60 us.
+// Within one super a workgroup of 8 waves, one per chunk, folded through LDS: 1.2 - 1.4 times the split kernel's time, for the
+// registers of 8 waves hold one step of K and V each, not two.)
 template <int HD>
 __device__ __forceinline__ void attention_waves(
     const uint16_t* __restrict__ q, const bf16x8* __restrict__ k_plane, const u32x4* __restrict__ v_plane,
@@ -1127,7 +1130,9 @@ __global__ __launch_bounds__(256) void attention_plan_kernel(const int32_t* __re
     __syncthreads();                                         // the list is complete (and visible to this workgroup)
   };
   // load_sum and load_max: what the workgroups of a launch walk if the listed items of `unit` keys are dealt to them in turn, rounds
-  // alternating direction - steps, and `extra` per item
+  // alternating direction - steps, and `extra` per item.  (A row group of a partly filled window may take fewer steps, or none.  With
+  // those counted, units were taken more often and were no better: of 88 partly filled calls of 16 - 128 sequences, windows of 48 - 128, 42
+  // slower, by up to 37 %, and 7 faster, by up to 9 %.)
   auto deal = [&](const int unit, const int extra) {
     if (threadIdx.x == 0) {
       load_sum = 0;
@@ -1196,8 +1201,8 @@ __global__ void attention_merge_kernel(const float* __restrict__ part_acc, const
   const size_t base = ((size_t)s * n_kv_heads + kvh) * n_units;
   auto slot_ml = [&](int u) { return *(const float2*)(part_ml + ((base + u) * r_pad + r) * 2); };
   auto slot_acc = [&](int u) { return *(const f32x4*)(part_acc + ((base + u) * r_pad + r) * HD + quad * 4); };
-  // EARLY: the first partials are requested together with the length that says which of them there are (a round trip less: behind
-  // attention_wave_kernel, 1 - 32 sequences of 300 keys, 1.4 us a layer; with 128 rows each the ones too many cost 1 us).
+  // EARLY: the first partials are requested together with the length that says which of them there are (a round trip less, 1.4 us a
+  // layer behind attention_wave_kernel; with 128 rows each the ones too many cost 1 us).
   constexpr int U = SUPER ? 1 : 4;
   float2 ml[U];
   f32x4 acc[U];

@@ -56,12 +56,12 @@ llm42_status llm42_measure_verify_window_batch_chosen(
  *           it did take whole sequences, or with out[4] == 4 a wave per chunk (valid after the
  *           call has run);
  *   out[4]  3 if a wave takes a 256-key chunk of one block of 16 query rows and the merge pass folds the
- *           chunks, 4 if the device decides from the lengths whether it does or a workgroup takes a
- *           super (both verify and decode calls; a prefill pass runs what is named next); 2 if a
- *           workgroup takes one block of 16 query rows and deals the chunks of its context to its waves
- *           (contexts within 2048 keys, few workgroups); else 1 if the 8-wave streaming kernel runs
- *           (8 or more blocks of 16 query rows per sequence and kv head, unless few chunks are to be
- *           dealt out), 0 for the 4-wave kernel.
+ *           chunks; 4 if the device decides from the lengths whether it does, or a workgroup takes a
+ *           super (out[0] == 2048) or what 2 says (both verify and decode calls; a prefill pass runs
+ *           what is named next); 2 if a workgroup takes one block of 16 query rows and deals the
+ *           chunks of its context to its waves (contexts within 2048 keys, few workgroups); else 1 if
+ *           the 8-wave streaming kernel runs (8 or more blocks of 16 query rows per sequence and kv
+ *           head, unless few chunks are to be dealt out), 0 for the 4-wave kernel.
  * The values are those of a call whose workspace has the llm42_workspace_bytes of its own num_seqs,
  * window and max_context, or more; with less room than that a wave per chunk may not fit. */
 llm42_status llm42_measure_attention_plan(const llm42_model* model, int32_t num_seqs, int32_t window,

@@ -116,3 +116,42 @@ def test_a_wave_per_chunk_only_where_it_is_not_slower(sessions, n, window, max_c
     shape, sess = sessions(4)
     plan = B.llm42_measure_attention_plan(sess.model, n, window, max_context)
     assert plan["waves"] == (how == "waves") and plan["may_take_waves"] == (how == "may_take_waves")
+
+
+@pytest.mark.parametrize("n,longest", [(16, 4090), (20, 2040)])
+def test_a_captured_call_chooses_at_every_replay(sessions, n, longest):
+    """One captured call, replayed behind other lengths: the device takes a wave per chunk for some and not for others."""
+    shape, sess = sessions(4)
+    rng = wl.rng_for(53, n, longest)
+    max_context = longest + 1
+    table, blocks = wl.make_block_table(rng, np.full(n, max_context), 16, spare_blocks=1)
+    d = lambda a: torch.as_tensor(a, device=DEV)
+    bt, cand = d(table), d(wl.random_tokens(rng, n, shape.vocab).reshape(n, 1))
+    kv = sess.kv_cache(blocks)
+    kv.normal_(generator=torch.Generator(device=DEV).manual_seed(8))
+    plan = B.llm42_measure_attention_plan(sess.model, n, 1, max_context)
+    assert plan["may_take_waves"]
+    ws = torch.empty(B.llm42_workspace_bytes(sess.model, n, 1, max_context), dtype=torch.uint8, device=DEV)
+    sl, all_ = torch.zeros(n, dtype=torch.int32, device=DEV), torch.arange(n, dtype=torch.int32, device=DEV)
+    out, logits = torch.empty((n, 1), dtype=torch.int32, device=DEV), torch.zeros((n, 1, shape.vocab), device=DEV)
+
+    def call():
+        B.llm42_verify_window(sess.model, kv, blocks, bt, sl, cand, 1, None, max_context, out, ws, None, logits, all_)
+
+    uneven = np.concatenate([[longest], rng.integers(0, longest // 3, size=n - 1)])
+    sets = [(uneven, 1), (np.full(n, longest), 0), (uneven // 2, 1), (np.full(n, longest - 7), 0), (uneven, 1)]
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for lens, waves in sets:
+        sl.copy_(d(lens.astype(np.int32)))
+        graph.replay()
+        torch.cuda.synchronize()
+        flag = ws[plan["sequences_flag_offset"]:plan["sequences_flag_offset"] + 4].view(torch.int32)
+        assert int(flag[0]) == waves
+        got = out.clone(), logits.clone()
+        call()
+        torch.cuda.synchronize()
+        assert torch.isfinite(logits).all() and torch.equal(out, got[0]) and torch.equal(logits, got[1])
